@@ -1,9 +1,13 @@
-"""ctypes binding of libopttree.so: argument marshalling only.
+"""Binding of libopttree.so: argument marshalling only.
 
 Function names mirror include/opttree.h.  PyTorch is used for device memory
 (tensors in, tensors out) and for the current HIP stream; every step of the
 path runs in the library's kernels.  There is no CPU fallback: if the library
 is missing or a call fails, an exception is raised.
+
+The calls of a decoding step go through a small native module (csrc/binding.cpp);
+`lib()` gives the same library through ctypes, for size queries, measurement and
+anything that talks to the C ABI directly.
 """
 from __future__ import annotations
 
@@ -16,6 +20,7 @@ OT_MAX_NODES, OT_MAX_TOPK, OT_MAX_DEPTH = 256, 16, 32
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libopttree.so")
 _lib = None
+_binding = None
 
 
 class OptTreeError(RuntimeError):
@@ -124,6 +129,21 @@ def lib():
     return _lib
 
 
+def _native():
+    """The native half of the binding (loaded once).  Raises if it has not been built."""
+    global _binding
+    if _binding is None:
+        lib()
+        import torch  # noqa: F401  (the module links against torch's libraries)
+        try:
+            from . import _binding as mod
+        except ImportError as e:
+            raise ImportError(f"the binding's native module did not load ({e}): build it with "
+                              "`python -m paper_2406_17276_amd.build`") from e
+        _binding = mod
+    return _binding
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise OptTreeError(status, where)
@@ -196,101 +216,58 @@ def build_workspace_bytes(p: BuildParams) -> int:
 
 def build_tree(logits, k: int, n: int, depth: int, out: Tree | None = None, workspace=None) -> Tree:
     """ot_build_tree: one-shot draft-tree construction on the current stream."""
-    import torch
-    p = build_params(logits, k, n, depth)
-    need = build_workspace_bytes(p)
-    if need == 0:
-        _check(lib().ot_build_tree(C.byref(p), logits.data_ptr(), None, 0, None, None), "ot_build_tree")
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
-    if out is None:
-        out = alloc_tree(p.batch, n, logits.device)
-    o = out.c_struct()
-    _check(lib().ot_build_tree(C.byref(p), logits.data_ptr(), workspace.data_ptr(), workspace.numel(),
-                               C.byref(o), _stream()), "ot_build_tree")
-    return out
+    st, tree = (_binding or _native()).build_tree(logits, k, n, depth, out, workspace, Tree)
+    if st:
+        raise OptTreeError(st, "ot_build_tree")
+    return tree
 
 
 def build_tree_adaptive(logits, k: int, n: int, depth: int, delta: float, out: Tree | None = None, workspace=None):
     """ot_build_tree_adaptive on the current stream; returns (tree, steps_used int32 [B], e_sub float64 [B])."""
-    import torch
-    p = build_params(logits, k, n, depth)
-    if out is None:
-        out = alloc_tree(p.batch, n, logits.device)
-    need = build_workspace_bytes(p)
-    if need == 0:
-        raise OptTreeError(-2, "ot_build_workspace_bytes")
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
-    steps = torch.empty(p.batch, dtype=torch.int32, device=logits.device)
-    e_sub = torch.empty(p.batch, dtype=torch.float64, device=logits.device)
-    o = out.c_struct()
-    _check(lib().ot_build_tree_adaptive(C.byref(p), float(delta), logits.data_ptr(), workspace.data_ptr(),
-                                        workspace.numel(), C.byref(o), steps.data_ptr(), e_sub.data_ptr(), _stream()),
-           "ot_build_tree_adaptive")
-    return out, steps, e_sub
+    st, tree, steps, e_sub = (_binding or _native()).build_tree_adaptive(logits, k, n, depth, delta, out, workspace, Tree)
+    if st:
+        raise OptTreeError(st, "ot_build_tree_adaptive" if steps is not None else "ot_build_workspace_bytes")
+    return tree, steps, e_sub
 
 
 class TreeStream:
     """ot_tree_begin / ot_tree_expand / ot_tree_finalize for one batch of trees."""
 
     def __init__(self, batch: int, vocab: int, k: int, n: int, depth: int, dtype_code: int, device="cuda"):
-        import torch
         self.p = BuildParams(batch, vocab, depth, k, n, dtype_code, 0, 0, vocab)
-        need = build_workspace_bytes(self.p)
-        if need == 0:
-            _check(lib().ot_tree_begin(C.byref(self.p), None, 0, None), "ot_tree_begin")
-        self.ws = torch.empty(need, dtype=torch.uint8, device=device)
-        self.frontier_token = torch.full((batch, n), -1, dtype=torch.int32, device=device)
-        self.frontier_parent = torch.full((batch, n), -1, dtype=torch.int32, device=device)
-        self.frontier_count = torch.zeros((batch,), dtype=torch.int32, device=device)
+        st, self.ws, self.frontier_token, self.frontier_parent, self.frontier_count = (_binding or _native()).stream_begin(
+            self.p, device)
         self.step = 0
-        _check(lib().ot_tree_begin(C.byref(self.p), self.ws.data_ptr(), self.ws.numel(), _stream()), "ot_tree_begin")
+        if st:
+            raise OptTreeError(st, "ot_tree_begin")
 
     def expand(self, rows):
         """rows: [B, >=F_t, V]; returns (tokens, parent_slots) views of the next frontier [B, n]."""
-        if rows.dim() != 3 or rows.stride(2) != 1:
-            raise ValueError("rows must be [B, F, V] with a contiguous last dimension")
-        if self.step >= self.p.depth:
-            raise ValueError(f"all {self.p.depth} drafting steps have been fed")
-        need = frontier_sizes(self.p.k, self.p.n, self.p.depth)[self.step]
-        if rows.shape[0] < self.p.batch or rows.shape[1] < need or rows.shape[2] < self.p.vocab:
-            raise ValueError(f"rows {tuple(rows.shape)} smaller than [batch {self.p.batch}, F_{self.step} = {need}, "
-                             f"vocab {self.p.vocab}]")
-        _check(lib().ot_tree_expand(C.byref(self.p), self.step, rows.data_ptr(), rows.stride(0), rows.stride(1),
-                                    self.ws.data_ptr(), self.ws.numel(), self.frontier_token.data_ptr(),
-                                    self.frontier_parent.data_ptr(), self.frontier_count.data_ptr(), _stream()),
-               "ot_tree_expand")
-        self.step += 1
-        return self.frontier_token, self.frontier_parent
+        st, token, parent = (_binding or _native()).stream_expand(self, rows)
+        if st:
+            raise OptTreeError(st, "ot_tree_expand")
+        return token, parent
 
     def frontier_mask(self):
         """ot_tree_frontier_mask after the latest expand: int64 [B, n, W] (bit pattern of the uint64 words),
         W = ceil(depth * n / 64), over pool indices step * n + slot."""
-        import torch
-        W = (self.p.depth * self.p.n + 63) // 64
-        m = torch.empty((self.p.batch, self.p.n, W), dtype=torch.int64, device=self.ws.device)
-        _check(lib().ot_tree_frontier_mask(C.byref(self.p), self.step, self.ws.data_ptr(), self.ws.numel(),
-                                           m.data_ptr(), _stream()), "ot_tree_frontier_mask")
-        return m
+        st, mask = (_binding or _native()).stream_mask(self)
+        if st:
+            raise OptTreeError(st, "ot_tree_frontier_mask")
+        return mask
 
     def e_sub(self, delta: float):
         """ot_tree_esub after the latest expand: (E_sub per sequence, go-on flag per sequence), device tensors."""
-        import torch
-        if not hasattr(self, "_esub"):
-            self._esub = torch.empty(self.p.batch, dtype=torch.float64, device=self.ws.device)
-            self._go = torch.empty(self.p.batch, dtype=torch.int32, device=self.ws.device)
-        _check(lib().ot_tree_esub(C.byref(self.p), self.step, float(delta), self.ws.data_ptr(), self.ws.numel(),
-                                  self._esub.data_ptr(), self._go.data_ptr(), _stream()), "ot_tree_esub")
-        return self._esub, self._go
+        st, e, go = (_binding or _native()).stream_esub(self, delta)
+        if st:
+            raise OptTreeError(st, "ot_tree_esub")
+        return e, go
 
     def finalize(self, out: Tree | None = None) -> Tree:
-        if out is None:
-            out = alloc_tree(self.p.batch, self.p.n, self.ws.device)
-        o = out.c_struct()
-        _check(lib().ot_tree_finalize(C.byref(self.p), self.step, self.ws.data_ptr(), self.ws.numel(),
-                                      C.byref(o), _stream()), "ot_tree_finalize")
-        return out
+        st, tree = (_binding or _native()).stream_finalize(self, out, Tree)
+        if st:
+            raise OptTreeError(st, "ot_tree_finalize")
+        return tree
 
 
 def attn_params(Q, K_prefix, V_prefix, K_tree, V_tree, max_prefix=None, softmax_scale: float = 0.0) -> AttnParams:
@@ -344,19 +321,12 @@ def tree_verify_attention(Q, K_prefix, V_prefix, K_tree, V_tree, prefix_len, mas
     """ot_tree_verify_attention on the current stream.  Q [B,Hq,n,D]; K/V_prefix [B,Hkv,Lmax,D] (or None);
     K/V_tree [B,Hkv,n,D]; prefix_len int32 [B]; mask int64 [B,n,W].  A caller-supplied workspace must be a
     prepared one (attn_workspace)."""
-    import torch
-    p = attn_params(Q, K_prefix, V_prefix, K_tree, V_tree, softmax_scale=softmax_scale)
-    if out is None:
-        out = torch.empty_like(Q)
-    p.o_strides = (C.c_int64 * 3)(out.stride(0), out.stride(1), out.stride(2))
     if workspace is None:
-        workspace = attn_workspace(p, Q.device)
-    ptr = lambda t: None if t is None else t.data_ptr()
-    _check(lib().ot_tree_verify_attention(
-        C.byref(p), ptr(Q), ptr(K_prefix), ptr(V_prefix), ptr(K_tree), ptr(V_tree), ptr(prefix_len), ptr(mask),
-        ptr(out), ptr(workspace), 0 if workspace is None else workspace.numel(), _stream()),
-        "ot_tree_verify_attention")
-    return out
+        workspace = attn_workspace(attn_params(Q, K_prefix, V_prefix, K_tree, V_tree, softmax_scale=softmax_scale), Q.device)
+    st, o = (_binding or _native()).attention(Q, K_prefix, V_prefix, K_tree, V_tree, prefix_len, mask, out, workspace, softmax_scale)
+    if st:
+        raise OptTreeError(st, "ot_tree_verify_attention")
+    return o
 
 
 def tree_verify_attention_noalloc(Q, K_prefix, V_prefix, K_tree, V_tree, prefix_len, mask, out, softmax_scale=0.0):
@@ -375,90 +345,41 @@ def tree_verify_attention_fp8kv(Q, K_prefix, V_prefix, K_tree, V_tree, k_scale, 
                                 workspace=None, softmax_scale: float = 0.0):
     """ot_tree_verify_attention_fp8kv on the current stream.  Q bf16 [B,Hq,n,D]; K/V uint8 tensors of FP8 E4M3 bytes
     [B,Hkv,rows,D]; k_scale, v_scale float32 [B,Hkv]."""
-    import torch
-    for t in (K_prefix, V_prefix, K_tree, V_tree):
-        if t is not None and t.dtype != torch.uint8:
-            raise TypeError("the 8-bit cache is passed as uint8 tensors")
-    for t in (k_scale, v_scale):
-        if t.dtype != torch.float32 or not t.is_contiguous() or tuple(t.shape) != (Q.shape[0], K_tree.shape[1]):
-            raise ValueError("scales must be contiguous float32 [B, Hkv]")
-    p = attn_params(Q, K_prefix, V_prefix, K_tree, V_tree, softmax_scale=softmax_scale)
-    if out is None:
-        out = torch.empty_like(Q)
-    p.o_strides = (C.c_int64 * 3)(out.stride(0), out.stride(1), out.stride(2))
     if workspace is None:
-        workspace = attn_workspace(p, Q.device)
-    ptr = lambda t: None if t is None else t.data_ptr()
-    _check(lib().ot_tree_verify_attention_fp8kv(
-        C.byref(p), ptr(Q), ptr(K_prefix), ptr(V_prefix), ptr(K_tree), ptr(V_tree), ptr(k_scale), ptr(v_scale),
-        ptr(prefix_len), ptr(mask), ptr(out), ptr(workspace), workspace.numel(), _stream()),
-        "ot_tree_verify_attention_fp8kv")
-    return out
+        workspace = attn_workspace(attn_params(Q, K_prefix, V_prefix, K_tree, V_tree, softmax_scale=softmax_scale), Q.device)
+    st, o = (_binding or _native()).attention_fp8kv(Q, K_prefix, V_prefix, K_tree, V_tree, k_scale, v_scale, prefix_len, mask, out,
+                                                    workspace, softmax_scale)
+    if st:
+        raise OptTreeError(st, "ot_tree_verify_attention_fp8kv")
+    return o
 
 
 def verify_greedy(target_logits, tree: "Tree", workspace=None):
     """ot_verify_greedy on the current stream.  target_logits [B, n + 1, V] (row 0 = the root position);
     returns (accept_len [B], accept_node [B, n], accept_token [B, n + 1]) as int32 device tensors."""
-    import torch
-    if target_logits.dim() != 3 or target_logits.stride(2) != 1:
-        raise ValueError("target_logits must be [B, n + 1, V] with a contiguous last dimension")
-    B, rows, V = target_logits.shape
-    n = rows - 1
-    p = VerifyParams(B, V, n, _dtype_code(target_logits), target_logits.stride(0), target_logits.stride(1))
-    need = int(lib().ot_verify_workspace_bytes(C.byref(p)))
-    if need == 0:
-        raise OptTreeError(-2, "ot_verify_workspace_bytes")
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=target_logits.device)
-    dev = target_logits.device
-    accept_len = torch.empty(B, dtype=torch.int32, device=dev)
-    accept_node = torch.empty((B, n), dtype=torch.int32, device=dev)
-    accept_token = torch.empty((B, n + 1), dtype=torch.int32, device=dev)
-    _check(lib().ot_verify_greedy(C.byref(p), target_logits.data_ptr(), tree.token.data_ptr(), tree.parent.data_ptr(),
-                                  tree.n_out.data_ptr(), workspace.data_ptr(), workspace.numel(),
-                                  accept_len.data_ptr(), accept_node.data_ptr(), accept_token.data_ptr(), _stream()),
-           "ot_verify_greedy")
-    return accept_len, accept_node, accept_token
+    st, length, node, token = (_binding or _native()).verify(target_logits, None, 0.0, tree.token, tree.parent, tree.n_out, workspace)
+    if st:
+        raise OptTreeError(-2, "ot_verify_workspace_bytes") if length is None else OptTreeError(st, "ot_verify_greedy")
+    return length, node, token
 
 
 def verify_sample(target_logits, u, temperature, tree: "Tree", workspace=None):
     """ot_verify_sample on the current stream.  target_logits [B, n + 1, V]; u float32 [B, n + 1] uniform
     numbers in [0, 1), one per target row; returns (accept_len, accept_node, accept_token) as in
     verify_greedy."""
-    import torch
-    if target_logits.dim() != 3 or target_logits.stride(2) != 1:
-        raise ValueError("target_logits must be [B, n + 1, V] with a contiguous last dimension")
-    B, rows, V = target_logits.shape
-    n = rows - 1
-    if u.dtype != torch.float32 or tuple(u.shape) != (B, rows) or not u.is_contiguous():
-        raise ValueError("u must be a contiguous float32 tensor [B, n + 1]")
-    p = VerifyParams(B, V, n, _dtype_code(target_logits), target_logits.stride(0), target_logits.stride(1))
-    need = int(lib().ot_verify_sample_workspace_bytes(C.byref(p)))
-    if need == 0:
-        raise OptTreeError(-2, "ot_verify_sample_workspace_bytes")
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=target_logits.device)
-    dev = target_logits.device
-    accept_len = torch.empty(B, dtype=torch.int32, device=dev)
-    accept_node = torch.empty((B, n), dtype=torch.int32, device=dev)
-    accept_token = torch.empty((B, n + 1), dtype=torch.int32, device=dev)
-    _check(lib().ot_verify_sample(C.byref(p), C.c_float(temperature), target_logits.data_ptr(), u.data_ptr(),
-                                  tree.token.data_ptr(), tree.parent.data_ptr(), tree.n_out.data_ptr(),
-                                  workspace.data_ptr(), workspace.numel(), accept_len.data_ptr(),
-                                  accept_node.data_ptr(), accept_token.data_ptr(), _stream()), "ot_verify_sample")
-    return accept_len, accept_node, accept_token
+    st, length, node, token = (_binding or _native()).verify(target_logits, u, temperature, tree.token, tree.parent, tree.n_out,
+                                                             workspace)
+    if st:
+        raise OptTreeError(-2, "ot_verify_sample_workspace_bytes") if length is None else OptTreeError(st, "ot_verify_sample")
+    return length, node, token
 
 
 def kv_append(K_prefix, V_prefix, K_tree, V_tree, prefix_len, accept_len, accept_node):
     """ot_kv_append on the current stream: the accepted nodes' K/V rows are appended to the prefix cache in
     place; returns the new prefix lengths (int32 [B])."""
-    import torch
-    B, Hkv, n, D = K_tree.shape
-    p = attn_params(K_tree, K_prefix, V_prefix, K_tree, V_tree)
-    new_len = torch.empty(B, dtype=torch.int32, device=K_tree.device)
-    _check(lib().ot_kv_append(C.byref(p), K_prefix.data_ptr(), V_prefix.data_ptr(), K_tree.data_ptr(),
-                              V_tree.data_ptr(), prefix_len.data_ptr(), accept_len.data_ptr(),
-                              accept_node.data_ptr(), new_len.data_ptr(), _stream()), "ot_kv_append")
+    st, new_len = (_binding or _native()).kv_append(K_prefix, V_prefix, K_tree, V_tree, prefix_len, accept_len, accept_node)
+    if st:
+        raise OptTreeError(st, "ot_kv_append")
     return new_len
 
 
@@ -478,9 +399,10 @@ class PreparedBuild:
         self.out = alloc_tree(self.p.batch, n, logits.device)
         self.o = self.out.c_struct()
         self._args = (C.byref(self.p), logits.data_ptr(), self.ws.data_ptr(), self.ws.numel(), C.byref(self.o))
+        self._run = _native().prepare_build(logits, k, n, depth, self.ws, self.out)
 
     def __call__(self, stream: int):
-        st = lib().ot_build_tree(*self._args, stream)
+        st = self._run(stream)
         if st:
             raise OptTreeError(st, "ot_build_tree")
 
@@ -500,9 +422,11 @@ class PreparedAttention:
         ptr = lambda t: None if t is None else t.data_ptr()
         self._args = (C.byref(self.p), ptr(Q), ptr(K_prefix), ptr(V_prefix), ptr(K_tree), ptr(V_tree),
                       ptr(prefix_len), ptr(mask), ptr(self.out), self.ws.data_ptr(), self.ws.numel())
+        self._run = _native().prepare_attention(Q, K_prefix, V_prefix, K_tree, V_tree, prefix_len, mask, self.out, self.ws,
+                                                softmax_scale)
 
     def __call__(self, stream: int):
-        st = lib().ot_tree_verify_attention(*self._args, stream)
+        st = self._run(stream)
         if st:
             raise OptTreeError(st, "ot_tree_verify_attention")
 

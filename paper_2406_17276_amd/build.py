@@ -1,14 +1,18 @@
-"""Compile the HIP sources into libopttree.so for gfx950 (in-tree, next to the sources)."""
+"""Compile the HIP sources into libopttree.so for gfx950 and the Python binding's native half into _binding.so
+(in-tree, next to the sources)."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libopttree.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["api.hip", "row_scan.hip", "tree_select.hip", "tree_attn.hip", "verify.hip", "yardstick.hip"]
 
 FLAGS = [
@@ -41,6 +45,9 @@ def build(verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    binding_obj = os.path.join(objdir, "binding.o")
+    procs.append(("binding.cpp", subprocess.Popen(binding_compile_command(binding_obj), stdout=subprocess.PIPE,
+                                                  stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, pr in procs:
         out, _ = pr.communicate()
@@ -54,8 +61,25 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed")
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.run(cmd, check=True)
+    torch_lib = os.path.join(torch_dir(), "lib")
+    subprocess.run(["g++", "-shared", "-o", BINDING, binding_obj, "-L" + HERE, "-lopttree", "-Wl,-rpath,$ORIGIN", "-L" + torch_lib,
+                    "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + torch_lib], check=True)
     build_abi_client()
     return LIB
+
+
+def torch_dir() -> str:
+    return os.path.dirname(importlib.util.find_spec("torch").origin)
+
+
+def binding_compile_command(obj: str):
+    """Host code only (tensors in, library calls, tensors out): the host compiler against torch's headers."""
+    inc = os.path.join(torch_dir(), "include")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-std=c++17", "-O2", "-fPIC", "-fvisibility=hidden", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-isystem", inc,
+            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
 
 
 def build_abi_client() -> str:

@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include "common.hpp"
+#include "internal.h"
 
 namespace ot {
 
@@ -214,7 +215,8 @@ int ot_build_tree_adaptive(const ot_build_params* p, double delta, const void* l
     return launch_tree_adaptive(g, delta, ws, *out, steps_used, e_sub, s);
 }
 
-int ot_tree_begin(const ot_build_params* p, void* workspace, size_t workspace_bytes, void* hip_stream) {
+static int begin_entry(const ot_build_params* p, void* workspace, size_t workspace_bytes, int32_t* frontier_token,
+                       int32_t* frontier_parent, int32_t* frontier_count, void* hip_stream) {
     int st = validate_build(p, false);
     if (st != OT_OK) return st;
     if (!workspace || (uintptr_t)workspace % 16) return OT_ERR_INVALID_ARG;
@@ -222,7 +224,18 @@ int ot_tree_begin(const ot_build_params* p, void* workspace, size_t workspace_by
     if (workspace_bytes < ws.bytes) return OT_ERR_WORKSPACE_TOO_SMALL;
     // every step overwrites the pool state it owns; only the per-sequence loop state (E = 0, no layer, not
     // stopped) has to be set
-    return launch_tree_begin(select_geometry(*p, make_frontier(p->k, p->n, p->depth)), ws, (hipStream_t)hip_stream);
+    return launch_tree_begin(select_geometry(*p, make_frontier(p->k, p->n, p->depth)), ws, (hipStream_t)hip_stream, frontier_token,
+                             frontier_parent, frontier_count);
+}
+
+int ot_tree_begin(const ot_build_params* p, void* workspace, size_t workspace_bytes, void* hip_stream) {
+    return begin_entry(p, workspace, workspace_bytes, nullptr, nullptr, nullptr, hip_stream);
+}
+
+int ot_internal_tree_begin(const ot_build_params* p, void* workspace, size_t workspace_bytes, int32_t* frontier_token,
+                           int32_t* frontier_parent_slot, int32_t* frontier_count, void* hip_stream) {
+    if (!frontier_token || !frontier_parent_slot || !frontier_count) return OT_ERR_INVALID_ARG;
+    return begin_entry(p, workspace, workspace_bytes, frontier_token, frontier_parent_slot, frontier_count, hip_stream);
 }
 
 int ot_tree_expand(const ot_build_params* p, int32_t step, const void* rows, int64_t stride_seq, int64_t stride_row,

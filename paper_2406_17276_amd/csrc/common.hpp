@@ -86,7 +86,8 @@ int launch_tree_step(const SelectGeometry& g, int step, const BuildWorkspace& ws
                      int32_t* frontier_parent, int32_t* frontier_count, hipStream_t s);
 int launch_tree_finalize(const SelectGeometry& g, int steps_done, const BuildWorkspace& ws, const ot_tree_out& out,
                          hipStream_t s);
-int launch_tree_begin(const SelectGeometry& g, const BuildWorkspace& ws, hipStream_t s);
+int launch_tree_begin(const SelectGeometry& g, const BuildWorkspace& ws, hipStream_t s, int32_t* frontier_token = nullptr,
+                      int32_t* frontier_parent = nullptr, int32_t* frontier_count = nullptr);
 bool tree_adaptive_supported(const SelectGeometry& g);
 int launch_tree_adaptive(const SelectGeometry& g, double delta, const BuildWorkspace& ws, const ot_tree_out& out,
                          int32_t* steps_used, double* e_sub, hipStream_t s);

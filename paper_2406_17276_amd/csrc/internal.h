@@ -1,0 +1,17 @@
+/* Library entry points that only the Python binding uses (not part of the public header). */
+#pragma once
+
+#include "opttree.h"
+
+#ifdef __cplusplus
+extern "C" {
+#endif
+
+/* ot_tree_begin that also sets the caller's frontier arrays in the same launch: token and parent slot [batch][n] to -1,
+ * count [batch] to 0. */
+OT_API int ot_internal_tree_begin(const ot_build_params* p, void* workspace, size_t workspace_bytes, int32_t* frontier_token,
+                                  int32_t* frontier_parent_slot, int32_t* frontier_count, void* hip_stream);
+
+#ifdef __cplusplus
+}
+#endif

@@ -781,9 +781,15 @@ __global__ __launch_bounds__(256) void tree_front_mask_kernel(const SelKArgs a) 
     }
 }
 
-__global__ void tree_begin_kernel(double* seq_E, int32_t* seq_steps, int32_t* seq_active, int batch) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < batch) { seq_E[b] = 0.0; seq_steps[b] = 0; seq_active[b] = 1; }
+// Loop state of every sequence; with frontier arrays given, these too (tokens and parents -1, counts 0).
+__global__ __launch_bounds__(256) void tree_begin_kernel(double* seq_E, int32_t* seq_steps, int32_t* seq_active, int batch, int n,
+                                                         int32_t* frontier_token, int32_t* frontier_parent, int32_t* frontier_count) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < batch) {
+        seq_E[i] = 0.0; seq_steps[i] = 0; seq_active[i] = 1;
+        if (frontier_count) frontier_count[i] = 0;
+    }
+    if (frontier_token && i < batch * n) { frontier_token[i] = -1; frontier_parent[i] = -1; }
 }
 
 // ---------------------------------------------------------------------------
@@ -1482,9 +1488,12 @@ int launch_esub_t(const SelKArgs& a, int batch, int NT, hipStream_t s) {
     return OT_OK;
 }
 
-int launch_tree_begin(const SelectGeometry& g, const BuildWorkspace& ws, hipStream_t s) {
-    hipLaunchKernelGGL(tree_begin_kernel, dim3((g.batch + 255) / 256), dim3(256), 0, s, ws.seq_E, ws.seq_steps,
-                       ws.seq_active, g.batch);
+int launch_tree_begin(const SelectGeometry& g, const BuildWorkspace& ws, hipStream_t s, int32_t* frontier_token,
+                      int32_t* frontier_parent, int32_t* frontier_count) {
+    const long long items = frontier_token ? (long long)g.batch * g.n : g.batch;
+    if (items > 0x7fffffffLL - 256) return OT_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(tree_begin_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, ws.seq_E, ws.seq_steps,
+                       ws.seq_active, g.batch, g.n, frontier_token, frontier_parent, frontier_count);
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
