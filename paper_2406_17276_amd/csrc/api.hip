@@ -84,11 +84,6 @@ static int check_tree_out(const ot_tree_out* o) {
     return OT_OK;
 }
 
-__global__ void copy_i32_kernel(const int32_t* src, int32_t* dst, int count) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) dst[i] = src[i];
-}
-
 static SelectGeometry select_geometry(const ot_build_params& p, const Frontier& f) {
     SelectGeometry g;
     g.batch = p.batch; g.k = p.k; g.n = p.n; g.depth = p.depth;
@@ -124,8 +119,15 @@ size_t ot_build_workspace_bytes(const ot_build_params* p) {
     return carve_build_workspace(*p, nullptr).bytes;
 }
 
-static int build_entry(const ot_build_params* p, const void* logits, void* workspace, size_t workspace_bytes,
-                       const ot_tree_out* out, void* hip_stream, void* ev0, void* ev1) {
+// One-shot build: the rows of all steps are scanned, then the tree is drafted from their statistics.  A tree is usually
+// complete long before the last step (tree_build.hip), so big inputs go in chunks of steps: scan a chunk, draft it, and
+// leave the rows of finished sequences unread from then on.  A chunk costs two more launches and another pass over the
+// pool, about 8 us on the stream, so it has at least kChunkBytes of rows: some 20 us of reading at the rate of the scan.
+static const long long kChunkBytes = 96ll << 20;
+
+static int build_steps(const ot_build_params* p, bool adapt, double delta, const void* logits, void* workspace,
+                       size_t workspace_bytes, const ot_tree_out* out, int32_t* steps_used, double* e_sub, void* hip_stream,
+                       void* ev0, void* ev1) {
     int st = validate_build(p, true);
     if (st != OT_OK) return st;
     if (!logits || !workspace) return OT_ERR_INVALID_ARG;
@@ -137,6 +139,7 @@ static int build_entry(const ot_build_params* p, const void* logits, void* works
     const BuildWorkspace ws = carve_build_workspace(*p, workspace);
     if (workspace_bytes < ws.bytes) return OT_ERR_WORKSPACE_TOO_SMALL;
     const Frontier f = make_frontier(p->k, p->n, p->depth);
+    const SelectGeometry g = select_geometry(*p, f);
     hipStream_t s = (hipStream_t)hip_stream;
 
     ScanGeometry sg;
@@ -144,19 +147,31 @@ static int build_entry(const ot_build_params* p, const void* logits, void* works
     sg.nsteps = p->depth; sg.rows_per_seq = f.rows;
     sg.grow_k = p->k; sg.grow_n = p->n;
     sg.stride_seq = p->stride_seq; sg.stride_depth = p->stride_depth; sg.stride_row = p->stride_row;
-    st = launch_row_scan(sg, logits, ws, s, (hipEvent_t)ev0, (hipEvent_t)ev1);
-    if (st != OT_OK) return st;
-    return launch_tree_oneshot(select_geometry(*p, f), ws, *out, s);
+    const long long row_bytes = (long long)p->batch * p->vocab * esize;
+    for (int t0 = 0; t0 < p->depth;) {
+        int t1 = t0 + 1;
+        while (t1 < p->depth && (f.row_start[t1] - f.row_start[t0]) * row_bytes < kChunkBytes) ++t1;
+        if ((f.rows - f.row_start[t1]) * row_bytes < kChunkBytes) t1 = p->depth;
+        if (ev0 || ev1) t1 = p->depth;                         // the timed form brackets one scan of everything
+        sg.row0 = f.row_start[t0]; sg.rows = f.row_start[t1] - f.row_start[t0];
+        st = launch_row_scan(sg, logits, ws, s, (hipEvent_t)ev0, (hipEvent_t)ev1, t0 > 0);
+        if (st != OT_OK) return st;
+        st = launch_tree_build(g, t0, t1, adapt, delta, ws, *out, steps_used, e_sub, s);
+        if (st != OT_OK) return st;
+        t0 = t1;
+    }
+    return OT_OK;
 }
 
 int ot_build_tree(const ot_build_params* p, const void* logits, void* workspace, size_t workspace_bytes,
                   const ot_tree_out* out, void* hip_stream) {
-    return build_entry(p, logits, workspace, workspace_bytes, out, hip_stream, nullptr, nullptr);
+    return build_steps(p, false, 0.0, logits, workspace, workspace_bytes, out, nullptr, nullptr, hip_stream, nullptr, nullptr);
 }
 
 int ot_build_tree_timed(const ot_build_params* p, const void* logits, void* workspace, size_t workspace_bytes,
                         const ot_tree_out* out, void* hip_stream, void* scan_begin_event, void* scan_end_event) {
-    return build_entry(p, logits, workspace, workspace_bytes, out, hip_stream, scan_begin_event, scan_end_event);
+    return build_steps(p, false, 0.0, logits, workspace, workspace_bytes, out, nullptr, nullptr, hip_stream, scan_begin_event,
+                       scan_end_event);
 }
 
 int ot_build_tree_adaptive(const ot_build_params* p, double delta, const void* logits, void* workspace,
@@ -165,54 +180,8 @@ int ot_build_tree_adaptive(const ot_build_params* p, double delta, const void* l
     int st = validate_build(p, true);
     if (st != OT_OK) return st;
     if (!(delta == delta)) return OT_ERR_INVALID_ARG;
-    if (!logits || !workspace || !steps_used || !e_sub) return OT_ERR_INVALID_ARG;
-    if ((uintptr_t)workspace % 16 || (uintptr_t)steps_used % 4 || (uintptr_t)e_sub % 8) return OT_ERR_INVALID_ARG;
-    const int esize = p->logits_dtype == OT_BF16 ? 2 : 4;
-    if ((uintptr_t)logits % esize) return OT_ERR_INVALID_ARG;
-    st = check_tree_out(out);
-    if (st != OT_OK) return st;
-    const Frontier f = make_frontier(p->k, p->n, p->depth);
-    const SelectGeometry g = select_geometry(*p, f);
-    const BuildWorkspace ws = carve_build_workspace(*p, workspace);
-    if (workspace_bytes < ws.bytes) return OT_ERR_WORKSPACE_TOO_SMALL;
-    hipStream_t s = (hipStream_t)hip_stream;
-    if (!tree_adaptive_supported(g)) {
-        // Shapes beyond the single-wavefront kernel (n > 64, large pools): the loop of Algorithm 1 as the streaming
-        // entry points run it, step by step on the stream -- scan of the step's F_t rows, selection, E_sub and the
-        // loop condition, all decided on the device (a sequence that stops is frozen there: later steps skip it,
-        // the final selection uses the layers it had), so the host neither waits nor reads anything back.  The
-        // frontier lists and the per-step decisions land in the output arrays, which the final selection overwrites.
-        st = launch_tree_begin(g, ws, s);
-        if (st != OT_OK) return st;
-        for (int t = 0; t < p->depth; ++t) {
-            ScanGeometry sg;
-            sg.batch = p->batch; sg.vocab = p->vocab; sg.k = p->k; sg.dtype = p->logits_dtype;
-            sg.nsteps = 1; sg.rows_per_seq = f.F[t];
-            sg.grow_k = 1; sg.grow_n = 1;
-            sg.stride_seq = p->stride_seq; sg.stride_depth = 0; sg.stride_row = p->stride_row;
-            st = launch_row_scan(sg, (const char*)logits + (size_t)t * p->stride_depth * esize, ws, s, nullptr, nullptr, true);
-            if (st != OT_OK) return st;
-            SelectGeometry gs = g;
-            gs.rows_per_seq = f.F[t];
-            st = launch_tree_step(gs, t, ws, out->token, out->parent, nullptr, s);
-            if (st != OT_OK) return st;
-            st = launch_tree_esub(g, t + 1, delta, ws, e_sub, out->depth, s);
-            if (st != OT_OK) return st;
-        }
-        st = launch_tree_finalize(g, p->depth, ws, *out, s);
-        if (st != OT_OK) return st;
-        hipLaunchKernelGGL(copy_i32_kernel, dim3((p->batch + 255) / 256), dim3(256), 0, s, ws.seq_steps, steps_used, p->batch);
-        OT_HIP_CHECK(hipGetLastError());
-        return OT_OK;
-    }
-    ScanGeometry sg;
-    sg.batch = p->batch; sg.vocab = p->vocab; sg.k = p->k; sg.dtype = p->logits_dtype;
-    sg.nsteps = p->depth; sg.rows_per_seq = f.rows;
-    sg.grow_k = p->k; sg.grow_n = p->n;
-    sg.stride_seq = p->stride_seq; sg.stride_depth = p->stride_depth; sg.stride_row = p->stride_row;
-    st = launch_row_scan(sg, logits, ws, s);
-    if (st != OT_OK) return st;
-    return launch_tree_adaptive(g, delta, ws, *out, steps_used, e_sub, s);
+    if (!steps_used || !e_sub || (uintptr_t)steps_used % 4 || (uintptr_t)e_sub % 8) return OT_ERR_INVALID_ARG;
+    return build_steps(p, true, delta, logits, workspace, workspace_bytes, out, steps_used, e_sub, hip_stream, nullptr, nullptr);
 }
 
 static int begin_entry(const ot_build_params* p, void* workspace, size_t workspace_bytes, int32_t* frontier_token,
@@ -258,7 +227,7 @@ int ot_tree_expand(const ot_build_params* p, int32_t step, const void* rows, int
 
     ScanGeometry sg;
     sg.batch = p->batch; sg.vocab = p->vocab; sg.k = p->k; sg.dtype = p->logits_dtype;
-    sg.nsteps = 1; sg.rows_per_seq = f.F[step];
+    sg.nsteps = 1; sg.rows_per_seq = f.F[step]; sg.row0 = 0; sg.rows = f.F[step];
     sg.grow_k = 1; sg.grow_n = 1;
     sg.stride_seq = stride_seq; sg.stride_depth = 0; sg.stride_row = stride_row;
     st = launch_row_scan(sg, rows, ws, s, nullptr, nullptr, true);      // rows of frozen sequences are not read

@@ -64,8 +64,9 @@ BuildWorkspace carve_build_workspace(const ot_build_params& p, void* base);
 // rows_per_seq rows: one plain block of rows).  Row (b, t, j) is at base + b*ss + t*sd + j*sr.
 struct ScanGeometry {
     int batch, vocab, k, dtype;
-    int nsteps;                       // steps covered by this launch
-    int rows_per_seq;
+    int nsteps;                       // steps a sequence has
+    int rows_per_seq;                 // rows a sequence has = stride of the per-row results
+    int row0, rows;                   // rows row0 .. row0 + rows - 1 of every sequence are scanned by this launch
     int grow_k, grow_n;               // frontier growth; unused when nsteps == 1
     long long stride_seq, stride_depth, stride_row;
 };
@@ -81,16 +82,17 @@ struct SelectGeometry {
     int F[OT_MAX_DEPTH + 2];
     int row_start[OT_MAX_DEPTH + 2];
 };
-int launch_tree_oneshot(const SelectGeometry& g, const BuildWorkspace& ws, const ot_tree_out& out, hipStream_t s);
+// Steps t0 .. t1-1 of a one-shot build (rows of these steps scanned); adapt: with the stopping rule of Algorithm 1.
+// The launch with t1 = depth, or the one in which a sequence's tree is complete, writes that sequence's outputs; with
+// several launches per build ws.seq_active says which sequences go on.
+int launch_tree_build(const SelectGeometry& g, int t0, int t1, bool adapt, double delta, const BuildWorkspace& ws,
+                      const ot_tree_out& out, int32_t* steps_used, double* e_sub, hipStream_t s);
 int launch_tree_step(const SelectGeometry& g, int step, const BuildWorkspace& ws, int32_t* frontier_token,
                      int32_t* frontier_parent, int32_t* frontier_count, hipStream_t s);
 int launch_tree_finalize(const SelectGeometry& g, int steps_done, const BuildWorkspace& ws, const ot_tree_out& out,
                          hipStream_t s);
 int launch_tree_begin(const SelectGeometry& g, const BuildWorkspace& ws, hipStream_t s, int32_t* frontier_token = nullptr,
                       int32_t* frontier_parent = nullptr, int32_t* frontier_count = nullptr);
-bool tree_adaptive_supported(const SelectGeometry& g);
-int launch_tree_adaptive(const SelectGeometry& g, double delta, const BuildWorkspace& ws, const ot_tree_out& out,
-                         int32_t* steps_used, double* e_sub, hipStream_t s);
 int launch_tree_front_mask(const SelectGeometry& g, int steps_done, const BuildWorkspace& ws, uint64_t* mask_out,
                            int mask_words, hipStream_t s);
 int launch_tree_esub(const SelectGeometry& g, int steps_done, double delta, const BuildWorkspace& ws, double* e_sub,
@@ -203,6 +205,24 @@ __device__ __forceinline__ double wave_sum_rows_d(float v) {
     v += __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(v), __float_as_int(v)));
     v += __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(v), __float_as_int(v)));
     return ((double)rl_f(v, 0) + (double)rl_f(v, 16)) + ((double)rl_f(v, 32) + (double)rl_f(v, 48));
+}
+// inclusive prefix sum inside the wavefront: Kogge-Stone inside rows (row_shr, zero fill), then row totals
+__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    const int t0 = rl(v, 15), t1 = rl(v, 31), t2 = rl(v, 47);
+    const int row = lane >> 4;
+    return v + (row > 0 ? t0 : 0) + (row > 1 ? t1 : 0) + (row > 2 ? t2 : 0);
+}
+// p^ = e^key for key <= 0, to about 1e-7 relative: fp32 exp2 of the leading part of key * log2(e), first-order
+// correction for the remainder (an fp64 exp costs an order of magnitude more instructions)
+__device__ __forceinline__ double exp_of_logp(double key) {
+    const double t = key * 1.4426950408889634;
+    const float hi = (float)t;
+    const double lo = t - (double)hi;
+    return (double)__builtin_amdgcn_exp2f(hi) * (1.0 + lo * 0.6931471805599453);
 }
 // max over the wavefront as a scalar
 __device__ __forceinline__ float wave_max_f(float v) {

@@ -30,7 +30,8 @@ constexpr long long kScanMaxGrid = 16384;      // workgroups per launch; more it
 
 struct ScanKArgs {
     int vocab, k, parts, part_elems;
-    int items;                        // rows x parts
+    int items;                        // rows of the launch x parts
+    int rows_per_seq;                 // stride of the per-row results
     // P == 1: final row results; P > 1: per-part results
     double* row_lse; float* row_topv; int32_t* row_topi;
     float* part_m; double* part_s; float* part_topv; int32_t* part_topi;
@@ -50,7 +51,7 @@ struct ScanHead {
     long long stride_seq, stride_depth, stride_row;
     int vocab;
     int part_geom;                    // parts | part_elems << 4
-    int rows_per_seq;
+    int rows;                         // rows of a sequence in this launch | first row << 16
     int grow;                         // nsteps | k << 8 | n << 16: step t covers F_t rows, F_0 = 1, F_{t+1} = min(n, k F_t)
 };
 
@@ -74,10 +75,11 @@ __device__ __forceinline__ void scan_item(const ScanHead& h, const ScanKArgs& a,
 
     const int tid = threadIdx.x;
     const int parts = h.part_geom & 15, part_elems = h.part_geom >> 4;
-    const int rid = wg / parts;
-    const int part = wg - rid * parts;
-    const int b = rid / h.rows_per_seq;
-    const int r = rid - b * h.rows_per_seq;
+    const int lrow = wg / parts;                      // row of this launch
+    const int part = wg - lrow * parts;
+    const int rows = h.rows & 0xffff;
+    const int b = lrow / rows;
+    const int r = (h.rows >> 16) + lrow - b * rows;
     // row r of a sequence is slot j of step t (Algorithm 1: the frontier grows k-fold per step up to n)
     const int nsteps = h.grow & 255, grow_k = (h.grow >> 8) & 255, grow_n = h.grow >> 16;
     int t = 0, start = 0, F = 1;
@@ -215,14 +217,15 @@ __device__ __forceinline__ void scan_item(const ScanHead& h, const ScanKArgs& a,
     __syncthreads();
     const int ncand = s_count;
 
+    const int rid = b * a.rows_per_seq + r;
     // where the k winners of this part go
     float* outv; int32_t* outi;
     if (a.parts == 1) {
         outv = a.row_topv + (size_t)rid * a.k;
         outi = a.row_topi + (size_t)rid * a.k;
     } else {
-        outv = a.part_topv + (size_t)wg * a.k;
-        outi = a.part_topi + (size_t)wg * a.k;
+        outv = a.part_topv + ((size_t)rid * parts + part) * a.k;
+        outi = a.part_topi + ((size_t)rid * parts + part) * a.k;
     }
     // ---- 5a. combine the wave partials in fp64 (last wavefront, 16 lanes) --
     if (wave == NW - 1 && lane < 16) {
@@ -244,8 +247,8 @@ __device__ __forceinline__ void scan_item(const ScanHead& h, const ScanKArgs& a,
                 // M by the same c puts the reference back into natural-log units without a bias in the constant
                 a.row_lse[rid] = (double)M / (double)kLog2e + log(part_sum);
             } else {
-                a.part_m[wg] = M;
-                a.part_s[wg] = part_sum;
+                a.part_m[(size_t)rid * parts + part] = M;
+                a.part_s[(size_t)rid * parts + part] = part_sum;
             }
         }
     }
@@ -381,25 +384,25 @@ __device__ __forceinline__ void scan_item(const ScanHead& h, const ScanKArgs& a,
 // much as a small item's share of the memory traffic.
 // SKIP: the scan of one drafting step in the loop of Algorithm 1 -- a sequence that the stopping rule has frozen
 // drafts no further, and its rows are not read (the flag is the step kernel's own, on the device).
-__device__ __forceinline__ bool scan_item_frozen(const ScanKArgs& a, int part_geom, int rows_per_seq, int wg) {
-    const int rid = wg / (part_geom & 15);
-    return a.seq_active[rid / rows_per_seq] == 0;
+__device__ __forceinline__ bool scan_item_frozen(const ScanKArgs& a, int part_geom, int rows, int wg) {
+    const int lrow = wg / (part_geom & 15);
+    return a.seq_active[lrow / (rows & 0xffff)] == 0;
 }
 template <int DT, int NT, int EPL, bool VECLOAD, bool SKIP>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT == 1024 && VECLOAD) ? 8 : 4, 8))) void row_scan_kernel(
     const void* logits, const long long stride_seq, const long long stride_depth, const long long stride_row,
-    const int vocab, const int part_geom, const int rows_per_seq, const int grow, const ScanKArgs a) {
-    if (SKIP && scan_item_frozen(a, part_geom, rows_per_seq, blockIdx.x)) return;
-    const ScanHead h{logits, stride_seq, stride_depth, stride_row, vocab, part_geom, rows_per_seq, grow};
+    const int vocab, const int part_geom, const int rows, const int grow, const ScanKArgs a) {
+    if (SKIP && scan_item_frozen(a, part_geom, rows, blockIdx.x)) return;
+    const ScanHead h{logits, stride_seq, stride_depth, stride_row, vocab, part_geom, rows, grow};
     scan_item<DT, NT, EPL, VECLOAD>(h, a, blockIdx.x);
 }
 template <int DT, int NT, int EPL, bool VECLOAD, bool SKIP>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT == 1024 && VECLOAD) ? 8 : 4, 8))) void row_scan_strided_kernel(
     const void* logits, const long long stride_seq, const long long stride_depth, const long long stride_row,
-    const int vocab, const int part_geom, const int rows_per_seq, const int grow, const ScanKArgs a) {
-    const ScanHead h{logits, stride_seq, stride_depth, stride_row, vocab, part_geom, rows_per_seq, grow};
+    const int vocab, const int part_geom, const int rows, const int grow, const ScanKArgs a) {
+    const ScanHead h{logits, stride_seq, stride_depth, stride_row, vocab, part_geom, rows, grow};
     for (int wg = blockIdx.x; wg < a.items; wg += gridDim.x) {
-        if (SKIP && scan_item_frozen(a, part_geom, rows_per_seq, wg)) continue;      // (the whole workgroup skips)
+        if (SKIP && scan_item_frozen(a, part_geom, rows, wg)) continue;      // (the whole workgroup skips)
         scan_item<DT, NT, EPL, VECLOAD>(h, a, wg);
         if (wg + (int)gridDim.x < a.items) __syncthreads();      // the next item reuses the shared arrays
     }
@@ -409,15 +412,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT == 1024 
 // One wavefront per row: the parts' statistics sit in the first lanes, the parts * k <= 128 candidates go through
 // LDS and every lane ranks its (at most two) candidates by counting those that precede them (value desc, token
 // asc: tokens of different parts differ, so the order is total); ranks below k are the row's list.
-__global__ __launch_bounds__(256) void merge_parts_kernel(int rows, int parts, int k, const float* part_m,
+__global__ __launch_bounds__(256) void merge_parts_kernel(int items, int rows, int row0, int rows_per_seq, const int32_t* seq_active,
+                                                          int parts, int k, const float* part_m,
                                                           const double* part_s, const float* part_topv,
                                                           const int32_t* part_topi, double* row_lse, float* row_topv,
                                                           int32_t* row_topi) {
     __shared__ float s_v[4][128];
     __shared__ int s_i[4][128];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int rid = blockIdx.x * 4 + w;
-    const bool live = rid < rows;
+    const int lrow = blockIdx.x * 4 + w;              // row of this launch; sequence b, row row0 + j of it
+    const int b = min(lrow, items - 1) / rows, j = min(lrow, items - 1) - b * rows;
+    const int rid = b * rows_per_seq + row0 + j;
+    const bool live = lrow < items && !(seq_active && seq_active[b] == 0);
     const size_t base = (size_t)(live ? rid : 0) * parts;
     const int total = parts * k;
     // part_m is the part's reference exponent in log2 units (fp32 max times the fp32 log2e of the scan kernel)
@@ -470,17 +476,20 @@ int launch_row_scan(const ScanGeometry& g, const void* logits, const BuildWorksp
     a.row_lse = ws.row_lse; a.row_topv = ws.row_topv; a.row_topi = ws.row_topi;
     a.part_m = ws.part_m; a.part_s = ws.part_s; a.part_topv = ws.part_topv; a.part_topi = ws.part_topi;
     a.seq_active = skip_frozen ? ws.seq_active : nullptr;
+    a.rows_per_seq = g.rows_per_seq;
+    if (g.rows < 1 || g.row0 < 0 || g.row0 + g.rows > g.rows_per_seq || g.rows_per_seq > 0x7fff) return OT_ERR_INVALID_ARG;
+    const int rows_arg = g.rows | (g.row0 << 16);
 
     const bool aligned = ((uintptr_t)logits % 16 == 0) && (g.stride_seq % vec == 0) && (g.stride_depth % vec == 0) &&
                          (g.stride_row % vec == 0) && (g.vocab % vec == 0);
     const bool small = a.part_elems <= 256 * 32;
-    const long long rows = (long long)g.batch * g.rows_per_seq;
+    const long long rows = (long long)g.batch * g.rows;
     const long long grid = rows * parts;
     if (grid <= 0 || grid > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;
     a.items = (int)grid;
     const dim3 gd((unsigned)(grid <= kScanMaxGrid ? grid : kScanMaxGrid));
 
-#define OT_SCAN_ARGS logits, g.stride_seq, g.stride_depth, g.stride_row, g.vocab, part_geom, g.rows_per_seq, grow, a
+#define OT_SCAN_ARGS logits, g.stride_seq, g.stride_depth, g.stride_row, g.vocab, part_geom, rows_arg, grow, a
 #define OT_SCAN_LAUNCH2(DT, NT, VL, SK)                                                                  \
     do {                                                                                                 \
         if (grid > kScanMaxGrid) {                                                                       \
@@ -503,7 +512,7 @@ int launch_row_scan(const ScanGeometry& g, const void* logits, const BuildWorksp
     OT_HIP_CHECK(hipGetLastError());
     if (parts > 1) {
         hipLaunchKernelGGL(merge_parts_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
-                           (int)rows, parts, g.k, ws.part_m, ws.part_s, ws.part_topv, ws.part_topi, ws.row_lse,
+                           (int)rows, g.rows, g.row0, g.rows_per_seq, a.seq_active, parts, g.k, ws.part_m, ws.part_s, ws.part_topv, ws.part_topi, ws.row_lse,
                            ws.row_topv, ws.row_topi);
         OT_HIP_CHECK(hipGetLastError());
     }

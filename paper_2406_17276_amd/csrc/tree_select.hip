@@ -36,12 +36,10 @@ struct SelKArgs {
                                                               // paths, the node itself last
     u64* mask_out; int mask_words;                            // output of the frontier-mask query
     int gridDim_batch;                                        // batch size (the grid of these kernels)
-    int32_t* steps_used;                                      // [batch] output of the one-shot adaptive build
     ot_tree_out out;
     int32_t* frontier_token; int32_t* frontier_parent;        // [batch][n]         (streaming step)
     int32_t* frontier_count;                                  // [batch] or null    (streaming step)
     int step;
-    int rehearse;                                             // fast kernel: 1 if the launch has LDS for the rehearsing wavefront
 };
 
 __device__ __forceinline__ double nan_d() { return __longlong_as_double(0x7ff8000000000000ll); }   // "absent"
@@ -69,17 +67,6 @@ __device__ __forceinline__ double wave_min_d(double v) {
     v = fmin(v, dpp_d<DPP_ROW_MIRROR>(v));
     return fmin(fmin(rl_d(v, 0), rl_d(v, 16)), fmin(rl_d(v, 32), rl_d(v, 48)));
 }
-// inclusive prefix sum inside the wavefront: Kogge-Stone inside rows (row_shr, zero fill), then row totals
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-    const int t0 = rl(v, 15), t1 = rl(v, 31), t2 = rl(v, 47);
-    const int row = lane >> 4;
-    return v + (row > 0 ? t0 : 0) + (row > 1 ? t1 : 0) + (row > 2 ? t2 : 0);
-}
-
 // Barrier that orders LDS traffic only.  __syncthreads() would also wait for the global loads that
 // prefetch the next step's row statistics; nothing here communicates through global memory.
 template <bool SINGLE>
@@ -601,46 +588,6 @@ __device__ void finalize_tree(const SelKArgs& a, const Pool& P, int steps, int b
     for (int i_ = threadIdx.x; i_ < kBuckets + 4; i_ += blockDim.x) s_hist[i_] = 0; \
     __syncthreads();
 
-// One-shot: all steps in one launch, pool resident in LDS.
-template <int KMAX, int DMAX, bool SINGLE>
-__global__ __launch_bounds__(256) void tree_oneshot_kernel(const SelKArgs a) {
-    OT_SELECT_SHARED
-    const int NT = blockDim.x, tid = threadIdx.x, b = blockIdx.x, D = a.depth;
-    const Pool P = carve_pool(smem, D, NT, DMAX, KMAX);
-
-    double lse, nlse;
-    float v[KMAX], nv[KMAX];
-    int id[KMAX], nid[KMAX];
-    double lo0 = nan_d();
-    load_row<KMAX>(a, (long long)b * a.rows_per_seq + tid, tid < a.F[0], nlse, nv, nid);
-    for (int t = 0; t < D; ++t) {
-        const int F = a.F[t], Fn = a.F[t + 1];
-        const bool active = tid < F;
-        lse = nlse;
-#pragma unroll
-        for (int r = 0; r < KMAX; ++r) { v[r] = nv[r]; id[r] = nid[r]; }
-        if (t + 1 < D)   // next step's row: its address does not depend on the tree, fetch it now
-            load_row<KMAX>(a, (long long)b * a.rows_per_seq + a.row_start[t + 1] + tid, tid < Fn, nlse, nv, nid);
-        const double S = (t == 0 || !active) ? 0.0 : P.key[(t - 1) * NT + tid];
-        double ck[KMAX];
-        candidate_scores<KMAX>(S, lse, v, active, a.k, ck);
-        int cnt, off;
-        double tau;
-        layer_cut<KMAX, SINGLE>(ck, P.kt, s_hist, active, a.k, F, Fn, a.r0[t], g, cnt, off, tau);
-        if (tau == tau) lo0 = (lo0 == lo0) ? fmax(lo0, tau) : tau;
-#pragma unroll
-        for (int r = 0; r < KMAX; ++r) {
-            if (r < cnt) {
-                P.key[t * NT + off + r] = ck[r];
-                P.tok[t * NT + off + r] = id[r];
-                P.par[t * NT + off + r] = (unsigned char)tid;
-            }
-        }
-        lds_sync<SINGLE>();
-    }
-    finalize_tree<DMAX, SINGLE>(a, P, D, b, lo0, g, s_cntw, s_hist);
-}
-
 // Streaming: one drafting step; the pool lives in the caller's workspace between launches.
 template <int KMAX, bool SINGLE>
 __global__ __launch_bounds__(256) void tree_step_kernel(const SelKArgs a) {
@@ -792,539 +739,6 @@ __global__ __launch_bounds__(256) void tree_begin_kernel(double* seq_E, int32_t*
     if (frontier_token && i < batch * n) { frontier_token[i] = -1; frontier_parent[i] = -1; }
 }
 
-// ---------------------------------------------------------------------------
-// Fast path: n <= 64 (one wavefront owns the whole frontier, no barriers after the prologue) and the
-// row statistics of the whole tree fit in LDS.
-//   prologue  256 threads turn (top-k logits, lse) of every row into log-probabilities
-//             dl[row][r] = x - lse (fp64) in LDS; three of the four wavefronts then leave.
-//   step t    lane j: ck[r] = S_j + dl[row(t, j)][r] -- already sorted by rank; cut_sorted() finds how
-//             many of them survive; only (log p^, parent slot, rank) go to the pool, token ids are
-//             fetched at the end, for the nodes of the tree only.
-//   finish    final selection, then every tree node moves to the lane of its output index: the
-//             ancestor masks (one 64-bit word) are built with lane permutes by pointer doubling
-//             and all outputs are written with one store each.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_max_d(double v) {
-    v = fmax(v, dpp_d<DPP_QUAD_XOR1>(v));
-    v = fmax(v, dpp_d<DPP_QUAD_XOR2>(v));
-    v = fmax(v, dpp_d<DPP_ROW_HALF_MIRROR>(v));
-    v = fmax(v, dpp_d<DPP_ROW_MIRROR>(v));
-    return fmax(fmax(rl_d(v, 0), rl_d(v, 16)), fmax(rl_d(v, 32), rl_d(v, 48)));
-}
-
-// Bounds of a bracket do not have to be tight, only safe: a value not above the smallest (not below the
-// largest) of the lanes' doubles, from an fp32 reduction (one DPP instruction per stage) widened by more
-// than the conversion error.  NaN lanes are ignored; all NaN gives NaN.
-__device__ __forceinline__ double wave_lower_bound(double v) {
-    float f = (float)v;
-    f = fminf(f, __int_as_float(dpp_i<DPP_QUAD_XOR1>(__float_as_int(f), __float_as_int(f))));
-    f = fminf(f, __int_as_float(dpp_i<DPP_QUAD_XOR2>(__float_as_int(f), __float_as_int(f))));
-    f = fminf(f, __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(f), __float_as_int(f))));
-    f = fminf(f, __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(f), __float_as_int(f))));
-    const float m = fminf(fminf(rl_f(f, 0), rl_f(f, 16)), fminf(rl_f(f, 32), rl_f(f, 48)));
-    return (double)m - (fabs((double)m) * 1.2e-7 + 1e-30);
-}
-__device__ __forceinline__ double wave_upper_bound(double v) {
-    const float m = wave_max_f((float)v);
-    return (double)m + (fabs((double)m) * 1.2e-7 + 1e-30);
-}
-
-// The cut bucket of a 256-bin histogram (one wavefront; lane L scans bins 4L..4L+3 and clears them):
-// B = the bin that holds the T-th largest key, above = keys in higher bins, inb = keys in bin B,
-// total = all keys.  B = -1 if there are fewer than T keys.
-__device__ __forceinline__ void hist_cut(int* hist, int T, int L, int& B, int& above, int& inb, int& total) {
-    constexpr int BPL = kBuckets / 64;
-    int c[BPL];
-    int sum = 0;
-#pragma unroll
-    for (int i = 0; i < BPL; ++i) { c[i] = hist[BPL * L + i]; sum += c[i]; }
-#pragma unroll
-    for (int i = 0; i < BPL; ++i) hist[BPL * L + i] = 0;
-    const int P = wave_incl_scan(sum, L);
-    total = rl(P, 63);
-    const int above_lane = total - P;                 // keys in higher lanes' bins
-    const bool has = above_lane < T && above_lane + sum >= T;
-    int Bl = BPL * L, abl = above_lane, inl = 0;
-    bool found = false;
-#pragma unroll
-    for (int i = BPL - 1; i >= 0; --i) {              // highest bin first
-        if (!found) {
-            if (abl + c[i] >= T) { found = true; Bl = BPL * L + i; inl = c[i]; }
-            else abl += c[i];
-        }
-    }
-    const u64 bal = __ballot(has);
-    B = -1; above = 0; inb = 0;
-    if (bal != 0ull) {
-        const int src = __ffsll((long long)bal) - 1;
-        B = rl(Bl, src); above = rl(abl, src); inb = rl(inl, src);
-    }
-}
-
-// "Keep the `want` largest of the wavefront's keys" for keys that are sorted inside every lane.
-// ck: this lane's keys, descending, NaN = absent (NaN last).  lo: at least `want` keys are >= lo.
-// Result: exact = true: the cnt largest keys of this lane are kept (all kept keys are strictly larger
-// than all others).  exact = false: the keys > tau are kept (cnt of this lane's), and `need` of the
-// `total_eq` keys == tau, in an order the caller defines.
-// The survivors of a lane are a prefix of its list, so the search keeps two prefix lengths per lane,
-// a (certainly kept) <= b (kept or undecided), instead of per-key flags:
-//   two histogram levels (256 bins each) over [lower bound, largest key] narrow the undecided keys to
-//   one of 65536 cells; if the cut falls between two bins the answer is exact and the search is over,
-//   otherwise the pivot rounds finish on the few keys left.
-struct SortedCut {
-    int cnt;
-    bool exact;
-    double tau;
-    int need, total_eq;
-};
-template <int M>
-__device__ __forceinline__ SortedCut cut_sorted(const double (&ck)[M], double* kt, int* hist, int want, double lo,
-                                                int lane, Group<true>& g) {
-    SortedCut out;
-    out.exact = false; out.tau = lo; out.need = 0; out.total_eq = 0;
-    const double gmax = wave_upper_bound(ck[0]);       // only the bracket's upper end: need not be a key
-    int a = 0, b = 0;
-#pragma unroll
-    for (int r = 0; r < M; ++r) b += ck[r] >= lo ? 1 : 0;
-    int f_hi = 0, f_lo = 0;
-    if (gmax > lo) {
-        // u = (key - lo) * scale lies in [0, 256) for every key in [lo, gmax]; the factor below 256 absorbs
-        // the error of the approximate reciprocal.  Keys below lo or absent give u <= 0 or NaN -> bin 0,
-        // and are kept out by the prefix length b.
-        const double scale = 255.9 * __builtin_amdgcn_rcp(gmax - lo);
-        double u[M];
-#pragma unroll
-        for (int r = 0; r < M; ++r) u[r] = (ck[r] - lo) * scale;
-        for (int level = 0; level < 2; ++level) {
-            int bk[M];
-#pragma unroll
-            for (int r = 0; r < M; ++r) {
-                const int q = (int)u[r];              // saturating; NaN -> 0
-                bk[r] = q < 0 ? 0 : q;                // keys above the range (level 1) keep a value >= 256
-            }
-#pragma unroll
-            for (int r = 0; r < M; ++r)
-                if (r >= a && r < b) atomicAdd(&hist[bk[r]], 1);
-            lds_sync<true>();
-            const int T = want - f_hi;                // rank of the cut among the undecided keys
-            int B, above, inb, total;
-            hist_cut(hist, T, lane, B, above, inb, total);
-            if (level == 0) f_lo = total;
-            if (B < 0) break;                         // cannot happen (at least `want` keys are >= lo); be safe
-            int n_gt = 0, n_ge = 0;                   // prefix lengths: keys above bin B, keys in or above it
-#pragma unroll
-            for (int r = 0; r < M; ++r) { n_gt += bk[r] > B ? 1 : 0; n_ge += bk[r] >= B ? 1 : 0; }
-            n_ge = n_ge < b ? n_ge : b;               // bin 0 also collects the keys below the range
-            n_gt = n_gt < b ? n_gt : b;
-            if (above + inb == T) {                   // the cut falls between two bins
-                out.cnt = n_ge; out.exact = true;
-                return out;
-            }
-            a = n_gt; b = n_ge;
-            f_hi += above; f_lo = f_hi + inb;
-#pragma unroll
-            for (int r = 0; r < M; ++r) u[r] = (u[r] - (double)B) * (double)kBuckets;
-        }
-    } else {
-        f_lo = wave_sum_u(b);                          // every key >= lo equals lo
-    }
-    Range rg;
-    rg.a = a; rg.b = b; rg.f_hi = f_hi; rg.f_lo = f_lo; rg.lo = lo;
-    rg = pivot_rounds<M, true>(ck, kt, want, rg, g);
-    int cnt = 0;
-#pragma unroll
-    for (int r = 0; r < M; ++r) cnt += ck[r] > rg.lo ? 1 : 0;
-    out.cnt = cnt; out.tau = rg.lo; out.need = want - rg.f_hi; out.total_eq = rg.f_lo - rg.f_hi;
-    return out;
-}
-
-// One drafting step: how many of this lane's candidates (sorted by rank) survive the cut to `want`.
-// r0: every lane that has candidates has more than r0 of them and (r0 + 1) x (such lanes) >= want, so the
-// smallest rank-r0 candidate is a lower bound of the cut.  Ties at the cut go to the smaller lane
-// (parent slot), then the smaller rank.
-template <int M>
-__device__ __forceinline__ int step_cut(const double (&ck)[M], double* kt, int* hist, int want, int r0, int lane,
-                                        Group<true>& g) {
-    double c0 = ck[0];
-    if (r0 != 0) {
-#pragma unroll
-        for (int r = 1; r < M; ++r) c0 = (r == r0) ? ck[r] : c0;
-    }
-    const SortedCut sc = cut_sorted<M>(ck, kt, hist, want, wave_lower_bound(c0), lane, g);
-    if (sc.exact) return sc.cnt;
-    int lane_eq = 0;
-#pragma unroll
-    for (int r = 0; r < M; ++r) lane_eq += ck[r] == sc.tau ? 1 : 0;
-    int take = lane_eq;
-    if (sc.total_eq != sc.need) {
-        const int before = wave_incl_scan(lane_eq, lane) - lane_eq;
-        take = sc.need - before;
-        take = take < 0 ? 0 : (take > lane_eq ? lane_eq : take);
-    }
-    return sc.cnt + take;
-}
-
-struct FastLds {
-    double* dl;               // [rows + 1][KMAX]  log-probabilities of the top-k of every row; last row: NaN
-    double* key;              // [DMAX][64]        pool: log p^ by (layer, slot); later the final selection's table
-    double* kt;               // [KMAX][64]        table of the pivot rounds; later the nodes by output index
-    unsigned short* meta;     // [DMAX][64]        pool: parent slot | rank << 8
-    unsigned char* oidx;      // [DMAX][64]        output index of a selected pool node
-};
-// pool keys, key table, meta, output indices: the part of the LDS layout the final selection works on
-__host__ __device__ inline size_t fast_pool_bytes(int KMAX, int DMAX) {
-    const int km = KMAX < 4 ? 4 : KMAX;               // the table doubles as 64 x 16 bytes of node records
-    return (size_t)DMAX * 64 * 8 + (size_t)km * 64 * 8 + (size_t)DMAX * 64 * 2 + (size_t)DMAX * 64;
-}
-// rehearse: a second copy of the pool part for the wavefront that rehearses the final selection
-__host__ __device__ inline size_t fast_lds_bytes(int rows, int KMAX, int DMAX, bool rehearse) {
-    return (size_t)(rows + 1) * KMAX * 8 + fast_pool_bytes(KMAX, DMAX) * (rehearse ? 2 : 1);
-}
-
-// p^ = e^key for key <= 0, to about 1e-7 relative: fp32 exp2 of the leading part of key * log2(e), first-order
-// correction for the remainder (an fp64 exp costs an order of magnitude more instructions)
-__device__ __forceinline__ double exp_of_logp(double key) {
-    const double t = key * 1.4426950408889634;
-    const float hi = (float)t;
-    const double lo = t - (double)hi;
-    return (double)__builtin_amdgcn_exp2f(hi) * (1.0 + lo * 0.6931471805599453);
-}
-
-// ADAPT: Algorithm 1 with its stopping rule inside the kernel.  The n best nodes drafted so far are kept as a
-// running set, one (log p^, p^) per lane; after every step the new layer is merged into it (top n of at most
-// 2n keys, two per lane), E_sub(T, n) is the sum of its p^, and drafting stops when E_sub - E <= delta.
-template <int KMAX, int DMAX, bool ADAPT>
-// The leading scalar arguments repeat fields of `a`: they are what the prologue's loads need, and as separate
-// arguments the hardware hands them over in registers at wavefront start (kernel-argument preload), so the loads
-// go out without waiting for a read of the argument block.
-__global__ __launch_bounds__(256) void tree_fast_kernel(const float* row_topv, const double* row_lse, const int k,
-                                                        const int rows, const SelKArgs a) {
-    extern __shared__ __attribute__((aligned(16))) u64 smem[];
-    __shared__ int s_hist2[2][kBuckets + 4];
-    const int tid = threadIdx.x, b = blockIdx.x, n = a.n;
-    int D = a.depth;                                  // ADAPT: becomes the number of steps drafted
-    FastLds P;
-    P.dl = (double*)smem;
-    P.key = P.dl + (size_t)(rows + 1) * KMAX;
-    P.kt = P.key + DMAX * 64;
-    P.meta = (unsigned short*)(P.kt + (KMAX < 4 ? 4 : KMAX) * 64);
-    P.oidx = (unsigned char*)(P.meta + DMAX * 64);
-    const size_t rbase = (size_t)b * rows;
-
-    // ---- prologue, all four wavefronts ----
-    for (int i = tid; i < 2 * (kBuckets + 4); i += 256) (&s_hist2[0][0])[i] = 0;
-    // one row per thread and pass: lse once, the k logits of the row, k subtractions; row `rows` is all NaN.  The
-    // loads of two passes go out together and unconditionally (indices clamped to valid entries, results
-    // discarded where they do not apply): each trip to memory costs more than the arithmetic of a pass.
-    {
-        const float* tv = row_topv + rbase * k;
-        const double* tl = row_lse + rbase;
-        for (int row0 = tid; row0 <= rows; row0 += 512) {
-            float x[2][KMAX];
-            double lse[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int rc = min(row0 + 256 * u, rows - 1);
-                lse[u] = tl[rc];
-#pragma unroll
-                for (int r = 0; r < KMAX; ++r) x[u][r] = tv[rc * k + min(r, k - 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int row = row0 + 256 * u;
-                if (row <= rows) {
-                    const bool real = row < rows;
-#pragma unroll
-                    for (int r = 0; r < KMAX; r += 2) {
-                        double2 d2;                   // log p = x - lse (Eq. 2, log space); NaN = absent
-                        d2.x = (real && r < k) ? (double)x[u][r] - lse[u] : nan_d();
-                        d2.y = (real && r + 1 < k) ? (double)x[u][r + 1] - lse[u] : nan_d();
-                        *(double2*)(P.dl + (size_t)row * KMAX + r) = d2;
-                    }
-                }
-            }
-        }
-    }
-    __syncthreads();
-    // Wavefront 0 builds the tree.  The kernel's one workgroup lands on a different compute unit from launch to
-    // launch, and the first pass through the final selection then waits about 2 us for its instructions.  So while
-    // wavefront 0 is drafting, wavefront 1 rehearses the final selection once on made-up keys in an LDS region of
-    // its own: the same instructions, no global memory access, results discarded.  (Rehearsing a drafting step in
-    // a third wavefront was tried: wavefront 0 reaches that code too soon for it to help.)
-    const bool live = __builtin_amdgcn_readfirstlane(tid) < 64;
-    if (tid >= (a.rehearse ? 128 : 64)) return;
-    const int lane = tid & 63;
-    int* const s_hist = s_hist2[live ? 0 : 1];
-    if (!live) {
-        char* sh = (char*)smem + (size_t)(rows + 1) * KMAX * 8 + fast_pool_bytes(KMAX, DMAX);
-        P.key = (double*)sh;
-        P.kt = P.key + DMAX * 64;
-        P.meta = (unsigned short*)(P.kt + (KMAX < 4 ? 4 : KMAX) * 64);
-        P.oidx = (unsigned char*)(P.meta + DMAX * 64);
-#pragma unroll
-        for (int t = 0; t < DMAX; ++t) {              // distinct keys, every node a first child of the slot above it
-            P.key[t * 64 + lane] = -0.5 - 0.01 * (double)(t * 64 + lane);
-            P.meta[t * 64 + lane] = (unsigned short)lane;
-        }
-        lds_sync<true>();
-    }
-    Group<true> g;
-    g.red = nullptr; g.bc = nullptr; g.redd = nullptr;
-    g.phase = g.bphase = g.dphase = 0;
-    g.tid = lane; g.lane = lane; g.wave = 0; g.nw = 1; g.nt = 64;
-
-    double run_key = nan_d(), run_p = 0.0;            // ADAPT: this lane's member of the running top-n set
-    double E_prev = 0.0, E_sub = 0.0;                 // ADAPT: E of Algorithm 1's loop, latest E_sub(T, n)
-    // ---- Algorithm 1, step by step ----
-    for (int t = 0; live && t < D; ++t) {
-        const int F = a.F[t], Fn = a.F[t + 1];
-        const bool active = lane < F;
-        const double* drow = P.dl + (size_t)(active ? a.row_start[t] + lane : rows) * KMAX;
-        const double S = t == 0 ? 0.0 : P.key[(t - 1) * 64 + lane];
-        double ck[KMAX];
-#pragma unroll
-        for (int r = 0; r < KMAX; r += 2) {
-            const double2 d2 = *(const double2*)(drow + r);
-            ck[r] = S + d2.x;                         // log p^(child) = log p^(parent) + log p   (Eq. 2)
-            ck[r + 1] = S + d2.y;
-        }
-        int cnt;
-        if (k * F <= Fn) cnt = active ? k : 0;
-        else cnt = step_cut<KMAX>(ck, P.kt, s_hist, Fn, a.r0[t], lane, g);
-        const int off = wave_incl_scan(cnt, lane) - cnt;
-#pragma unroll
-        for (int r = 0; r < KMAX; ++r) {
-            if (r < cnt) {
-                P.key[t * 64 + off + r] = ck[r];
-                P.meta[t * 64 + off + r] = (unsigned short)(lane | (r << 8));
-            }
-        }
-        lds_sync<true>();
-        if (ADAPT) {
-            // merge the new layer (slot `lane`, if any) into the running set: this lane's pair, larger key first
-            const bool has_new = lane < Fn;
-            const double nkey = has_new ? P.key[t * 64 + lane] : nan_d();
-            const double np = has_new ? exp_of_logp(nkey) : 0.0;
-            const bool new_first = (nkey == nkey) && !(run_key >= nkey);
-            double pr[2], pp[2];
-            pr[0] = new_first ? nkey : run_key; pp[0] = new_first ? np : run_p;
-            pr[1] = new_first ? run_key : nkey; pp[1] = new_first ? run_p : np;
-            const int have = (pr[0] == pr[0] ? 1 : 0) + (pr[1] == pr[1] ? 1 : 0);
-            const int total = wave_sum_u(have);
-            int keep = have;
-            if (total > n) {
-                const SortedCut sc = cut_sorted<2>(pr, P.kt, s_hist, n, wave_lower_bound(fmin(pr[0], pr[1])), lane, g);
-                keep = sc.cnt;
-                if (!sc.exact) {                      // equal keys at the cut: equal p^, any of them will do (lane order)
-                    int lane_eq = (pr[0] == sc.tau ? 1 : 0) + (pr[1] == sc.tau ? 1 : 0);
-                    int take = lane_eq;
-                    if (sc.total_eq != sc.need) {
-                        const int before = wave_incl_scan(lane_eq, lane) - lane_eq;
-                        take = sc.need - before;
-                        take = take < 0 ? 0 : (take > lane_eq ? lane_eq : take);
-                    }
-                    keep += take;
-                }
-            }
-            E_sub = wave_sum_d((keep > 0 ? pp[0] : 0.0) + (keep > 1 ? pp[1] : 0.0));
-            // back to one member per lane
-            const int koff = wave_incl_scan(keep, lane) - keep;
-            double* rec = P.kt;                       // [64][2]: (log p^, p^)
-            if (keep > 0) { rec[2 * koff] = pr[0]; rec[2 * koff + 1] = pp[0]; }
-            if (keep > 1) { rec[2 * koff + 2] = pr[1]; rec[2 * koff + 3] = pp[1]; }
-            lds_sync<true>();
-            const bool mine = lane < (total < n ? total : n);
-            run_key = mine ? rec[2 * lane] : nan_d();
-            run_p = mine ? rec[2 * lane + 1] : 0.0;
-            lds_sync<true>();
-            // the loop condition of Algorithm 1: another step only while the gain of the last one exceeds delta
-            if (t + 1 < D) {
-                if (!(E_sub - E_prev > a.delta)) { D = t + 1; break; }
-                E_prev = E_sub;
-            }
-        }
-    }
-    if (ADAPT && live && lane == 0) { a.steps_used[b] = D; a.e_sub[b] = E_sub; }
-
-    // ---- last line of Algorithm 1: the n best nodes of the pool ----
-    int pool_nodes = 0;
-    for (int t = 0; t < D; ++t) pool_nodes += a.F[t + 1];
-    const int n_out = pool_nodes < n ? pool_nodes : n;
-    double pk[DMAX];
-    int tk[DMAX], mt[DMAX];
-#pragma unroll
-    for (int t = 0; t < DMAX; ++t) {
-        const bool valid = t < D && lane < a.F[t + 1];
-        pk[t] = valid ? P.key[t * 64 + lane] : nan_d();
-        mt[t] = valid ? (int)P.meta[t * 64 + lane] : 0;
-    }
-    const int32_t* ti = a.row_topi + rbase * k;
-#pragma unroll
-    for (int t = 0; t < DMAX; ++t) {                  // token ids: in flight during the selection
-        tk[t] = 0;
-        if (live && t < D && lane < a.F[t + 1]) tk[t] = ti[(a.row_start[t] + (mt[t] & 255)) * k + (mt[t] >> 8)];
-    }
-    unsigned int sel = 0;                             // bit t: pool node (layer t+1, slot lane) is in the tree
-    if (pool_nodes <= n) {
-#pragma unroll
-        for (int t = 0; t < DMAX; ++t) sel |= (pk[t] == pk[t] ? 1u : 0u) << t;
-    } else {
-        // lower bound of the cut: a layer with n nodes -- at least n pool nodes reach its smallest log p^;
-        // failing that, the smallest log p^ of the pool
-        double lo0 = nan_d();
-        int used = 0;
-#pragma unroll
-        for (int t = 0; t < DMAX; ++t)
-            if (t < D && a.F[t + 1] >= n && used < 2) { lo0 = fmax(lo0, wave_lower_bound(pk[t])); ++used; }
-        if (used == 0) {
-            double lmin = nan_d();
-#pragma unroll
-            for (int t = 0; t < DMAX; ++t) lmin = fmin(lmin, pk[t]);
-            lo0 = wave_lower_bound(lmin);
-        }
-        // Quick search on the unsorted keys: every key >= lo0 gets a 16-bit code, monotone in the key, over
-        // [lo0, largest key]; a 256-bin histogram of the high byte finds the bin of the cut, if needed a second
-        // one of the low byte inside that bin.  When the cut falls between two codes the tree is "code >= cut
-        // code"; otherwise (ties or near-ties at the cut) the exact search below decides.
-        bool done = false;
-        {
-            double lmax = nan_d();
-#pragma unroll
-            for (int t = 0; t < DMAX; ++t) lmax = fmax(lmax, pk[t]);
-            const double gmax = wave_upper_bound(lmax);
-            if (gmax > lo0) {
-                const double scale = 65535.0 * __builtin_amdgcn_rcp(gmax - lo0);
-                int code[DMAX];
-#pragma unroll
-                for (int t = 0; t < DMAX; ++t) {
-                    const int q = (int)((pk[t] - lo0) * scale);          // saturating; NaN -> 0
-                    code[t] = pk[t] >= lo0 ? (q > 65535 ? 65535 : q) : -1;    // -1: below the bound or absent
-                }
-#pragma unroll
-                for (int t = 0; t < DMAX; ++t)
-                    if (code[t] >= 0) atomicAdd(&s_hist[code[t] >> 8], 1);
-                lds_sync<true>();
-                int B0, above0, inb0, total0;
-                hist_cut(s_hist, n, lane, B0, above0, inb0, total0);
-                if (B0 >= 0) {
-                    int cut_code = -1;
-                    if (above0 + inb0 == n) {
-                        cut_code = B0 << 8;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < DMAX; ++t)
-                            if ((code[t] >> 8) == B0) atomicAdd(&s_hist[code[t] & 255], 1);
-                        lds_sync<true>();
-                        int B1, above1, inb1, total1;
-                        hist_cut(s_hist, n - above0, lane, B1, above1, inb1, total1);
-                        if (B1 >= 0 && above1 + inb1 == n - above0) cut_code = (B0 << 8) | B1;
-                    }
-                    if (cut_code >= 0) {
-#pragma unroll
-                        for (int t = 0; t < DMAX; ++t) sel |= (code[t] >= cut_code ? 1u : 0u) << t;
-                        done = true;
-                    }
-                }
-            }
-        }
-        if (!done) {
-        // exact search: the lane's pool keys, sorted, go through the same routine as a drafting step
-        double ps[DMAX];
-#pragma unroll
-        for (int t = 0; t < DMAX; ++t) ps[t] = pk[t];
-        sort_desc<DMAX>(ps);
-        lds_sync<true>();                             // the pool keys sit in registers: their LDS region becomes the table
-        const SortedCut sc = cut_sorted<DMAX>(ps, P.key, s_hist, n, lo0, lane, g);
-        if (sc.exact) {
-            double thr = nan_d();                     // this lane's smallest kept key
-#pragma unroll
-            for (int t = 0; t < DMAX; ++t) thr = (t == sc.cnt - 1) ? ps[t] : thr;
-#pragma unroll
-            for (int t = 0; t < DMAX; ++t) sel |= (pk[t] >= thr ? 1u : 0u) << t;      // thr = NaN: none
-        } else {
-#pragma unroll
-            for (int t = 0; t < DMAX; ++t) sel |= (pk[t] > sc.tau ? 1u : 0u) << t;
-            int need = sc.need;
-            if (need > 0 && sc.total_eq == need) {
-#pragma unroll
-                for (int t = 0; t < DMAX; ++t) sel |= (pk[t] == sc.tau ? 1u : 0u) << t;
-            } else if (need > 0) {                    // ties at the cut: shallower first, then smaller slot
-#pragma unroll
-                for (int t = 0; t < DMAX; ++t) {
-                    if (t < D) {
-                        const u64 bal = __ballot(pk[t] == sc.tau);
-                        const int before = __popcll(bal & ((1ull << lane) - 1ull));
-                        if (pk[t] == sc.tau && before < need) sel |= 1u << t;
-                        const int layer_eq = __popcll(bal);
-                        need -= layer_eq < need ? layer_eq : need;
-                    }
-                }
-            }
-        }
-        }
-    }
-
-    // output index = rank in (depth, slot) order among the selected nodes
-    int my_i[DMAX];
-    {
-        int base = 0;
-#pragma unroll
-        for (int t = 0; t < DMAX; ++t) {
-            const u64 bal = __ballot((sel >> t) & 1u);
-            my_i[t] = base + __popcll(bal & ((1ull << lane) - 1ull));
-            if ((sel >> t) & 1u) P.oidx[t * 64 + lane] = (unsigned char)my_i[t];
-            base += __popcll(bal);
-        }
-    }
-    lds_sync<true>();
-    // every tree node moves to the lane of its output index: 16-byte record (log p^, token, parent | depth << 16)
-    u64* rec = (u64*)P.kt;
-#pragma unroll
-    for (int t = 0; t < DMAX; ++t) {
-        if ((sel >> t) & 1u) {
-            const int pi = t > 0 ? (int)P.oidx[(t - 1) * 64 + (mt[t] & 255)] : 0xffff;
-            rec[2 * my_i[t]] = (u64)__double_as_longlong(pk[t]);
-            rec[2 * my_i[t] + 1] = (u64)(unsigned)tk[t] | ((u64)(unsigned)(pi | ((t + 1) << 16)) << 32);
-        }
-    }
-    lds_sync<true>();
-    const bool node = lane < n_out;
-    double key = nan_d();
-    int tok = -1, par = -1, dep = 0;
-    if (node) {
-        key = __longlong_as_double((long long)rec[2 * lane]);
-        const u64 w = rec[2 * lane + 1];
-        tok = (int)(unsigned)w;
-        const unsigned pd = (unsigned)(w >> 32);
-        par = (pd & 0xffff) == 0xffff ? -1 : (int)(pd & 0xffff);
-        dep = (int)(pd >> 16);
-    }
-    // ancestor masks (Algorithm 2) by pointer doubling: after round r, m covers the node and its 2^(r+1) - 1
-    // nearest ancestors, anc is the 2^(r+1)-th ancestor (a depth-1 node stands for "none": it points at itself)
-    u64 m = node ? 1ull << lane : 0ull;
-    int anc = (node && par >= 0) ? par : lane;
-    for (int span = 1; span < D; span *= 2) {
-        const unsigned lo32 = (unsigned)__shfl((int)(unsigned)m, anc);
-        const unsigned hi32 = (unsigned)__shfl((int)(unsigned)(m >> 32), anc);
-        m |= (u64)lo32 | ((u64)hi32 << 32);
-        anc = __shfl(anc, anc);
-    }
-    if (live && lane < n) {
-        const size_t o = (size_t)b * n + lane;
-        a.out.token[o] = tok;
-        a.out.parent[o] = par;
-        a.out.depth[o] = dep;
-        a.out.score[o] = node ? (float)key : -INFINITY;
-        a.out.mask[o] = m;                            // n <= 64: one mask word per node
-    }
-    // E = sum of p^ (Eq. 3)
-    const double e_sum = wave_sum_d(node ? exp_of_logp(key) : 0.0);
-    if (live && lane == 0) {
-        a.out.expect[b] = e_sum;
-        a.out.n_out[b] = n_out;
-    }
-}
-
 SelKArgs make_args(const SelectGeometry& g, const BuildWorkspace& ws) {
     SelKArgs a;
     a.row_lse = ws.row_lse; a.row_topv = ws.row_topv; a.row_topi = ws.row_topi;
@@ -1341,12 +755,10 @@ SelKArgs make_args(const SelectGeometry& g, const BuildWorkspace& ws) {
     a.pool_key = ws.pool_key; a.pool_tok = ws.pool_tok; a.pool_par = ws.pool_par; a.step_tau = ws.step_tau;
     a.pool_p = ws.pool_p; a.seq_E = ws.seq_E; a.seq_steps = ws.seq_steps; a.seq_active = ws.seq_active;
     a.e_sub = nullptr; a.go_on = nullptr; a.delta = 0.0;
-    a.steps_used = nullptr;
     a.front_anc = ws.front_anc; a.mask_out = nullptr; a.mask_words = 0; a.gridDim_batch = g.batch;
     a.out = ot_tree_out{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     a.frontier_token = nullptr; a.frontier_parent = nullptr; a.frontier_count = nullptr;
     a.step = 0;
-    a.rehearse = 0;
     return a;
 }
 
@@ -1359,32 +771,6 @@ int set_lds(K kernel, size_t bytes) {
         OT_HIP_CHECK(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
     }
     return OT_OK;
-}
-
-template <int KMAX, int DMAX, bool SINGLE>
-int launch_oneshot_t(const SelKArgs& a, int batch, int NT, hipStream_t s) {
-    const size_t lds = pool_lds_bytes(a.depth, NT, DMAX, KMAX);
-    int st = set_lds(tree_oneshot_kernel<KMAX, DMAX, SINGLE>, lds);
-    if (st != OT_OK) return st;
-    hipLaunchKernelGGL((tree_oneshot_kernel<KMAX, DMAX, SINGLE>), dim3(batch), dim3(NT), lds, s, a);
-    OT_HIP_CHECK(hipGetLastError());
-    return OT_OK;
-}
-template <int KMAX, bool SINGLE>
-int launch_oneshot_k(const SelKArgs& a, int batch, int NT, hipStream_t s) {
-    if (a.depth <= 8) return launch_oneshot_t<KMAX, 8, SINGLE>(a, batch, NT, s);
-    if (a.depth <= 10) return launch_oneshot_t<KMAX, 10, SINGLE>(a, batch, NT, s);
-    if (a.depth <= 12) return launch_oneshot_t<KMAX, 12, SINGLE>(a, batch, NT, s);
-    if (a.depth <= 16) return launch_oneshot_t<KMAX, 16, SINGLE>(a, batch, NT, s);
-    if (a.depth <= 20) return launch_oneshot_t<KMAX, 20, SINGLE>(a, batch, NT, s);
-    return launch_oneshot_t<KMAX, 32, SINGLE>(a, batch, NT, s);
-}
-template <bool SINGLE>
-int launch_oneshot_s(const SelKArgs& a, int batch, int NT, hipStream_t s) {
-    if (a.k <= 4) return launch_oneshot_k<4, SINGLE>(a, batch, NT, s);
-    if (a.k <= 8) return launch_oneshot_k<8, SINGLE>(a, batch, NT, s);
-    if (a.k <= 10) return launch_oneshot_k<10, SINGLE>(a, batch, NT, s);
-    return launch_oneshot_k<16, SINGLE>(a, batch, NT, s);
 }
 
 template <int KMAX, bool SINGLE>
@@ -1412,62 +798,7 @@ int launch_finalize_t(const SelKArgs& a, int batch, int NT, hipStream_t s) {
     return OT_OK;
 }
 
-// LDS the fast path may use (of the 160 KB of a compute unit)
-constexpr size_t kFastLdsLimit = 144 * 1024;
-
-template <int KMAX, int DMAX, bool ADAPT>
-int launch_fast_t(const SelKArgs& a, int batch, hipStream_t s) {
-    SelKArgs k = a;
-    k.rehearse = fast_lds_bytes(a.rows_per_seq, KMAX, DMAX, true) <= kFastLdsLimit ? 1 : 0;
-    const size_t lds = fast_lds_bytes(a.rows_per_seq, KMAX, DMAX, k.rehearse != 0);
-    int st = set_lds(tree_fast_kernel<KMAX, DMAX, ADAPT>, lds);
-    if (st != OT_OK) return st;
-    hipLaunchKernelGGL((tree_fast_kernel<KMAX, DMAX, ADAPT>), dim3(batch), dim3(256), lds, s, k.row_topv, k.row_lse, k.k,
-                       k.rows_per_seq, k);
-    OT_HIP_CHECK(hipGetLastError());
-    return OT_OK;
-}
-template <int KMAX, bool ADAPT>
-int launch_fast_k(const SelKArgs& a, int batch, hipStream_t s) {
-    if (a.depth <= 8) return launch_fast_t<KMAX, 8, ADAPT>(a, batch, s);
-    if (a.depth <= 10) return launch_fast_t<KMAX, 10, ADAPT>(a, batch, s);
-    if (a.depth <= 12) return launch_fast_t<KMAX, 12, ADAPT>(a, batch, s);
-    if (a.depth <= 16) return launch_fast_t<KMAX, 16, ADAPT>(a, batch, s);
-    if (a.depth <= 20) return launch_fast_t<KMAX, 20, ADAPT>(a, batch, s);
-    return launch_fast_t<KMAX, 32, ADAPT>(a, batch, s);
-}
-template <bool ADAPT>
-int launch_fast(const SelKArgs& a, int batch, hipStream_t s) {
-    if (a.k <= 4) return launch_fast_k<4, ADAPT>(a, batch, s);
-    if (a.k <= 8) return launch_fast_k<8, ADAPT>(a, batch, s);
-    if (a.k <= 10) return launch_fast_k<10, ADAPT>(a, batch, s);
-    return launch_fast_k<16, ADAPT>(a, batch, s);
-}
-int fast_kmax(int k) { return k <= 4 ? 4 : (k <= 8 ? 8 : (k <= 10 ? 10 : 16)); }
-int fast_dmax(int d) { return d <= 8 ? 8 : (d <= 10 ? 10 : (d <= 12 ? 12 : (d <= 16 ? 16 : (d <= 20 ? 20 : 32)))); }
-
 }  // namespace
-
-int launch_tree_oneshot(const SelectGeometry& g, const BuildWorkspace& ws, const ot_tree_out& out, hipStream_t s) {
-    SelKArgs a = make_args(g, ws);
-    a.out = out;
-    if (g.n <= 64 && fast_lds_bytes(g.rows_per_seq, fast_kmax(g.k), fast_dmax(g.depth), false) <= kFastLdsLimit)
-        return launch_fast<false>(a, g.batch, s);
-    const int NT = threads_for(g.n);
-    return NT == 64 ? launch_oneshot_s<true>(a, g.batch, NT, s) : launch_oneshot_s<false>(a, g.batch, NT, s);
-}
-
-bool tree_adaptive_supported(const SelectGeometry& g) {
-    return g.n <= 64 && fast_lds_bytes(g.rows_per_seq, fast_kmax(g.k), fast_dmax(g.depth), false) <= kFastLdsLimit;
-}
-
-int launch_tree_adaptive(const SelectGeometry& g, double delta, const BuildWorkspace& ws, const ot_tree_out& out,
-                         int32_t* steps_used, double* e_sub, hipStream_t s) {
-    if (!tree_adaptive_supported(g)) return OT_ERR_UNSUPPORTED;
-    SelKArgs a = make_args(g, ws);
-    a.out = out; a.delta = delta; a.steps_used = steps_used; a.e_sub = e_sub;
-    return launch_fast<true>(a, g.batch, s);
-}
 
 int launch_tree_step(const SelectGeometry& g, int step, const BuildWorkspace& ws, int32_t* frontier_token,
                      int32_t* frontier_parent, int32_t* frontier_count, hipStream_t s) {
