@@ -206,15 +206,17 @@ __device__ __forceinline__ double wave_sum_rows_d(float v) {
     v += __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(v), __float_as_int(v)));
     return ((double)rl_f(v, 0) + (double)rl_f(v, 16)) + ((double)rl_f(v, 32) + (double)rl_f(v, 48));
 }
-// inclusive prefix sum inside the wavefront: Kogge-Stone inside rows (row_shr, zero fill), then row totals
+// inclusive prefix sum inside the wavefront: Kogge-Stone inside rows of 16 (row_shr, zero fill), then the last lane of a
+// row is added to the next row (row_bcast 15, rows 1 and 3) and of the lower half to the upper (row_bcast 31)
 __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
+    (void)lane;
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
     v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
     v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
     v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-    const int t0 = rl(v, 15), t1 = rl(v, 31), t2 = rl(v, 47);
-    const int row = lane >> 4;
-    return v + (row > 0 ? t0 : 0) + (row > 1 ? t1 : 0) + (row > 2 ? t2 : 0);
+    v += __builtin_amdgcn_update_dpp(0, v, DPP_ROW_BCAST15, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, DPP_ROW_BCAST31, 0xc, 0xf, false);
+    return v;
 }
 // p^ = e^key for key <= 0, to about 1e-7 relative: fp32 exp2 of the leading part of key * log2(e), first-order
 // correction for the remainder (an fp64 exp costs an order of magnitude more instructions)
