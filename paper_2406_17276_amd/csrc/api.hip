@@ -36,7 +36,7 @@ static int validate_build(const ot_build_params* p, bool check_strides) {
     if (p->k > p->vocab) return OT_ERR_INVALID_ARG;
     if (p->logits_dtype != OT_F32 && p->logits_dtype != OT_BF16) return OT_ERR_INVALID_ARG;
     if (p->k > OT_MAX_TOPK || p->n > OT_MAX_NODES || p->depth > OT_MAX_DEPTH) return OT_ERR_UNSUPPORTED;
-    if (scan_parts(p->vocab) > 8) return OT_ERR_UNSUPPORTED;
+    if (p->vocab > kMaxVocab) return OT_ERR_UNSUPPORTED;
     if (check_strides) {
         if (p->stride_row < p->vocab || p->stride_depth < 0 || p->stride_seq < 0) return OT_ERR_INVALID_ARG;
     }
@@ -46,7 +46,7 @@ static int validate_build(const ot_build_params* p, bool check_strides) {
 BuildWorkspace carve_build_workspace(const ot_build_params& p, void* base) {
     const Frontier f = make_frontier(p.k, p.n, p.depth);
     const size_t rows = (size_t)p.batch * (size_t)(f.rows > p.n ? f.rows : p.n);
-    const size_t parts = (size_t)scan_parts(p.vocab);
+    const size_t parts = (size_t)max_scan_parts(p.vocab);
     const size_t k = (size_t)p.k;
     const size_t pool = (size_t)p.batch * p.depth * p.n;
     BuildWorkspace w;
@@ -122,7 +122,8 @@ size_t ot_build_workspace_bytes(const ot_build_params* p) {
 // One-shot build: the rows of all steps are scanned, then the tree is drafted from their statistics.  A tree is usually
 // complete long before the last step (tree_build.hip), so big inputs go in chunks of steps: scan a chunk, draft it, and
 // leave the rows of finished sequences unread from then on.  A chunk costs two more launches and another pass over the
-// pool, about 8 us on the stream, so it has at least kChunkBytes of rows: some 20 us of reading at the rate of the scan.
+// pool, about 8 us on the stream, so it has at least kChunkBytes of rows, some 20 us of reading, and
+// a sixth of what was read before (few trees get that deep, and a launch over the rows of finished sequences is not free).
 static const long long kChunkBytes = 96ll << 20;
 
 static int build_steps(const ot_build_params* p, bool adapt, double delta, const void* logits, void* workspace,
@@ -150,8 +151,9 @@ static int build_steps(const ot_build_params* p, bool adapt, double delta, const
     const long long row_bytes = (long long)p->batch * p->vocab * esize;
     for (int t0 = 0; t0 < p->depth;) {
         int t1 = t0 + 1;
-        while (t1 < p->depth && (f.row_start[t1] - f.row_start[t0]) * row_bytes < kChunkBytes) ++t1;
-        if ((f.rows - f.row_start[t1]) * row_bytes < kChunkBytes) t1 = p->depth;
+        const long long before = f.row_start[t0] * row_bytes, least = before / 6 > kChunkBytes ? before / 6 : kChunkBytes;
+        while (t1 < p->depth && (f.row_start[t1] - f.row_start[t0]) * row_bytes < least) ++t1;
+        if ((f.rows - f.row_start[t1]) * row_bytes < least) t1 = p->depth;
         if (ev0 || ev1) t1 = p->depth;                         // the timed form brackets one scan of everything
         sg.row0 = f.row_start[t0]; sg.rows = f.row_start[t1] - f.row_start[t0];
         st = launch_row_scan(sg, logits, ws, s, (hipEvent_t)ev0, (hipEvent_t)ev1, t0 > 0);

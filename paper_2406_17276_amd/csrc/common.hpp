@@ -33,9 +33,10 @@ struct Frontier {
 };
 Frontier make_frontier(int k, int n, int depth);
 
-// Elements of one vocabulary row handled by one workgroup of the row scan.
-constexpr int kScanPartElems = 32768;
-inline int scan_parts(int vocab) { return (vocab + kScanPartElems - 1) / kScanPartElems; }
+// Longest vocabulary, and the parts a row of the scan may be split into: 131072 bf16 or 65536 f32 elements each, less a
+// 16-byte vector where rows start at odd addresses.
+constexpr int kMaxVocab = 262144;
+inline int max_scan_parts(int vocab) { return (vocab + 65532 - 1) / 65532; }
 
 // Workspace of the tree builder (device memory, caller-owned), carved by the host.
 struct BuildWorkspace {

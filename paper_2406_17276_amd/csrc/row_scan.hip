@@ -1,87 +1,124 @@
 // Row scan: for every logits row of the draft model, one pass over the row yields
 //   lse  = log sum_v exp(x_v)            (normaliser of p_d = softmax(row), Sec. 2 "Inference")
 //   top-k tokens by logit, equal logits -> smaller token id   (children of a node, Sec. 3 after Eq. 2)
-// This is the HBM-bound part of tree construction: every element is read exactly once,
-// 16 bytes per lane per load, and held in registers for both the maximum and the exp-sum.
+// This is the HBM-bound part of tree construction: every element is read once, 16 bytes per lane per load, from
+// addresses aligned to 16 bytes whatever the row's own alignment is (the elements of the first and the last vector that
+// do not belong to the row count as -inf).
 //
-// One workgroup handles one "part" (<= 32768 elements) of one row.  Inside a workgroup:
-//   1. every lane loads its 32 elements (all loads are issued before the first use),
-//   2. every wavefront, on its own: lane maxima -> wave maximum m_w, then s_w = sum exp(x - m_w)
-//      over its registers (no workgroup barrier before this, so wavefronts whose data arrived
-//      early do their arithmetic while the others still wait for memory),
-//   3. barrier; tau = the k-th largest of the group maxima (a group = a row of 16 lanes, 64 groups in a
-//      1024-thread workgroup): each group holds an element >= its maximum, so at least k elements are >= tau,
-//   4. sweep over the registers: elements >= tau go to an LDS candidate list (a 16-byte vector is
-//      skipped when its own maximum is below tau),
-//   5. the k best candidates are ranked by counting (value desc, token asc); the wave partials are
-//      combined in fp64: M = max m_w, s = sum s_w exp(m_w - M), lse = M + log s,
-//   6. part results are written; rows split over several parts are merged by merge_parts_kernel.
-// If the candidate list overflows (massive ties), a slow exact path extracts the k best
-// by k rounds of a workgroup-wide arg-max over the part, re-read from memory.
+// One workgroup handles one row, or one part of a row longer than the workgroup's capacity.
+//   1. every wavefront, on its own, vector by vector: the vector's maximum, and sum of exp(x - ref) over its elements.
+//      ref is the maximum of the wavefront's first vectors; it moves up when an element exceeds it by more than 40
+//      (fp32 sums of terms up to e^40 lose nothing), so exponentials need no second pass over the row.
+//   2. barrier; tau = a lower bound of the k-th largest element: the k-th largest (or a little less) of the maxima of 64
+//      groups of lanes -- each group holds an element >= its maximum, so at least k elements are >= tau,
+//   3. elements >= tau (about k + 3) of the vectors whose own maximum reaches tau become candidates,
+//   4. the k best candidates are ranked by counting (value desc, token asc); the wave partials are combined in fp64:
+//      M = max ref_w, s = sum s_w exp(ref_w - M), lse = M + log s,
+//   5. part results are written; rows split over several parts are merged by merge_parts_kernel.
+// If the candidate list overflows (massive ties), a slow exact path extracts the k best by k rounds of a workgroup-wide
+// arg-max over the part, re-read from memory.
+//
+// Two forms of step 1.  KEEP: few rows (the launch does not fill the chip): many threads per row, all loads in flight at
+// once, the vectors stay in registers and step 3 takes the candidates from there.  Rolling: many rows: 16 vectors per
+// lane pass through a ring of six in flight, which leaves a fourth of the fixed work per element, and the dozen vectors
+// that hold candidates are read again.
 #include "common.hpp"
 #include <type_traits>
 
 namespace ot {
 namespace {
 
-constexpr int kCandCap = 2048;
+typedef unsigned long long u64;
+
+constexpr int kCandCap = 1024;         // candidates of one part
+constexpr int kVecCap = 512;           // rolling form: pairs of vectors that hold candidates
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr long long kScanMaxGrid = 16384;      // workgroups per launch; more items are walked with a grid stride
+constexpr float kSlack = 40.f;         // how far an element may exceed the reference (natural-log units)
+constexpr int kRollVpl = 16;
 
 struct ScanKArgs {
-    int vocab, k, parts, part_elems;
-    int items;                        // rows of the launch x parts
+    int k, parts;
     int rows_per_seq;                 // stride of the per-row results
-    // P == 1: final row results; P > 1: per-part results
+    // parts == 1: final row results; parts > 1: per-part results
     double* row_lse; float* row_topv; int32_t* row_topi;
     float* part_m; double* part_s; float* part_topv; int32_t* part_topi;
     const int32_t* seq_active;        // SKIP kernels: rows of sequence b are left unread when seq_active[b] == 0
 };
 
-__device__ __forceinline__ unsigned int f32_key(float v) {
-    unsigned int u = __float_as_uint(v);
-    return (u >> 31) ? ~u : (u | 0x80000000u);
+// The order of candidates as one integer: value desc, token asc
+__device__ __forceinline__ u64 cand_key(float v, int e) {
+    const unsigned u = __float_as_uint(v);
+    const unsigned f = (u >> 31) ? ~u : (u | 0x80000000u);
+    return ((u64)f << 32) | (u64)(0xffffffffu - (unsigned)e);
+}
+__device__ __forceinline__ float cand_val(u64 key) {
+    const unsigned f = (unsigned)(key >> 32);
+    return __uint_as_float((f >> 31) ? (f & 0x7fffffffu) : ~f);
+}
+__device__ __forceinline__ int cand_tok(u64 key) { return (int)(0xffffffffu - (unsigned)key); }
+// order-preserving map from float to int
+__device__ __forceinline__ int ordered(float v) {
+    const int i = __float_as_int(v);
+    return i ^ ((i >> 31) & 0x7fffffff);
 }
 
-// What a work item needs to find its logits.  The kernels take these as leading scalar arguments, which the
-// hardware hands over in registers at wavefront start (kernel-argument preload): the loads of a work item go out
-// without waiting for a read of the argument block.
-struct ScanHead {
-    const void* logits;
-    long long stride_seq, stride_depth, stride_row;
-    int vocab;
-    int part_geom;                    // parts | part_elems << 4
-    int rows;                         // rows of a sequence in this launch | first row << 16
-    int grow;                         // nsteps | k << 8 | n << 16: step t covers F_t rows, F_0 = 1, F_{t+1} = min(n, k F_t)
+template <int DT> struct VecOf {
+    static constexpr int N = DT == OT_BF16 ? 8 : 4;                                    // elements per 16-byte vector
+    __device__ static __forceinline__ void unpack(const u32x4& w, float (&x)[N]) {
+        if constexpr (DT == OT_BF16) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { x[2 * c] = bf16_lo(w[c]); x[2 * c + 1] = bf16_hi(w[c]); }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = __uint_as_float(w[c]);
+        }
+    }
 };
 
-// One work item = one row part (a whole row when the vocabulary fits one part).
-template <int DT, int NT, int EPL, bool VECLOAD>
-__device__ __forceinline__ void scan_item(const ScanHead& h, const ScanKArgs& a, const int wg) {
-    constexpr int VEC = (DT == OT_BF16) ? 8 : 4;   // elements per 16-byte vector; EPL = elements per lane
-    constexpr int VPL = EPL / VEC;      // 16-byte vectors per lane
-    constexpr int NW = NT / 64;
+// max over groups of G consecutive lanes (4, 8 or 16), result in every lane of the group
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+    v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR1>(__float_as_int(v), __float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR2>(__float_as_int(v), __float_as_int(v))));
+    if (G >= 8) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(v), __float_as_int(v))));
+    if (G >= 16) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(v), __float_as_int(v))));
+    return v;
+}
 
-    constexpr int G = NT / 16;          // groups for the threshold: the rows of 16 lanes (16, 32 or 64 of them)
-    __shared__ float s_gmax[G];
-    __shared__ float s_wm[16];
-    __shared__ double s_ws[16];
-    __shared__ float s_tau;
-    __shared__ float s_cv[kCandCap];
-    __shared__ int s_ci[kCandCap];
-    __shared__ int s_rank[kCandCap];
-    __shared__ int s_count;
-    __shared__ unsigned long long s_best[16];
+template <int NT, bool KEEP>
+struct ScanShared {
+    static constexpr int NW = NT / 64;
+    // groups for the threshold (ranked one ballot per group and wavefront in the KEEP form: fewer for small workgroups)
+    static constexpr int G = KEEP && NT < 512 ? NT / 8 : 64, GL = NT / G;
+    u64 key[kCandCap];
+    int vec[KEEP ? 1 : kVecCap];
+    int g[G];
+    float wm[NW];                      // reference exponent and sum of every wavefront
+    double ws[NW];
+    int count, nvec;                   // candidates; rolling form: pairs of vectors that hold some
+    int tau;
+    u64 best[NW];
+};
 
-    const int tid = threadIdx.x;
-    const int parts = h.part_geom & 15, part_elems = h.part_geom >> 4;
-    const int lrow = wg / parts;                      // row of this launch
-    const int part = wg - lrow * parts;
-    const int rows = h.rows & 0xffff;
-    const int b = lrow / rows;
-    const int r = (h.rows >> 16) + lrow - b * rows;
+// Where a work item's elements are (the same for the whole workgroup): vector v of the item holds its elements
+// v VEC - shift .. v VEC - shift + VEC - 1, base is aligned to 16 bytes.
+struct Item {
+    const char* base;
+    int shift, len, nvec;
+    int e_begin;                      // token id of the item's first element
+    int rid, part;                    // row of the results, part of it
+};
+// Part `part` of row r of sequence b.
+//   part_geom  parts | part_elems << 4
+//   grow       nsteps | k << 8 | n << 16: step t covers F_t rows, F_0 = 1, F_{t+1} = min(n, k F_t)
+template <int DT>
+__device__ __forceinline__ Item locate(const void* logits, const long long stride_seq, const long long stride_depth,
+                                       const long long stride_row, const int vocab, const int part_geom, const int grow,
+                                       const int rows_per_seq, const int b, const int r, const int part) {
+    constexpr int VEC = VecOf<DT>::N, ESIZE = 16 / VEC;
+    const int part_elems = part_geom >> 4;
     // row r of a sequence is slot j of step t (Algorithm 1: the frontier grows k-fold per step up to n)
-    const int nsteps = h.grow & 255, grow_k = (h.grow >> 8) & 255, grow_n = h.grow >> 16;
+    const int nsteps = grow & 255, grow_k = (grow >> 8) & 255, grow_n = grow >> 16;
     int t = 0, start = 0, F = 1;
     while (t + 1 < nsteps && r >= start + F) {
         start += F;
@@ -89,323 +126,335 @@ __device__ __forceinline__ void scan_item(const ScanHead& h, const ScanKArgs& a,
         ++t;
     }
     const int j = r - start;
-    const long long row_off = (long long)b * h.stride_seq + (long long)t * h.stride_depth + (long long)j * h.stride_row;
+    const long long row_off = (long long)b * stride_seq + (long long)t * stride_depth + (long long)j * stride_row;
     const int e_begin = part * part_elems;
-    const int e_end = min(h.vocab, e_begin + part_elems);
+    const int len = min(vocab, e_begin + part_elems) - e_begin;
 
-    if (tid == 0) s_count = 0;
+    const char* const first = (const char*)logits + (row_off + e_begin) * ESIZE;
+    Item it;
+    it.shift = (int)((uintptr_t)first & 15) / ESIZE;
+    it.base = first - it.shift * ESIZE;
+    it.len = len;
+    it.nvec = (it.shift + len + VEC - 1) / VEC;
+    it.e_begin = e_begin;
+    it.rid = b * rows_per_seq + r;
+    it.part = part;
+    return it;
+}
 
-    // ---- 1. load ----------------------------------------------------------
-    // VECLOAD: the host guarantees 16-byte aligned rows and vocab % VEC == 0, so a vector is
-    // either wholly inside the part or wholly outside.  A lane's address is (uniform start of the part) + (a 32-bit
-    // byte offset); lanes past the end of the part re-read the part's first vector and are set to -inf afterwards,
-    // which only the part's last vectors need (a uniform test).  Otherwise: guarded scalar loads.
-    float x[EPL];
-    const int len = e_end - e_begin;
-    if (VECLOAD) {
-        typedef typename std::conditional<DT == OT_BF16, u32x4, f32x4>::type vec_t;
-        constexpr int ESIZE = DT == OT_BF16 ? 2 : 4;
-        const char* part = (const char*)h.logits + (row_off + e_begin) * ESIZE;
-        vec_t w[VPL];
+template <int DT, int NT, int VPL, bool KEEP>
+struct Scan {
+    static constexpr int VEC = VecOf<DT>::N, ESIZE = 16 / VEC;
+    static constexpr int NW = NT / 64, G = ScanShared<NT, KEEP>::G, GL = ScanShared<NT, KEEP>::GL;
+    static constexpr int R = KEEP ? VPL : 6;                  // vectors in flight per lane (64 registers in all)
+    ScanShared<NT, KEEP>& sh;
+    const ScanKArgs& a;
+    const int wave;
+
+    __device__ __forceinline__ static u32x4 load(const Item& it, int i, int tid) {
+        const unsigned v = (unsigned)min(i * NT + tid, it.nvec - 1);
+        return __builtin_nontemporal_load((const u32x4*)(it.base + v * 16u));
+    }
+    // the elements >= tau of vector v
+    __device__ __forceinline__ void take(const Item& it, const float (&x)[VEC], int v, float tau) {
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) {                   // all loads go out before the first use
-            const int e = (i * NT + tid) * VEC;
-            w[i] = __builtin_nontemporal_load((const vec_t*)(part + (e < len ? (unsigned int)e * ESIZE : 0u)));
+        for (int c = 0; c < VEC; ++c) {
+            const int e = v * VEC + c - it.shift;
+            if (x[c] >= tau && (unsigned)e < (unsigned)it.len) {
+                const int p = atomicAdd(&sh.count, 1);
+                if (p < kCandCap) sh.key[p] = cand_key(x[c], it.e_begin + e);
+            }
         }
+    }
+    __device__ __forceinline__ void take_again(const Item& it, int v, float tau) {
+        const int v2 = v + NT;
+        const u32x4 w0 = *(const u32x4*)(it.base + (unsigned)v * 16u), w1 = *(const u32x4*)(it.base + (unsigned)min(v2, it.nvec - 1) * 16u);
+        float x[VEC];
+        VecOf<DT>::unpack(w0, x);
+        take(it, x, v, tau);
+        VecOf<DT>::unpack(w1, x);
+        take(it, x, v2, tau);                          // (past the end: no element in range)
+    }
+
+    // Steps 1 to 3 on an item whose first R vectors are requested; returns tau.
+    __device__ __forceinline__ float stream(const Item& it, u32x4 (&w)[R]) {
+        const int tid = threadIdx.x, lane = tid & 63, nvec = it.nvec;
+        // ---- 1. the vectors ---------------------------------------------------
+        auto mask_edges = [&](float (&x)[VEC], int v) {
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            if ((i + 1) * NT * VEC > len) {
-                asm volatile("");      // keeps this a branch: full vectors skip the selects
-                const bool have = (i * NT + tid) * VEC < len;
+            for (int c = 0; c < VEC; ++c) x[c] = (unsigned)(v * VEC + c - it.shift) < (unsigned)it.len ? x[c] : -INFINITY;
+        };
+        auto edge = [&](int i) { return (i == 0 && it.shift > 0) || (i + 1) * NT * VEC > it.shift + it.len; };
+        // maximum of every vector; rolling form: of every pair of vectors, which are read again together (registers)
+        constexpr int PER = KEEP ? 1 : 2;
+        float vmax[VPL / PER];
+        float xk[KEEP ? VPL : 1][VEC];                            // KEEP: all elements of this lane
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        float m, mc;                                              // this lane's maximum; reference exponent (log2 units)
+        if constexpr (KEEP) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (DT == OT_BF16) w[i][c] = have ? w[i][c] : 0xff80ff80u;     // a pair of -inf
-                    else               w[i][c] = have ? w[i][c] : -INFINITY;
+            for (int i = 0; i < VPL; ++i) {
+                VecOf<DT>::unpack(w[i], xk[i]);
+                if (edge(i)) {
+                    asm volatile("");      // keeps this a branch: full vectors skip the selects
+                    mask_edges(xk[i], i * NT + tid);
                 }
+                float v = xk[i][0];
+#pragma unroll
+                for (int c = 1; c < VEC; ++c) v = fmaxf(v, xk[i][c]);
+                vmax[i] = v;
             }
-            if (DT == OT_BF16) {
+            m = vmax[0];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    x[i * 8 + 2 * c] = bf16_lo((uint32_t)w[i][c]);
-                    x[i * 8 + 2 * c + 1] = bf16_hi((uint32_t)w[i][c]);
-                }
-            } else {
+            for (int i = 1; i < VPL; ++i) m = fmaxf(m, vmax[i]);
+            const float mw = wave_max_f(m);
+            mc = mw * kLog2e;
+            if (mw > -INFINITY) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) x[i * 4 + c] = (float)w[i][c];
-            }
-        }
-    } else if (DT == OT_BF16) {
-        const unsigned short* row = (const unsigned short*)h.logits + row_off;
+                for (int i = 0; i < VPL; ++i)
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const int e0 = e_begin + (i * NT + tid) * VEC;
-#pragma unroll
-            for (int c = 0; c < VEC; ++c)
-                x[i * 8 + c] = (e0 + c < e_end) ? __uint_as_float((unsigned)row[e0 + c] << 16) : -INFINITY;
-        }
-    } else {
-        const float* row = (const float*)h.logits + row_off;
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const int e0 = e_begin + (i * NT + tid) * VEC;
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) x[i * 4 + c] = (e0 + c < e_end) ? row[e0 + c] : -INFINITY;
-        }
-    }
-
-    // ---- 2. per-wavefront statistics -------------------------------------
-    float vmax[VPL];
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-        float v = x[i * VEC];
-#pragma unroll
-        for (int c = 1; c < VEC; ++c) v = fmaxf(v, x[i * VEC + c]);
-        vmax[i] = v;
-    }
-    float m = vmax[0];
-#pragma unroll
-    for (int i = 1; i < VPL; ++i) m = fmaxf(m, vmax[i]);
-    const float rmax = row16_max(m);                  // max of this lane's row of 16 lanes
-    const float m_w = fmaxf(fmaxf(rl_f(rmax, 0), rl_f(rmax, 16)), fmaxf(rl_f(rmax, 32), rl_f(rmax, 48)));
-    // e^(x - m) = 2^(x log2e - mc) with mc = fl(m log2e): one fma per element.  mc is carried along as the
-    // wave's reference exponent, so its rounding cancels when the partial sums are combined.
-    const float mc_w = m_w * kLog2e;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (m_w > -INFINITY) {
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) acc[i & 3] += __builtin_amdgcn_exp2f(fmaf(x[i], kLog2e, -mc_w));
-    }
-    const double s_w = wave_sum_rows_d((acc[0] + acc[1]) + (acc[2] + acc[3]));
-    const int lane = tid & 63, wave = tid >> 6;
-    if (lane == 0) { s_wm[wave] = mc_w; s_ws[wave] = s_w; }     // (reference exponent in log2 units, sum)
-    // group maxima: a group is a row of 16 lanes
-    if ((lane & 15) == 0) s_gmax[tid >> 4] = rmax;
-    __syncthreads();
-
-    // ---- 3. tau: the kk-th largest of the G group maxima -------------------
-    // Every group holds an element >= its maximum, so at least kk elements are >= tau; the more groups, the
-    // tighter the threshold (k = 16 over 16 groups would take the smallest maximum and let several times k
-    // elements through).  Wavefront w ranks maxima w, w + NW, ...: one ballot per maximum, all wavefronts at once.
-    {
-        const int kk = a.k < G ? a.k : G;
-        const float mine = lane < G ? s_gmax[lane] : -INFINITY;
-#pragma unroll
-        for (int q = wave; q < G; q += NW) {
-            const float v = s_gmax[q];
-            const unsigned long long before = __ballot(lane < G && (mine > v || (mine == v && lane < q)));
-            if (__popcll(before) == kk - 1 && lane == 0) s_tau = v;
-        }
-    }
-    __syncthreads();
-    const float tau = s_tau;
-
-    // ---- 4. candidates -----------------------------------------------------
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-        if (vmax[i] >= tau) {
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) {
-                const float v = x[i * VEC + c];
-                const int e = e_begin + (i * NT + tid) * VEC + c;
-                if (v >= tau && e < e_end) {
-                    const int p = atomicAdd(&s_count, 1);
-                    if (p < kCandCap) { s_cv[p] = v; s_ci[p] = e; }
-                }
-            }
-        }
-    }
-    __syncthreads();
-    const int ncand = s_count;
-
-    const int rid = b * a.rows_per_seq + r;
-    // where the k winners of this part go
-    float* outv; int32_t* outi;
-    if (a.parts == 1) {
-        outv = a.row_topv + (size_t)rid * a.k;
-        outi = a.row_topi + (size_t)rid * a.k;
-    } else {
-        outv = a.part_topv + ((size_t)rid * parts + part) * a.k;
-        outi = a.part_topi + ((size_t)rid * parts + part) * a.k;
-    }
-    // ---- 5a. combine the wave partials in fp64 (last wavefront, 16 lanes) --
-    if (wave == NW - 1 && lane < 16) {
-        const bool have = lane < NW;
-        const float mw = have ? s_wm[lane] : -INFINITY;
-        float M = mw;
-        M = fmaxf(M, __int_as_float(dpp_i<DPP_QUAD_XOR1>(__float_as_int(M), __float_as_int(M))));
-        M = fmaxf(M, __int_as_float(dpp_i<DPP_QUAD_XOR2>(__float_as_int(M), __float_as_int(M))));
-        M = fmaxf(M, __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(M), __float_as_int(M))));
-        M = fmaxf(M, __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(M), __float_as_int(M))));
-        double part_sum = (have && mw > -INFINITY) ? s_ws[lane] * (double)__builtin_amdgcn_exp2f(mw - M) : 0.0;
-        part_sum += dpp_d<DPP_QUAD_XOR1>(part_sum);
-        part_sum += dpp_d<DPP_QUAD_XOR2>(part_sum);
-        part_sum += dpp_d<DPP_ROW_HALF_MIRROR>(part_sum);
-        part_sum += dpp_d<DPP_ROW_MIRROR>(part_sum);
-        if (lane == 0) {
-            if (a.parts == 1) {
-                // the terms are 2^(x c - M) with c = the fp32 constant, i.e. e^((x - M / c) c / log2e): dividing
-                // M by the same c puts the reference back into natural-log units without a bias in the constant
-                a.row_lse[rid] = (double)M / (double)kLog2e + log(part_sum);
-            } else {
-                a.part_m[(size_t)rid * parts + part] = M;
-                a.part_s[(size_t)rid * parts + part] = part_sum;
-            }
-        }
-    }
-
-    // ---- 5b. rank the candidates -------------------------------------------
-    if (ncand <= kCandCap) {
-        constexpr int PR = NT >= 1024 ? 32 : 16;          // PR x PR pairs fit the workgroup
-        if (ncand <= PR && NT >= PR * PR) {
-            // one (candidate i, rival j) pair per thread: rank of i = rivals that precede it, counted with a ballot
-            const int i = tid / PR, j = tid % PR;
-            if (tid < PR * PR) {
-                const float v = s_cv[i < ncand ? i : 0], u = s_cv[j < ncand ? j : 0];
-                const int id = s_ci[i < ncand ? i : 0], ui = s_ci[j < ncand ? j : 0];
-                const unsigned long long bal = __ballot(j < ncand && (u > v || (u == v && ui < id)));
-                // a wavefront holds 64 / PR candidates, PR consecutive lanes each
-                const int rank = __popcll(PR == 32 ? ((lane & 32) ? (bal >> 32) : (bal & 0xffffffffull))
-                                                   : ((bal >> (lane & 48)) & 0xffffull));
-                if (j == 0 && i < ncand && rank < a.k) { outv[rank] = v; outi[rank] = id; }
-            }
-            return;
-        }
-        if (ncand <= 64 && NT >= 1024) {
-            // 64 x 64 pairs: thread = (candidate i, 4 rivals); the 16 threads of a candidate share a row of lanes
-            const int i = tid >> 4, j0 = (tid & 15) * 4;
-            const float v = s_cv[i < ncand ? i : 0];
-            const int id = s_ci[i < ncand ? i : 0];
-            int cnt = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int jj = j0 + c;
-                const float u = s_cv[jj < ncand ? jj : 0];
-                const int ui = s_ci[jj < ncand ? jj : 0];
-                cnt += (jj < ncand && (u > v || (u == v && ui < id))) ? 1 : 0;
-            }
-            cnt += dpp_i<DPP_QUAD_XOR1>(0, cnt);
-            cnt += dpp_i<DPP_QUAD_XOR2>(0, cnt);
-            cnt += dpp_i<DPP_ROW_HALF_MIRROR>(0, cnt);
-            cnt += dpp_i<DPP_ROW_MIRROR>(0, cnt);
-            if ((tid & 15) == 0 && i < ncand && cnt < a.k) { outv[cnt] = v; outi[cnt] = id; }
-            return;
-        }
-        if (ncand <= 64) {
-            if (wave == 0) {          // candidate i sits in lane i; the others are broadcast by v_readlane
-                const float v = lane < ncand ? s_cv[lane] : -INFINITY;
-                const int id = lane < ncand ? s_ci[lane] : 0x7fffffff;
-                int rank = 0;
-                for (int jj = 0; jj < ncand; ++jj) {
-                    const float u = rl_f(v, jj);
-                    const int ui = rl(id, jj);
-                    rank += (u > v || (u == v && ui < id)) ? 1 : 0;
-                }
-                if (lane < ncand && rank < a.k) { outv[rank] = v; outi[rank] = id; }
-            }
-            return;
-        }
-        for (int i = tid; i < kCandCap; i += NT) s_rank[i] = 0;
-        __syncthreads();
-        int cp = 64;
-        while (cp < ncand) cp <<= 1;
-        const int q_cnt = (NT / cp) > 0 ? (NT / cp) : 1;   // slices of the inner loop per candidate
-        if (cp <= NT) {
-            const int i = tid & (cp - 1);
-            const int q = tid / cp;
-            if (i < ncand) {
-                const float v = s_cv[i];
-                const int id = s_ci[i];
-                int rank = 0;
-                for (int jj = q; jj < ncand; jj += q_cnt) {
-                    const float u = s_cv[jj];
-                    const int ui = s_ci[jj];
-                    rank += (u > v || (u == v && ui < id)) ? 1 : 0;
-                }
-                if (q_cnt > 1) atomicAdd(&s_rank[i], rank); else s_rank[i] = rank;
+                    for (int c = 0; c < VEC; ++c) acc[c & 3] += __builtin_amdgcn_exp2f(fmaf(xk[i][c], kLog2e, -mc));
             }
         } else {
-            for (int i = tid; i < ncand; i += NT) {
-                const float v = s_cv[i];
-                const int id = s_ci[i];
-                int rank = 0;
-                for (int jj = 0; jj < ncand; ++jj) {
-                    const float u = s_cv[jj];
-                    const int ui = s_ci[jj];
-                    rank += (u > v || (u == v && ui < id)) ? 1 : 0;
-                }
-                s_rank[i] = rank;
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < ncand; i += NT) {
-            const int rank = s_rank[i];
-            if (rank < a.k) { outv[rank] = s_cv[i]; outi[rank] = s_ci[i]; }
-        }
-        return;
-    }
-
-    // ---- slow exact path: k rounds of arg-max, re-reading the part from memory ----
-    float prev_v = INFINITY;
-    int prev_i = -1;
-    for (int round = 0; round < a.k; ++round) {
-        unsigned long long best = 0ull;
-        for (int e = e_begin + tid; e < e_end; e += NT) {
-            float v;
-            if (DT == OT_BF16) v = __uint_as_float((unsigned)((const unsigned short*)h.logits + row_off)[e] << 16);
-            else v = ((const float*)h.logits + row_off)[e];
-            const bool after = (v < prev_v) || (v == prev_v && e > prev_i);
-            if (after) {
-                const unsigned long long key =
-                    ((unsigned long long)f32_key(v) << 32) | (unsigned long long)(0xffffffffu - (unsigned)e);
-                best = key > best ? key : best;
-            }
-        }
+            float lim = -INFINITY;                                // largest element the reference admits
+            mc = 0.f;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long other = __shfl_xor(best, o);
-            best = other > best ? other : best;
+            for (int i = 0; i < VPL; ++i) {
+                const u32x4 cur = w[i % R];
+                if (i + R < VPL) w[i % R] = load(it, i + R, tid);
+                if (i % 2 == 0) vmax[i / 2] = -INFINITY;
+                if (i * NT < nvec) {
+                    float x[VEC];
+                    VecOf<DT>::unpack(cur, x);
+                    if (edge(i)) {
+                        asm volatile("");      // keeps this a branch: full vectors skip the selects
+                        mask_edges(x, i * NT + tid);
+                    }
+                    float v = x[0];
+#pragma unroll
+                    for (int c = 1; c < VEC; ++c) v = fmaxf(v, x[c]);
+                    vmax[i / 2] = i % 2 == 0 ? v : fmaxf(vmax[i / 2], v);
+                    // e^(x - m) = 2^(x log2e - mc) with mc = fl(m log2e): one fma per element.  mc is carried along as the
+                    // wave's reference exponent, so its rounding cancels when the partial sums are combined.
+                    if (__any(v > lim)) {
+                        const float m = wave_max_f(v), mn = fmaxf(m, -1e38f) * kLog2e;     // (finite for the lowest masks too)
+                        if (i > 0) {
+                            const float f = __builtin_amdgcn_exp2f(mc - mn);
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) acc[c] = acc[c] > 0.f ? acc[c] * f : 0.f;
+                        }
+                        mc = mn; lim = m + kSlack;
+                    }
+#pragma unroll
+                    for (int c = 0; c < VEC; ++c) acc[c & 3] += __builtin_amdgcn_exp2f(fmaf(x[c], kLog2e, -mc));
+                }
+            }
+            m = vmax[0];
+#pragma unroll
+            for (int i = 1; i < VPL / 2; ++i) m = fmaxf(m, vmax[i]);
+        }
+        const double s_w = wave_sum_rows_d((acc[0] + acc[1]) + (acc[2] + acc[3]));
+        if (lane == 0) { sh.wm[wave] = s_w > 0.0 ? mc : -INFINITY; sh.ws[wave] = s_w; }
+        const float gm = group_max<GL>(m);
+        if ((lane & (GL - 1)) == 0) sh.g[tid / GL] = ordered(gm);
+        __syncthreads();
+
+        // ---- 2. tau -----------------------------------------------------------
+        const int kk = min(a.k, G);
+        const int mine = G == 64 || lane < G ? sh.g[lane] : (int)0x80000000;
+        float tau;
+        if (KEEP) {
+            // latency counts: wavefront w ranks maxima w, w + NW, ...: one ballot per maximum, all wavefronts at once
+#pragma unroll
+            for (int q = 0; q < G / NW; ++q) {
+                const int v = rl(mine, q * NW + wave);
+                const u64 before = __ballot(mine > v || (mine == v && lane < q * NW + wave));
+                if (__popcll(before) == kk - 1 && lane == 0) sh.tau = v;
+            }
+            __syncthreads();
+            const int o = sh.tau;
+            tau = __int_as_float(o ^ ((o >> 31) & 0x7fffffff));
+        } else {
+            // issue slots count: every wavefront bisects for a value that k to k + 2 of the maxima reach, one vector
+            // instruction per round
+            int lo = ordered(-INFINITY), hi = ordered(INFINITY) + 1;      // count(>= lo) >= k > count(>= hi)
+            for (int round = 0; round < 32; ++round) {
+                const int mid = (int)(((long long)lo + (long long)hi) >> 1);
+                if (mid == lo) break;
+                const int cnt = __popcll(__ballot(mine >= mid));
+                if (cnt >= kk) { lo = mid; if (cnt <= kk + 2) break; }
+                else hi = mid;
+            }
+            tau = __int_as_float(lo ^ ((lo >> 31) & 0x7fffffff));
+        }
+
+        // ---- 3. candidates ----------------------------------------------------
+        if constexpr (KEEP) {
+#pragma unroll
+            for (int i = 0; i < VPL; ++i)
+                if (vmax[i] >= tau && i * NT + tid < nvec) take(it, xk[i], i * NT + tid, tau);
+        } else if (m >= tau) {
+#pragma unroll
+            for (int i = 0; i < VPL; i += 2)
+                if (vmax[i / 2] >= tau && i * NT + tid < nvec) {
+                    const int p = atomicAdd(&sh.nvec, 1);
+                    if (p < kVecCap) sh.vec[p] = i * NT + tid;
+                }
         }
         __syncthreads();
-        if ((tid & 63) == 0) s_best[tid >> 6] = best;
-        __syncthreads();
-        best = s_best[0];
-        for (int w = 1; w < NW; ++w) best = s_best[w] > best ? s_best[w] : best;
-        if (best == 0ull) break;      // fewer than k valid elements in this part
-        const unsigned int fk = (unsigned int)(best >> 32);
-        const unsigned int fu = (fk >> 31) ? (fk & 0x7fffffffu) : ~fk;
-        prev_v = __uint_as_float(fu);
-        prev_i = (int)(0xffffffffu - (unsigned)(best & 0xffffffffu));
-        if (tid == 0) { outv[round] = prev_v; outi[round] = prev_i; }
+        return tau;
     }
-}
 
-// Launches of up to kScanMaxGrid items have one workgroup per item; larger ones (long-vocabulary, large-batch
-// shapes with 10^5..10^6 items) are walked with a grid stride, because starting a workgroup costs about as
-// much as a small item's share of the memory traffic.
-// SKIP: the scan of one drafting step in the loop of Algorithm 1 -- a sequence that the stopping rule has frozen
-// drafts no further, and its rows are not read (the flag is the step kernel's own, on the device).
-__device__ __forceinline__ bool scan_item_frozen(const ScanKArgs& a, int part_geom, int rows, int wg) {
-    const int lrow = wg / (part_geom & 15);
-    return a.seq_active[lrow / (rows & 0xffff)] == 0;
-}
-template <int DT, int NT, int EPL, bool VECLOAD, bool SKIP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT == 1024 && VECLOAD) ? 8 : 4, 8))) void row_scan_kernel(
-    const void* logits, const long long stride_seq, const long long stride_depth, const long long stride_row,
-    const int vocab, const int part_geom, const int rows, const int grow, const ScanKArgs a) {
-    if (SKIP && scan_item_frozen(a, part_geom, rows, blockIdx.x)) return;
-    const ScanHead h{logits, stride_seq, stride_depth, stride_row, vocab, part_geom, rows, grow};
-    scan_item<DT, NT, EPL, VECLOAD>(h, a, blockIdx.x);
-}
-template <int DT, int NT, int EPL, bool VECLOAD, bool SKIP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT == 1024 && VECLOAD) ? 8 : 4, 8))) void row_scan_strided_kernel(
-    const void* logits, const long long stride_seq, const long long stride_depth, const long long stride_row,
-    const int vocab, const int part_geom, const int rows, const int grow, const ScanKArgs a) {
-    const ScanHead h{logits, stride_seq, stride_depth, stride_row, vocab, part_geom, rows, grow};
-    for (int wg = blockIdx.x; wg < a.items; wg += gridDim.x) {
-        if (SKIP && scan_item_frozen(a, part_geom, rows, wg)) continue;      // (the whole workgroup skips)
-        scan_item<DT, NT, EPL, VECLOAD>(h, a, wg);
-        if (wg + (int)gridDim.x < a.items) __syncthreads();      // the next item reuses the shared arrays
+    // Step 4 of an item.  Rolling form: wavefronts 0 and 1 alone, unless an unusual number of vectors holds candidates.
+    __device__ __forceinline__ void finish(const Item& it, float tau) {
+        const int tid = threadIdx.x, lane = tid & 63;
+        bool slow = false;
+        int nv = 0;                                               // rolling form: pairs of vectors that hold candidates
+        if constexpr (!KEEP) {
+            nv = sh.nvec;
+            slow = nv > kVecCap;
+            if (nv <= 64) {
+                if (wave > 1) return;
+                if (tid < nv) take_again(it, sh.vec[tid], tau);
+            } else {
+                for (int q = tid; q < min(nv, kVecCap); q += NT) take_again(it, sh.vec[q], tau);
+                __syncthreads();
+            }
+        }
+
+        const int rid = it.rid;
+        // where the k winners of this part go
+        float* outv; int32_t* outi;
+        if (a.parts == 1) {
+            outv = a.row_topv + (size_t)rid * a.k;
+            outi = a.row_topi + (size_t)rid * a.k;
+        } else {
+            outv = a.part_topv + ((size_t)rid * a.parts + it.part) * a.k;
+            outi = a.part_topi + ((size_t)rid * a.parts + it.part) * a.k;
+        }
+        // ---- 4a. combine the wave partials in fp64 (one wavefront, 16 lanes) ----
+        if (wave == (KEEP ? NW - 1 : 1) && lane < 16) {
+            const bool have = lane < NW;
+            const float mw = have ? sh.wm[lane] : -INFINITY;
+            const float M = group_max<16>(mw);
+            double part_sum = (have && mw > -INFINITY) ? sh.ws[lane] * (double)__builtin_amdgcn_exp2f(mw - M) : 0.0;
+            part_sum += dpp_d<DPP_QUAD_XOR1>(part_sum);
+            part_sum += dpp_d<DPP_QUAD_XOR2>(part_sum);
+            part_sum += dpp_d<DPP_ROW_HALF_MIRROR>(part_sum);
+            part_sum += dpp_d<DPP_ROW_MIRROR>(part_sum);
+            if (lane == 0) {
+                if (a.parts == 1) {
+                    // the terms are 2^(x c - M) with c = the fp32 constant, i.e. e^((x - M / c) c / log2e): dividing
+                    // M by the same c puts the reference back into natural-log units without a bias in the constant
+                    a.row_lse[rid] = (double)M / (double)kLog2e + log(part_sum);
+                } else {
+                    a.part_m[(size_t)rid * a.parts + it.part] = M;
+                    a.part_s[(size_t)rid * a.parts + it.part] = part_sum;
+                }
+            }
+        }
+
+        // ---- 4b. rank the candidates -------------------------------------------
+        if (!KEEP && nv <= 64) {
+            if (wave != 0) return;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");    // (the list is this wavefront's own work)
+        }
+        const int ncand = sh.count;
+        if (!slow && ncand <= kCandCap) {
+            if (KEEP && ncand <= 32 && NT >= 1024) {
+                // one (candidate i, rival j) pair per thread: rank of i = rivals that precede it, counted with a ballot
+                const int i = tid >> 5, q = tid & 31;
+                const u64 key = sh.key[i < ncand ? i : 0], u = sh.key[q < ncand ? q : 0];
+                const u64 bal = __ballot(q < ncand && u > key);
+                const int rank = __popcll((lane & 32) ? (bal >> 32) : (bal & 0xffffffffull));
+                if (q == 0 && i < ncand && rank < a.k) { outv[rank] = cand_val(key); outi[rank] = cand_tok(key); }
+                return;
+            }
+            if (ncand <= 64) {
+                if (wave == 0) {          // candidate i sits in lane i; the others are broadcast by v_readlane
+                    const u64 key = lane < ncand ? sh.key[lane] : 0ull;
+                    const int hi = (int)(key >> 32), lo = (int)(unsigned)key;
+                    int rank = 0;
+                    for (int q = 0; q < ncand; ++q) {
+                        const u64 u = ((u64)(unsigned)rl(hi, q) << 32) | (u64)(unsigned)rl(lo, q);
+                        rank += u > key ? 1 : 0;
+                    }
+                    if (lane < ncand && rank < a.k) { outv[rank] = cand_val(key); outi[rank] = cand_tok(key); }
+                }
+                return;
+            }
+            if (!KEEP && nv <= 64) {                          // wavefront 0 alone, up to 64 VEC candidates
+                for (int i = lane; i < ncand; i += 64) {
+                    const u64 key = sh.key[i];
+                    int rank = 0;
+                    for (int q = 0; q < ncand; ++q) rank += sh.key[q] > key ? 1 : 0;
+                    if (rank < a.k) { outv[rank] = cand_val(key); outi[rank] = cand_tok(key); }
+                }
+                return;
+            }
+            for (int i = tid; i < ncand; i += NT) {
+                const u64 key = sh.key[i];
+                int rank = 0;
+                for (int q = 0; q < ncand; ++q) rank += sh.key[q] > key ? 1 : 0;
+                if (rank < a.k) { outv[rank] = cand_val(key); outi[rank] = cand_tok(key); }
+            }
+            return;
+        }
+
+        // ---- slow exact path: k rounds of arg-max, re-reading the part from memory ----
+        u64 prev = ~0ull;
+        for (int round = 0; round < a.k; ++round) {
+            u64 best = 0ull;
+            const char* const first = it.base + it.shift * ESIZE;
+            for (int e = tid; e < it.len; e += NT) {
+                float v;
+                if (DT == OT_BF16) v = __uint_as_float((unsigned)((const unsigned short*)first)[e] << 16);
+                else v = ((const float*)first)[e];
+                const u64 key = cand_key(v, it.e_begin + e);
+                if (key < prev) best = key > best ? key : best;
+            }
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const u64 other = __shfl_xor(best, o);
+                best = other > best ? other : best;
+            }
+            __syncthreads();
+            if (lane == 0) sh.best[wave] = best;
+            __syncthreads();
+            best = sh.best[0];
+            for (int q = 1; q < NW; ++q) best = sh.best[q] > best ? sh.best[q] : best;
+            if (best == 0ull) break;      // fewer than k valid elements in this part
+            prev = best;
+            if (tid == 0) { outv[round] = cand_val(best); outi[round] = cand_tok(best); }
+        }
     }
+};
+
+// The kernel's leading scalar arguments are what a work item needs to find its logits; the hardware hands them over in
+// registers at wavefront start (kernel-argument preload), so the loads go out without a read of the argument block.
+//   rows       rows of a sequence in this launch | first row << 16
+// SKIP: rows of sequences that are finished (stopped by the rule of Algorithm 1, or their tree complete) are not read;
+// the flags are on the device.  (A fixed set of workgroups that walks the rows of the live sequences makes launches over
+// finished ones cheaper, 4.9 against 12 us at 8192 rows, but reads 5 to 8 % slower: 335 against 309 us for 2.1 GB.)
+template <int DT, int NT, int VPL, bool KEEP, bool SKIP>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void row_scan_kernel(
+    const void* logits, const long long stride_seq, const long long stride_depth, const long long stride_row,
+    const int vocab, const int part_geom, const int rows, const int grow, const ScanKArgs a) {
+    __shared__ ScanShared<NT, KEEP> sh;
+    const int parts = part_geom & 15, rows_here = rows & 0xffff, row0 = rows >> 16;
+    if (threadIdx.x == 0) { sh.count = 0; sh.nvec = 0; }
+    typedef Scan<DT, NT, VPL, KEEP> S;
+    const int tid = threadIdx.x;
+    const int lrow = blockIdx.x / parts, b = lrow / rows_here;
+    if (SKIP && a.seq_active[b] == 0) return;
+    const Item it = locate<DT>(logits, stride_seq, stride_depth, stride_row, vocab, part_geom, grow, a.rows_per_seq, b,
+                               row0 + lrow - b * rows_here, blockIdx.x - lrow * parts);
+    u32x4 w[S::R];
+#pragma unroll
+    for (int i = 0; i < S::R; ++i) w[i] = S::load(it, i, tid);
+    S scan{sh, a, __builtin_amdgcn_readfirstlane(tid >> 6)};
+    const float tau = scan.stream(it, w);
+    scan.finish(it, tau);
 }
 
 // Rows that span several parts: combine the per-part (max, sum) pairs and merge the per-part top-k lists.
@@ -459,64 +508,75 @@ __global__ __launch_bounds__(256) void merge_parts_kernel(int items, int rows, i
 
 }  // namespace
 
+namespace {
+
+template <int DT, int NT, int VPL, bool KEEP>
+int launch_scan_t(const ScanGeometry& g, const void* logits, const ScanKArgs& a, int part_elems, hipStream_t s, hipEvent_t ev0,
+                  hipEvent_t ev1) {
+    const int part_geom = a.parts | (part_elems << 4);
+    const int grow = g.nsteps | (g.grow_k << 8) | (g.grow_n << 16);
+    const int rows = g.rows | (g.row0 << 16);
+    const dim3 gd((unsigned)((long long)g.batch * g.rows * a.parts));
+#define OT_SCAN_ARGS logits, g.stride_seq, g.stride_depth, g.stride_row, g.vocab, part_geom, rows, grow, a
+    if (a.seq_active) hipLaunchKernelGGL((row_scan_kernel<DT, NT, VPL, KEEP, true>), gd, dim3(NT), 0, s, OT_SCAN_ARGS);
+    else if (ev0 || ev1) hipExtLaunchKernelGGL((row_scan_kernel<DT, NT, VPL, KEEP, false>), gd, dim3(NT), 0, s, ev0, ev1, 0, OT_SCAN_ARGS);
+    else hipLaunchKernelGGL((row_scan_kernel<DT, NT, VPL, KEEP, false>), gd, dim3(NT), 0, s, OT_SCAN_ARGS);
+#undef OT_SCAN_ARGS
+    OT_HIP_CHECK(hipGetLastError());
+    return OT_OK;
+}
+
+template <int DT>
+int launch_scan_dt(const ScanGeometry& g, const void* logits, ScanKArgs& a, const BuildWorkspace& ws, hipStream_t s, hipEvent_t ev0,
+                   hipEvent_t ev1) {
+    constexpr int KV = 32 / VecOf<DT>::N;                     // KEEP: 32 elements per lane
+    const int vec = VecOf<DT>::N;
+    const long long rows = (long long)g.batch * g.rows;
+    // elements a workgroup can take: where a row may start inside a vector, one vector less
+    const bool aligned = (uintptr_t)logits % 16 == 0 && g.stride_seq % vec == 0 && g.stride_depth % vec == 0 && g.stride_row % vec == 0;
+    auto capacity = [&](int NT, int VPL) { return (NT * VPL - (aligned ? 0 : 1)) * vec; };
+    auto split = [&](int cap) {
+        a.parts = (g.vocab + cap - 1) / cap;
+        return ((g.vocab + a.parts - 1) / a.parts + vec - 1) / vec * vec;
+    };
+    // Which form: KEEP while a workgroup's registers hold the row and the rows do not fill the chip a few times over.
+    // Measured at 32000 bf16 (64 KB a row), KEEP / rolling: 512 rows 10.1 / 11.8 us, 1024 16.4 / 17.3, 1536 22.2 / 21.9,
+    // 2048 26.9 / 26.0, 4096 48.7 / 45.3 (6.8 TB/s beyond the launch's first 6 us); fp32 (128 KB a row): 1024 23.7 / 24.4,
+    // 2048 40.9 / 41.2.  Longer rows would need parts and a merge launch (4 us and more) in the KEEP form, so they roll at
+    // any number of rows: 128256 bf16, 256 rows 20.2 / 17.3 us, 2048 rows 97 / 83.
+    a.parts = 1;
+    if (g.vocab <= capacity(256, KV)) return launch_scan_t<DT, 256, KV, true>(g, logits, a, g.vocab, s, ev0, ev1);
+    if (rows >= 1536 && g.vocab <= capacity(256, kRollVpl))
+        return launch_scan_t<DT, 256, kRollVpl, false>(g, logits, a, g.vocab, s, ev0, ev1);
+    if (g.vocab <= capacity(1024, KV)) return launch_scan_t<DT, 1024, KV, true>(g, logits, a, g.vocab, s, ev0, ev1);
+    if (g.vocab <= capacity(512, kRollVpl)) return launch_scan_t<DT, 512, kRollVpl, false>(g, logits, a, g.vocab, s, ev0, ev1);
+    const int part_elems = split(capacity(1024, kRollVpl));
+    const int st = launch_scan_t<DT, 1024, kRollVpl, false>(g, logits, a, part_elems, s, ev0, ev1);
+    if (st != OT_OK || a.parts == 1) return st;
+    hipLaunchKernelGGL(merge_parts_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
+                       (int)rows, g.rows, g.row0, g.rows_per_seq, a.seq_active, a.parts, g.k, ws.part_m, ws.part_s, ws.part_topv,
+                       ws.part_topi, ws.row_lse, ws.row_topv, ws.row_topi);
+    OT_HIP_CHECK(hipGetLastError());
+    return OT_OK;
+}
+
+}  // namespace
+
 int launch_row_scan(const ScanGeometry& g, const void* logits, const BuildWorkspace& ws, hipStream_t s, hipEvent_t ev0,
                     hipEvent_t ev1, bool skip_frozen) {
-    const int parts = scan_parts(g.vocab);
-    if (parts > 8) return OT_ERR_UNSUPPORTED;
-    const int esize = g.dtype == OT_BF16 ? 2 : 4;
-    const int vec = 16 / esize;
-    ScanKArgs a;
-    a.vocab = g.vocab; a.k = g.k; a.parts = parts;
-    const int per = (g.vocab + parts - 1) / parts;
-    a.part_elems = (per + vec - 1) / vec * vec;
+    if (g.vocab > kMaxVocab) return OT_ERR_UNSUPPORTED;
     if (g.nsteps < 1 || g.nsteps > 255 || g.grow_k < 1 || g.grow_k > 255 || g.grow_n < 1 || g.grow_n > 32767)
         return OT_ERR_INVALID_ARG;
-    const int part_geom = parts | (a.part_elems << 4);
-    const int grow = g.nsteps | (g.grow_k << 8) | (g.grow_n << 16);
+    if (g.rows < 1 || g.row0 < 0 || g.row0 + g.rows > g.rows_per_seq || g.rows_per_seq > 0x7fff) return OT_ERR_INVALID_ARG;
+    if ((long long)g.batch * g.rows * max_scan_parts(g.vocab) > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;
+    ScanKArgs a;
+    a.k = g.k;
+    a.rows_per_seq = g.rows_per_seq;
     a.row_lse = ws.row_lse; a.row_topv = ws.row_topv; a.row_topi = ws.row_topi;
     a.part_m = ws.part_m; a.part_s = ws.part_s; a.part_topv = ws.part_topv; a.part_topi = ws.part_topi;
     a.seq_active = skip_frozen ? ws.seq_active : nullptr;
-    a.rows_per_seq = g.rows_per_seq;
-    if (g.rows < 1 || g.row0 < 0 || g.row0 + g.rows > g.rows_per_seq || g.rows_per_seq > 0x7fff) return OT_ERR_INVALID_ARG;
-    const int rows_arg = g.rows | (g.row0 << 16);
-
-    const bool aligned = ((uintptr_t)logits % 16 == 0) && (g.stride_seq % vec == 0) && (g.stride_depth % vec == 0) &&
-                         (g.stride_row % vec == 0) && (g.vocab % vec == 0);
-    const bool small = a.part_elems <= 256 * 32;
-    const long long rows = (long long)g.batch * g.rows;
-    const long long grid = rows * parts;
-    if (grid <= 0 || grid > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;
-    a.items = (int)grid;
-    const dim3 gd((unsigned)(grid <= kScanMaxGrid ? grid : kScanMaxGrid));
-
-#define OT_SCAN_ARGS logits, g.stride_seq, g.stride_depth, g.stride_row, g.vocab, part_geom, rows_arg, grow, a
-#define OT_SCAN_LAUNCH2(DT, NT, VL, SK)                                                                  \
-    do {                                                                                                 \
-        if (grid > kScanMaxGrid) {                                                                       \
-            if (ev0 || ev1) hipExtLaunchKernelGGL((row_scan_strided_kernel<DT, NT, 32, VL, SK>), gd, dim3(NT), 0, s, ev0, ev1, 0, OT_SCAN_ARGS); \
-            else hipLaunchKernelGGL((row_scan_strided_kernel<DT, NT, 32, VL, SK>), gd, dim3(NT), 0, s, OT_SCAN_ARGS);   \
-        } else if (ev0 || ev1) hipExtLaunchKernelGGL((row_scan_kernel<DT, NT, 32, VL, SK>), gd, dim3(NT), 0, s, ev0, ev1, 0, OT_SCAN_ARGS); \
-        else hipLaunchKernelGGL((row_scan_kernel<DT, NT, 32, VL, SK>), gd, dim3(NT), 0, s, OT_SCAN_ARGS);               \
-    } while (0)
-#define OT_SCAN_LAUNCH(DT, NT, VL) do { if (skip_frozen) OT_SCAN_LAUNCH2(DT, NT, VL, true); else OT_SCAN_LAUNCH2(DT, NT, VL, false); } while (0)
-    if (g.dtype == OT_BF16) {
-        if (small) { if (aligned) OT_SCAN_LAUNCH(OT_BF16, 256, true); else OT_SCAN_LAUNCH(OT_BF16, 256, false); }
-        else       { if (aligned) OT_SCAN_LAUNCH(OT_BF16, 1024, true); else OT_SCAN_LAUNCH(OT_BF16, 1024, false); }
-    } else {
-        if (small) { if (aligned) OT_SCAN_LAUNCH(OT_F32, 256, true); else OT_SCAN_LAUNCH(OT_F32, 256, false); }
-        else       { if (aligned) OT_SCAN_LAUNCH(OT_F32, 1024, true); else OT_SCAN_LAUNCH(OT_F32, 1024, false); }
-    }
-#undef OT_SCAN_LAUNCH2
-#undef OT_SCAN_LAUNCH
-#undef OT_SCAN_ARGS
-    OT_HIP_CHECK(hipGetLastError());
-    if (parts > 1) {
-        hipLaunchKernelGGL(merge_parts_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
-                           (int)rows, g.rows, g.row0, g.rows_per_seq, a.seq_active, parts, g.k, ws.part_m, ws.part_s, ws.part_topv, ws.part_topi, ws.row_lse,
-                           ws.row_topv, ws.row_topi);
-        OT_HIP_CHECK(hipGetLastError());
-    }
-    return OT_OK;
+    return g.dtype == OT_BF16 ? launch_scan_dt<OT_BF16>(g, logits, a, ws, s, ev0, ev1)
+                              : launch_scan_dt<OT_F32>(g, logits, a, ws, s, ev0, ev1);
 }
 
 }  // namespace ot

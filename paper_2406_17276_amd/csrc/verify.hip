@@ -295,7 +295,7 @@ size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 // row statistics of the (n + 1) target rows per sequence, k = 1
 BuildWorkspace carve_verify_workspace(const ot_verify_params& p, void* base) {
     const size_t rows = (size_t)p.batch * (size_t)(p.n + 1);
-    const size_t parts = (size_t)scan_parts(p.vocab);
+    const size_t parts = (size_t)max_scan_parts(p.vocab);
     BuildWorkspace w;
     memset(&w, 0, sizeof(w));
     size_t off = 0;
@@ -347,7 +347,7 @@ int validate_verify(const ot_verify_params* p) {
     if (p->batch < 1 || p->vocab < 1 || p->n < 1) return OT_ERR_INVALID_ARG;
     if (p->logits_dtype != OT_F32 && p->logits_dtype != OT_BF16) return OT_ERR_INVALID_ARG;
     if (p->stride_row < p->vocab || p->stride_seq < 0) return OT_ERR_INVALID_ARG;
-    if (p->n > OT_MAX_NODES || scan_parts(p->vocab) > 8) return OT_ERR_UNSUPPORTED;
+    if (p->n > OT_MAX_NODES || p->vocab > kMaxVocab) return OT_ERR_UNSUPPORTED;
     return OT_OK;
 }
 
