@@ -7,8 +7,7 @@
 // The keys of one (sequence, KV head) are cut into 64-key tiles: ceil(L_b/64) prefix tiles,
 // then ceil(n_keys/64) tree tiles.  Contiguous tile ranges ("splits") go to different workgroups so
 // that a single small sequence still fills the chip; every split leaves an un-normalised
-// partial (running max m, sum l, O).  The bf16 kernel merges the partials itself (the last workgroup
-// of a row block to finish does it), the f32 kernel leaves them to attn_combine_kernel.
+// partial (running max m, sum l, O); the last workgroup of a row block to finish merges them.
 //
 // bf16 path (attn_mfma_kernel): one workgroup = 64 or 128 packed query rows of one KV head (GQA: the
 // g = q_heads/kv_heads query heads that share the KV head are stacked, row = head*n + node), four
@@ -34,7 +33,7 @@
 // shapes, so the prologue is kept short: divisions are multiplications by constants prepared on the host, the
 // prefix length is fetched first, Q is requested before and the first tiles right after it is known.
 //
-// f32 path (attn_f32_kernel): plain fp32 FMA arithmetic, 16 query rows x 32-key tiles.
+// f32 path (attn_f32_kernel): fp32 matrix instructions, operands straight from memory; see there.
 #include <math.h>
 
 #include <mutex>
@@ -62,7 +61,7 @@ struct AttnKArgs {
     unsigned int* counters;   // one ticket counter per (sequence, KV head, row block), zero between launches
     float* part_o;      // per-split partial O   (layout: see the kernel that writes it)
     float* part_ml;     // per-split (m, l)
-    int batch, q_heads, kv_heads, g, n, nk, D, max_prefix, splits, W, dtype, row_blocks;   // n query rows, nk tree keys
+    int batch, kv_heads, g, n, nk, max_prefix, splits, W, row_blocks;   // n query rows, nk tree keys
     int splits_share_xcd;   // workgroup numbering of the bf16 kernel, see there
     unsigned int inv_splits, inv_kv_heads, inv_n;   // division by multiplication (fast_div): ceil(2^32 / d), unused for d = 1
     float scale_log2;   // softmax scale * log2(e)
@@ -911,176 +910,279 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
 }
 
 // ---------------------------------------------------------------------------
-// f32 kernel: 16 query rows of one query head x 32-key tiles, fp32 FMA arithmetic
+// f32 kernel: fp32 matrix instructions throughout
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const AttnKArgs a) {
-    constexpr int TK = 32, RB = 16;
-    constexpr int KPAD = D + 4;
-    constexpr int EPT = D / 16;            // output columns per thread
-    __shared__ __attribute__((aligned(16))) float s_q[RB * D];
-    __shared__ __attribute__((aligned(16))) float s_k[TK * KPAD];
-    __shared__ __attribute__((aligned(16))) float s_v[TK * D];
-    __shared__ float s_p[RB * TK];
-
-    const int tid = threadIdx.x, r = tid >> 4, c = tid & 15;
-    const int split = blockIdx.x, rb = blockIdx.y;
-    const int b = blockIdx.z / a.q_heads, hq = blockIdx.z - b * a.q_heads;
-    const int hk = hq / a.g;
-    const int n = a.n;
+// What bounds it: v_mfma_f32_32x32x2_f32 does 64 flop per cycle and SIMD, a sixteenth of the bf16 rate, so 32 query rows
+// against 32 keys keep a SIMD busy for 8192 cycles (head_dim 128) over 32 KB of K/V: operands can come straight from
+// memory into registers, one block ahead of their use, with no staging in LDS and no barrier in the loop.
+//
+// A wavefront takes 32 packed query rows (GQA: the rows of the heads that share a KV head are stacked, as in the bf16
+// kernel) and every KS-th 32-key block of its workgroup's range; a workgroup is eight wavefronts = QB row blocks x KS key
+// slices, whose results meet in LDS at the end.
+//   S^T = K Q^T  A = K: lane (key l32, half h) holds K[key][8 j + 4 h + i], i = 0..3 -- one 16-byte load serves four
+//                instructions (the order of the contraction is free); B = Q in the same order, from LDS
+//   O^T += V^T P^T  B = register v of the accumulator: keys 8 (v/4) + 4 h + v%4 of the block, query l32; A = V of that
+//                key, columns EV l32 .. EV l32 + EV - 1 (one load of a whole row per half-wave): instruction e of a key
+//                pair yields output columns EV row + e
+// Key ranges that are split over workgroups are merged by the workgroup that finishes last (tickets, as in the bf16
+// kernel).
+// Measured (MI355X, whole call; before: one FMA per LDS operand pair, a merge launch): 32 heads x 128 rows, 4096 keys of
+// 128: 413 -> 114 us (78 TFLOP/s of 157); 8 KV heads x 480 rows x 4 sequences, 2048 keys: 805 -> 209 us; 4 heads x 16 rows,
+// 128 keys of 64: 18.8 -> 10.2 us.
+template <int D, int QB, int KS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnKArgs a) {
+    static_assert(QB * KS == 8, "eight wavefronts");
+    constexpr int NT = 512, ROWS = 32 * QB, J = D / 8, EV = D / 32, QST = D + 4;
+    typedef float fv __attribute__((ext_vector_type(EV)));
+    typedef unsigned long long u64;
+    extern __shared__ __attribute__((aligned(16))) float s_f[];      // Q [ROWS][QST]; later the exchange between key slices
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    const int qb = wave % QB, ks = wave / QB;
+    const int xcd = blockIdx.x & 7, rb = blockIdx.x >> 3;            // numbering: see the bf16 kernel
+    const int unit = blockIdx.y * 8 + xcd;
+    if (unit >= a.batch * a.kv_heads * a.splits) return;
+    const int bz = unit / a.splits, split = unit - bz * a.splits;
+    const int b = bz / a.kv_heads, hk = bz - b * a.kv_heads;
+    const int n = a.n, rows_all = a.g * n;
     const int L = clamp_len(a.prefix_len[b], a.max_prefix);
-    if (tid == 0 && hq == 0 && split == 0 && rb == 0) report_clamp(a.counters, a.prefix_len[b], a.max_prefix);
-    const int ptiles = (L + TK - 1) / TK, ttiles = (a.nk + TK - 1) / TK;
-    int t0, t1;
-    split_range(ptiles + ttiles, a.splits, a.inv_splits, split, t0, t1);
-    const int node = rb * RB + r;
-    const bool row_ok = node < n;
+    if (tid == 0 && hk == 0 && split == 0 && rb == 0) report_clamp(a.counters, a.prefix_len[b], a.max_prefix);
+    const int pblocks = (L + 31) / 32, T = pblocks + (a.nk + 31) / 32;
+    const int t0 = (int)((long long)T * split / a.splits), t1 = (int)((long long)T * (split + 1) / a.splits);
 
-    const float* qbase = (const float*)a.Q + (long long)b * a.qs[0] + (long long)hq * a.qs[1];
-    for (int i = tid; i < RB * D / 4; i += 256) {
-        const int rr = i / (D / 4), cc = (i % (D / 4)) * 4;
+    const int rho = rb * ROWS + qb * 32 + l32;                       // packed row inside the KV head
+    const bool row_ok = rho < rows_all;
+    const int rho_c = row_ok ? rho : rows_all - 1;
+    const int head = rho_c / n, hq = hk * a.g + head, node = rho_c - head * n;
+    const uint64_t* const mask_row = a.mask + ((long long)b * n + node) * a.W;
+    const float* const kp = (const float*)a.Kp + (long long)b * a.kps[0] + (long long)hk * a.kps[1];
+    const float* const vp = (const float*)a.Vp + (long long)b * a.vps[0] + (long long)hk * a.vps[1];
+    const float* const kt = (const float*)a.Kt + (long long)b * a.kts[0] + (long long)hk * a.kts[1];
+    const float* const vt = (const float*)a.Vt + (long long)b * a.vts[0] + (long long)hk * a.vts[1];
+
+    f32x4 kr[J];
+    fv vr[16];
+    uint64_t mword = 0;
+    // rows past the end of the keys repeat the last one: their scores are masked
+    auto load_k = [&](int t) {
+        const bool tree = t >= pblocks;
+        const int key0 = 32 * (tree ? t - pblocks : t), last = (tree ? a.nk : L) - 1;
+        const float* const row = (tree ? kt : kp) + (long long)min(key0 + l32, last) * (tree ? a.kts[2] : a.kps[2]) + 4 * h;
+#pragma unroll
+        for (int j = 0; j < J; ++j) kr[j] = *(const f32x4*)(row + 8 * j);
+    };
+    auto load_v = [&](int t) {
+        const bool tree = t >= pblocks;
+        const int key0 = 32 * (tree ? t - pblocks : t), last = (tree ? a.nk : L) - 1;
+        const float* const base = (tree ? vt : vp) + EV * l32;
+        const long long st = tree ? a.vts[2] : a.vps[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) vr[v] = *(const fv*)(base + min(key0 + 8 * (v >> 2) + 4 * h + (v & 3), last) * st);
+        mword = tree ? mask_row[key0 >> 6] : 0ull;
+    };
+    int t = t0 + ks;
+    if (t < t1) { load_k(t); load_v(t); }
+    for (int i = tid; i < ROWS * D / 4; i += NT) {
+        const int rr = i / (D / 4), cc = (i % (D / 4)) * 4, r = rb * ROWS + rr;
         f32x4 w = {0.f, 0.f, 0.f, 0.f};
-        if (rb * RB + rr < n) w = *(const f32x4*)(qbase + (long long)(rb * RB + rr) * a.qs[2] + cc);
-        *(f32x4*)(s_q + rr * D + cc) = w;
+        if (r < rows_all) {
+            const int hh = r / n;
+            w = *(const f32x4*)((const float*)a.Q + (long long)b * a.qs[0] + (long long)(hk * a.g + hh) * a.qs[1] +
+                                (long long)(r - hh * n) * a.qs[2] + cc);
+        }
+        *(f32x4*)(s_f + rr * QST + cc) = w;
     }
-    // this row's ancestor mask: the 64-bit word that covers a 32-key tree tile is read with the tile
-    const uint64_t* const mask_row = a.mask + ((long long)b * n + (row_ok ? node : 0)) * a.W;
+    __syncthreads();
 
-    const float* kp = (const float*)a.Kp + (long long)b * a.kps[0] + (long long)hk * a.kps[1];
-    const float* vp = (const float*)a.Vp + (long long)b * a.vps[0] + (long long)hk * a.vps[1];
-    const float* kt = (const float*)a.Kt + (long long)b * a.kts[0] + (long long)hk * a.kts[1];
-    const float* vt = (const float*)a.Vt + (long long)b * a.vts[0] + (long long)hk * a.vts[1];
-
+    const float c = a.scale_log2;
     float m_run = -INFINITY, l_run = 0.f;
-    float o[EPT];
+    f32x16 o[EV];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) o[e] = 0.f;
-
-    for (int t = t0; t < t1; ++t) {
-        const bool tree = t >= ptiles;
-        const int key0 = tree ? (t - ptiles) * TK : t * TK;
-        const int kend = tree ? a.nk : L;
-        const float* kb = tree ? kt : kp;
-        const float* vb = tree ? vt : vp;
-        const long long ks = tree ? a.kts[2] : a.kps[2];
-        const long long vs = tree ? a.vts[2] : a.vps[2];
-        __syncthreads();
-        const uint64_t mword = (tree && row_ok) ? mask_row[key0 >> 6] : 0ull;
-        for (int i = tid; i < TK * D / 4; i += 256) {
-            const int key = i / (D / 4), cc = (i % (D / 4)) * 4;
-            f32x4 kw = {0.f, 0.f, 0.f, 0.f}, vw = {0.f, 0.f, 0.f, 0.f};
-            if (key0 + key < kend) {
-                kw = *(const f32x4*)(kb + (long long)(key0 + key) * ks + cc);
-                vw = *(const f32x4*)(vb + (long long)(key0 + key) * vs + cc);
-            }
-            *(f32x4*)(s_k + key * KPAD + cc) = kw;
-            *(f32x4*)(s_v + key * D + cc) = vw;
+    for (int e = 0; e < EV; ++e)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[e][v] = 0.f;
+    const float* const q_row = s_f + (qb * 32 + l32) * QST + 4 * h;
+    for (; t < t1; t += KS) {
+        f32x16 sc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sc[v] = 0.f;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const f32x4 q = *(const f32x4*)(q_row + 8 * j);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[j][i], q[i], sc, 0, 0, 0);
         }
-        __syncthreads();
-        float s2[2];
+        const int next = min(t + KS, t1 - 1);                        // (the last block is asked for twice)
+        __builtin_amdgcn_sched_barrier(0);
+        load_k(next);
+        __builtin_amdgcn_sched_barrier(0);
+        // visibility; accumulator element v is key 8 (v/4) + 4 h + v%4 of the block
+        const bool tree = t >= pblocks;
+        const int key0 = 32 * (tree ? t - pblocks : t), left = (tree ? a.nk : L) - key0;
+        if (tree || left < 32) {
+            unsigned vis = left >= 32 ? 0xffffffffu : (1u << left) - 1u;
+            if (tree) vis &= (unsigned)(mword >> (key0 & 32));
+            vis >>= 4 * h;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int kl = c + 16 * u;
-            float acc = 0.f;
-#pragma unroll 8
-            for (int d = 0; d < D; d += 4) {
-                const f32x4 qv = *(const f32x4*)(s_q + r * D + d);
-                const f32x4 kv = *(const f32x4*)(s_k + kl * KPAD + d);
-                acc = fmaf(qv.x, kv.x, acc); acc = fmaf(qv.y, kv.y, acc);
-                acc = fmaf(qv.z, kv.z, acc); acc = fmaf(qv.w, kv.w, acc);
-            }
-            const int key = key0 + kl;
-            bool ok = row_ok && key < kend;
-            if (tree) ok = ok && ((mword >> (key & 63)) & 1ull);
-            s2[u] = ok ? acc * a.scale_log2 : -INFINITY;
+            for (int v = 0; v < 16; ++v) sc[v] = (vis >> (8 * (v >> 2) + (v & 3))) & 1u ? sc[v] : -INFINITY;
         }
-        const float tmax = row16_max(fmaxf(s2[0], s2[1]));
-        const float m_new = fmaxf(m_run, tmax);
-        float alpha = 1.f, p0 = 0.f, p1 = 0.f;
-        if (m_new != -INFINITY) {
-            alpha = exp2f(m_run - m_new);
-            p0 = exp2f(s2[0] - m_new);
-            p1 = exp2f(s2[1] - m_new);
-            m_run = m_new;
-        }
-        s_p[r * TK + c] = p0;
-        s_p[r * TK + c + 16] = p1;
-        __syncthreads();
-        float psum = 0.f;
+        float tmax = sc[0];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) o[e] *= alpha;
-        for (int jj = 0; jj < TK; ++jj) {
-            const float p = s_p[r * TK + jj];
-            psum += p;
+        for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, sc[v]);
+        const float m_new = fmaxf(m_run, xhalf_max(tmax));
+        if (m_new == -INFINITY) {
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) o[e] = fmaf(p, s_v[jj * D + c + 16 * e], o[e]);
-        }
-        l_run = l_run * alpha + psum;
-    }
-    if (!row_ok) return;
-    const long long row = ((long long)b * a.q_heads + hq) * n + node;
-    if (a.splits == 1) {
-        const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-        float* orow = (float*)a.O + (long long)b * a.os[0] + (long long)hq * a.os[1] + (long long)node * a.os[2];
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) orow[c + 16 * e] = o[e] * inv;
-    } else {
-        float* po = a.part_o + (row * a.splits + split) * D;
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) po[c + 16 * e] = o[e];
-        if (c == 0) {
-            a.part_ml[(row * a.splits + split) * 2] = m_run;
-            a.part_ml[(row * a.splits + split) * 2 + 1] = l_run;
-        }
-    }
-}
-
-// f32 path only (the bf16 kernel merges its own partials).
-// Merge the per-split partials of one output row: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
-// One wavefront per row (4 rows per workgroup); lane s holds split s's (m, l), the weights are
-// broadcast with v_readlane, every lane accumulates D/64 columns.
-__global__ __launch_bounds__(256) void attn_combine_kernel(const AttnKArgs a) {
-    const int lane = threadIdx.x & 63;
-    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const long long rows = (long long)a.batch * a.q_heads * a.n;
-    if (row >= rows) return;
-    const int n = a.n;
-    const int node = (int)(row % n);
-    const int hq = (int)((row / n) % a.q_heads);
-    const int b = (int)(row / ((long long)n * a.q_heads));
-    const float* ml = a.part_ml + row * a.splits * 2;
-    const float* po = a.part_o + row * a.splits * a.D;
-    float m = -INFINITY, l = 0.f;
-    if (lane < a.splits) { m = ml[2 * lane]; l = ml[2 * lane + 1]; }
-    const float M = wave_max_f(m);
-    const float w = (m == -INFINITY) ? 0.f : exp2f(m - M);
-    float wl = w * l;
-    wl += __int_as_float(dpp_i<DPP_QUAD_XOR1>(0, __float_as_int(wl)));
-    wl += __int_as_float(dpp_i<DPP_QUAD_XOR2>(0, __float_as_int(wl)));
-    wl += __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(0, __float_as_int(wl)));
-    wl += __int_as_float(dpp_i<DPP_ROW_MIRROR>(0, __float_as_int(wl)));
-    const float Lsum = (rl_f(wl, 0) + rl_f(wl, 16)) + (rl_f(wl, 32) + rl_f(wl, 48));
-    const float inv = Lsum > 0.f ? 1.f / Lsum : 0.f;
-    const int per = a.D / 64;                 // 1 or 2 columns per lane
-    float acc0 = 0.f, acc1 = 0.f;
-    for (int s = 0; s < a.splits; ++s) {
-        const float ws = rl_f(w, s);
-        if (per == 2) {
-            const float2 v = *(const float2*)(po + (long long)s * a.D + 2 * lane);
-            acc0 = fmaf(ws, v.x, acc0); acc1 = fmaf(ws, v.y, acc1);
+            for (int v = 0; v < 16; ++v) sc[v] = 0.f;
         } else {
-            acc0 = fmaf(ws, po[(long long)s * a.D + lane], acc0);
+            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;      // m_run = -inf gives 0
+            float sum = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -mc));
+                sum += sc[v];
+            }
+            l_run = l_run * alpha + sum;
+            m_run = m_new;
+            if (__any(alpha != 1.f)) {
+#pragma unroll
+                for (int e = 0; e < EV; ++e)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o[e][v] *= alpha;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int e = 0; e < EV; ++e) o[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[v][e], sc[v], o[e], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(next);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    l_run = xhalf_sum(l_run);
+
+    // the key slices of a row block meet in LDS, halving their number every round
+    if (KS > 1) {
+        __syncthreads();                                             // (Q is no longer needed)
+#pragma unroll
+        for (int half = KS / 2; half >= 1; half /= 2) {
+            // [half x QB wavefronts][EV 4 + 1][64] x 16 bytes
+            f32x4* const slot = (f32x4*)s_f + (size_t)((ks & (half - 1)) * QB + qb) * (EV * 4 + 1) * 64 + lane;
+            if (ks >= half && ks < 2 * half) {
+#pragma unroll
+                for (int e = 0; e < EV; ++e)
+#pragma unroll
+                    for (int v4 = 0; v4 < 4; ++v4)
+                        slot[(e * 4 + v4) * 64] = f32x4{o[e][4 * v4], o[e][4 * v4 + 1], o[e][4 * v4 + 2], o[e][4 * v4 + 3]};
+                slot[EV * 4 * 64] = f32x4{m_run, l_run, 0.f, 0.f};
+            }
+            __syncthreads();
+            if (ks < half) {
+                const f32x4 ml = slot[EV * 4 * 64];
+                const float mm = fmaxf(m_run, ml.x);
+                float a1 = 0.f, a2 = 0.f;
+                if (mm != -INFINITY) {
+                    a1 = __builtin_amdgcn_exp2f((m_run - mm) * c);
+                    a2 = __builtin_amdgcn_exp2f((ml.x - mm) * c);
+                }
+                l_run = l_run * a1 + ml.y * a2;
+                m_run = mm;
+#pragma unroll
+                for (int e = 0; e < EV; ++e)
+#pragma unroll
+                    for (int v4 = 0; v4 < 4; ++v4) {
+                        const f32x4 x = slot[(e * 4 + v4) * 64];
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) o[e][4 * v4 + w] = o[e][4 * v4 + w] * a1 + x[w] * a2;
+                    }
+            }
+            if (half > 1) __syncthreads();
         }
     }
-    const long long off = (long long)b * a.os[0] + (long long)hq * a.os[1] + (long long)node * a.os[2] + per * lane;
-    if (a.dtype == OT_BF16) {
-        unsigned short* o = (unsigned short*)a.O + off;
-        o[0] = __builtin_bit_cast(unsigned short, (__bf16)(acc0 * inv));
-        if (per == 2) o[1] = __builtin_bit_cast(unsigned short, (__bf16)(acc1 * inv));
-    } else {
-        float* o = (float*)a.O + off;
-        o[0] = acc0 * inv;
-        if (per == 2) o[1] = acc1 * inv;
+
+    // element v of o[0 .. EV-1] are columns EV (8 (v/4) + 4 h + v%4) .. + EV - 1 of row l32
+    if (a.splits == 1) {
+        if (ks == 0 && row_ok) {
+            const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+            float* const orow = (float*)a.O + (long long)b * a.os[0] + (long long)hq * a.os[1] + (long long)node * a.os[2];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                fv x;
+#pragma unroll
+                for (int e = 0; e < EV; ++e) x[e] = o[e][v] * inv;
+                *(fv*)(orow + EV * (8 * (v >> 2) + 4 * h + (v & 3))) = x;
+            }
+        }
+        return;
+    }
+    // part_o [group][split][ROWS][D], part_ml [group][split][ROWS] (m c, l): written through and read around the caches, in
+    // the order stores - barrier - ticket (see the bf16 kernel)
+    auto pack2 = [](float x, float y) -> u64 { return (u64)__float_as_uint(x) | ((u64)__float_as_uint(y) << 32); };
+    const int group = bz * a.row_blocks + rb;
+    if (ks == 0 && row_ok) {
+        const size_t pr = ((size_t)group * a.splits + split) * ROWS + qb * 32 + l32;
+        u64* const po = (u64*)(a.part_o + pr * D);
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int e = 0; e < EV; e += 2)
+                __hip_atomic_store(po + (EV * (8 * (v >> 2) + 4 * h + (v & 3)) + e) / 2, pack2(o[e][v], o[e + 1][v]), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        if (h == 0)
+            __hip_atomic_store((u64*)a.part_ml + pr, pack2(m_run == -INFINITY ? -INFINITY : m_run * c, l_run), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(a.counters + group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                         (unsigned)(a.splits - 1) ? 1 : 0;
+    __syncthreads();
+    if (!s_last) return;
+    if (tid == 0) __hip_atomic_store(a.counters + group, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    const int live = min(ROWS, rows_all - rb * ROWS);
+    const u64* const ml0 = (const u64*)a.part_ml + (size_t)group * a.splits * ROWS;
+    const u64* const po0 = (const u64*)(a.part_o + (size_t)group * a.splits * ROWS * D);
+    for (int i = tid; i < live * (D / 4); i += NT) {                 // four columns of a row per thread and round
+        const int rr = i / (D / 4), cc = i % (D / 4);
+        float M = -INFINITY, Ls = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < a.splits; s0 += 8) {                   // eight splits per trip to memory
+            u64 ml[8], x[8][2];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const size_t si = min(s0 + u, a.splits - 1);         // past the end: a copy, weight 0
+                ml[u] = __hip_atomic_load(ml0 + si * ROWS + rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    x[u][e] = __hip_atomic_load(po0 + (si * ROWS + rr) * (D / 2) + 2 * cc + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            float mi[8], m_new = M;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                mi[u] = s0 + u < a.splits ? __uint_as_float((unsigned)ml[u]) : -INFINITY;
+                m_new = fmaxf(m_new, mi[u]);
+            }
+            if (m_new == -INFINITY) continue;
+            const float alpha = __builtin_amdgcn_exp2f(M - m_new);
+            Ls *= alpha;
+            acc *= alpha;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float w = mi[u] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mi[u] - m_new);
+                Ls = fmaf(w, __uint_as_float((unsigned)(ml[u] >> 32)), Ls);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    acc[2 * e] = fmaf(w, __uint_as_float((unsigned)x[u][e]), acc[2 * e]);
+                    acc[2 * e + 1] = fmaf(w, __uint_as_float((unsigned)(x[u][e] >> 32)), acc[2 * e + 1]);
+                }
+            }
+            M = m_new;
+        }
+        const float inv = Ls > 0.f ? 1.f / Ls : 0.f;
+        const int r = rb * ROWS + rr, hh = r / n;
+        *(f32x4*)((float*)a.O + (long long)b * a.os[0] + (long long)(hk * a.g + hh) * a.os[1] + (long long)(r - hh * n) * a.os[2] + 4 * cc) =
+            acc * inv;
     }
 }
 
@@ -1117,6 +1219,15 @@ static int attn_rows_per_workgroup(int rows_per_kv_head) {
     return rows_per_kv_head <= 64 ? 64 : (rows_per_kv_head >= OT_ATTN_ROWS256_FROM ? 256 : 128);
 }
 
+// Packed query rows per workgroup of the f32 kernel (its eight wavefronts = rows / 32 row blocks x key slices): as many as
+// there are up to 128 where the row blocks alone fill the chip; fewer, with the rest of the wavefronts on the keys, where
+// key ranges are split over workgroups -- 256 workgroups then leave at most 4 MB of partials.
+static int f32_rows_per_workgroup(const ot_attn_params& p) {
+    const int rows = p.q_heads / p.kv_heads * p.n, most = rows <= 32 ? 32 : (rows <= 64 ? 64 : 128);
+    if (most == 32 || (long long)p.batch * p.kv_heads * ((rows + most - 1) / most) >= 256) return most;
+    return p.head_dim == 64 ? 64 : 32;
+}
+
 AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
     AttnPlan pl;
     pl.balance = 0;
@@ -1138,10 +1249,12 @@ AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
         // lengths out by themselves and the ranking's extra trip to memory per workgroup costs 1 %.
         if (OT_ATTN_BALANCE && wide && p.batch > 1 && p.batch <= 64 && splits <= 1 && base < 4 * target) pl.balance = 1;
     } else {
-        pl.row_blocks = (p.n + 15) / 16;
-        base = p.batch * p.q_heads * pl.row_blocks;
-        tile = 32;
-        splits = (512 + base - 1) / base;
+        // one workgroup per compute unit at a time (eight wavefronts, two per SIMD); a split has work for all its key slices
+        rows_wg = f32_rows_per_workgroup(p);
+        pl.row_blocks = (g * p.n + rows_wg - 1) / rows_wg;
+        base = p.batch * p.kv_heads * pl.row_blocks;
+        tile = 32 * (256 / rows_wg);
+        splits = 256 / base;
     }
     const int nk = p.n_keys > 0 ? p.n_keys : p.n;
     const int max_tiles = (p.max_prefix + tile - 1) / tile + (nk + tile - 1) / tile;
@@ -1157,8 +1270,8 @@ AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
         splits = (max_tiles + per - 1) / per;
     }
     pl.splits = splits;
-    // bf16: partials are stored per workgroup (rows padded to the row block); f32: per output row
-    const size_t rows = p.dtype == OT_BF16 ? (size_t)base * rows_wg : (size_t)p.batch * p.q_heads * p.n;
+    // partials are stored per workgroup (rows padded to the row block)
+    const size_t rows = (size_t)base * rows_wg;
     const size_t part_elem = (p.dtype == OT_BF16 && OT_ATTN_PART_BF16) ? 2 : 4;
     pl.part_o_bytes = splits > 1 ? align_up(rows * splits * p.head_dim * part_elem, 256) : 0;
     pl.part_ml_bytes = splits > 1 ? align_up(rows * splits * 2 * 4, 256) : 0;
@@ -1179,9 +1292,9 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
     a.counters = (unsigned int*)workspace;
     a.part_o = (float*)((char*)workspace + OT_ATTN_SYNC_BYTES);
     a.part_ml = (float*)((char*)workspace + OT_ATTN_SYNC_BYTES + plan.part_o_bytes);
-    a.batch = p.batch; a.q_heads = p.q_heads; a.kv_heads = p.kv_heads; a.g = p.q_heads / p.kv_heads;
-    a.n = p.n; a.nk = p.n_keys > 0 ? p.n_keys : p.n; a.D = p.head_dim; a.max_prefix = p.max_prefix; a.splits = plan.splits;
-    a.W = OT_MASK_WORDS(a.nk); a.dtype = p.dtype;
+    a.batch = p.batch; a.kv_heads = p.kv_heads; a.g = p.q_heads / p.kv_heads;
+    a.n = p.n; a.nk = p.n_keys > 0 ? p.n_keys : p.n; a.max_prefix = p.max_prefix; a.splits = plan.splits;
+    a.W = OT_MASK_WORDS(a.nk);
     const float scale = p.softmax_scale != 0.f ? p.softmax_scale : 1.0f / sqrtf((float)p.head_dim);
     a.scale_log2 = scale * kLog2e;
     for (int i = 0; i < 3; ++i) {
@@ -1226,21 +1339,33 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
 #undef OT_ATTN_LAUNCH
 #undef OT_ATTN_ARGS
     } else {
-        const dim3 grid(plan.splits, plan.row_blocks, p.batch * p.q_heads);
-        if (ev0 || ev1) {
-            if (p.head_dim == 128) hipExtLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, ev0, ev1, 0, a);
-            else                   hipExtLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, ev0, ev1, 0, a);
-        } else {
-            if (p.head_dim == 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, a);
-            else                   hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, a);
-        }
+        const int rows_wg = f32_rows_per_workgroup(p);
+        const long long unit_groups = ((long long)p.batch * p.kv_heads * plan.splits + 7) / 8;
+        if (unit_groups > 65535 || 8LL * plan.row_blocks > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;   // cannot happen within the limits
+        if (plan.splits > 1 && (long long)p.batch * p.kv_heads * plan.row_blocks * 4 > OT_ATTN_STATUS_OFFSET)
+            return OT_ERR_UNSUPPORTED;      // cannot happen: splits > 1 only with few workgroups
+        const dim3 grid((unsigned)(8 * plan.row_blocks), (unsigned)unit_groups);
+#define OT_F32_LAUNCH(DD, QQ, KK)                                                                                      \
+    do {                                                                                                               \
+        const size_t q = (size_t)32 * QQ * (DD + 4) * 4, x = (KK) > 1 ? (size_t)4 * (DD / 8 + 1) * 64 * 16 : 0;          \
+        const size_t lds = q > x ? q : x;                                                                              \
+        if (lds > 64 * 1024)                                                                                           \
+            OT_HIP_CHECK(hipFuncSetAttribute((const void*)attn_f32_kernel<DD, QQ, KK>,                                  \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));                   \
+        if (ev0 || ev1) hipExtLaunchKernelGGL((attn_f32_kernel<DD, QQ, KK>), grid, dim3(512), lds, s, ev0, ev1, 0, a);  \
+        else hipLaunchKernelGGL((attn_f32_kernel<DD, QQ, KK>), grid, dim3(512), lds, s, a);                             \
+    } while (0)
+#define OT_F32_PICK(DD)                                                                                                \
+    do {                                                                                                               \
+        if (rows_wg == 32) OT_F32_LAUNCH(DD, 1, 8);                                                                    \
+        else if (rows_wg == 64) OT_F32_LAUNCH(DD, 2, 4);                                                               \
+        else OT_F32_LAUNCH(DD, 4, 2);                                                                                  \
+    } while (0)
+        if (p.head_dim == 128) OT_F32_PICK(128); else OT_F32_PICK(64);
+#undef OT_F32_PICK
+#undef OT_F32_LAUNCH
     }
     OT_HIP_CHECK(hipGetLastError());
-    if (plan.splits > 1 && p.dtype != OT_BF16) {
-        const long long rows = (long long)p.batch * p.q_heads * p.n;
-        hipLaunchKernelGGL(attn_combine_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, a);
-        OT_HIP_CHECK(hipGetLastError());
-    }
     return OT_OK;
 }
 
