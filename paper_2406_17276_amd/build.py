@@ -27,9 +27,9 @@ FLAGS = [
 # per-file additions.  row_scan.hip: its streaming kernel walks many items per workgroup at 64 registers per lane;
 # hoisting constants and per-lane indices out of that loop (machine LICM) costs more registers than there are,
 # and a spilled value's reload would wait for the loads that are meant to stay in flight.
-# -fno-honor-nans: the scan's maxima need no NaN handling (logits are finite or -inf by contract; infinities stay
+# -fno-honor-nans (verify.hip too): the maxima over logits need no NaN handling (logits are finite or -inf by contract; infinities stay
 # honoured), which saves the quieting instruction in front of every maximum.
-EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"]}
+EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"], "verify.hip": ["-fno-honor-nans"]}
 
 
 def build(verbose: bool = False) -> str:

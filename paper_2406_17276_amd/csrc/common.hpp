@@ -135,6 +135,20 @@ __device__ __forceinline__ double key_f64(unsigned long long k) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// The elements of a 16-byte vector of logits as floats
+template <int DT> struct VecOf {
+    static constexpr int N = DT == OT_BF16 ? 8 : 4;                                    // elements per 16-byte vector
+    __device__ static __forceinline__ void unpack(const u32x4& w, float (&x)[N]) {
+        if constexpr (DT == OT_BF16) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) { x[2 * c] = bf16_lo(w[c]); x[2 * c + 1] = bf16_hi(w[c]); }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = __uint_as_float(w[c]);
+        }
+    }
+};
+
 // DPP moves inside a 64-lane wavefront (GCN/CDNA encodings).
 // BOUND (bound_ctrl): a lane whose source does not exist reads 0 instead of keeping `old`.  The quad and mirror
 // permutations have a source for every lane, so the flag changes nothing there -- except that the compiler may

@@ -62,19 +62,6 @@ __device__ __forceinline__ int ordered(float v) {
     return i ^ ((i >> 31) & 0x7fffffff);
 }
 
-template <int DT> struct VecOf {
-    static constexpr int N = DT == OT_BF16 ? 8 : 4;                                    // elements per 16-byte vector
-    __device__ static __forceinline__ void unpack(const u32x4& w, float (&x)[N]) {
-        if constexpr (DT == OT_BF16) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) { x[2 * c] = bf16_lo(w[c]); x[2 * c + 1] = bf16_hi(w[c]); }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) x[c] = __uint_as_float(w[c]);
-        }
-    }
-};
-
 // max over groups of G consecutive lanes (4, 8 or 16), result in every lane of the group
 template <int G>
 __device__ __forceinline__ float group_max(float v) {

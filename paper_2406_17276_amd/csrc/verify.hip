@@ -1,18 +1,20 @@
-// Greedy verification of a draft tree (Preliminaries, "Speculative Decoding"; Algorithm 2, "Verify"):
+// Verification of a draft tree (Preliminaries, "Speculative Decoding"; Algorithm 2, "Verify"):
 //   ground truth after a position = the target model's most probable token there;
 //   the longest root branch of the tree that agrees with the ground truth is accepted, and the target's token
 //   after the last accepted node is produced as well (A tokens for A - 1 accepted nodes);
 //   the accepted nodes' K/V rows are appended to the cache.
-// Three kernels: the row scan of the tree builder with k = 1 (arg-max of every target row; ties -> smaller
-// token id), a walk down the tree (one workgroup per sequence, thread i = node i, one step per accepted
-// node), and a row gather for the K/V append.
-//
 // Random sampling (Sec. 4, non-greedy settings): the paper changes only which tokens are acceptable and gives no
 // rule; here the ground truth after a position is DRAWN from softmax(target logits / temperature) by the inverse
-// CDF in token order of a caller-supplied uniform number, the walk is the same.  Two kernels replace the arg-max:
-// sample_seg_kernel reads every row once and leaves (max, sum of exp) per segment of 64 lanes x 16 bytes;
-// sample_pick_kernel (one wavefront per row) finds the segment in which the cumulative sum passes u x total and
-// re-reads that one segment to find the token.
+// CDF in token order of a caller-supplied uniform number, the walk is the same.
+//
+// One launch: a workgroup per target row finds the row's ground truth and publishes it; the workgroup that completes a
+// sequence's set walks down the tree.  A second launch copies K/V rows.
+//
+// What bounds it: one sequence's rows are 3 MB, so launches and trips to memory count; for batches, reading the rows.
+// The greedy form needs no exponentials and, since the threshold of the builder's scan would be the maximum itself, no
+// candidate lists.  Measured (MI355X, verification and append together; before: scan with statistics + walk + append,
+// segment sums + pick + walk + append): one sequence of 51 rows of 32000, greedy 14.3 -> 10.5 us; 16 x 61 rows, sampled 28.0 ->
+// 21.0 us.
 #include <string.h>
 
 #include "common.hpp"
@@ -20,99 +22,169 @@
 namespace ot {
 namespace {
 
-struct WalkKArgs {
-    const int32_t* row_top;      // [batch][n + 1]  arg-max of the target's rows (row 0 = the root position)
+typedef unsigned long long u64;
+
+struct VerifyKArgs {
+    const void* logits;
+    long long stride_seq, stride_row;
+    int vocab, n;
+    float c;                     // sampling: log2(e) / temperature
+    const float* u;              // sampling: [batch][n + 1]
     const int32_t *token, *parent, *n_out;
+    u64* truth;                  // [batch][n + 1]  kPublished | token
     int32_t *accept_len, *accept_node, *accept_token;
-    int n;
 };
 
-// Thread i owns node i.  Children of one node carry distinct tokens, so at most one thread matches per step;
-// the chain of matches is at most n_out long, which bounds the loop.
-__global__ __launch_bounds__(256) void verify_walk_kernel(const WalkKArgs a) {
-    __shared__ int s_next[2];
-    const int b = blockIdx.x, i = threadIdx.x, n = a.n;
-    const int n_out = a.n_out[b] < n ? a.n_out[b] : n;
-    const bool have = i < n_out;
-    const int my_tok = have ? a.token[(size_t)b * n + i] : -1;
-    const int my_par = have ? a.parent[(size_t)b * n + i] : -2;
-    const int32_t* top = a.row_top + (size_t)b * (n + 1);
+// A row's result as one 64-bit word, so that the words of a sequence tell both whether all its rows are there and what
+// they are.  The workspace needs no preparation: a word counts only with this upper half, and the workgroup that walks
+// the tree clears the words again.
+constexpr u64 kPublished = 0x7f4a91c3ull << 32;
+constexpr int kBatch = 4;        // vectors per lane requested at once; the next batch is in flight while one is processed
+
+// One wavefront: publish the row's ground truth, and walk the tree if that completes the sequence.  Words travel through
+// device-scope stores and loads (rows of a sequence are on different XCDs).  Every workgroup's word has reached memory
+// before it looks at the others', so at least the last one sees them all; should two see them all, both write the same.
+__device__ __forceinline__ void publish_and_walk(const VerifyKArgs& a, int b, int j, int truth, int lane) {
+    constexpr int Q = (OT_MAX_NODES + 1 + 63) / 64, QN = OT_MAX_NODES / 64;
+    const int n = a.n;
+    u64* const words = a.truth + (size_t)b * (n + 1);
+    if (lane == 0) __hip_atomic_store(words + j, kPublished | (u64)(unsigned)truth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the tree: lane owns nodes lane, lane + 64, ...
+    const int n_out = min(a.n_out[b], n);
+    int tok[QN], par[QN];
+#pragma unroll
+    for (int q = 0; q < QN; ++q) {
+        const int i = min(lane + 64 * q, n - 1);
+        tok[q] = a.token[(size_t)b * n + i];
+        par[q] = lane + 64 * q < n_out ? a.parent[(size_t)b * n + i] : -2;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    u64 w[Q];
+    bool all = true;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        w[q] = kPublished;
+        if (lane + 64 * q <= n) w[q] = __hip_atomic_load(words + lane + 64 * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        all = all && (w[q] >> 32) == (kPublished >> 32);
+    }
+    if (!__all(all)) return;
+    int32_t* const out_tok = a.accept_token + (size_t)b * (n + 1);
+    int32_t* const out_node = a.accept_node + (size_t)b * n;
     int cur = -1, A = 0;
+    // children of one node carry distinct tokens, so at most one node matches per step; a branch has at most n_out nodes
     for (int step = 0; step <= n_out; ++step) {
-        if (i == 0) s_next[step & 1] = -1;
-        __syncthreads();
-        const int g = top[cur + 1];                          // ground truth after `cur`
-        if (have && my_par == cur && my_tok == g) s_next[step & 1] = i;
-        __syncthreads();
-        const int nx = s_next[step & 1];
-        if (i == 0) {
-            a.accept_token[(size_t)b * (n + 1) + A] = g;
-            if (nx >= 0) a.accept_node[(size_t)b * n + A] = nx;
+        int g = 0;                                            // ground truth after `cur`
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (((cur + 1) >> 6) == q) g = rl((int)(unsigned)w[q], (cur + 1) & 63);
+        int nx = -1;
+#pragma unroll
+        for (int q = 0; q < QN; ++q) {
+            const u64 hit = __ballot(par[q] == cur && tok[q] == g);
+            if (hit && nx < 0) nx = 64 * q + __ffsll((long long)hit) - 1;
+        }
+        if (lane == 0) {
+            out_tok[A] = g;
+            if (nx >= 0 && A < n) out_node[A] = nx;
         }
         ++A;
         if (nx < 0) break;
         cur = nx;
     }
     // A tokens produced, A - 1 nodes accepted; the rest of the output rows is padding
-    for (int j = A - 1 + i; j < n; j += blockDim.x) a.accept_node[(size_t)b * n + j] = -1;
-    for (int j = A + i; j < n + 1; j += blockDim.x) a.accept_token[(size_t)b * (n + 1) + j] = -1;
-    if (i == 0) a.accept_len[b] = A;
+    for (int i = A - 1 + lane; i < n; i += 64) out_node[i] = -1;
+    for (int i = A + lane; i < n + 1; i += 64) out_tok[i] = -1;
+    if (lane == 0) a.accept_len[b] = A;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (lane + 64 * q <= n) __hip_atomic_store(words + lane + 64 * q, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// Drawing the ground truth at a temperature
-// ---------------------------------------------------------------------------------------------------------
-struct SampleKArgs {
-    const void* logits;
-    const float* u;              // [batch][n + 1]
-    float* seg_m;                // [rows][nseg]   largest logit of the segment's wavefront (-inf: nothing finite)
-    double* seg_s;               // [rows][nseg]   sum of exp2((x - seg_m) c) over the segment
-    int32_t* truth;              // [rows]
-    int rows_per_seq, vocab, nseg;
-    long long stride_seq, stride_row;
-    float c;                     // log2(e) / temperature
+// A row's vectors: vector v holds elements v VEC - shift .. v VEC - shift + VEC - 1; loads are aligned whatever the row's
+// alignment is.
+template <int DT>
+struct Row {
+    static constexpr int VEC = VecOf<DT>::N, ESIZE = 16 / VEC;
+    const char* base;
+    int shift, len, nvec;
+    __device__ __forceinline__ Row(const VerifyKArgs& a, int b, int j) {
+        const char* const first = (const char*)a.logits + ((long long)b * a.stride_seq + (long long)j * a.stride_row) * ESIZE;
+        shift = (int)((uintptr_t)first & 15) / ESIZE;
+        base = first - shift * ESIZE;
+        len = a.vocab;
+        nvec = (shift + len + VEC - 1) / VEC;
+    }
+    __device__ __forceinline__ u32x4 load(int v) const { return *(const u32x4*)(base + (unsigned)min(v, nvec - 1) * 16u); }
+    __device__ __forceinline__ u32x4 stream(int v) const {
+        return __builtin_nontemporal_load((const u32x4*)(base + (unsigned)min(v, nvec - 1) * 16u));
+    }
+    // vectors v0 .. v0 + count - 1 may hold elements that are not the row's (uniform)
+    __device__ __forceinline__ bool edge(int v0, int count) const { return (v0 == 0 && shift > 0) || (v0 + count) * VEC > shift + len; }
+    __device__ __forceinline__ void mask(float (&x)[VEC], int v) const {
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) x[c] = (unsigned)(v * VEC + c - shift) < (unsigned)len ? x[c] : -INFINITY;
+    }
 };
 
-constexpr int kSegPerWave = 4;   // segments whose loads one wavefront keeps in flight
-
-template <typename DT> struct SegOf { static constexpr int VEC = 16 / (int)sizeof(DT), ELEMS = 64 * VEC; };
-
-// the VEC logits of one lane as floats; out-of-range elements read as -inf (probability 0)
-template <typename DT, bool VECLOAD>
-__device__ __forceinline__ void load_lane_elems(const DT* row, long long base, int vocab, float* v) {
-    constexpr int VEC = SegOf<DT>::VEC;
-    if (VECLOAD && base + VEC <= vocab) {
-        const u32x4 w = *(const u32x4*)(row + base);
-        if constexpr (sizeof(DT) == 2) {
+// Greedy: the most probable token of a row (equal logits: the smaller token id)
+template <int DT, int NT>
+__global__ __launch_bounds__(NT) void verify_greedy_kernel(const VerifyKArgs a) {
+    constexpr int NW = NT / 64, VEC = Row<DT>::VEC;
+    __shared__ float s_m[NW];
+    __shared__ int s_tok;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x / (a.n + 1), j = blockIdx.x - b * (a.n + 1);
+    const Row<DT> row(a, b, j);
+    if (tid == 0) s_tok = 0x7fffffff;
+    u32x4 w[kBatch], nw[kBatch];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { v[2 * i] = bf16_lo(w[i]); v[2 * i + 1] = bf16_hi(w[i]); }
-        } else {
+    for (int i = 0; i < kBatch; ++i) w[i] = row.stream(i * NT + tid);
+    float m = -INFINITY;                                      // this lane's maximum and the first of its vectors that has it
+    int at = tid;
+    for (int v0 = 0; v0 < row.nvec; v0 += kBatch * NT) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(w[i]);
+        for (int i = 0; i < kBatch; ++i) nw[i] = w[i];
+        if (v0 + kBatch * NT < row.nvec) {
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) nw[i] = row.stream(v0 + (kBatch + i) * NT + tid);
         }
-    } else {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            float x = -INFINITY;
-            if (base + i < vocab) {
-                if constexpr (sizeof(DT) == 2) x = __uint_as_float((uint32_t)((const uint16_t*)row)[base + i] << 16);
-                else x = ((const float*)row)[base + i];
+        for (int i = 0; i < kBatch; ++i) {
+            const int v = v0 + i * NT;
+            if (v < row.nvec) {
+                float x[VEC];
+                VecOf<DT>::unpack(w[i], x);
+                if (row.edge(v, NT)) row.mask(x, v + tid);
+                float q = x[0];
+#pragma unroll
+                for (int c = 1; c < VEC; ++c) q = fmaxf(q, x[c]);
+                at = q > m ? v + tid : at;
+                m = fmaxf(q, m);
             }
-            v[i] = x;
         }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) w[i] = nw[i];
     }
+    const float mw = wave_max_f(m);
+    if (lane == 0) s_m[wave] = mw;
+    __syncthreads();
+    float M = s_m[lane & (NW - 1)];
+    M = wave_max_f(M);
+    if (m == M) {                                             // (few lanes: their vectors again)
+        float x[VEC];
+        VecOf<DT>::unpack(row.load(at), x);
+        int e = 0x7fffffff;
+#pragma unroll
+        for (int c = VEC - 1; c >= 0; --c) {
+            const int t = at * VEC + c - row.shift;
+            e = (x[c] == M && (unsigned)t < (unsigned)row.len) ? t : e;
+        }
+        atomicMin(&s_tok, e);
+    }
+    __syncthreads();
+    if (wave == 0) publish_and_walk(a, b, j, s_tok, lane);
 }
 
-__device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
 // inclusive prefix sum over the lanes of a wavefront
 __device__ __forceinline__ double wave_scan_f64(double v, int lane) {
 #pragma unroll
@@ -123,139 +195,189 @@ __device__ __forceinline__ double wave_scan_f64(double v, int lane) {
     return v;
 }
 
-// grid (segment groups, rows); every wavefront works alone: no LDS, no barrier
-template <typename DT, bool VECLOAD>
-__global__ __launch_bounds__(256) void sample_seg_kernel(const SampleKArgs a) {
-    constexpr int VEC = SegOf<DT>::VEC, ELEMS = SegOf<DT>::ELEMS;
-    const int row = blockIdx.y, b = row / a.rows_per_seq, j = row - b * a.rows_per_seq;
-    const DT* x = (const DT*)a.logits + (long long)b * a.stride_seq + (long long)j * a.stride_row;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int seg0 = (blockIdx.x * 4 + wave) * kSegPerWave;
-    if (seg0 >= a.nseg) return;
-    float v[kSegPerWave][VEC];
+// Sampling: the token at which the cumulative sum of exp(x / T), in token order, passes u x total.  The sums of all
+// 16-byte vectors stay in LDS (fp32 inside a vector, fp64 above); 64 consecutive vectors are a segment, which one
+// wavefront reads in one go with one reference exponent.  The segment that holds the draw, then the vector, are found by
+// prefix sums over lanes; only that vector is read again.
+constexpr int kMaxSeg = 512;
+template <int DT, int NT>
+__global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) {
+    constexpr int VEC = Row<DT>::VEC, PER_MAX = kMaxSeg / 64 + 1;    // (the longest row may start inside a vector)
+    extern __shared__ __attribute__((aligned(16))) float s_e[];      // [segments x 64]  sum of exp2(x c - ref) per vector
+    __shared__ float s_ref[kMaxSeg + 1];                             // reference exponent of a segment
+    __shared__ double s_seg[kMaxSeg + 1];                              // sum over a segment
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x / (a.n + 1), j = blockIdx.x - b * (a.n + 1);
+    const Row<DT> row(a, b, j);
+    const int nseg = (row.nvec + 63) / 64;
+    const float slack = 57.f / a.c;                                  // terms up to 2^57 of the reference: fp32 has the room
+    float u = 0.f;
+    u32x4 w[kBatch], nw[kBatch];
 #pragma unroll
-    for (int s = 0; s < kSegPerWave; ++s)
-        load_lane_elems<DT, VECLOAD>(x, (long long)(seg0 + s) * ELEMS + lane * VEC, a.vocab, v[s]);
-    float m = -INFINITY;
+    for (int i = 0; i < kBatch; ++i) w[i] = row.stream(i * NT + tid);
+    if (wave == 0) u = a.u[blockIdx.x];
+    float mc = 0.f, lim = -INFINITY;                                 // reference exponent, largest element it admits
+    for (int v0 = 0; v0 < row.nvec; v0 += kBatch * NT) {
 #pragma unroll
-    for (int s = 0; s < kSegPerWave; ++s)
+        for (int i = 0; i < kBatch; ++i) nw[i] = w[i];
+        if (v0 + kBatch * NT < row.nvec) {
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) m = fmaxf(m, v[s][i]);
-    m = wave_max_f(m);
-    const float mu = m == -INFINITY ? 0.f : m;
-#pragma unroll
-    for (int s = 0; s < kSegPerWave; ++s) {
-        float e = 0.f;
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) e += __builtin_amdgcn_exp2f((v[s][i] - mu) * a.c);
-        const double tot = wave_sum_f64((double)e);
-        if (lane == 0 && seg0 + s < a.nseg) {
-            a.seg_m[(size_t)row * a.nseg + seg0 + s] = m;
-            a.seg_s[(size_t)row * a.nseg + seg0 + s] = tot;
+            for (int i = 0; i < kBatch; ++i) nw[i] = row.stream(v0 + (kBatch + i) * NT + tid);
         }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int v = v0 + i * NT, seg = v / 64 + wave;
+            if (v < row.nvec && seg < nseg) {
+                float x[VEC];
+                VecOf<DT>::unpack(w[i], x);
+                if (row.edge(v, NT)) row.mask(x, v + tid);
+                float q = x[0];
+#pragma unroll
+                for (int c = 1; c < VEC; ++c) q = fmaxf(q, x[c]);
+                if (__any(q > lim)) {
+                    const float m = wave_max_f(q);
+                    mc = fminf(fmaxf(m * a.c, -1e38f), 1e38f);       // (finite for the lowest masks too)
+                    lim = m + slack;
+                }
+                float e = 0.f;
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) e += __builtin_amdgcn_exp2f(fmaf(x[c], a.c, -mc));
+                s_e[v + tid] = e;
+                if (lane == 0) s_ref[seg] = lim == -INFINITY ? -INFINITY : mc;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) w[i] = nw[i];
     }
-}
-
-// one wavefront per row; lane L owns the segments [L per, (L + 1) per)
-template <typename DT, bool VECLOAD>
-__global__ __launch_bounds__(64) void sample_pick_kernel(const SampleKArgs a) {
-    constexpr int VEC = SegOf<DT>::VEC, ELEMS = SegOf<DT>::ELEMS;
-    constexpr int PER_MAX = 8;
-    const int row = blockIdx.x, b = row / a.rows_per_seq, j = row - b * a.rows_per_seq;
-    const DT* x = (const DT*)a.logits + (long long)b * a.stride_seq + (long long)j * a.stride_row;
-    const int lane = threadIdx.x;
-    const int per = (a.nseg + 63) / 64;                    // <= PER_MAX, checked by the host
-    const float* sm = a.seg_m + (size_t)row * a.nseg;
-    const double* ss = a.seg_s + (size_t)row * a.nseg;
-    float ms[PER_MAX];
-    double w[PER_MAX];
-    float M = -INFINITY;
+    __syncthreads();
+    // segment sums, four threads each
+    for (int q = tid; q < nseg * 4; q += NT) {
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 x = *(const f32x4*)(s_e + 16 * q + 4 * i);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum += (double)x[c];
+        }
+        sum += dpp_d<DPP_QUAD_XOR1>(sum);
+        sum += dpp_d<DPP_QUAD_XOR2>(sum);
+        if ((q & 3) == 0) s_seg[q >> 2] = sum;
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    // lane L owns the segments [L per, (L + 1) per)
+    const int per = (nseg + 63) / 64;                                // <= PER_MAX, checked by the host
+    float ms[PER_MAX], M = -INFINITY;
 #pragma unroll
     for (int i = 0; i < PER_MAX; ++i) {
         const int s = lane * per + i;
-        const bool ok = i < per && s < a.nseg;
-        ms[i] = ok ? sm[s] : -INFINITY;
-        w[i] = ok ? ss[s] : 0.0;
+        ms[i] = i < per && s < nseg ? s_ref[s] : -INFINITY;
         M = fmaxf(M, ms[i]);
     }
     M = wave_max_f(M);
-    if (M == -INFINITY) {                                  // no finite logit in the row: nothing to draw from
-        if (lane == 0) a.truth[row] = 0;
-        return;
-    }
-    double lane_sum = 0.0;
-    double sc[PER_MAX];
+    int truth = 0;                                                   // no finite logit in the row: nothing to draw from
+    if (M != -INFINITY) {
+        double sc[PER_MAX], wt[PER_MAX], lane_sum = 0.0;
 #pragma unroll
-    for (int i = 0; i < PER_MAX; ++i) {
-        // weight of the segment relative to the row maximum (double exp2: relative error 1e-16)
-        sc[i] = ms[i] == -INFINITY ? 0.0 : exp2(((double)ms[i] - (double)M) * (double)a.c);
-        w[i] *= sc[i];
-        lane_sum += w[i];
-    }
-    const double incl = wave_scan_f64(lane_sum, lane);
-    const double total = __shfl(incl, 63);
-    const double target = (double)a.u[row] * total;
-    // first lane whose segments reach past the target; by rounding there may be none: the last lane with weight
-    const unsigned long long past = __ballot(incl > target), any = __ballot(lane_sum > 0.0);
-    const int L = past ? __ffsll((long long)past) - 1 : 63 - __clzll((long long)any);
-    // inside lane L: the first segment that passes the target, else (rounding) the end of its last one with weight
-    bool found = false;
-    int seg = 0;
-    float mseg = 0.f;
-    double before = incl - lane_sum, rs = 0.0;                  // rs: residual in the segment's own units
-#pragma unroll
-    for (int i = 0; i < PER_MAX; ++i) {
-        if (w[i] > 0.0 && !found) {
-            seg = lane * per + i;
-            mseg = ms[i];
-            if (before + w[i] > target) { found = true; rs = (target - before) / sc[i]; }
-            else rs = w[i] / sc[i];
+        for (int i = 0; i < PER_MAX; ++i) {
+            sc[i] = wt[i] = 0.0;
+            if (i < per) {
+                // weight of the segment relative to the largest reference (double exp2: relative error 1e-16)
+                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2((double)ms[i] - (double)M);
+                wt[i] = ms[i] == -INFINITY ? 0.0 : s_seg[lane * per + i] * sc[i];
+                lane_sum += wt[i];
+            }
         }
-        if (!found) before += w[i];
-    }
-    seg = __shfl(seg, L);
-    mseg = __shfl(mseg, L);
-    rs = __shfl(rs, L);
-
-    float v[VEC];
-    load_lane_elems<DT, VECLOAD>(x, (long long)seg * ELEMS + lane * VEC, a.vocab, v);
-    float e[VEC];
-    double lane_e = 0.0;
+        const double incl = wave_scan_f64(lane_sum, lane);
+        const double target = (double)u * __shfl(incl, 63);
+        // first lane whose segments reach past the target; by rounding there may be none: the last lane with weight
+        const u64 past = __ballot(incl > target), any = __ballot(lane_sum > 0.0);
+        const int Ls = past ? __ffsll((long long)past) - 1 : 63 - __clzll((long long)any);
+        // inside that lane: the first segment that passes the target, else (rounding) the end of its last one with weight
+        bool found = false;
+        int seg = 0;
+        float mseg = 0.f;
+        double before = incl - lane_sum, rs = 0.0;                   // rs: residual in the segment's own units
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) { e[i] = __builtin_amdgcn_exp2f((v[i] - mseg) * a.c); lane_e += (double)e[i]; }
-    const double incl_e = wave_scan_f64(lane_e, lane);
-    const unsigned long long past_e = __ballot(incl_e > rs), any_e = __ballot(lane_e > 0.0);
-    const int Le = past_e ? __ffsll((long long)past_e) - 1 : 63 - __clzll((long long)any_e);
-    if (lane == Le) {
-        double acc = incl_e - lane_e;
+        for (int i = 0; i < PER_MAX; ++i) {
+            if (i < per && wt[i] > 0.0 && !found) {
+                seg = lane * per + i;
+                mseg = ms[i];
+                if (before + wt[i] > target) { found = true; rs = (target - before) / sc[i]; }
+                else rs = wt[i] / sc[i];
+            }
+            if (!found) before += wt[i];
+        }
+        seg = __shfl(seg, Ls);
+        mseg = __shfl(mseg, Ls);
+        rs = __shfl(rs, Ls);
+        // inside the segment: the vector
+        const int v = seg * 64 + lane;
+        const double e = v < row.nvec ? (double)s_e[v] : 0.0;
+        const double incl_e = wave_scan_f64(e, lane);
+        const u64 past_e = __ballot(incl_e > rs), any_e = __ballot(e > 0.0);
+        const int Le = past_e ? __ffsll((long long)past_e) - 1 : 63 - __clzll((long long)any_e);
+        // inside the vector: the element (every lane does the same)
+        const double start = __shfl(incl_e - e, Le);
+        float x[VEC];
+        VecOf<DT>::unpack(row.load(seg * 64 + Le), x);
+        row.mask(x, seg * 64 + Le);
+        double acc = start;
         int k = -1, lastk = 0;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-            acc += (double)e[i];
-            if (e[i] > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
+            const float p = __builtin_amdgcn_exp2f(fmaf(x[i], a.c, -mseg));
+            acc += (double)p;
+            if (p > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
         }
-        if (k < 0) k = lastk;
-        a.truth[row] = seg * ELEMS + lane * VEC + k;
+        truth = (seg * 64 + Le) * VEC + (k < 0 ? lastk : k) - row.shift;
     }
+    publish_and_walk(a, b, j, truth, lane);
 }
 
-template <typename DT, bool VECLOAD>
-int launch_sample_t(const SampleKArgs& a, int rows, hipStream_t s) {
-    const int groups = (a.nseg + 4 * kSegPerWave - 1) / (4 * kSegPerWave);
-    hipLaunchKernelGGL((sample_seg_kernel<DT, VECLOAD>), dim3(groups, rows), dim3(256), 0, s, a);
-    OT_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL((sample_pick_kernel<DT, VECLOAD>), dim3(rows), dim3(64), 0, s, a);
+// Threads per row: about 131072 in all, a quarter of what is resident at a time -- more wavefronts per row shorten a row's
+// latency, fewer leave less fixed work per element.  Measured, greedy / sampled us: 32000 bf16, 64 rows, 256 threads
+// 6.4 / 9.6, 1024 threads 6.0 / 8.6; 512 rows 10.0 / 12.2 against 11.5 / 14.0; 1024 rows 16.5 / 18.1 against 21.7 / 21.7.
+// 128256 bf16, 64 rows 13.8 / 20.2 against 10.2 / 14.5; 512 rows 24.2 / 27.1 against 30.2 / 29.4.
+template <int DT>
+int launch_rows(const VerifyKArgs& a, int batch, bool sample, hipStream_t s) {
+    const long long rows = (long long)batch * (a.n + 1), bytes = (long long)a.vocab * Row<DT>::ESIZE;
+    const int nt = bytes <= 16384 || rows > 256 ? 256 : (rows > 128 ? 512 : 1024);
+    const int nseg = (a.vocab + Row<DT>::VEC - 1 + 64 * Row<DT>::VEC - 1) / (64 * Row<DT>::VEC);
+    const size_t lds = sample ? (size_t)nseg * 64 * 4 : 0;
+#define OT_ROWS(KERNEL, NT)                                                                                                  \
+    do {                                                                                                                     \
+        if (lds > 48 * 1024)                                                                                                 \
+            OT_HIP_CHECK(hipFuncSetAttribute((const void*)KERNEL<DT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+        hipLaunchKernelGGL((KERNEL<DT, NT>), dim3((unsigned)rows), dim3(NT), lds, s, a);                                     \
+    } while (0)
+#define OT_ROWS_NT(KERNEL)                                                          \
+    do {                                                                            \
+        if (nt == 256) OT_ROWS(KERNEL, 256);                                        \
+        else if (nt == 512) OT_ROWS(KERNEL, 512);                                   \
+        else OT_ROWS(KERNEL, 1024);                                                 \
+    } while (0)
+    if (sample) OT_ROWS_NT(verify_sample_kernel);
+    else OT_ROWS_NT(verify_greedy_kernel);
+#undef OT_ROWS_NT
+#undef OT_ROWS
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
 
-struct SampleWorkspace {
-    float* seg_m;
-    double* seg_s;
-    int32_t* truth;
-    size_t bytes;
-    int nseg;
-};
+int launch_verify(const ot_verify_params& p, bool sample, float c, const void* logits, const float* u, const int32_t* token,
+                  const int32_t* parent, const int32_t* n_out, void* workspace, int32_t* accept_len, int32_t* accept_node,
+                  int32_t* accept_token, hipStream_t s) {
+    VerifyKArgs a;
+    a.logits = logits; a.stride_seq = p.stride_seq; a.stride_row = p.stride_row; a.vocab = p.vocab; a.n = p.n;
+    a.c = c; a.u = u;
+    a.token = token; a.parent = parent; a.n_out = n_out;
+    a.truth = (u64*)workspace;
+    a.accept_len = accept_len; a.accept_node = accept_node; a.accept_token = accept_token;
+    return p.logits_dtype == OT_BF16 ? launch_rows<OT_BF16>(a, p.batch, sample, s) : launch_rows<OT_F32>(a, p.batch, sample, s);
+}
+
+size_t verify_bytes(const ot_verify_params& p) { return ((size_t)p.batch * (size_t)(p.n + 1) * 8 + 255) / 256 * 256; }
 
 struct AppendKArgs {
     void *Kp, *Vp;
@@ -266,80 +388,30 @@ struct AppendKArgs {
     long long kps[3], vps[3], kts[3], vts[3];
 };
 
-// grid (accepted row j, batch x KV head); one wavefront copies the K row and the V row of node accept_node[j]
-// to prefix row L + j, 16 bytes per lane
-__global__ __launch_bounds__(64) void kv_append_kernel(const AppendKArgs a) {
-    const int j = blockIdx.x, bh = blockIdx.y;
-    const int b = bh / a.kv_heads, h = bh - b * a.kv_heads;
+// One workgroup per (sequence, KV head): K and V rows of the accepted nodes accept_node[j] go to prefix rows L + j, 16 bytes
+// per lane, all of a branch's usual few rows at once.  Three trips to memory bound it (lengths and node, rows, writes).
+// (A wavefront for every row that could be accepted had n times as many workgroups, nearly all without work.)
+__global__ __launch_bounds__(256) void kv_append_kernel(const AppendKArgs a) {
+    const int b = blockIdx.x / a.kv_heads, h = blockIdx.x - b * a.kv_heads;
+    const int chunks = a.D * a.esize / 16;                    // 16-byte chunks per row
+    // the first round's node, asked for together with the lengths
+    int node = a.accept_node[(size_t)b * a.n + min((int)threadIdx.x / (2 * chunks), a.n - 1)];
     int L = a.prefix_len[b];
     L = L < 0 ? 0 : (L > a.max_prefix ? a.max_prefix : L);
-    const int cnt = a.accept_len[b] - 1;                     // accepted nodes
-    if (j == 0 && h == 0 && threadIdx.x == 0) a.new_prefix_len[b] = L + cnt < a.max_prefix ? L + cnt : a.max_prefix;
-    if (j >= cnt || L + j >= a.max_prefix) return;
-    const int node = a.accept_node[(size_t)b * a.n + j];
-    if (node < 0 || node >= a.n) return;
-    const int chunks = a.D * a.esize / 16;                    // 16-byte chunks per row
-    const int lane = threadIdx.x;
-    const char* ks = (const char*)a.Kt + ((long long)b * a.kts[0] + (long long)h * a.kts[1] + (long long)node * a.kts[2]) * a.esize;
-    const char* vs = (const char*)a.Vt + ((long long)b * a.vts[0] + (long long)h * a.vts[1] + (long long)node * a.vts[2]) * a.esize;
-    char* kd = (char*)a.Kp + ((long long)b * a.kps[0] + (long long)h * a.kps[1] + (long long)(L + j) * a.kps[2]) * a.esize;
-    char* vd = (char*)a.Vp + ((long long)b * a.vps[0] + (long long)h * a.vps[1] + (long long)(L + j) * a.vps[2]) * a.esize;
-    for (int c = lane; c < chunks; c += 64) {
-        *(u32x4*)(kd + 16 * c) = *(const u32x4*)(ks + 16 * c);
-        *(u32x4*)(vd + 16 * c) = *(const u32x4*)(vs + 16 * c);
+    const int cnt = a.accept_len[b] - 1;                      // accepted nodes
+    if (h == 0 && threadIdx.x == 0) a.new_prefix_len[b] = L + cnt < a.max_prefix ? L + cnt : a.max_prefix;
+    const int rows = min(min(cnt, a.n), a.max_prefix - L);
+    for (int i = threadIdx.x; i < rows * 2 * chunks; i += 256) {
+        const int r = i / chunks, c = i - r * chunks, j = r >> 1;
+        if (i >= 256) node = a.accept_node[(size_t)b * a.n + j];
+        if (node < 0 || node >= a.n) continue;
+        const bool v = r & 1;
+        const long long* const ts = v ? a.vts : a.kts;
+        const long long* const ps = v ? a.vps : a.kps;
+        const char* const src = (const char*)(v ? a.Vt : a.Kt) + ((long long)b * ts[0] + (long long)h * ts[1] + (long long)node * ts[2]) * a.esize;
+        char* const dst = (char*)(v ? a.Vp : a.Kp) + ((long long)b * ps[0] + (long long)h * ps[1] + (long long)(L + j) * ps[2]) * a.esize;
+        *(u32x4*)(dst + 16 * c) = *(const u32x4*)(src + 16 * c);
     }
-}
-
-size_t align256(size_t v) { return (v + 255) / 256 * 256; }
-
-// row statistics of the (n + 1) target rows per sequence, k = 1
-BuildWorkspace carve_verify_workspace(const ot_verify_params& p, void* base) {
-    const size_t rows = (size_t)p.batch * (size_t)(p.n + 1);
-    const size_t parts = (size_t)max_scan_parts(p.vocab);
-    BuildWorkspace w;
-    memset(&w, 0, sizeof(w));
-    size_t off = 0;
-    char* b = (char*)base;
-    // (a null base is the sizing pass: offsets only)
-    auto take = [&](size_t bytes) { char* q = b ? b + off : nullptr; off = align256(off + bytes); return (void*)q; };
-    w.row_lse = (double*)take(rows * 8);
-    w.row_topv = (float*)take(rows * 4);
-    w.row_topi = (int32_t*)take(rows * 4);
-    if (parts > 1) {
-        w.part_m = (float*)take(rows * parts * 4);
-        w.part_s = (double*)take(rows * parts * 8);
-        w.part_topv = (float*)take(rows * parts * 4);
-        w.part_topi = (int32_t*)take(rows * parts * 4);
-    }
-    w.bytes = off;
-    return w;
-}
-
-SampleWorkspace carve_sample_workspace(const ot_verify_params& p, void* base) {
-    const size_t rows = (size_t)p.batch * (size_t)(p.n + 1);
-    const int elems = p.logits_dtype == OT_BF16 ? SegOf<uint16_t>::ELEMS : SegOf<float>::ELEMS;
-    SampleWorkspace w;
-    w.nseg = (p.vocab + elems - 1) / elems;
-    size_t off = 0;
-    char* b = (char*)base;
-    // (a null base is the sizing pass: offsets only)
-    auto take = [&](size_t bytes) { char* q = b ? b + off : nullptr; off = align256(off + bytes); return (void*)q; };
-    w.seg_s = (double*)take(rows * w.nseg * 8);
-    w.seg_m = (float*)take(rows * w.nseg * 4);
-    w.truth = (int32_t*)take(rows * 4);
-    w.bytes = off;
-    return w;
-}
-
-int launch_walk(const ot_verify_params& p, const int32_t* row_top, const int32_t* token, const int32_t* parent,
-                const int32_t* n_out, int32_t* accept_len, int32_t* accept_node, int32_t* accept_token, hipStream_t s) {
-    WalkKArgs a;
-    a.row_top = row_top; a.token = token; a.parent = parent; a.n_out = n_out;
-    a.accept_len = accept_len; a.accept_node = accept_node; a.accept_token = accept_token; a.n = p.n;
-    const int threads = (p.n + 63) / 64 * 64;
-    hipLaunchKernelGGL(verify_walk_kernel, dim3(p.batch), dim3(threads), 0, s, a);
-    OT_HIP_CHECK(hipGetLastError());
-    return OT_OK;
 }
 
 int validate_verify(const ot_verify_params* p) {
@@ -351,6 +423,9 @@ int validate_verify(const ot_verify_params* p) {
     return OT_OK;
 }
 
+// segments of 64 vectors that the picking wavefront has room for
+bool sample_supported(const ot_verify_params& p) { return p.vocab <= kMaxSeg * 64 * (p.logits_dtype == OT_BF16 ? 8 : 4); }
+
 }  // namespace
 }  // namespace ot
 
@@ -360,7 +435,7 @@ extern "C" {
 
 size_t ot_verify_workspace_bytes(const ot_verify_params* p) {
     if (validate_verify(p) != OT_OK) return 0;
-    return carve_verify_workspace(*p, nullptr).bytes;
+    return verify_bytes(*p);
 }
 
 int ot_verify_greedy(const ot_verify_params* p, const void* target_logits, const int32_t* token, const int32_t* parent,
@@ -376,25 +451,14 @@ int ot_verify_greedy(const ot_verify_params* p, const void* target_logits, const
     const void* ip[6] = {token, parent, n_out, accept_len, accept_node, accept_token};
     for (int i = 0; i < 6; ++i)
         if ((uintptr_t)ip[i] % 4) return OT_ERR_INVALID_ARG;
-    const BuildWorkspace ws = carve_verify_workspace(*p, workspace);
-    if (workspace_bytes < ws.bytes) return OT_ERR_WORKSPACE_TOO_SMALL;
-    hipStream_t s = (hipStream_t)hip_stream;
-
-    ScanGeometry sg;
-    sg.batch = p->batch; sg.vocab = p->vocab; sg.k = 1; sg.dtype = p->logits_dtype;
-    sg.nsteps = 1; sg.rows_per_seq = p->n + 1; sg.row0 = 0; sg.rows = p->n + 1;
-    sg.grow_k = 1; sg.grow_n = 1;
-    sg.stride_seq = p->stride_seq; sg.stride_depth = 0; sg.stride_row = p->stride_row;
-    st = launch_row_scan(sg, target_logits, ws, s);
-    if (st != OT_OK) return st;
-
-    return launch_walk(*p, ws.row_topi, token, parent, n_out, accept_len, accept_node, accept_token, s);
+    if (workspace_bytes < verify_bytes(*p)) return OT_ERR_WORKSPACE_TOO_SMALL;
+    return launch_verify(*p, false, 0.f, target_logits, nullptr, token, parent, n_out, workspace, accept_len, accept_node,
+                         accept_token, (hipStream_t)hip_stream);
 }
 
 size_t ot_verify_sample_workspace_bytes(const ot_verify_params* p) {
     if (validate_verify(p) != OT_OK) return 0;
-    const SampleWorkspace w = carve_sample_workspace(*p, nullptr);
-    return w.nseg > 64 * 8 ? 0 : w.bytes;
+    return sample_supported(*p) ? verify_bytes(*p) : 0;
 }
 
 int ot_verify_sample(const ot_verify_params* p, float temperature, const void* target_logits, const float* u,
@@ -412,27 +476,11 @@ int ot_verify_sample(const ot_verify_params* p, float temperature, const void* t
     const void* ip[7] = {u, token, parent, n_out, accept_len, accept_node, accept_token};
     for (int i = 0; i < 7; ++i)
         if ((uintptr_t)ip[i] % 4) return OT_ERR_INVALID_ARG;
-    const SampleWorkspace ws = carve_sample_workspace(*p, workspace);
-    if (ws.nseg > 64 * 8) return OT_ERR_UNSUPPORTED;          // segments per lane of the picking wavefront
+    if (!sample_supported(*p)) return OT_ERR_UNSUPPORTED;
     if ((long long)p->batch * (p->n + 1) > 65535) return OT_ERR_UNSUPPORTED;
-    if (workspace_bytes < ws.bytes) return OT_ERR_WORKSPACE_TOO_SMALL;
-    hipStream_t s = (hipStream_t)hip_stream;
-
-    SampleKArgs a;
-    a.logits = target_logits; a.u = u; a.seg_m = ws.seg_m; a.seg_s = ws.seg_s; a.truth = ws.truth;
-    a.rows_per_seq = p->n + 1; a.vocab = p->vocab; a.nseg = ws.nseg;
-    a.stride_seq = p->stride_seq; a.stride_row = p->stride_row;
-    a.c = (float)(1.4426950408889634 / (double)temperature);
-    const int rows = p->batch * (p->n + 1);
-    // 16-byte loads need every row to start on a 16-byte boundary
-    const int vec = 16 / esize;
-    const bool vecload = (uintptr_t)target_logits % 16 == 0 && p->stride_seq % vec == 0 && p->stride_row % vec == 0;
-    if (p->logits_dtype == OT_BF16)
-        st = vecload ? launch_sample_t<uint16_t, true>(a, rows, s) : launch_sample_t<uint16_t, false>(a, rows, s);
-    else
-        st = vecload ? launch_sample_t<float, true>(a, rows, s) : launch_sample_t<float, false>(a, rows, s);
-    if (st != OT_OK) return st;
-    return launch_walk(*p, ws.truth, token, parent, n_out, accept_len, accept_node, accept_token, s);
+    if (workspace_bytes < verify_bytes(*p)) return OT_ERR_WORKSPACE_TOO_SMALL;
+    return launch_verify(*p, true, (float)(1.4426950408889634 / (double)temperature), target_logits, u, token, parent, n_out,
+                         workspace, accept_len, accept_node, accept_token, (hipStream_t)hip_stream);
 }
 
 int ot_kv_append(const ot_attn_params* p, void* K_prefix, void* V_prefix, const void* K_tree, const void* V_tree,
@@ -471,8 +519,7 @@ int ot_kv_append(const ot_attn_params* p, void* K_prefix, void* V_prefix, const 
     for (int i = 0; i < 3; ++i) {
         a.kps[i] = p->kp_strides[i]; a.vps[i] = p->vp_strides[i]; a.kts[i] = p->kt_strides[i]; a.vts[i] = p->vt_strides[i];
     }
-    // at most n nodes can be accepted; rows beyond a sequence's accepted count end at once
-    hipLaunchKernelGGL(kv_append_kernel, dim3(p->n, p->batch * p->kv_heads), dim3(64), 0, (hipStream_t)hip_stream, a);
+    hipLaunchKernelGGL(kv_append_kernel, dim3(p->batch * p->kv_heads), dim3(256), 0, (hipStream_t)hip_stream, a);
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
