@@ -36,9 +36,11 @@ struct VerifyKArgs {
 };
 
 // A row's result as one 64-bit word, so that the words of a sequence tell both whether all its rows are there and what
-// they are.  The workspace needs no preparation: a word counts only with this upper half, and the workgroup that walks
-// the tree clears the words again.
-constexpr u64 kPublished = 0x7f4a91c3ull << 32;
+// they are.  The workspace needs no preparation: a word counts only with these upper 46 bits (the lower 18 hold any
+// token), and the workgroup that walks the tree clears the words again.
+constexpr int kTokenBits = 18;
+constexpr u64 kPublished = 0x1fd2a470cb5dull << kTokenBits;
+static_assert(kMaxVocab <= 1 << kTokenBits, "a token fits the word");
 constexpr int kBatch = 4;        // vectors per lane requested at once; the next batch is in flight while one is processed
 
 // One wavefront: publish the row's ground truth, and walk the tree if that completes the sequence.  Words travel through
@@ -65,7 +67,7 @@ __device__ __forceinline__ void publish_and_walk(const VerifyKArgs& a, int b, in
     for (int q = 0; q < Q; ++q) {
         w[q] = kPublished;
         if (lane + 64 * q <= n) w[q] = __hip_atomic_load(words + lane + 64 * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        all = all && (w[q] >> 32) == (kPublished >> 32);
+        all = all && (w[q] >> kTokenBits) == (kPublished >> kTokenBits);
     }
     if (!__all(all)) return;
     int32_t* const out_tok = a.accept_token + (size_t)b * (n + 1);
@@ -76,7 +78,7 @@ __device__ __forceinline__ void publish_and_walk(const VerifyKArgs& a, int b, in
         int g = 0;                                            // ground truth after `cur`
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (((cur + 1) >> 6) == q) g = rl((int)(unsigned)w[q], (cur + 1) & 63);
+            if (((cur + 1) >> 6) == q) g = rl((int)((unsigned)w[q] & ((1u << kTokenBits) - 1u)), (cur + 1) & 63);
         int nx = -1;
 #pragma unroll
         for (int q = 0; q < QN; ++q) {
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(NT) void verify_greedy_kernel(const VerifyKArgs a) 
         atomicMin(&s_tok, e);
     }
     __syncthreads();
-    if (wave == 0) publish_and_walk(a, b, j, s_tok, lane);
+    if (wave == 0) publish_and_walk(a, b, j, s_tok < row.len ? s_tok : 0, lane);     // (a row of NaNs only: token 0)
 }
 
 // inclusive prefix sum over the lanes of a wavefront
@@ -193,6 +195,58 @@ __device__ __forceinline__ double wave_scan_f64(double v, int lane) {
         if (lane >= o) v += t;
     }
     return v;
+}
+
+// The same draw for a row whose every term vanished against its reference (all logits near the type's lowest value, where
+// x log2(e) / T overflows): one wavefront, from the row's maximum down.  NaNs weigh nothing.
+template <int DT>
+__device__ int draw_from_maximum(const Row<DT>& row, float c, float u, int lane) {
+    constexpr int VEC = Row<DT>::VEC;
+    float M = -INFINITY;
+    for (int v = lane; v < row.nvec; v += 64) {
+        float x[VEC];
+        VecOf<DT>::unpack(row.load(v), x);
+        row.mask(x, v);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) M = fmaxf(M, x[i]);
+    }
+    M = wave_max_f(M);
+    if (M == -INFINITY) return 0;
+    auto weight = [&](float x) { return fmaxf(__builtin_amdgcn_exp2f((x - M) * c), 0.f); };      // (NaN: 0)
+    auto vector_sum = [&](int v) {
+        float x[VEC], e = 0.f;
+        VecOf<DT>::unpack(row.load(v), x);
+        row.mask(x, v);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) e += weight(x[i]);
+        return v < row.nvec ? (double)e : 0.0;
+    };
+    double sum = 0.0;
+    for (int v0 = 0; v0 < row.nvec; v0 += 64) sum += vector_sum(v0 + lane);
+    const double target = (double)u * __shfl(wave_scan_f64(sum, lane), 63);
+    double before = 0.0;
+    int last = 0;                                                    // (by rounding the target may not be passed)
+    for (int v0 = 0; v0 < row.nvec; v0 += 64) {
+        const double e = vector_sum(v0 + lane), incl = before + wave_scan_f64(e, lane);
+        const u64 past = __ballot(incl > target), any = __ballot(e > 0.0);
+        if (past || any) {
+            const int L = past ? __ffsll((long long)past) - 1 : 63 - __clzll((long long)any);
+            double acc = __shfl(incl - e, L);
+            float x[VEC];
+            VecOf<DT>::unpack(row.load(v0 + L), x);
+            row.mask(x, v0 + L);
+            bool found = false;
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                const float p = weight(x[i]);
+                acc += (double)p;
+                if (p > 0.f && !found) { last = (v0 + L) * VEC + i - row.shift; found = acc > target; }
+            }
+            if (past) break;
+        }
+        before = __shfl(incl, 63);
+    }
+    return last;
 }
 
 // Sampling: the token at which the cumulative sum of exp(x / T), in token order, passes u x total.  The sums of all
@@ -292,45 +346,49 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
         const double target = (double)u * __shfl(incl, 63);
         // first lane whose segments reach past the target; by rounding there may be none: the last lane with weight
         const u64 past = __ballot(incl > target), any = __ballot(lane_sum > 0.0);
-        const int Ls = past ? __ffsll((long long)past) - 1 : 63 - __clzll((long long)any);
-        // inside that lane: the first segment that passes the target, else (rounding) the end of its last one with weight
-        bool found = false;
-        int seg = 0;
-        float mseg = 0.f;
-        double before = incl - lane_sum, rs = 0.0;                   // rs: residual in the segment's own units
+        const int Ls = past ? __ffsll((long long)past) - 1 : max(63 - __clzll((long long)any), 0);
+        if (!past && !any) {
+            truth = draw_from_maximum<DT>(row, a.c, u, lane);
+        } else {
+            // inside that lane: the first segment that passes the target, else (rounding) the end of its last one with weight
+            bool found = false;
+            int seg = 0;
+            float mseg = 0.f;
+            double before = incl - lane_sum, rs = 0.0;               // rs: residual in the segment's own units
 #pragma unroll
-        for (int i = 0; i < PER_MAX; ++i) {
-            if (i < per && wt[i] > 0.0 && !found) {
-                seg = lane * per + i;
-                mseg = ms[i];
-                if (before + wt[i] > target) { found = true; rs = (target - before) / sc[i]; }
-                else rs = wt[i] / sc[i];
+            for (int i = 0; i < PER_MAX; ++i) {
+                if (i < per && wt[i] > 0.0 && !found) {
+                    seg = lane * per + i;
+                    mseg = ms[i];
+                    if (before + wt[i] > target) { found = true; rs = (target - before) / sc[i]; }
+                    else rs = wt[i] / sc[i];
+                }
+                if (!found) before += wt[i];
             }
-            if (!found) before += wt[i];
-        }
-        seg = __shfl(seg, Ls);
-        mseg = __shfl(mseg, Ls);
-        rs = __shfl(rs, Ls);
-        // inside the segment: the vector
-        const int v = seg * 64 + lane;
-        const double e = v < row.nvec ? (double)s_e[v] : 0.0;
-        const double incl_e = wave_scan_f64(e, lane);
-        const u64 past_e = __ballot(incl_e > rs), any_e = __ballot(e > 0.0);
-        const int Le = past_e ? __ffsll((long long)past_e) - 1 : 63 - __clzll((long long)any_e);
-        // inside the vector: the element (every lane does the same)
-        const double start = __shfl(incl_e - e, Le);
-        float x[VEC];
-        VecOf<DT>::unpack(row.load(seg * 64 + Le), x);
-        row.mask(x, seg * 64 + Le);
-        double acc = start;
-        int k = -1, lastk = 0;
+            seg = __shfl(seg, Ls);
+            mseg = __shfl(mseg, Ls);
+            rs = __shfl(rs, Ls);
+            // inside the segment: the vector
+            const int v = seg * 64 + lane;
+            const double e = v < row.nvec ? (double)s_e[v] : 0.0;
+            const double incl_e = wave_scan_f64(e, lane);
+            const u64 past_e = __ballot(incl_e > rs), any_e = __ballot(e > 0.0);
+            const int Le = past_e ? __ffsll((long long)past_e) - 1 : max(63 - __clzll((long long)any_e), 0);
+            // inside the vector: the element (every lane does the same)
+            const double start = __shfl(incl_e - e, Le);
+            float x[VEC];
+            VecOf<DT>::unpack(row.load(seg * 64 + Le), x);
+            row.mask(x, seg * 64 + Le);
+            double acc = start;
+            int k = -1, lastk = 0;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            const float p = __builtin_amdgcn_exp2f(fmaf(x[i], a.c, -mseg));
-            acc += (double)p;
-            if (p > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
+            for (int i = 0; i < VEC; ++i) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(x[i], a.c, -mseg));
+                acc += (double)p;
+                if (p > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
+            }
+            truth = min(max((seg * 64 + Le) * VEC + (k < 0 ? lastk : k) - row.shift, 0), row.len - 1);
         }
-        truth = (seg * 64 + Le) * VEC + (k < 0 ? lastk : k) - row.shift;
     }
     publish_and_walk(a, b, j, truth, lane);
 }

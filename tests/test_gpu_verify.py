@@ -187,3 +187,68 @@ def test_low_temperature_draw_is_the_greedy_result():
     torch.cuda.synchronize()
     for x, y in zip(a, b_):
         assert torch.equal(x, y)
+
+
+def _at_offset(stored, dtype, offset):
+    """The rows as a view that starts `offset` elements into a buffer, its rows offset + 5 elements longer."""
+    import torch
+    t = U.to_device(stored, dtype)
+    flat = torch.zeros((*t.shape[:-1], t.shape[-1] + offset + 5), dtype=t.dtype, device="cuda")
+    view = flat[..., offset:offset + t.shape[-1]]
+    view.copy_(t)
+    return view
+
+
+@pytest.mark.parametrize("V,n,B,dtype,offset", [
+    (8192, 255, 2, "bf16", 0),         # 256 threads per row by length; 512 rows
+    (8200, 127, 1, "bf16", 1),         # 128 rows: 1024 threads; every row starts inside a vector
+    (8201, 128, 1, "bf16", 7),         # 129 rows: 512 threads
+    (8197, 255, 1, "f32", 3),          # 256 rows: still 512
+    (8196, 128, 2, "f32", 2),          # 258 rows: 256 threads, several batches of vectors
+    (5, 3, 1, "bf16", 6),              # a row shorter than a vector, across two of them
+    (1, 1, 1, "f32", 1),
+])
+def test_every_row_result_at_any_alignment_and_width_of_workgroup(V, n, B, dtype, offset):
+    """A chain that carries every row's ground truth is accepted whole, so the tokens are the results of all rows."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = np.random.default_rng(V + n)
+    target = wl.store((g.standard_normal((B, n + 1, V)) * 2.0).astype(np.float32), dtype)
+    t64 = wl.to_f64(target, dtype)
+    u = np.stack([_uniforms_with_margin(t64[b], 1.0, g) for b in range(B)])
+    rows = _at_offset(target, dtype, offset)
+    for sampled in (False, True):
+        truth = np.array([[vf.sample_truth(t64[b, r], 1.0, float(u[b, r])) if sampled else int(np.argmax(t64[b, r]))
+                           for r in range(n + 1)] for b in range(B)])
+        trees = [dict(token=truth[b, :n], parent=np.arange(-1, n - 1), n_out=n) for b in range(B)]
+        dev = _tree_to_device(api, trees, B, n)
+        alen, _, atok = (api.verify_sample(rows, torch.from_numpy(u).cuda(), 1.0, dev) if sampled
+                         else api.verify_greedy(rows, dev))
+        torch.cuda.synchronize()
+        assert list(alen.cpu().numpy()) == [n + 1] * B
+        np.testing.assert_array_equal(atok.cpu().numpy(), truth)
+
+
+@pytest.mark.parametrize("V,dtype", [(70, "f32"), (8, "bf16"), (9001, "bf16")])
+def test_rows_at_the_types_lowest_value_or_without_numbers(V, dtype):
+    """Rows masked with the type's lowest value: alone they are a uniform distribution, beside an ordinary logit they
+    weigh nothing.  Rows of NaNs have no ground truth, but name a token of the vocabulary."""
+    import torch
+    from paper_2406_17276_amd import api
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    low = torch.finfo(dt).min
+    x = torch.full((1, 5, V), low, dtype=dt, device="cuda")
+    x[0, 1, V // 2] = 1.0
+    x[0, 2] = float("-inf")
+    x[0, 3] = float("nan")
+    x[0, 4, 0] = float("nan")
+    want = [V // 3, V // 2, 0]
+    u = torch.full((1, 5), (V // 3 + 0.5) / V, dtype=torch.float32, device="cuda")
+    for sampled in (False, True):
+        truth = want if sampled else [0, V // 2, 0]
+        tree = _tree_to_device(api, [dict(token=np.array(truth + [0]), parent=np.arange(-1, 3), n_out=4)], 1, 4)
+        alen, _, atok = api.verify_sample(x, u, 1.0, tree) if sampled else api.verify_greedy(x, tree)
+        torch.cuda.synchronize()
+        got = list(atok.cpu().numpy()[0])
+        assert int(alen) >= 4 and got[:3] == truth
+        assert all(0 <= t < V for t in got[:int(alen)])
