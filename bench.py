@@ -445,7 +445,7 @@ def main():
         else:
             result["roofline"], result["roofline_attention"] = scan_roof, attn_roof
         result["config"]["longest_kernel_note"] = (
-            "the tree-selection kernel (one wavefront per sequence, a chain of dependent selections) is not bound by a "
+            "the tree-selection kernel (one workgroup per sequence, a chain of dependent selections) is not bound by a "
             "memory or arithmetic roof; its time is ms_per_step minus the two kernels above")
     if yard:
         result["yardsticks"] = yard

@@ -370,3 +370,25 @@ def test_scores_that_jump_between_tiles(Hq, Hkv, n):
     want = _oracle_attention(x, mask, "bf16")
     assert np.isfinite(got).all()
     assert np.abs(got - want).max() < TOL["bf16"]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
+    (1, 2, 2, 64, 31, 32),             # 32 rows per workgroup, eight key slices; key blocks one short
+    (1, 2, 2, 128, 33, 33),            # 33 rows in blocks of 32; one key past a block
+    (1, 2, 1, 64, 1, 32),              # 64 rows, a single prefix key
+    (2, 2, 2, 64, 500, 65),            # 64-row workgroups, key ranges split and merged
+    (1, 4, 1, 128, 1500, 64),          # 256 rows in blocks of 32, split
+    (4, 64, 64, 64, 20, 65),           # enough workgroups without splits: 128 rows, two key slices
+    (4, 64, 64, 128, 32, 64),          # 64 rows, four key slices
+    (4, 64, 64, 128, 5, 10),           # 32 rows, fewer key blocks than slices
+])
+def test_f32_row_blocks_and_key_slices_at_their_edges(B, Hq, Hkv, D, L, n):
+    w = _shape("f32", B, Hq, Hkv, D, L, n)
+    x = wl.make_attention_inputs(w, 9)
+    mask = _random_masks(B, n, 5)
+    got = _gpu_attention(x, mask, "f32")
+    heads = sorted(set(np.linspace(0, Hkv - 1, 5).astype(int)))       # the oracle takes some of the KV heads
+    q = [h * (Hq // Hkv) + i for h in heads for i in range(Hq // Hkv)]
+    sub = {k: v if k == "prefix_len" else v[:, q if k == "Q" else heads] for k, v in x.items()}
+    want = _oracle_attention(sub, mask, "f32")
+    assert np.abs(got[:, q] - want).max() < TOL["f32"]

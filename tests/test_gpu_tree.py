@@ -355,3 +355,74 @@ def test_one_shot_adaptive_build_with_a_threshold_nothing_passes_stops_after_one
     assert list(steps.cpu().numpy()) == [1, 1]
     want = [ot_oracle.build_tree_adaptive(x[b].astype(np.float64), 2, 100, 3, 10.0) for b in range(2)]
     U.assert_tree_equal(got, want, 100)
+
+
+@pytest.mark.parametrize("V,k,n,d,B,dtype,offset", [
+    (8192, 4, 12, 3, 1, "bf16", 0), (8185, 4, 12, 3, 1, "bf16", 3),          # 256 threads: all of it; one vector too long
+    (32768, 4, 12, 3, 1, "bf16", 0), (32761, 4, 12, 3, 1, "bf16", 5),        # 1024 threads, rows in registers
+    (65536, 4, 12, 3, 1, "bf16", 8), (65529, 4, 12, 3, 1, "bf16", 1),        # rolling, 512 and 1024 threads
+    (131072, 4, 12, 3, 1, "bf16", 0), (131065, 4, 12, 3, 1, "bf16", 7),      # one part; two
+    (16385, 4, 12, 3, 1, "f32", 1), (32766, 16, 20, 3, 1, "f32", 2), (65533, 5, 12, 3, 1, "f32", 3),
+    (8191, 16, 64, 7, 5, "bf16", 1),                                         # 1685 rows: rolling, 256 threads
+    (4093, 16, 64, 7, 5, "f32", 3),
+])
+def test_scan_forms_at_the_ends_of_their_ranges_and_rows_at_any_alignment(V, k, n, d, B, dtype, offset):
+    import torch
+    from paper_2406_17276_amd import api
+    stored, want = _random_case(V, k, n, d, B, dtype, seed=V + offset)
+    dev = U.to_device(stored, dtype)
+    big = torch.zeros((B, d, n, V + offset + (5 if V % 2 else 8)), dtype=dev.dtype, device="cuda")
+    view = big[..., offset:offset + V]
+    view.copy_(dev)
+    got = api.build_tree(view, k, n, d)
+    torch.cuda.synchronize()
+    U.assert_tree_equal(got, want, n)
+
+
+@pytest.mark.parametrize("k,n,d", [
+    (16, 16, 6), (16, 17, 6),          # 256 candidates per step; more: 512 threads
+    (16, 32, 5), (16, 33, 5),          # 512; two per thread
+    (16, 64, 5), (16, 65, 5),          # 1024; 1024 threads
+    (16, 128, 4), (16, 129, 4),        # 2048; four per thread
+    (3, 85, 32),                       # 255 candidates, but a pool of more nodes than 256 threads take
+    (16, 256, 32),                     # the largest pool
+])
+def test_selection_at_the_ends_of_each_number_of_threads(k, n, d):
+    stored, want = _random_case(200, k, n, d, 2, "f32", seed=k + n + d, scale=2.0)
+    got = _run(stored, "f32", k, n, d)
+    U.assert_tree_equal(got, want, n)
+
+
+@pytest.mark.parametrize("V,k,n,d,B", [(32000, 16, 256, 9, 2), (50001, 10, 200, 8, 2)])
+def test_builds_in_several_launches_match_the_streaming_builder(V, k, n, d, B):
+    """More than 96 MB of rows: the call goes in chunks of steps, the rows of finished sequences are left unread.  The
+    streaming builder takes every step by itself."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V)
+    x = torch.randn((B, d, n, V), generator=g, device="cuda")
+    x *= torch.tensor([1.5, 5.0], device="cuda")[:, None, None, None]        # sequences that finish at different steps
+    x = x.to(torch.bfloat16)
+    for delta in (None, -1.0, 0.01, 0.3):
+        ts = api.TreeStream(B, V, k, n, d, api.OT_BF16, "cuda")
+        steps = torch.zeros(B, dtype=torch.int32)
+        on = torch.ones(B, dtype=torch.bool)
+        F = 1
+        for t in range(d):
+            ts.expand(x[:, t, :F].contiguous())
+            F = min(n, k * F)
+            steps += on.int()
+            if delta is not None:
+                _, go = ts.e_sub(delta)
+                on &= go.cpu().bool()
+        want = ts.finalize()
+        if delta is None:
+            got = api.build_tree(x, k, n, d)
+        else:
+            got, used, _ = api.build_tree_adaptive(x, k, n, d, delta)
+            assert used.cpu().tolist() == steps.tolist()
+        torch.cuda.synchronize()
+        for name in ("token", "parent", "depth", "mask", "n_out"):
+            assert torch.equal(getattr(got, name), getattr(want, name)), (delta, name)
+        torch.testing.assert_close(got.expect, want.expect, rtol=1e-6, atol=0.0)
