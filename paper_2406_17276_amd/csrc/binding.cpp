@@ -61,13 +61,16 @@ int32_t dtype_code(const at::Tensor& t) {
 }
 void* current_stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
+// Data pointers are taken before the GIL is released: a tensor without storage (functorch wrappers, sparse, fake) answers
+// data_ptr() with an exception, which becomes a Python error only under the GIL.
+struct NoGil {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
 template <typename F>
 int without_gil(F&& f) {
-    int st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return st;
+    const NoGil released;
+    return f();
 }
 
 struct Ref {                             // owned reference
@@ -177,14 +180,17 @@ PyObject* build_tree(PyObject* const* a, Py_ssize_t na) {
     const at::Tensor& x = tensor(a[0]);
     const ot_build_params p = build_params(x, as_int(a[1]), as_int(a[2]), as_int(a[3]));
     const size_t need = ot_build_workspace_bytes(&p);
-    if (need == 0) return Py_BuildValue("iO", ot_build_tree(&p, ptr(x), nullptr, 0, nullptr, nullptr), Py_None);
+    const void* const px = ptr(x);
+    if (need == 0) return Py_BuildValue("iO", ot_build_tree(&p, px, nullptr, 0, nullptr, nullptr), Py_None);
     at::Tensor own;
     const at::Tensor* ws = tensor_or_null(a[5]);
     if (!ws) { own = new_tensor({(int64_t)need}, at::kByte, x.device()); ws = &own; }
     Ref tree(a[4] == Py_None ? new_tree(a[6], p.batch, p.n, x.device()) : (Py_INCREF(a[4]), a[4]));
     const ot_tree_out o = tree_pointers(tree.p);
+    void* const pw = ptr(*ws);
+    const size_t nw = bytes_of(*ws);
     void* s = current_stream();
-    const int st = without_gil([&] { return ot_build_tree(&p, ptr(x), ptr(*ws), bytes_of(*ws), &o, s); });
+    const int st = without_gil([&] { return ot_build_tree(&p, px, pw, nw, &o, s); });
     return Py_BuildValue("iO", st, tree.p);
 }
 
@@ -202,10 +208,13 @@ PyObject* build_tree_adaptive(PyObject* const* a, Py_ssize_t na) {
     Ref tree(a[5] == Py_None ? new_tree(a[7], p.batch, p.n, x.device()) : (Py_INCREF(a[5]), a[5]));
     const ot_tree_out o = tree_pointers(tree.p);
     const at::Tensor steps = new_tensor({p.batch}, at::kInt, x.device()), e = new_tensor({p.batch}, at::kDouble, x.device());
+    const void* const px = ptr(x);
+    void* const pw = ptr(*ws);
+    const size_t nw = bytes_of(*ws);
+    int32_t* const psteps = (int32_t*)ptr(steps);
+    double* const pe = (double*)ptr(e);
     void* s = current_stream();
-    const int st = without_gil([&] {
-        return ot_build_tree_adaptive(&p, delta, ptr(x), ptr(*ws), bytes_of(*ws), &o, (int32_t*)ptr(steps), (double*)ptr(e), s);
-    });
+    const int st = without_gil([&] { return ot_build_tree_adaptive(&p, delta, px, pw, nw, &o, psteps, pe, s); });
     Ref ws_(wrap(steps)), we_(wrap(e));
     return Py_BuildValue("iOOO", st, tree.p, ws_.p, we_.p);
 }
@@ -223,11 +232,11 @@ PyObject* stream_begin(PyObject* const* a, Py_ssize_t na) {
     const at::Tensor ws = new_tensor({(int64_t)need}, at::kByte, dev);
     const at::Tensor tok = new_tensor({p.batch, p.n}, at::kInt, dev), par = new_tensor({p.batch, p.n}, at::kInt, dev);
     const at::Tensor cnt = new_tensor({p.batch}, at::kInt, dev);
+    void* const pw = ptr(ws);
+    int32_t *const pt = (int32_t*)ptr(tok), *const pp = (int32_t*)ptr(par), *const pc = (int32_t*)ptr(cnt);
     void* s = current_stream();
     // one small kernel sets the loop state and the frontier arrays (tokens and parents -1, counts 0)
-    const int st = without_gil([&] {
-        return ot_internal_tree_begin(&p, ptr(ws), bytes_of(ws), (int32_t*)ptr(tok), (int32_t*)ptr(par), (int32_t*)ptr(cnt), s);
-    });
+    const int st = without_gil([&] { return ot_internal_tree_begin(&p, pw, need, pt, pp, pc, s); });
     Ref w(wrap(ws)), t(wrap(tok)), q(wrap(par)), c(wrap(cnt));
     return Py_BuildValue("iOOOO", st, w.p, t.p, q.p, c.p);
 }
@@ -251,10 +260,12 @@ PyObject* stream_expand(PyObject* const* a, Py_ssize_t na) {
     Ref par(PyObject_GetAttr(self, names.frontier_parent)), cnt(PyObject_GetAttr(self, names.frontier_count));
     const at::Tensor& w = tensor(ws.p);
     int32_t *pt = (int32_t*)ptr(tensor(tok.p)), *pp = (int32_t*)ptr(tensor(par.p)), *pc = (int32_t*)ptr(tensor(cnt.p));
+    const void* const pr = ptr(rows);
+    void* const pw = ptr(w);
+    const size_t nw = bytes_of(w);
+    const int64_t stride_seq = rows.stride(0), stride_row = rows.stride(1);
     void* s = current_stream();
-    const int st = without_gil([&] {
-        return ot_tree_expand(&p, step, ptr(rows), rows.stride(0), rows.stride(1), ptr(w), bytes_of(w), pt, pp, pc, s);
-    });
+    const int st = without_gil([&] { return ot_tree_expand(&p, step, pr, stride_seq, stride_row, pw, nw, pt, pp, pc, s); });
     if (st == OT_OK) {
         Ref next(PyLong_FromLong(step + 1));
         if (PyObject_SetAttr(self, names.step, next.p)) throw PyErrSet();
@@ -270,8 +281,11 @@ PyObject* stream_mask(PyObject* const* a, Py_ssize_t na) {
     const int step = as_int(so.p);
     const at::Tensor& w = tensor(ws.p);
     const at::Tensor m = new_tensor({p.batch, p.n, ((int64_t)p.depth * p.n + 63) / 64}, at::kLong, w.device());
+    void* const pw = ptr(w);
+    const size_t nw = bytes_of(w);
+    uint64_t* const pm = (uint64_t*)ptr(m);
     void* s = current_stream();
-    const int st = without_gil([&] { return ot_tree_frontier_mask(&p, step, ptr(w), bytes_of(w), (uint64_t*)ptr(m), s); });
+    const int st = without_gil([&] { return ot_tree_frontier_mask(&p, step, pw, nw, pm, s); });
     Ref mo(wrap(m));
     return Py_BuildValue("iO", st, mo.p);
 }
@@ -291,8 +305,10 @@ PyObject* stream_esub(PyObject* const* a, Py_ssize_t na) {
     Ref e(PyObject_GetAttr(a[0], names.esub)), g(PyObject_GetAttr(a[0], names.go));
     double* pe = (double*)ptr(tensor(e.p));
     int32_t* pg = (int32_t*)ptr(tensor(g.p));
+    void* const pw = ptr(w);
+    const size_t nw = bytes_of(w);
     void* s = current_stream();
-    const int st = without_gil([&] { return ot_tree_esub(&p, step, delta, ptr(w), bytes_of(w), pe, pg, s); });
+    const int st = without_gil([&] { return ot_tree_esub(&p, step, delta, pw, nw, pe, pg, s); });
     return Py_BuildValue("iOO", st, e.p, g.p);
 }
 
@@ -305,8 +321,10 @@ PyObject* stream_finalize(PyObject* const* a, Py_ssize_t na) {
     const at::Tensor& w = tensor(ws.p);
     Ref tree(a[1] == Py_None ? new_tree(a[2], p.batch, p.n, w.device()) : (Py_INCREF(a[1]), a[1]));
     const ot_tree_out o = tree_pointers(tree.p);
+    void* const pw = ptr(w);
+    const size_t nw = bytes_of(w);
     void* s = current_stream();
-    const int st = without_gil([&] { return ot_tree_finalize(&p, step, ptr(w), bytes_of(w), &o, s); });
+    const int st = without_gil([&] { return ot_tree_finalize(&p, step, pw, nw, &o, s); });
     return Py_BuildValue("iO", st, tree.p);
 }
 
@@ -320,11 +338,13 @@ PyObject* attention(PyObject* const* a, Py_ssize_t na) {
     if (!O) { own = at::empty_like(Q); O = &own; }
     const at::Tensor& w = tensor(a[8]);
     const ot_attn_params p = attn_params(Q, Kp, Vp, Kt, Vt, *O, (float)as_double(a[9]));
+    const void *const q = ptr(Q), *const kp = ptr(Kp), *const vp = ptr(Vp), *const kt = ptr(Kt), *const vt = ptr(Vt);
+    const int32_t* const pl = (const int32_t*)ptr(len);
+    const uint64_t* const pm = (const uint64_t*)ptr(mask);
+    void *const po = ptr(*O), *const pw = ptr(w);
+    const size_t nw = bytes_of(w);
     void* s = current_stream();
-    const int st = without_gil([&] {
-        return ot_tree_verify_attention(&p, ptr(Q), ptr(Kp), ptr(Vp), ptr(Kt), ptr(Vt), (const int32_t*)ptr(len),
-                                        (const uint64_t*)ptr(mask), ptr(*O), ptr(w), bytes_of(w), s);
-    });
+    const int st = without_gil([&] { return ot_tree_verify_attention(&p, q, kp, vp, kt, vt, pl, pm, po, pw, nw, s); });
     Ref o(wrap(*O));
     return Py_BuildValue("iO", st, o.p);
 }
@@ -347,12 +367,14 @@ PyObject* attention_fp8kv(PyObject* const* a, Py_ssize_t na) {
     if (!O) { own = at::empty_like(Q); O = &own; }
     const at::Tensor& w = tensor(a[10]);
     const ot_attn_params p = attn_params(Q, Kp, Vp, Kt, Vt, *O, (float)as_double(a[11]));
+    const void *const q = ptr(Q), *const kp = ptr(Kp), *const vp = ptr(Vp), *const kt = ptr(Kt), *const vt = ptr(Vt);
+    const float *const ks = (const float*)ptr(sc[0]), *const vs = (const float*)ptr(sc[1]);
+    const int32_t* const pl = (const int32_t*)ptr(len);
+    const uint64_t* const pm = (const uint64_t*)ptr(mask);
+    void *const po = ptr(*O), *const pw = ptr(w);
+    const size_t nw = bytes_of(w);
     void* s = current_stream();
-    const int st = without_gil([&] {
-        return ot_tree_verify_attention_fp8kv(&p, ptr(Q), ptr(Kp), ptr(Vp), ptr(Kt), ptr(Vt), (const float*)ptr(sc[0]),
-                                              (const float*)ptr(sc[1]), (const int32_t*)ptr(len), (const uint64_t*)ptr(mask), ptr(*O),
-                                              ptr(w), bytes_of(w), s);
-    });
+    const int st = without_gil([&] { return ot_tree_verify_attention_fp8kv(&p, q, kp, vp, kt, vt, ks, vs, pl, pm, po, pw, nw, s); });
     Ref o(wrap(*O));
     return Py_BuildValue("iO", st, o.p);
 }
@@ -381,10 +403,14 @@ PyObject* verify(PyObject* const* a, Py_ssize_t na) {
     const at::Tensor out = new_tensor({B, rows}, at::kInt, x.device());
     const int32_t *pt = (const int32_t*)ptr(tok), *pp = (const int32_t*)ptr(par), *pn = (const int32_t*)ptr(n_out);
     int32_t *ol = (int32_t*)ptr(len), *on = (int32_t*)ptr(node), *ot = (int32_t*)ptr(out);
+    const void* const px = ptr(x);
+    const float* const pu = (const float*)ptr(u);
+    void* const pw = ptr(*ws);
+    const size_t nw = bytes_of(*ws);
     void* s = current_stream();
     const int st = without_gil([&] {
-        return u ? ot_verify_sample(&p, T, ptr(x), (const float*)ptr(*u), pt, pp, pn, ptr(*ws), bytes_of(*ws), ol, on, ot, s)
-                 : ot_verify_greedy(&p, ptr(x), pt, pp, pn, ptr(*ws), bytes_of(*ws), ol, on, ot, s);
+        return u ? ot_verify_sample(&p, T, px, pu, pt, pp, pn, pw, nw, ol, on, ot, s)
+                 : ot_verify_greedy(&p, px, pt, pp, pn, pw, nw, ol, on, ot, s);
     });
     Ref l(wrap(len)), d(wrap(node)), o(wrap(out));
     return Py_BuildValue("iOOO", st, l.p, d.p, o.p);
@@ -397,11 +423,12 @@ PyObject* kv_append(PyObject* const* a, Py_ssize_t na) {
     const at::Tensor &len = tensor(a[4]), &alen = tensor(a[5]), &anode = tensor(a[6]);
     const ot_attn_params p = attn_params(Kt, &Kp, &Vp, Kt, Vt, Kt, 0.f);
     const at::Tensor nl = new_tensor({p.batch}, at::kInt, Kt.device());
+    void *const kp = ptr(Kp), *const vp = ptr(Vp);
+    const void *const kt = ptr(Kt), *const vt = ptr(Vt);
+    const int32_t *const pl = (const int32_t*)ptr(len), *const pa = (const int32_t*)ptr(alen), *const pn = (const int32_t*)ptr(anode);
+    int32_t* const po = (int32_t*)ptr(nl);
     void* s = current_stream();
-    const int st = without_gil([&] {
-        return ot_kv_append(&p, ptr(Kp), ptr(Vp), ptr(Kt), ptr(Vt), (const int32_t*)ptr(len), (const int32_t*)ptr(alen),
-                            (const int32_t*)ptr(anode), (int32_t*)ptr(nl), s);
-    });
+    const int st = without_gil([&] { return ot_kv_append(&p, kp, vp, kt, vt, pl, pa, pn, po, s); });
     Ref o(wrap(nl));
     return Py_BuildValue("iO", st, o.p);
 }

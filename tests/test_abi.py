@@ -166,6 +166,46 @@ def test_binding_rejects_tensors_smaller_than_the_frontier():
         ts.expand(torch.zeros((2, 16, 64)))                               # all steps fed
 
 
+def _stream(ws):
+    import torch
+    ts = api.TreeStream.__new__(api.TreeStream)
+    ts.p, ts.step, ts.ws = api.BuildParams(1, 64, 3, 4, 16, api.OT_F32, 0, 0, 64), 1, ws
+    ts.frontier_token = ts.frontier_parent = torch.zeros((1, 16), dtype=torch.int32)
+    ts.frontier_count = torch.zeros(1, dtype=torch.int32)
+    return ts
+
+
+def _storageless_calls():
+    """Every call of the binding, with the one tensor it is handed in place of an input or a workspace."""
+    import torch
+    i = lambda *s: torch.zeros(s, dtype=torch.int32)
+    f = lambda *s: torch.zeros(s)
+    tree, ws, mask = api.alloc_tree(1, 16, "cpu"), torch.zeros(1 << 20, dtype=torch.uint8), torch.zeros((1, 16, 1), dtype=torch.int64)
+    q, by, sc, rows = f(1, 4, 16, 64), torch.zeros((1, 4, 16, 64), dtype=torch.uint8), f(1, 4), f(1, 17, 64)
+    return {
+        "build_tree": (f(1, 3, 16, 64), lambda x: api.build_tree(x, 4, 16, 3)),
+        "build_tree_adaptive": (f(1, 3, 16, 64), lambda x: api.build_tree_adaptive(x, 4, 16, 3, 0.1)),
+        "expand": (f(1, 16, 64), lambda x: _stream(ws).expand(x)),
+        "frontier_mask": (ws, lambda x: _stream(x).frontier_mask()),
+        "e_sub": (ws, lambda x: _stream(x).e_sub(0.1)),
+        "finalize": (ws, lambda x: _stream(x).finalize()),
+        "attention": (q, lambda x: api.tree_verify_attention(x, None, None, q, q, i(1), mask, workspace=ws)),
+        "attention_fp8kv": (q, lambda x: api.tree_verify_attention_fp8kv(x, None, None, by, by, sc, sc, i(1), mask, workspace=ws)),
+        "verify_greedy": (rows, lambda x: api.verify_greedy(x, tree)),
+        "verify_sample": (rows, lambda x: api.verify_sample(x, f(1, 17), 1.0, tree)),
+        "kv_append": (q, lambda x: api.kv_append(x, q, q, q, i(1), i(1), i(1, 16))),
+    }
+
+
+@pytest.mark.parametrize("call", sorted(_storageless_calls()))
+def test_binding_raises_for_tensors_without_storage(call):
+    """torch.vmap hands its function tensors that have no storage: an error, before anything else is looked at."""
+    import torch
+    t, fn = _storageless_calls()[call]
+    with pytest.raises(RuntimeError, match="data pointer"):
+        torch.vmap(fn)(torch.stack([t, t]))
+
+
 def test_binding_fails_loudly_when_library_is_missing(monkeypatch):
     monkeypatch.setattr(api, "_lib", None)
     monkeypatch.setattr(api, "_LIB_PATH", "/nonexistent/libopttree.so")
