@@ -555,7 +555,8 @@ int launch_row_scan(const ScanGeometry& g, const void* logits, const BuildWorksp
     if (g.nsteps < 1 || g.nsteps > 255 || g.grow_k < 1 || g.grow_k > 255 || g.grow_n < 1 || g.grow_n > 32767)
         return OT_ERR_INVALID_ARG;
     if (g.rows < 1 || g.row0 < 0 || g.row0 + g.rows > g.rows_per_seq || g.rows_per_seq > 0x7fff) return OT_ERR_INVALID_ARG;
-    if ((long long)g.batch * g.rows * max_scan_parts(g.vocab) > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;
+    // the results of all rows of all sequences are indexed with 32 bits, however few of them this launch covers
+    if ((long long)g.batch * g.rows_per_seq * max_scan_parts(g.vocab) > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;
     ScanKArgs a;
     a.k = g.k;
     a.rows_per_seq = g.rows_per_seq;

@@ -68,6 +68,17 @@ def test_build_tree_rejects_bad_arguments_without_launching():
     assert L.ot_tree_finalize(C.byref(p), 0, fake, need, C.byref(out), None) == -1
 
 
+def test_builds_of_more_rows_than_32_bits_count_are_refused_without_launching():
+    """294912 sequences of 7697 rows: refused as a whole, also where the call would go in launches of a few rows each."""
+    L = api.lib()
+    fake, out = C.c_void_p(0x1000), api.TreeOut(*([0x1000] * 7))
+    p = _bp(batch=294912, vocab=16, depth=32, k=16, n=256, logits_dtype=1, stride_seq=131072, stride_depth=4096, stride_row=16)
+    need = api.build_workspace_bytes(p)
+    assert sum(api.frontier_sizes(16, 256, 32)[:32]) * p.batch > 0x7fffffff
+    assert L.ot_build_tree(C.byref(p), fake, fake, need, C.byref(out), None) == -2
+    assert L.ot_build_tree_adaptive(C.byref(p), 0.1, fake, fake, need, C.byref(out), fake, fake, None) == -2
+
+
 def _ap(**kw):
     s = (C.c_int64 * 3)
     d = dict(batch=1, q_heads=4, kv_heads=4, head_dim=64, n=16, max_prefix=128, dtype=0, softmax_scale=0.0,
