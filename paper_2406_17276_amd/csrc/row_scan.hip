@@ -45,9 +45,9 @@ struct ScanKArgs {
     const int32_t* seq_active;        // SKIP kernels: rows of sequence b are left unread when seq_active[b] == 0
 };
 
-// The order of candidates as one integer: value desc, token asc
+// The order of candidates as one integer: value desc, token asc (-0 counts as +0: equal logits)
 __device__ __forceinline__ u64 cand_key(float v, int e) {
-    const unsigned u = __float_as_uint(v);
+    const unsigned bits = __float_as_uint(v), u = bits == 0x80000000u ? 0u : bits;
     const unsigned f = (u >> 31) ? ~u : (u | 0x80000000u);
     return ((u64)f << 32) | (u64)(0xffffffffu - (unsigned)e);
 }

@@ -426,3 +426,26 @@ def test_builds_in_several_launches_match_the_streaming_builder(V, k, n, d, B):
         for name in ("token", "parent", "depth", "mask", "n_out"):
             assert torch.equal(getattr(got, name), getattr(want, name)), (delta, name)
         torch.testing.assert_close(got.expect, want.expect, rtol=1e-6, atol=0.0)
+
+
+@pytest.mark.parametrize("V,k,n,d,B,dtype", [
+    (300, 8, 12, 3, 2, "f32"), (20000, 16, 20, 3, 1, "bf16"),          # rows in registers: 256 and 1024 threads
+    (40000, 16, 20, 3, 1, "bf16"), (8200, 16, 64, 7, 5, "bf16"),       # rolling: 512 threads; 256
+    (140000, 16, 20, 3, 1, "bf16"),                                    # two parts and their merge
+    (2500, 16, 16, 3, 1, "f32"),                                       # 1200 zeros: more candidates than the list holds
+])
+def test_zeros_of_either_sign_are_equal_logits(V, k, n, d, B, dtype):
+    """Equal logits: the smaller token id first, so a -0 precedes a +0 of a larger token."""
+    zeros = 1200 if V == 2500 else 24
+    for seed in range(V, V + 16):
+        g = np.random.default_rng(seed)
+        x = -1.0 - np.abs(g.standard_normal((B, d, n, V)).astype(np.float32))
+        for row in x.reshape(-1, V):
+            row[g.choice(V, zeros, replace=False)] = np.where(g.random(zeros) < 0.5, np.float32(0.0), np.float32(-0.0))
+        stored = wl.store(x, dtype)
+        want = U.oracle_trees(stored, dtype, k, n, d)
+        if min(t["min_gap"] for t in want) > U.GAP:
+            break
+    else:
+        raise RuntimeError("no gapped input")
+    U.assert_tree_equal(_run(stored, dtype, k, n, d), want, n)
