@@ -7,8 +7,8 @@
 //
 // One workgroup handles one row, or one part of a row longer than the workgroup's capacity.
 //   1. every wavefront, on its own, vector by vector: the vector's maximum, and sum of exp(x - ref) over its elements.
-//      ref is the maximum of the wavefront's first vectors; it moves up when an element exceeds it by more than 40
-//      (fp32 sums of terms up to e^40 lose nothing), so exponentials need no second pass over the row.
+//      ref is the wavefront's maximum so far; when it moves up, the sum so far is scaled once, so exponentials need no
+//      second pass over the row, and the terms that matter have exponents near 0, which fp32 rounds least.
 //   2. barrier; tau = a lower bound of the k-th largest element: the k-th largest (or a little less) of the maxima of 64
 //      groups of lanes -- each group holds an element >= its maximum, so at least k elements are >= tau,
 //   3. elements >= tau (about k + 3) of the vectors whose own maximum reaches tau become candidates,
@@ -33,7 +33,6 @@ typedef unsigned long long u64;
 constexpr int kCandCap = 1024;         // candidates of one part
 constexpr int kVecCap = 512;           // rolling form: pairs of vectors that hold candidates
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kSlack = 40.f;         // how far an element may exceed the reference (natural-log units)
 constexpr int kRollVpl = 16;
 
 struct ScanKArgs {
@@ -70,6 +69,21 @@ __device__ __forceinline__ float group_max(float v) {
     if (G >= 8) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(v), __float_as_int(v))));
     if (G >= 16) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(v), __float_as_int(v))));
     return v;
+}
+
+// 2^x in fp64 for the factor between two references, to 1e-8 (Taylor series of e^t on |t| <= ln 2 / 2, seven terms): the
+// exponential instruction's 2^-24 would be an error of everything summed so far
+__device__ __forceinline__ double exp2_factor(double x) {
+    const double n = rint(x), t = (x - n) * 0.6931471805599453;
+    double p = 1.0 / 5040;
+    p = fma(p, t, 1.0 / 720);
+    p = fma(p, t, 1.0 / 120);
+    p = fma(p, t, 1.0 / 24);
+    p = fma(p, t, 1.0 / 6);
+    p = fma(p, t, 0.5);
+    p = fma(p, t, 1.0);
+    p = fma(p, t, 1.0);
+    return ldexp(p, (int)n);
 }
 
 template <int NT, bool KEEP>
@@ -176,9 +190,10 @@ struct Scan {
         constexpr int PER = KEEP ? 1 : 2;
         float vmax[VPL / PER];
         float xk[KEEP ? VPL : 1][VEC];                            // KEEP: all elements of this lane
-        float acc[4] = {0.f, 0.f, 0.f, 0.f};
         float m, mc;                                              // this lane's maximum; reference exponent (log2 units)
+        double s_w;                                               // sum over the wavefront
         if constexpr (KEEP) {
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < VPL; ++i) {
                 VecOf<DT>::unpack(w[i], xk[i]);
@@ -202,8 +217,11 @@ struct Scan {
 #pragma unroll
                     for (int c = 0; c < VEC; ++c) acc[c & 3] += __builtin_amdgcn_exp2f(fmaf(xk[i][c], kLog2e, -mc));
             }
+            s_w = wave_sum_rows_d((acc[0] + acc[1]) + (acc[2] + acc[3]));
         } else {
-            float lim = -INFINITY;                                // largest element the reference admits
+            // a lane adds up 16 vectors: fp32 inside a vector, fp64 above
+            float ref = -INFINITY;                                // the wavefront's maximum so far
+            double acc = 0.0;
             mc = 0.f;
 #pragma unroll
             for (int i = 0; i < VPL; ++i) {
@@ -223,24 +241,27 @@ struct Scan {
                     vmax[i / 2] = i % 2 == 0 ? v : fmaxf(vmax[i / 2], v);
                     // e^(x - m) = 2^(x log2e - mc) with mc = fl(m log2e): one fma per element.  mc is carried along as the
                     // wave's reference exponent, so its rounding cancels when the partial sums are combined.
-                    if (__any(v > lim)) {
-                        const float m = wave_max_f(v), mn = fmaxf(m, -1e38f) * kLog2e;     // (finite for the lowest masks too)
-                        if (i > 0) {
-                            const float f = __builtin_amdgcn_exp2f(mc - mn);
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) acc[c] = acc[c] > 0.f ? acc[c] * f : 0.f;
-                        }
-                        mc = mn; lim = m + kSlack;
+                    if (__any(v > ref)) {
+                        ref = wave_max_f(v);
+                        const float mn = fmaxf(ref, -1e38f) * kLog2e;                      // (finite for the lowest masks too)
+                        if (i > 0) acc = acc > 0.0 ? acc * exp2_factor((double)mc - (double)mn) : 0.0;
+                        mc = mn;
                     }
+                    float e[VEC];
 #pragma unroll
-                    for (int c = 0; c < VEC; ++c) acc[c & 3] += __builtin_amdgcn_exp2f(fmaf(x[c], kLog2e, -mc));
+                    for (int c = 0; c < VEC; ++c) e[c] = __builtin_amdgcn_exp2f(fmaf(x[c], kLog2e, -mc));
+#pragma unroll
+                    for (int h = VEC / 2; h >= 1; h /= 2)
+#pragma unroll
+                        for (int c = 0; c < h; ++c) e[c] += e[c + h];
+                    acc += (double)e[0];
                 }
             }
             m = vmax[0];
 #pragma unroll
             for (int i = 1; i < VPL / 2; ++i) m = fmaxf(m, vmax[i]);
+            s_w = wave_sum_d(acc);
         }
-        const double s_w = wave_sum_rows_d((acc[0] + acc[1]) + (acc[2] + acc[3]));
         if (lane == 0) { sh.wm[wave] = s_w > 0.0 ? mc : -INFINITY; sh.ws[wave] = s_w; }
         const float gm = group_max<GL>(m);
         if ((lane & (GL - 1)) == 0) sh.g[tid / GL] = ordered(gm);

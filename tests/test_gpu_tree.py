@@ -449,3 +449,33 @@ def test_zeros_of_either_sign_are_equal_logits(V, k, n, d, B, dtype):
     else:
         raise RuntimeError("no gapped input")
     U.assert_tree_equal(_run(stored, dtype, k, n, d), want, n)
+
+
+@pytest.mark.parametrize("B,V,dtype", [
+    (256, 32000, "bf16"), (64, 8000, "f32"),             # rows in registers
+    (2048, 32000, "bf16"), (1600, 15000, "f32"),         # rolling: 256 threads
+    (128, 60000, "bf16"), (64, 120000, "bf16"),          # 512, 1024
+    (64, 200000, "bf16"), (64, 70000, "f32"),            # two parts
+])
+@pytest.mark.parametrize("sigma,peak", [(1.0, 0.0), (4.0, 6.0), (2.0, 20.0), (2.0, 30.0), (3.0, 40.0)])
+def test_normaliser_of_flat_and_of_confident_rows(B, V, dtype, sigma, peak):
+    """A tree of one node has E = p of its token, so log E = x - lse to the precision of the normaliser.  The term that
+    dominates errs by 2^-23 (v_exp_f32, one unit in the last place) and by 2^-24 for the rounding of an exponent near 0;
+    the fp32 additions on its way (13 at most) err by half a unit of a sum each, 2^-24 x sqrt(13) at random: 4e-7.  The
+    sigma = 2, peak = 20 rows (one element among thousands that weigh as much) come closest."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B + V)
+    x = torch.randn((B, V), generator=g, device="cuda") * sigma
+    x[torch.arange(B, device="cuda"), torch.randint(0, V, (B,), generator=g, device="cuda")] += peak
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ts = api.TreeStream(B, V, 1, 1, 1, api.OT_BF16 if dtype == "bf16" else api.OT_F32, "cuda")
+    ts.expand(x[:, None, :])
+    got = ts.finalize().expect.log()
+    worst = 0.0
+    for b in range(0, B, 128):
+        y = x[b:b + 128].double()
+        worst = max(worst, float((got[b:b + 128] - (y.max(1).values - torch.logsumexp(y, 1))).abs().max()))
+    print(f"largest error of a normaliser: {worst:.2e}", flush=True)
+    assert worst < 5e-7
