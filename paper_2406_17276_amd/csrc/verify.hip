@@ -197,80 +197,30 @@ __device__ __forceinline__ double wave_scan_f64(double v, int lane) {
     return v;
 }
 
-// The same draw for a row whose every term vanished against its reference (all logits near the type's lowest value, where
-// x log2(e) / T overflows): one wavefront, from the row's maximum down.  NaNs weigh nothing.
-template <int DT>
-__device__ int draw_from_maximum(const Row<DT>& row, float c, float u, int lane) {
-    constexpr int VEC = Row<DT>::VEC;
-    float M = -INFINITY;
-    for (int v = lane; v < row.nvec; v += 64) {
-        float x[VEC];
-        VecOf<DT>::unpack(row.load(v), x);
-        row.mask(x, v);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) M = fmaxf(M, x[i]);
-    }
-    M = wave_max_f(M);
-    if (M == -INFINITY) return 0;
-    auto weight = [&](float x) { return fmaxf(__builtin_amdgcn_exp2f((x - M) * c), 0.f); };      // (NaN: 0)
-    auto vector_sum = [&](int v) {
-        float x[VEC], e = 0.f;
-        VecOf<DT>::unpack(row.load(v), x);
-        row.mask(x, v);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) e += weight(x[i]);
-        return v < row.nvec ? (double)e : 0.0;
-    };
-    double sum = 0.0;
-    for (int v0 = 0; v0 < row.nvec; v0 += 64) sum += vector_sum(v0 + lane);
-    const double target = (double)u * __shfl(wave_scan_f64(sum, lane), 63);
-    double before = 0.0;
-    int last = 0;                                                    // (by rounding the target may not be passed)
-    for (int v0 = 0; v0 < row.nvec; v0 += 64) {
-        const double e = vector_sum(v0 + lane), incl = before + wave_scan_f64(e, lane);
-        const u64 past = __ballot(incl > target), any = __ballot(e > 0.0);
-        if (past || any) {
-            const int L = past ? __ffsll((long long)past) - 1 : 63 - __clzll((long long)any);
-            double acc = __shfl(incl - e, L);
-            float x[VEC];
-            VecOf<DT>::unpack(row.load(v0 + L), x);
-            row.mask(x, v0 + L);
-            bool found = false;
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                const float p = weight(x[i]);
-                acc += (double)p;
-                if (p > 0.f && !found) { last = (v0 + L) * VEC + i - row.shift; found = acc > target; }
-            }
-            if (past) break;
-        }
-        before = __shfl(incl, 63);
-    }
-    return last;
-}
-
 // Sampling: the token at which the cumulative sum of exp(x / T), in token order, passes u x total.  The sums of all
 // 16-byte vectors stay in LDS (fp32 inside a vector, fp64 above); 64 consecutive vectors are a segment, which one
 // wavefront reads in one go with one reference exponent.  The segment that holds the draw, then the vector, are found by
 // prefix sums over lanes; only that vector is read again.
+// The reference of a segment is the wavefront's maximum so far: no term exceeds 1, whatever the temperature, and the terms
+// that matter have exponents near 0, which fp32 rounds least.
 constexpr int kMaxSeg = 512;
+__device__ __forceinline__ float sample_term(float x, float ref, float c) { return __builtin_amdgcn_exp2f((x - ref) * c); }
 template <int DT, int NT>
 __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) {
     constexpr int VEC = Row<DT>::VEC, PER_MAX = kMaxSeg / 64 + 1;    // (the longest row may start inside a vector)
-    extern __shared__ __attribute__((aligned(16))) float s_e[];      // [segments x 64]  sum of exp2(x c - ref) per vector
-    __shared__ float s_ref[kMaxSeg + 1];                             // reference exponent of a segment
+    extern __shared__ __attribute__((aligned(16))) float s_e[];      // [segments x 64]  sum of exp2((x - ref) c) per vector
+    __shared__ float s_ref[kMaxSeg + 1];                             // reference of a segment
     __shared__ double s_seg[kMaxSeg + 1];                              // sum over a segment
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.x / (a.n + 1), j = blockIdx.x - b * (a.n + 1);
     const Row<DT> row(a, b, j);
     const int nseg = (row.nvec + 63) / 64;
-    const float slack = 57.f / a.c;                                  // terms up to 2^57 of the reference: fp32 has the room
     float u = 0.f;
     u32x4 w[kBatch], nw[kBatch];
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) w[i] = row.stream(i * NT + tid);
     if (wave == 0) u = a.u[blockIdx.x];
-    float mc = 0.f, lim = -INFINITY;                                 // reference exponent, largest element it admits
+    float ref = -INFINITY;
     for (int v0 = 0; v0 < row.nvec; v0 += kBatch * NT) {
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) nw[i] = w[i];
@@ -288,16 +238,13 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
                 float q = x[0];
 #pragma unroll
                 for (int c = 1; c < VEC; ++c) q = fmaxf(q, x[c]);
-                if (__any(q > lim)) {
-                    const float m = wave_max_f(q);
-                    mc = fminf(fmaxf(m * a.c, -1e38f), 1e38f);       // (finite for the lowest masks too)
-                    lim = m + slack;
-                }
+                if (__any(q > ref)) ref = wave_max_f(q);
+                const float r = ref == -INFINITY ? 0.f : ref;        // (no logit yet: every term is 0)
                 float e = 0.f;
 #pragma unroll
-                for (int c = 0; c < VEC; ++c) e += __builtin_amdgcn_exp2f(fmaf(x[c], a.c, -mc));
-                s_e[v + tid] = e;
-                if (lane == 0) s_ref[seg] = lim == -INFINITY ? -INFINITY : mc;
+                for (int c = 0; c < VEC; ++c) e += sample_term(x[c], r, a.c);
+                s_e[v + tid] = fmaxf(e, 0.f);                        // (a vector with a NaN weighs nothing)
+                if (lane == 0) s_ref[seg] = ref;
             }
         }
 #pragma unroll
@@ -337,7 +284,7 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
             sc[i] = wt[i] = 0.0;
             if (i < per) {
                 // weight of the segment relative to the largest reference (double exp2: relative error 1e-16)
-                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2((double)ms[i] - (double)M);
+                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2(((double)ms[i] - (double)M) * (double)a.c);
                 wt[i] = ms[i] == -INFINITY ? 0.0 : s_seg[lane * per + i] * sc[i];
                 lane_sum += wt[i];
             }
@@ -346,10 +293,8 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
         const double target = (double)u * __shfl(incl, 63);
         // first lane whose segments reach past the target; by rounding there may be none: the last lane with weight
         const u64 past = __ballot(incl > target), any = __ballot(lane_sum > 0.0);
-        const int Ls = past ? __ffsll((long long)past) - 1 : max(63 - __clzll((long long)any), 0);
-        if (!past && !any) {
-            truth = draw_from_maximum<DT>(row, a.c, u, lane);
-        } else {
+        if (past || any) {
+            const int Ls = past ? __ffsll((long long)past) - 1 : 63 - __clzll((long long)any);
             // inside that lane: the first segment that passes the target, else (rounding) the end of its last one with weight
             bool found = false;
             int seg = 0;
@@ -383,7 +328,7 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
             int k = -1, lastk = 0;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(x[i], a.c, -mseg));
+                const float p = sample_term(x[i], mseg, a.c);
                 acc += (double)p;
                 if (p > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
             }
@@ -537,7 +482,8 @@ int ot_verify_sample(const ot_verify_params* p, float temperature, const void* t
     if (!sample_supported(*p)) return OT_ERR_UNSUPPORTED;
     if ((long long)p->batch * (p->n + 1) > 65535) return OT_ERR_UNSUPPORTED;
     if (workspace_bytes < verify_bytes(*p)) return OT_ERR_WORKSPACE_TOO_SMALL;
-    return launch_verify(*p, true, (float)(1.4426950408889634 / (double)temperature), target_logits, u, token, parent, n_out,
+    const float c = fminf((float)(1.4426950408889634 / (double)temperature), 3.4028234e38f);      // (finite for any temperature)
+    return launch_verify(*p, true, c, target_logits, u, token, parent, n_out,
                          workspace, accept_len, accept_node, accept_token, (hipStream_t)hip_stream);
 }
 

@@ -252,3 +252,60 @@ def test_rows_at_the_types_lowest_value_or_without_numbers(V, dtype):
         got = list(atok.cpu().numpy()[0])
         assert int(alen) >= 4 and got[:3] == truth
         assert all(0 <= t < V for t in got[:int(alen)])
+
+
+@pytest.mark.parametrize("V,dtype,sigma,peak,T", [
+    (32000, "bf16", 2.0, 8.0, 0.3), (32000, "f32", 1.0, 0.0, 0.05),    # several wavefronts' and segments' references
+    (128256, "bf16", 1.0, 0.0, 0.05), (128256, "bf16", 2.0, 8.0, 0.3),
+    (3000, "bf16", 2.0, 30.0, 2.0),
+])
+def test_boundaries_of_the_sampled_distribution(V, dtype, sigma, peak, T):
+    """Draws with uniform numbers next to a boundary of the CDF, 8192 of them within 4e-6 of it: where they change over is
+    the boundary as the kernel has it.  A term near the reference errs by 2^-23 (v_exp_f32) and 2^-24 (its exponent), the
+    sum of a vector by 7 x 2^-24 at most, both of a share of the whole that is below 1, and u is an fp32 number: 2.5e-7."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V)
+    B, worst = 8192, 0.0
+    for rep in range(12):
+        x = torch.randn(V, generator=g, device="cuda") * sigma
+        x[int(torch.randint(0, V, (1,), generator=g, device="cuda"))] += peak
+        x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        z = x.double() / T
+        e = torch.exp(z - z.max())
+        cdf = torch.cumsum(e, 0) / e.sum()
+        for t in (int(torch.argmax(e)), int(torch.searchsorted(cdf, torch.tensor(0.02 + 0.075 * rep, device="cuda", dtype=torch.double)))):
+            edge = float(cdf[t])
+            if not 1e-4 < edge < 1.0 - 1e-5:
+                continue
+            u = (edge + (torch.arange(B, device="cuda", dtype=torch.double) - B / 2) * (8e-6 / B)).float()
+            rows = torch.as_strided(x.repeat(2), (B, 2, V), (0, V, 1))            # every sequence: the same two rows
+            tree = api.alloc_tree(B, 1)
+            tree.token.fill_(-1), tree.parent.fill_(-1), tree.n_out.zero_()
+            _, _, tok = api.verify_sample(rows, u[:, None].repeat(1, 2).contiguous(), T, tree)
+            past = tok[:, 0] > t
+            if bool(past.any()):
+                worst = max(worst, edge - float(u[past].double().min()))
+            if not bool(past.all()):
+                worst = max(worst, float(u[~past].double().max()) - edge)
+    print(f"largest error of a boundary: {worst:.2e}", flush=True)
+    assert worst < 2.5e-7
+
+
+@pytest.mark.parametrize("T", [1e-30, 1e-37, 2e-38, 1e-39, 1e-45])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_vanishing_temperatures_draw_the_most_probable_token(T, dtype):
+    import torch
+    from paper_2406_17276_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x = (torch.randn((4, 9, 5000), generator=g, device="cuda") * 3.0)
+    x[1] -= 40.0
+    x[2] += 40.0
+    x.scatter_(2, torch.randint(0, 5000, (4, 9, 1), generator=g, device="cuda"), float(x.max()) + 20.0)
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    truth = x.float().argmax(2).cpu().numpy()
+    tree = _tree_to_device(api, [dict(token=truth[b, :8], parent=np.arange(-1, 7), n_out=8) for b in range(4)], 4, 8)
+    _, _, tok = api.verify_sample(x, torch.rand((4, 9), generator=g, device="cuda"), T, tree)
+    np.testing.assert_array_equal(tok.cpu().numpy(), truth)
