@@ -233,14 +233,6 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
     v += __builtin_amdgcn_update_dpp(0, v, DPP_ROW_BCAST31, 0xc, 0xf, false);
     return v;
 }
-// p^ = e^key for key <= 0, to about 1e-7 relative: fp32 exp2 of the leading part of key * log2(e), first-order
-// correction for the remainder (an fp64 exp costs an order of magnitude more instructions)
-__device__ __forceinline__ double exp_of_logp(double key) {
-    const double t = key * 1.4426950408889634;
-    const float hi = (float)t;
-    const double lo = t - (double)hi;
-    return (double)__builtin_amdgcn_exp2f(hi) * (1.0 + lo * 0.6931471805599453);
-}
 // max over the wavefront as a scalar
 __device__ __forceinline__ float wave_max_f(float v) {
     v = row16_max(v);

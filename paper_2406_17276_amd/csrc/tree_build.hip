@@ -415,10 +415,10 @@ __global__ __launch_bounds__(NT) void tree_build_kernel(const float* topv, const
         }
         if (ADAPT) {
             pkeep = pool_best<NT>(pkey, pool, n, s, tid, lane, wave);
-            double e = 0.0;
+            double e = 0.0;                                   // fp64 exp, as in the streaming form: both stop at the same step
 #pragma unroll 1
             for (int i = 0; i * NT < pool; ++i)
-                if ((pkeep >> i) & 1u) e += NT > 512 ? exp(pkey[i * NT + tid]) : exp_of_logp(pkey[i * NT + tid]);
+                if ((pkeep >> i) & 1u) e += exp(pkey[i * NT + tid]);
             e = wave_sum_d(e);
             if (lane == 0) s.red[wave] = e;
             lds_barrier();
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(NT) void tree_build_kernel(const float* topv, const
         }
     }
     // E = sum of p^ (Eq. 3)
-    double e = wave_sum_d(node ? (NT > 512 ? exp(key) : exp_of_logp(key)) : 0.0);
+    double e = wave_sum_d(node ? exp(key) : 0.0);
     if (n > 64) {
         if (lane == 0) s.red[wave] = e;
         lds_barrier();

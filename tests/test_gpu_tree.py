@@ -479,3 +479,27 @@ def test_normaliser_of_flat_and_of_confident_rows(B, V, dtype, sigma, peak):
         worst = max(worst, float((got[b:b + 128] - (y.max(1).values - torch.logsumexp(y, 1))).abs().max()))
     print(f"largest error of a normaliser: {worst:.2e}", flush=True)
     assert worst < 5e-7
+
+
+@pytest.mark.parametrize("V,k,n,d", [(3000, 10, 50, 7), (3000, 10, 65, 7), (1000, 4, 200, 9), (1000, 16, 256, 6)])
+def test_one_shot_and_streaming_builds_agree_on_e(V, k, n, d):
+    """Both forms scan these rows the same way and add up p^ = e^(log p^) in fp64 over the same nodes, so E and E_sub differ
+    by the order of at most 256 additions (2^-53 each) and by a unit or two of exp: 1e-13."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    x = torch.randn((2, d, n, V), generator=g, device="cuda") * 3.0
+    ts = api.TreeStream(2, V, k, n, d, api.OT_F32, "cuda")
+    F = 1
+    for t in range(d):
+        ts.expand(x[:, t, :F].contiguous())
+        F = min(n, k * F)
+        e_sub, _ = ts.e_sub(-1.0)
+    want = ts.finalize()
+    got = api.build_tree(x, k, n, d)
+    adaptive, _, got_sub = api.build_tree_adaptive(x, k, n, d, -1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(got.token, want.token) and torch.equal(adaptive.token, want.token)
+    for value, ref in ((got.expect, want.expect), (adaptive.expect, want.expect), (got_sub, e_sub)):
+        torch.testing.assert_close(value, ref, rtol=1e-13, atol=0.0)
