@@ -23,6 +23,12 @@ void set_last_hip_error(int e);
         }                                                    \
     } while (0)
 
+// A grid holds fewer than 2^32 threads, so larger batches go in several launches: sequences of each (slices of equal size).
+inline int sequences_per_launch(int batch, long long threads_per_sequence) {
+    const long long most = 0xffffffffLL / threads_per_sequence, launches = (batch + most - 1) / most;
+    return (int)((batch + launches - 1) / launches);
+}
+
 // Frontier sizes F_0 = 1, F_{t+1} = min(n, k F_t) and their prefix sums
 // (Algorithm 1: each drafting step keeps at most n candidates).
 struct Frontier {

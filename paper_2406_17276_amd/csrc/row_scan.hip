@@ -535,8 +535,7 @@ int launch_scan_t(const ScanGeometry& g, const void* logits, const ScanKArgs& a,
 }
 
 template <int DT>
-int launch_scan_dt(const ScanGeometry& g, const void* logits, ScanKArgs& a, const BuildWorkspace& ws, hipStream_t s, hipEvent_t ev0,
-                   hipEvent_t ev1) {
+int launch_scan_dt(const ScanGeometry& g, const void* logits, ScanKArgs& a, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int KV = 32 / VecOf<DT>::N;                     // KEEP: 32 elements per lane
     const int vec = VecOf<DT>::N;
     const long long rows = (long long)g.batch * g.rows;
@@ -562,8 +561,8 @@ int launch_scan_dt(const ScanGeometry& g, const void* logits, ScanKArgs& a, cons
     const int st = launch_scan_t<DT, 1024, kRollVpl, false>(g, logits, a, part_elems, s, ev0, ev1);
     if (st != OT_OK || a.parts == 1) return st;
     hipLaunchKernelGGL(merge_parts_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s,
-                       (int)rows, g.rows, g.row0, g.rows_per_seq, a.seq_active, a.parts, g.k, ws.part_m, ws.part_s, ws.part_topv,
-                       ws.part_topi, ws.row_lse, ws.row_topv, ws.row_topi);
+                       (int)rows, g.rows, g.row0, g.rows_per_seq, a.seq_active, a.parts, g.k, a.part_m, a.part_s, a.part_topv,
+                       a.part_topi, a.row_lse, a.row_topv, a.row_topi);
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
@@ -584,8 +583,26 @@ int launch_row_scan(const ScanGeometry& g, const void* logits, const BuildWorksp
     a.row_lse = ws.row_lse; a.row_topv = ws.row_topv; a.row_topi = ws.row_topi;
     a.part_m = ws.part_m; a.part_s = ws.part_s; a.part_topv = ws.part_topv; a.part_topi = ws.part_topi;
     a.seq_active = skip_frozen ? ws.seq_active : nullptr;
-    return g.dtype == OT_BF16 ? launch_scan_dt<OT_BF16>(g, logits, a, ws, s, ev0, ev1)
-                              : launch_scan_dt<OT_F32>(g, logits, a, ws, s, ev0, ev1);
+    auto launch = [&](const ScanGeometry& q, const void* x, hipEvent_t e0, hipEvent_t e1) {
+        return q.dtype == OT_BF16 ? launch_scan_dt<OT_BF16>(q, x, a, s, e0, e1) : launch_scan_dt<OT_F32>(q, x, a, s, e0, e1);
+    };
+    const int per = sequences_per_launch(g.batch, 1024LL * g.rows * max_scan_parts(g.vocab));
+    if (per == g.batch) return launch(g, logits, ev0, ev1);
+    const size_t rows = (size_t)g.rows_per_seq, parts = (size_t)max_scan_parts(g.vocab);
+    for (long long b = 0; b < g.batch; b += per) {
+        ScanGeometry q = g;
+        q.batch = g.batch - b < per ? (int)(g.batch - b) : per;
+        const int st = launch(q, (const char*)logits + b * g.stride_seq * (g.dtype == OT_BF16 ? 2 : 4),
+                              b == 0 ? ev0 : nullptr, b + per >= g.batch ? ev1 : nullptr);
+        if (st != OT_OK) return st;
+        a.row_lse += per * rows; a.row_topv += per * rows * g.k; a.row_topi += per * rows * g.k;
+        if (parts > 1) {
+            a.part_m += per * rows * parts; a.part_s += per * rows * parts;
+            a.part_topv += per * rows * parts * g.k; a.part_topi += per * rows * parts * g.k;
+        }
+        if (a.seq_active) a.seq_active += per;
+    }
+    return OT_OK;
 }
 
 }  // namespace ot

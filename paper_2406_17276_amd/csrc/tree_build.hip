@@ -26,6 +26,8 @@
 // tree is complete after 4 to 7 of 10 steps.)
 //
 // Measured, MI355X, whole kernel: see the dispatch rule at the end of the file.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ot {
@@ -550,9 +552,21 @@ int launch_t(const TreeBuildArgs& a, const SelectGeometry& g, const BuildWorkspa
     if (lds + sizeof(Shared<NT>) > 64 * 1024)
         OT_HIP_CHECK(hipFuncSetAttribute((const void*)tree_build_kernel<NT, KPT, STAGE, ADAPT>,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((tree_build_kernel<NT, KPT, STAGE, ADAPT>), dim3(g.batch), dim3(NT), lds, s, ws.row_topv, ws.row_lse, g.k,
-                       g.rows_per_seq, g.n, g.depth, t0, t1, a);
-    OT_HIP_CHECK(hipGetLastError());
+    const int per = sequences_per_launch(g.batch, NT);
+    for (size_t b = 0; b < (size_t)g.batch; b += per) {
+        const size_t rows = b * g.rows_per_seq, pool = b * a.batch_pool, nodes = b * g.n, words = nodes * OT_MASK_WORDS(g.n);
+        TreeBuildArgs c = a;
+        c.topi += rows * g.k;
+        c.pool_key += pool; c.pool_meta += pool; c.pool_par += pool;
+        if (c.seq_active) c.seq_active += b;
+        c.seq_E += b;
+        if (ADAPT) { c.steps_used += b; c.e_sub += b; }
+        c.out.token += nodes; c.out.parent += nodes; c.out.depth += nodes; c.out.score += nodes; c.out.mask += words;
+        c.out.n_out += b; c.out.expect += b;
+        hipLaunchKernelGGL((tree_build_kernel<NT, KPT, STAGE, ADAPT>), dim3(std::min<size_t>(per, g.batch - b)), dim3(NT), lds, s,
+                           ws.row_topv + rows * g.k, ws.row_lse + rows, g.k, g.rows_per_seq, g.n, g.depth, t0, t1, c);
+        OT_HIP_CHECK(hipGetLastError());
+    }
     return OT_OK;
 }
 

@@ -343,7 +343,7 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
 // 6.4 / 9.6, 1024 threads 6.0 / 8.6; 512 rows 10.0 / 12.2 against 11.5 / 14.0; 1024 rows 16.5 / 18.1 against 21.7 / 21.7.
 // 128256 bf16, 64 rows 13.8 / 20.2 against 10.2 / 14.5; 512 rows 24.2 / 27.1 against 30.2 / 29.4.
 template <int DT>
-int launch_rows(const VerifyKArgs& a, int batch, bool sample, hipStream_t s) {
+int launch_rows(VerifyKArgs a, int batch, bool sample, hipStream_t s) {
     const long long rows = (long long)batch * (a.n + 1), bytes = (long long)a.vocab * Row<DT>::ESIZE;
     const int nt = bytes <= 16384 || rows > 256 ? 256 : (rows > 128 ? 512 : 1024);
     const int nseg = (a.vocab + Row<DT>::VEC - 1 + 64 * Row<DT>::VEC - 1) / (64 * Row<DT>::VEC);
@@ -352,7 +352,7 @@ int launch_rows(const VerifyKArgs& a, int batch, bool sample, hipStream_t s) {
     do {                                                                                                                     \
         if (lds > 48 * 1024)                                                                                                 \
             OT_HIP_CHECK(hipFuncSetAttribute((const void*)KERNEL<DT, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-        hipLaunchKernelGGL((KERNEL<DT, NT>), dim3((unsigned)rows), dim3(NT), lds, s, a);                                     \
+        hipLaunchKernelGGL((KERNEL<DT, NT>), dim3(grid), dim3(NT), lds, s, a);                                               \
     } while (0)
 #define OT_ROWS_NT(KERNEL)                                                          \
     do {                                                                            \
@@ -360,11 +360,21 @@ int launch_rows(const VerifyKArgs& a, int batch, bool sample, hipStream_t s) {
         else if (nt == 512) OT_ROWS(KERNEL, 512);                                   \
         else OT_ROWS(KERNEL, 1024);                                                 \
     } while (0)
-    if (sample) OT_ROWS_NT(verify_sample_kernel);
-    else OT_ROWS_NT(verify_greedy_kernel);
+    const int per = sequences_per_launch(batch, (long long)nt * (a.n + 1));
+    for (long long b = 0; b < batch; b += per) {
+        const unsigned grid = (unsigned)((batch - b < per ? batch - b : per) * (a.n + 1));
+        if (sample) OT_ROWS_NT(verify_sample_kernel);
+        else OT_ROWS_NT(verify_greedy_kernel);
+        OT_HIP_CHECK(hipGetLastError());
+        const size_t nodes = (size_t)per * a.n, words = nodes + per;
+        a.logits = (const char*)a.logits + per * a.stride_seq * Row<DT>::ESIZE;
+        if (sample) a.u += words;
+        a.token += nodes; a.parent += nodes; a.n_out += per;
+        a.truth += words;
+        a.accept_len += per; a.accept_node += nodes; a.accept_token += words;
+    }
 #undef OT_ROWS_NT
 #undef OT_ROWS
-    OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
 

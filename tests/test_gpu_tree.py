@@ -503,3 +503,20 @@ def test_one_shot_and_streaming_builds_agree_on_e(V, k, n, d):
     assert torch.equal(got.token, want.token) and torch.equal(adaptive.token, want.token)
     for value, ref in ((got.expect, want.expect), (adaptive.expect, want.expect), (got_sub, e_sub)):
         torch.testing.assert_close(value, ref, rtol=1e-13, atol=0.0)
+
+
+def test_builds_of_more_threads_than_a_grid_holds():
+    """2^24 + 3 sequences of one row: at 256 threads each more than 2^32 threads, in the scan as in the tree kernel."""
+    import torch
+    from paper_2406_17276_amd import api
+    B, V = (1 << 24) + 3, 16
+    x = torch.arange(V, device="cuda", dtype=torch.bfloat16).mul_(0.5).repeat(B, 1)
+    best = torch.randint(0, V, (B,), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
+    x.scatter_(1, best[:, None], 9.0)
+    want = torch.softmax(x[-4:].double(), 1).gather(1, best[-4:, None])[:, 0]
+    for build in (lambda: api.build_tree(x[:, None, None], 1, 1, 1), lambda: api.build_tree_adaptive(x[:, None, None], 1, 1, 1, 0.1)[0]):
+        tree = build()
+        assert torch.equal(tree.token[:, 0], best.int())
+        assert bool((tree.n_out == 1).all()) and bool((tree.parent == -1).all()) and bool((tree.mask == 1).all())
+        torch.testing.assert_close(tree.expect[-4:], want, rtol=1e-6, atol=0.0)
+        del tree

@@ -309,3 +309,22 @@ def test_vanishing_temperatures_draw_the_most_probable_token(T, dtype):
     tree = _tree_to_device(api, [dict(token=truth[b, :8], parent=np.arange(-1, 7), n_out=8) for b in range(4)], 4, 8)
     _, _, tok = api.verify_sample(x, torch.rand((4, 9), generator=g, device="cuda"), T, tree)
     np.testing.assert_array_equal(tok.cpu().numpy(), truth)
+
+
+def test_verification_of_more_threads_than_a_grid_holds():
+    """2^23 + 2 sequences of two rows: at 256 threads a row more than 2^32 threads."""
+    import torch
+    from paper_2406_17276_amd import api
+    B, V = (1 << 23) + 2, 16
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.zeros((B, 2, V), device="cuda", dtype=torch.bfloat16)
+    best = torch.randint(0, V, (B, 2), generator=g, device="cuda")
+    x.scatter_(2, best[..., None], 9.0)
+    tree = api.alloc_tree(B, 1)
+    hit = torch.rand(B, generator=g, device="cuda") < 0.5
+    tree.token.copy_(torch.where(hit, best[:, 0], (best[:, 0] + 1) % V).int()[:, None])
+    tree.parent.fill_(-1), tree.n_out.fill_(1)
+    length, node, token = api.verify_greedy(x, tree)
+    assert torch.equal(length, 1 + hit.int()) and torch.equal(node[:, 0], hit.int() - 1)
+    assert torch.equal(token[:, 0], best[:, 0].int())
+    assert torch.equal(token[:, 1], torch.where(hit, best[:, 1], torch.full_like(best[:, 1], -1)).int())
