@@ -24,12 +24,12 @@ FLAGS = [
     "-mllvm", "-amdgpu-kernarg-preload-count=12",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
-# per-file additions.  row_scan.hip: its streaming kernel walks many items per workgroup at 64 registers per lane;
-# hoisting constants and per-lane indices out of that loop (machine LICM) costs more registers than there are,
-# and a spilled value's reload would wait for the loads that are meant to stay in flight.
-# -fno-honor-nans (verify.hip too): the maxima over logits need no NaN handling (logits are finite or -inf by contract; infinities stay
-# honoured), which saves the quieting instruction in front of every maximum.
-EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"], "verify.hip": ["-fno-honor-nans"]}
+# per-file additions, row_scan.hip.
+# -fno-honor-nans: the maxima over logits need no NaN handling (logits are finite or -inf by contract; infinities stay
+# honoured), which saves the quieting instruction in front of every maximum.  (Not for verify.hip, whose rows may hold NaNs.)
+# -disable-machine-licm: without it 1 % slower (13B-shaped adaptive build 23.2 -> 23.5 us, builds of 128256-token rows 2191 ->
+# 2201 us), at the same number of registers and no spills either way.
+EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"]}
 
 
 def build(verbose: bool = False) -> str:

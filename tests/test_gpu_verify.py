@@ -254,6 +254,32 @@ def test_rows_at_the_types_lowest_value_or_without_numbers(V, dtype):
         assert all(0 <= t < V for t in got[:int(alen)])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_nans_among_the_logits(dtype):
+    """A NaN is never the most probable token; a 16-byte vector that holds one weighs nothing in the draw."""
+    import torch
+    from paper_2406_17276_amd import api
+    V, n, vec = 9000, 40, 8 if dtype == "bf16" else 4
+    g = np.random.default_rng(vec)
+    stored = wl.store((g.standard_normal((1, n + 1, V)) * 2.0).astype(np.float32), dtype)
+    at = g.integers(0, V, (n + 1, 200))
+    at[:n // 2, 0] = wl.to_f64(stored, dtype)[0, :n // 2].argmax(1) ^ 1      # beside the best token
+    rows = U.to_device(stored, dtype)
+    greedy = wl.to_f64(stored, dtype)[0]
+    drawn = greedy.copy()
+    for r in range(n + 1):
+        rows[0, r, torch.from_numpy(at[r]).cuda()] = float("nan")
+        greedy[r, at[r]] = -np.inf
+        drawn[r].reshape(-1, vec)[at[r] // vec] = -np.inf
+    u = _uniforms_with_margin(drawn, 1.0, g)
+    for sampled in (False, True):
+        truth = np.array([vf.sample_truth(drawn[r], 1.0, float(u[r])) if sampled else int(np.argmax(greedy[r])) for r in range(n + 1)])
+        tree = _tree_to_device(api, [dict(token=truth[:n], parent=np.arange(-1, n - 1), n_out=n)], 1, n)
+        _, _, tok = (api.verify_sample(rows, torch.from_numpy(u[None]).cuda(), 1.0, tree) if sampled
+                     else api.verify_greedy(rows, tree))
+        np.testing.assert_array_equal(tok.cpu().numpy()[0], truth)
+
+
 @pytest.mark.parametrize("V,dtype,sigma,peak,T", [
     (32000, "bf16", 2.0, 8.0, 0.3), (32000, "f32", 1.0, 0.0, 0.05),    # several wavefronts' and segments' references
     (128256, "bf16", 1.0, 0.0, 0.05), (128256, "bf16", 2.0, 8.0, 0.3),
