@@ -2,6 +2,8 @@
 // No arithmetic of the method lives here.
 #include <string.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.h"
 
@@ -122,9 +124,17 @@ size_t ot_build_workspace_bytes(const ot_build_params* p) {
 // One-shot build: the rows of all steps are scanned, then the tree is drafted from their statistics.  A tree is usually
 // complete long before the last step (tree_build.hip), so big inputs go in chunks of steps: scan a chunk, draft it, and
 // leave the rows of finished sequences unread from then on.  A chunk costs two more launches and another pass over the
-// pool, about 8 us on the stream, so it has at least kChunkBytes of rows, some 20 us of reading, and
-// a sixth of what was read before (few trees get that deep, and a launch over the rows of finished sequences is not free).
-static const long long kChunkBytes = 96ll << 20;
+// pool, 8 to 14 us on the stream, which is all that it brings where no tree is complete before the last step (rows in which
+// one token has nearly all of the probability).  So a chunk has at least 192 MB of rows, some 35 us of reading, and later
+// ones half of what was read before, up to 1 GB, and a sixth of it.  Measured, us, trees that stay open / trees complete
+// after half of the steps: one launch, chunks of 96 MB and a sixth, this rule (n = 60, k = 8, 10 steps, 32000 tokens):
+// 8 sequences 63 / 54, 76 / 40, 63 / 54; 16: 102 / 94, 146 / 76, 115 / 60; 32: 180 / 174, 255 / 148, 206 / 126;
+// 64: 332 / 326, 408 / 214, 374 / 219; n = 256, k = 16, 20 steps, 8 sequences of 128256 tokens: 1496 / 1439, 1739 / 515,
+// 1619 / 523.
+static long long chunk_bytes(long long before) {
+    const long long mb = 1ll << 20;
+    return std::max({192 * mb, std::min(before / 2, 1024 * mb), before / 6});
+}
 
 static int build_steps(const ot_build_params* p, bool adapt, double delta, const void* logits, void* workspace,
                        size_t workspace_bytes, const ot_tree_out* out, int32_t* steps_used, double* e_sub, void* hip_stream,
@@ -151,7 +161,7 @@ static int build_steps(const ot_build_params* p, bool adapt, double delta, const
     const long long row_bytes = (long long)p->batch * p->vocab * esize;
     for (int t0 = 0; t0 < p->depth;) {
         int t1 = t0 + 1;
-        const long long before = f.row_start[t0] * row_bytes, least = before / 6 > kChunkBytes ? before / 6 : kChunkBytes;
+        const long long least = chunk_bytes(f.row_start[t0] * row_bytes);
         while (t1 < p->depth && (f.row_start[t1] - f.row_start[t0]) * row_bytes < least) ++t1;
         if ((f.rows - f.row_start[t1]) * row_bytes < least) t1 = p->depth;
         if (ev0 || ev1) t1 = p->depth;                         // the timed form brackets one scan of everything

@@ -393,9 +393,12 @@ def test_selection_at_the_ends_of_each_number_of_threads(k, n, d):
     U.assert_tree_equal(got, want, n)
 
 
-@pytest.mark.parametrize("V,k,n,d,B", [(32000, 16, 256, 9, 2), (50001, 10, 200, 8, 2)])
+@pytest.mark.parametrize("V,k,n,d,B", [
+    (32000, 16, 256, 9, 2), (50001, 10, 200, 8, 2),       # one launch
+    (32000, 16, 256, 24, 2), (50001, 10, 200, 16, 2),     # three; two, rows at odd addresses
+])
 def test_builds_in_several_launches_match_the_streaming_builder(V, k, n, d, B):
-    """More than 96 MB of rows: the call goes in chunks of steps, the rows of finished sequences are left unread.  The
+    """More than 384 MB of rows: the call goes in chunks of steps, the rows of finished sequences are left unread.  The
     streaming builder takes every step by itself."""
     import torch
     from paper_2406_17276_amd import api
