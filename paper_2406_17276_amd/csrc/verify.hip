@@ -17,6 +17,8 @@
 // 21.0 us.
 #include <string.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ot {
@@ -401,22 +403,26 @@ struct AppendKArgs {
     long long kps[3], vps[3], kts[3], vts[3];
 };
 
-// One workgroup per (sequence, KV head): K and V rows of the accepted nodes accept_node[j] go to prefix rows L + j, 16 bytes
-// per lane, all of a branch's usual few rows at once.  Three trips to memory bound it (lengths and node, rows, writes).
-// (A wavefront for every row that could be accepted had n times as many workgroups, nearly all without work.)
+// A workgroup per (sequence, KV head) and kAppendRounds x 256 vectors that could be accepted: K and V rows of the accepted
+// nodes accept_node[j] go to prefix rows L + j, 16 bytes per lane, all of a branch's usual few rows at once.  Three trips to
+// memory bound it (lengths and node, rows, writes).  (A wavefront for every row that could be accepted had n times as many
+// workgroups, nearly all without work; one workgroup whatever n and head_dim are took 235 us for 256 accepted rows of 1024
+// fp32 of four heads, 7 as now.)
+constexpr int kAppendRounds = 8;
 __global__ __launch_bounds__(256) void kv_append_kernel(const AppendKArgs a) {
     const int b = blockIdx.x / a.kv_heads, h = blockIdx.x - b * a.kv_heads;
     const int chunks = a.D * a.esize / 16;                    // 16-byte chunks per row
     // the first round's node, asked for together with the lengths
-    int node = a.accept_node[(size_t)b * a.n + min((int)threadIdx.x / (2 * chunks), a.n - 1)];
+    const int first = blockIdx.y * 256 + threadIdx.x, step = gridDim.y * 256;
+    int node = a.accept_node[(size_t)b * a.n + min(first / (2 * chunks), a.n - 1)];
     int L = a.prefix_len[b];
     L = L < 0 ? 0 : (L > a.max_prefix ? a.max_prefix : L);
     const int cnt = a.accept_len[b] - 1;                      // accepted nodes
-    if (h == 0 && threadIdx.x == 0) a.new_prefix_len[b] = L + cnt < a.max_prefix ? L + cnt : a.max_prefix;
+    if (h == 0 && first == 0) a.new_prefix_len[b] = L + cnt < a.max_prefix ? L + cnt : a.max_prefix;
     const int rows = min(min(cnt, a.n), a.max_prefix - L);
-    for (int i = threadIdx.x; i < rows * 2 * chunks; i += 256) {
+    for (int i = first; i < rows * 2 * chunks; i += step) {
         const int r = i / chunks, c = i - r * chunks, j = r >> 1;
-        if (i >= 256) node = a.accept_node[(size_t)b * a.n + j];
+        if (i != first) node = a.accept_node[(size_t)b * a.n + j];
         if (node < 0 || node >= a.n) continue;
         const bool v = r & 1;
         const long long* const ts = v ? a.vts : a.kts;
@@ -533,7 +539,9 @@ int ot_kv_append(const ot_attn_params* p, void* K_prefix, void* V_prefix, const 
     for (int i = 0; i < 3; ++i) {
         a.kps[i] = p->kp_strides[i]; a.vps[i] = p->vp_strides[i]; a.kts[i] = p->kt_strides[i]; a.vts[i] = p->vt_strides[i];
     }
-    hipLaunchKernelGGL(kv_append_kernel, dim3(p->batch * p->kv_heads), dim3(256), 0, (hipStream_t)hip_stream, a);
+    const long long vectors = 2LL * p->n * (p->head_dim / vec);
+    const unsigned groups = (unsigned)std::min((vectors + kAppendRounds * 256 - 1) / (kAppendRounds * 256), 65535LL);
+    hipLaunchKernelGGL(kv_append_kernel, dim3(p->batch * p->kv_heads, groups), dim3(256), 0, (hipStream_t)hip_stream, a);
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }

@@ -354,3 +354,26 @@ def test_verification_of_more_threads_than_a_grid_holds():
     assert torch.equal(length, 1 + hit.int()) and torch.equal(node[:, 0], hit.int() - 1)
     assert torch.equal(token[:, 0], best[:, 0].int())
     assert torch.equal(token[:, 1], torch.where(hit, best[:, 1], torch.full_like(best[:, 1], -1)).int())
+
+
+@pytest.mark.parametrize("B,H,n,D,dtype", [
+    (1, 4, 256, 1024, "f32"), (2, 3, 256, 128, "bf16"), (1, 2, 129, 64, "f32"), (3, 1, 5, 8, "bf16"), (1, 1, 33, 4100, "f32"),
+])
+def test_append_of_long_branches(B, H, n, D, dtype):
+    """Every node accepted, in reverse order, up to the cache's end."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Lmax, L = n + 20, [0, 17, 23][:B]                              # the last: room for n - 3 rows
+    m = lambda rows: torch.randn((B, H, rows, D), generator=g, device="cuda").to(dt)
+    kp, vp, kt, vt = m(Lmax), m(Lmax), m(n), m(n)
+    wk, wv = kp.clone(), vp.clone()
+    nodes = torch.arange(n - 1, -1, -1, dtype=torch.int32, device="cuda").repeat(B, 1)
+    for b in range(B):
+        rows = min(n, Lmax - L[b])
+        wk[b, :, L[b]:L[b] + rows], wv[b, :, L[b]:L[b] + rows] = kt[b].flip(1)[:, :rows], vt[b].flip(1)[:, :rows]
+    new = api.kv_append(kp, vp, kt, vt, torch.tensor(L, dtype=torch.int32, device="cuda"),
+                        torch.full((B,), n + 1, dtype=torch.int32, device="cuda"), nodes)
+    assert torch.equal(kp, wk) and torch.equal(vp, wv)
+    assert new.cpu().tolist() == [min(l + n, Lmax) for l in L]
