@@ -356,6 +356,50 @@ def test_verification_of_more_threads_than_a_grid_holds():
     assert torch.equal(token[:, 1], torch.where(hit, best[:, 1], torch.full_like(best[:, 1], -1)).int())
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 255, 256])
+def test_walk_over_every_position(n):
+    """A chain whose nodes have a sibling each that disagrees, a twin (the same token: the smaller index counts) or a node
+    with a parent that does not exist behind them; cut off, or with nodes past n_out, at random."""
+    import torch
+    from paper_2406_17276_amd import api
+    g = np.random.default_rng(n)
+    B, V = 24, 16
+    truth = g.integers(0, V, (B, n + 1)).astype(np.int32)
+    token, parent, n_out = np.zeros((B, n), np.int32), np.zeros((B, n), np.int32), np.zeros(B, np.int32)
+    want = []
+    for b in range(B):
+        cur, stop = -1, g.random() * 0.1 * (b % 3)
+        for i in range(n):
+            kind = g.random()
+            parent[b, i], token[b, i] = cur, truth[b, cur + 1]
+            if kind < 0.2:
+                token[b, i] ^= 1                                   # disagrees
+            elif kind < 0.3:
+                parent[b, i] = int(g.choice([-7, -2, n, 10 ** 6, 2 ** 31 - 1, -2 ** 31]))
+            elif kind < 0.4 and i > 0:
+                parent[b, i], token[b, i] = parent[b, i - 1], token[b, i - 1]      # a twin
+            elif g.random() >= stop:
+                cur = i
+        n_out[b] = n if b % 4 else int(g.integers(0, n + 1))
+        path, cur = [], -1
+        while True:
+            kids = [i for i in range(n_out[b]) if parent[b, i] == cur and token[b, i] == truth[b, cur + 1]]
+            if not kids:
+                break
+            cur = kids[0]
+            path.append(cur)
+        want.append(path)
+    rows = torch.zeros((B, n + 1, V), device="cuda")
+    rows.scatter_(2, torch.from_numpy(truth).long().cuda()[..., None], 3.0)
+    tree = api.alloc_tree(B, n)
+    tree.token.copy_(torch.from_numpy(token)), tree.parent.copy_(torch.from_numpy(parent)), tree.n_out.copy_(torch.from_numpy(n_out))
+    length, node, tok = (t.cpu().numpy() for t in api.verify_greedy(rows, tree))
+    for b, path in enumerate(want):
+        A = len(path) + 1
+        assert length[b] == A and list(node[b, :A - 1]) == path and (node[b, A - 1:] == -1).all()
+        assert list(tok[b, :A]) == [truth[b, p + 1] for p in [-1] + path] and (tok[b, A:] == -1).all()
+
+
 @pytest.mark.parametrize("B,H,n,D,dtype", [
     (1, 4, 256, 1024, "f32"), (2, 3, 256, 128, "bf16"), (1, 2, 129, 64, "f32"), (3, 1, 5, 8, "bf16"), (1, 1, 33, 4100, "f32"),
 ])
