@@ -56,25 +56,36 @@ __device__ __forceinline__ void publish_and_walk(const VerifyKArgs& a, int b, in
     const int n = a.n;
     u64* const words = a.truth + (size_t)b * (n + 1);
     if (lane == 0) __hip_atomic_store(words + j, kPublished | (u64)(unsigned)truth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the tree: lane owns nodes lane, lane + 64, ...
-    const int n_out = min(a.n_out[b], n);
-    int tok[QN], par[QN];
+    // the tree: lane owns nodes lane, lane + 64, ...; few rows ask for it ahead of knowing whether it is needed
+    int n_out = 0, tok[QN], par[QN];
+    auto load_tree = [&]() {
+        n_out = min(a.n_out[b], n);
 #pragma unroll
-    for (int q = 0; q < QN; ++q) {
-        const int i = min(lane + 64 * q, n - 1);
-        tok[q] = a.token[(size_t)b * n + i];
-        par[q] = a.parent[(size_t)b * n + i];
-    }
+        for (int q = 0; q < QN; ++q) {
+            const int i = min(lane + 64 * q, n - 1);
+            tok[q] = a.token[(size_t)b * n + i];
+            par[q] = a.parent[(size_t)b * n + i];
+        }
+    };
+    const bool early = gridDim.x <= 1024;
+    if (early) load_tree();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    auto word = [&](int i) -> u64 {
+        return i <= n ? __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kPublished;
+    };
+    auto there = [](u64 v) { return (v >> kTokenBits) == (kPublished >> kTokenBits); };
+    // many rows: most workgroups see from the 64 words around their own that rows are missing (32 sequences of 257 sampled
+    // rows of 8192 fp32, every workgroup reading all words past the caches: 66 us, against 56)
+    if (!early && n >= 64 && !__all(there(word((j & ~63) + lane)))) return;
     u64 w[Q];
     bool all = true;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        w[q] = kPublished;
-        if (lane + 64 * q <= n) w[q] = __hip_atomic_load(words + lane + 64 * q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        all = all && (w[q] >> kTokenBits) == (kPublished >> kTokenBits);
+        w[q] = word(lane + 64 * q);
+        all = all && there(w[q]);
     }
     if (!__all(all)) return;
+    if (!early) load_tree();
     int32_t* const out_tok = a.accept_token + (size_t)b * (n + 1);
     int32_t* const out_node = a.accept_node + (size_t)b * n;
     // Position 0 is the root, position i + 1 node i.  next[p] = ground truth after position p | the child that carries it
@@ -367,14 +378,18 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
     publish_and_walk(a, b, j, truth, lane);
 }
 
-// Threads per row: about 131072 in all, a quarter of what is resident at a time -- more wavefronts per row shorten a row's
-// latency, fewer leave less fixed work per element.  Measured, greedy / sampled us: 32000 bf16, 64 rows, 256 threads
-// 6.4 / 9.6, 1024 threads 6.0 / 8.6; 512 rows 10.0 / 12.2 against 11.5 / 14.0; 1024 rows 16.5 / 18.1 against 21.7 / 21.7.
-// 128256 bf16, 64 rows 13.8 / 20.2 against 10.2 / 14.5; 512 rows 24.2 / 27.1 against 30.2 / 29.4.
+// Threads per row.  Few rows: more wavefronts per row shorten its latency; many: fewer leave less fixed work per element.
+// Sampled rows keep 4 bytes of LDS per vector, so long ones leave room for few workgroups on a compute unit, which then need
+// more threads each.  Measured, greedy / sampled us at 64, 256, 512, 1024 threads: 1000 bf16, 8100 rows 12.8 / 21.0,
+// 19.5 / 27.7, 31.6 / 40.1, 60.7 / 57.2; 32000 bf16, 51 rows 13.4 / 20.0, 7.5 / 10.4, 7.5 / 9.5, 7.8 / 9.6; 976 rows
+// 17.6 / 22.4, 15.5 / 19.4, 16.8 / 19.0, 18.3 / 22.8; 128256 bf16, 51 rows 39 / 60, 14.5 / 21.4, 10.6 / 16.8, 10.5 / 16.0;
+// 2040 rows 79 / 259, 81 / 102, 81 / 90, 81 / 96; 128256 fp32, 2040 rows 154 / 722, 157 / 244, 158 / 188, 154 / 181.
 template <int DT>
 int launch_rows(VerifyKArgs a, int batch, bool sample, hipStream_t s) {
     const long long rows = (long long)batch * (a.n + 1), bytes = (long long)a.vocab * Row<DT>::ESIZE;
-    const int nt = bytes <= 16384 || rows > 256 ? 256 : (rows > 128 ? 512 : 1024);
+    int nt = bytes <= 16384 || rows > 256 ? 256 : (rows > 128 ? 512 : 1024);
+    if (bytes <= 8192 && rows > 512) nt = 64;
+    if (sample && bytes > 65536 && rows > 256) nt = bytes > 262144 ? 1024 : 512;
     const int nseg = (a.vocab + Row<DT>::VEC - 1 + 64 * Row<DT>::VEC - 1) / (64 * Row<DT>::VEC);
     const size_t lds = sample ? (size_t)nseg * 64 * 4 : 0;
 #define OT_ROWS(KERNEL, NT)                                                                                                  \
@@ -385,7 +400,8 @@ int launch_rows(VerifyKArgs a, int batch, bool sample, hipStream_t s) {
     } while (0)
 #define OT_ROWS_NT(KERNEL)                                                          \
     do {                                                                            \
-        if (nt == 256) OT_ROWS(KERNEL, 256);                                        \
+        if (nt == 64) OT_ROWS(KERNEL, 64);                                          \
+        else if (nt == 256) OT_ROWS(KERNEL, 256);                                        \
         else if (nt == 512) OT_ROWS(KERNEL, 512);                                   \
         else OT_ROWS(KERNEL, 1024);                                                 \
     } while (0)
