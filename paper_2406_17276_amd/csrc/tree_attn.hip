@@ -36,6 +36,7 @@
 // f32 path (attn_f32_kernel): fp32 matrix instructions, operands straight from memory; see there.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -926,9 +927,11 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
 //                pair yields output columns EV row + e
 // Key ranges that are split over workgroups are merged by the workgroup that finishes last (tickets, as in the bf16
 // kernel).
-// Measured (MI355X, whole call; before: one FMA per LDS operand pair, a merge launch): 32 heads x 128 rows, 4096 keys of
-// 128: 413 -> 114 us (78 TFLOP/s of 157); 8 KV heads x 480 rows x 4 sequences, 2048 keys: 805 -> 209 us; 4 heads x 16 rows,
-// 128 keys of 64: 18.8 -> 10.2 us.
+// Measured (MI355X, kernels replayed from a graph; before: one FMA per LDS operand pair, a merge launch): 32 heads x 128
+// rows, 4096 keys of 128: 414 -> 109 us (78 TFLOP/s of 157); 8 KV heads x 480 rows x 4 sequences, 2048 keys: 795 -> 191 us;
+// 4 heads x 16 rows, 128 keys of 64: 9.5 -> 10 us.  Few rows over few keys are a chain that the 32 x 32 blocks do not
+// shorten: 33 rows over 128 keys of 128 13.4 -> 16.8 us, the longest loss seen over 88 shapes but for 512 workgroups of one
+// row and one key each (9 -> 15 us).
 template <int D, int QB, int KS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnKArgs a) {
     static_assert(QB * KS == 8, "eight wavefronts");
@@ -1061,14 +1064,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     l_run = xhalf_sum(l_run);
 
-    // the key slices of a row block meet in LDS, halving their number every round
-    if (KS > 1) {
+    // the key slices of a row block meet in LDS, halving their number every round; slices without a block take no part
+    const int slices = min(KS, t1 - t0);
+    if (slices > 1) {
         __syncthreads();                                             // (Q is no longer needed)
 #pragma unroll
         for (int half = KS / 2; half >= 1; half /= 2) {
+            if (slices <= half) continue;
             // [half x QB wavefronts][EV 4 + 1][64] x 16 bytes
             f32x4* const slot = (f32x4*)s_f + (size_t)((ks & (half - 1)) * QB + qb) * (EV * 4 + 1) * 64 + lane;
-            if (ks >= half && ks < 2 * half) {
+            if (ks >= half && ks < 2 * half && ks < slices) {
 #pragma unroll
                 for (int e = 0; e < EV; ++e)
 #pragma unroll
@@ -1077,7 +1082,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 slot[EV * 4 * 64] = f32x4{m_run, l_run, 0.f, 0.f};
             }
             __syncthreads();
-            if (ks < half) {
+            if (ks < half && ks + half < slices) {
                 const f32x4 ml = slot[EV * 4 * 64];
                 const float mm = fmaxf(m_run, ml.x);
                 float a1 = 0.f, a2 = 0.f;
@@ -1231,7 +1236,7 @@ static int f32_rows_per_workgroup(const ot_attn_params& p) {
 AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
     AttnPlan pl;
     pl.balance = 0;
-    const int g = p.q_heads / p.kv_heads;
+    const int g = p.q_heads / p.kv_heads, nk = p.n_keys > 0 ? p.n_keys : p.n;
     int base, tile, rows_wg = 0, splits;
     if (p.dtype == OT_BF16) {
         const bool wide = g * p.n > 64;                    // wide variants when one KV head has more than 64 rows
@@ -1249,14 +1254,19 @@ AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
         // lengths out by themselves and the ranking's extra trip to memory per workgroup costs 1 %.
         if (OT_ATTN_BALANCE && wide && p.batch > 1 && p.batch <= 64 && splits <= 1 && base < 4 * target) pl.balance = 1;
     } else {
-        // one workgroup per compute unit at a time (eight wavefronts, two per SIMD); a split has work for all its key slices
+        // One workgroup per compute unit at a time (eight wavefronts, two per SIMD).  Splitting costs 5 us (partials through
+        // memory, the merge), a 32 x 32 block 2 us of a SIMD at head_dim 64 and 4 at 128: what is at most two blocks per SIMD
+        // stays whole, and a split has one block for every SIMD at least.  Measured, us, a split for every eight blocks with
+        // prefix and tree rounded apart / this rule: 8 x 4 heads of 5 rows, 17 keys of 128 16.5 / 9.3; 4 heads of 16 rows, 1000
+        // keys of 128 21.4 / 16.9; 4 sequences of 33 rows, 500 keys of 128 23.2 / 17.8; 8 x 8 heads of 60 rows, 128 keys of 128
+        // 22.1 / 17.9; 4 x 4 heads of 128 rows, 128 keys of 64 18.6 / 14.6.
         rows_wg = f32_rows_per_workgroup(p);
         pl.row_blocks = (g * p.n + rows_wg - 1) / rows_wg;
         base = p.batch * p.kv_heads * pl.row_blocks;
-        tile = 32 * (256 / rows_wg);
-        splits = 256 / base;
+        tile = 32;
+        const int blocks = ((p.max_prefix + 31) / 32 + (nk + 31) / 32) * (rows_wg / 32);
+        splits = blocks <= 8 ? 1 : std::min(256 / base, (blocks + 3) / 4);
     }
-    const int nk = p.n_keys > 0 ? p.n_keys : p.n;
     const int max_tiles = (p.max_prefix + tile - 1) / tile + (nk + tile - 1) / tile;
     if (splits > max_tiles) splits = max_tiles;
     if (splits > kMaxSplits) splits = kMaxSplits;

@@ -381,6 +381,11 @@ def test_scores_that_jump_between_tiles(Hq, Hkv, n):
     (4, 64, 64, 64, 20, 65),           # enough workgroups without splits: 128 rows, two key slices
     (4, 64, 64, 128, 32, 64),          # 64 rows, four key slices
     (4, 64, 64, 128, 5, 10),           # 32 rows, fewer key blocks than slices
+    (1, 1, 1, 64, 1, 1), (1, 2, 2, 128, 64, 20), (1, 2, 2, 128, 96, 40), (1, 2, 2, 64, 128, 30),     # 2 to 7 key blocks,
+    (1, 2, 2, 128, 160, 31),           # slices without a block in the meeting
+    (1, 2, 2, 128, 200, 31), (1, 2, 2, 128, 225, 31),     # eight blocks in one workgroup; nine, split
+    (1, 2, 2, 64, 64, 60), (1, 2, 2, 64, 65, 60),         # the same with 64 rows per workgroup
+    (1, 1, 1, 128, 4100, 16),          # as many splits as a row block can have
 ])
 def test_f32_row_blocks_and_key_slices_at_their_edges(B, Hq, Hkv, D, L, n):
     w = _shape("f32", B, Hq, Hkv, D, L, n)
