@@ -180,7 +180,8 @@ def gqa_leg(name: str, steps: int, hip, stream):
                          "unit": "TFLOP/s", "frac": tf / MFMA_BF16_PEAK_TFLOPS, "algorithmic_flops": flops,
                          "avg_kernel_us": attn_us, "traffic": traffic.get("attn_mfma_kernel"),
                          "traffic_source": traffic_src},
-            "roofline_scan": {"kernel": "row_scan_kernel", "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
+            "roofline_scan": {"kernel": "row_scan_kernel", "rows": "all in one launch (ot_build_tree: chunks of steps)",
+                              "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
                               "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "algorithmic_bytes": logit_bytes,
                               "avg_kernel_us": scan_us, "traffic": traffic.get("row_scan_kernel"),
                               "traffic_source": traffic_src}}

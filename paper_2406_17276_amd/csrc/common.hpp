@@ -190,15 +190,6 @@ __device__ __forceinline__ double wave_sum(double v) {
     for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
     return v;
 }
-__device__ __forceinline__ int wave_max_i(int v) {
-    v = max(v, dpp_i<DPP_QUAD_XOR1>(v, v));
-    v = max(v, dpp_i<DPP_QUAD_XOR2>(v, v));
-    v = max(v, dpp_i<DPP_ROW_HALF_MIRROR>(v, v));
-    v = max(v, dpp_i<DPP_ROW_MIRROR>(v, v));
-    v = max(v, __shfl_xor(v, 16));
-    v = max(v, __shfl_xor(v, 32));
-    return v;
-}
 
 // ---- wavefront reductions that end in a scalar (DPP inside rows of 16, v_readlane across rows) ----
 __device__ __forceinline__ int rl(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }

@@ -547,10 +547,12 @@ int launch_scan_dt(const ScanGeometry& g, const void* logits, ScanKArgs& a, hipS
         return ((g.vocab + a.parts - 1) / a.parts + vec - 1) / vec * vec;
     };
     // Which form: KEEP while a workgroup's registers hold the row and the rows do not fill the chip a few times over.
-    // Measured at 32000 bf16 (64 KB a row), KEEP / rolling: 512 rows 10.1 / 11.8 us, 1024 16.4 / 17.3, 1536 22.2 / 21.9,
-    // 2048 26.9 / 26.0, 4096 48.7 / 45.3 (6.8 TB/s beyond the launch's first 6 us); fp32 (128 KB a row): 1024 23.7 / 24.4,
-    // 2048 40.9 / 41.2.  Longer rows would need parts and a merge launch (4 us and more) in the KEEP form, so they roll at
-    // any number of rows: 128256 bf16, 256 rows 20.2 / 17.3 us, 2048 rows 97 / 83.
+    // The line is where rows of the registers' whole capacity break even (32000 bf16, 16000 fp32), KEEP / rolling: 512 rows
+    // 12.6 / 15.0 us, 1024 19.5 / 21.1, 1536 24.7 / 25.4, 2048 31.0 / 31.5, 4096 53.5 / 52.1, 8192 96.5 / 90.0; fp32 1024
+    // 19.1 / 18.5, 2048 31.1 / 28.8, 8192 96.9 / 86.5.  Shorter rows would roll profitably from about 700 rows on (their
+    // 1024 threads have less than a register set each): 16384 bf16 512 rows 11.1 / 13.0, 1024 18.0 / 16.4, 4096 50.6 / 32.7;
+    // 9000 bf16 512 11.7 / 12.1, 1024 17.9 / 14.8, 4096 51.0 / 27.4.  Longer rows would need parts and a merge launch (4 us
+    // and more) in the KEEP form, so they roll at any number of rows: 128256 bf16, 256 rows 20.2 / 17.3 us, 2048 rows 97 / 83.
     a.parts = 1;
     if (g.vocab <= capacity(256, KV)) return launch_scan_t<DT, 256, KV, true>(g, logits, a, g.vocab, s, ev0, ev1);
     if (rows >= 1536 && g.vocab <= capacity(256, kRollVpl))

@@ -24,7 +24,6 @@ struct SelKArgs {
     const double* row_lse; const float* row_topv; const int32_t* row_topi;
     int k, n, depth, rows_per_seq;
     int F[OT_MAX_DEPTH + 2];
-    int row_start[OT_MAX_DEPTH + 2];
     int r0[OT_MAX_DEPTH + 2];      // rank whose per-lane minimum is a lower bound of step t's cut
     double* pool_key; int32_t* pool_tok; int32_t* pool_par;   // [batch][depth][n]  (streaming state)
     double* step_tau;                                         // [batch][depth]     (streaming state)
@@ -67,8 +66,8 @@ __device__ __forceinline__ double wave_min_d(double v) {
     v = fmin(v, dpp_d<DPP_ROW_MIRROR>(v));
     return fmin(fmin(rl_d(v, 0), rl_d(v, 16)), fmin(rl_d(v, 32), rl_d(v, 48)));
 }
-// Barrier that orders LDS traffic only.  __syncthreads() would also wait for the global loads that
-// prefetch the next step's row statistics; nothing here communicates through global memory.
+// Barrier that orders LDS traffic only: nothing here communicates through global memory, so loads and stores that are still
+// under way need not end first.
 template <bool SINGLE>
 __device__ __forceinline__ void lds_sync() {
     if (SINGLE) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -414,8 +413,6 @@ inline size_t pool_lds_bytes(int D, int NT, int DK, int KM) {
     return (size_t)DK * NT * 8 + (size_t)KM * NT * 8 + (size_t)NT * 4 * 8 + (size_t)D * NT * (4 + 1 + 1);
 }
 
-// Last line of Algorithm 1 and the outputs.  `steps` layers are in the pool; lo0 (or NaN) is a
-// value that at least n pool nodes reach (the largest cut value of the steps that cut to n).
 // The n best nodes of a pool of `steps` layers (last line of Algorithm 1; also the set whose p^ sum is
 // E_sub(T, n)).  pk[t] = log p^ of pool node (layer t+1, slot tid), NaN = absent; lo0 (or NaN) is a value that
 // at least n pool nodes reach.  Returns bit t set for the selected nodes of this thread.  Ties at the cut:
@@ -452,6 +449,8 @@ __device__ unsigned int pool_select(const SelKArgs& a, const Pool& P, const doub
     return sel;
 }
 
+// Last line of Algorithm 1 and the outputs.  `steps` layers are in the pool; lo0 (or NaN) is a
+// value that at least n pool nodes reach (the largest cut value of the steps that cut to n).
 template <int DMAX, bool SINGLE>
 __device__ void finalize_tree(const SelKArgs& a, const Pool& P, int steps, int b, double lo0, Group<SINGLE>& g,
                               int* s_cntw /*[OT_MAX_DEPTH][4]*/, int* s_hist) {
@@ -789,7 +788,6 @@ SelKArgs make_args(const SelectGeometry& g, const BuildWorkspace& ws) {
     a.k = g.k; a.n = g.n; a.depth = g.depth; a.rows_per_seq = g.rows_per_seq;
     for (int i = 0; i < OT_MAX_DEPTH + 2; ++i) {
         a.F[i] = g.F[i];
-        a.row_start[i] = g.row_start[i];
         a.r0[i] = 0;
     }
     for (int t = 0; t < g.depth; ++t) {
