@@ -25,8 +25,8 @@
 // above every candidate of a step, neither that step nor any later one has a node in the tree.  (7B-shaped rows: the
 // tree is complete after 4 to 7 of 10 steps.)
 //
-// Measured, MI355X, whole kernel under rocprofv3 (one wavefront per selection before): 7B-shaped build 24.4 -> 9.9 us,
-// 13B-shaped 9.3; adaptive 13B-shaped 13.5 -> 9.8.
+// Measured, MI355X, whole kernel under rocprofv3 (one wavefront per selection before): 7B-shaped build 22 to 24 ->
+// 9.9 us, 13B-shaped 9.3.
 #include <algorithm>
 
 #include "common.hpp"

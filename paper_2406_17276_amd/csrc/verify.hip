@@ -33,7 +33,7 @@ struct VerifyKArgs {
     float c;                     // sampling: log2(e) / temperature
     const float* u;              // sampling: [batch][n + 1]
     const int32_t *token, *parent, *n_out;
-    u64* truth;                  // [batch][n + 1]  kPublished | token
+    u64* truth;                  // [batch][word_stride(n)]  kPublished | token
     int32_t *accept_len, *accept_node, *accept_token;
 };
 
@@ -43,6 +43,8 @@ struct VerifyKArgs {
 constexpr int kTokenBits = 18;
 constexpr u64 kPublished = 0x1fd2a470cb5dull << kTokenBits;
 static_assert(kMaxVocab <= 1 << kTokenBits, "a token fits the word");
+// Words of a sequence start a cache line of their own (side by side: greedy 62 us instead of 50 in the case below).
+__host__ __device__ inline int word_stride(int n) { return (n + 16) & ~15; }
 constexpr int kBatch = 4;        // vectors per lane requested at once; the next batch is in flight while one is processed
 
 // One wavefront: publish the row's ground truth, and walk the tree if that completes the sequence.  Words travel through
@@ -54,7 +56,7 @@ constexpr int kBatch = 4;        // vectors per lane requested at once; the next
 __device__ __forceinline__ void publish_and_walk(const VerifyKArgs& a, int b, int j, int truth, int lane) {
     constexpr int Q = (OT_MAX_NODES + 1 + 63) / 64, QN = OT_MAX_NODES / 64;
     const int n = a.n;
-    u64* const words = a.truth + (size_t)b * (n + 1);
+    u64* const words = a.truth + (size_t)b * word_stride(n);
     if (lane == 0) __hip_atomic_store(words + j, kPublished | (u64)(unsigned)truth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // the tree: lane owns nodes lane, lane + 64, ...; few rows ask for it ahead of knowing whether it is needed
     int n_out = 0, tok[QN], par[QN];
@@ -74,8 +76,9 @@ __device__ __forceinline__ void publish_and_walk(const VerifyKArgs& a, int b, in
         return i <= n ? __hip_atomic_load(words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kPublished;
     };
     auto there = [](u64 v) { return (v >> kTokenBits) == (kPublished >> kTokenBits); };
-    // many rows: most workgroups see from the 64 words around their own that rows are missing (32 sequences of 257 sampled
-    // rows of 8192 fp32, every workgroup reading all words past the caches: 66 us, against 56)
+    // many rows: most workgroups see from the 64 words around their own that rows are missing (32 sequences of 257 rows of
+    // 8192 fp32, greedy / sampled, all words read past the caches by every row, words of sequences side by side 67 / 66 us; now
+    // 52 / 54.  A look at the 16 words of the own cache line first gains 1 us at 62 rows a sequence and loses 2 at 257.)
     if (!early && n >= 64 && !__all(there(word((j & ~63) + lane)))) return;
     u64 w[Q];
     bool all = true;
@@ -415,7 +418,7 @@ int launch_rows(VerifyKArgs a, int batch, bool sample, hipStream_t s) {
         a.logits = (const char*)a.logits + per * a.stride_seq * Row<DT>::ESIZE;
         if (sample) a.u += words;
         a.token += nodes; a.parent += nodes; a.n_out += per;
-        a.truth += words;
+        a.truth += (size_t)per * word_stride(a.n);
         a.accept_len += per; a.accept_node += nodes; a.accept_token += words;
     }
 #undef OT_ROWS_NT
@@ -435,7 +438,7 @@ int launch_verify(const ot_verify_params& p, bool sample, float c, const void* l
     return p.logits_dtype == OT_BF16 ? launch_rows<OT_BF16>(a, p.batch, sample, s) : launch_rows<OT_F32>(a, p.batch, sample, s);
 }
 
-size_t verify_bytes(const ot_verify_params& p) { return ((size_t)p.batch * (size_t)(p.n + 1) * 8 + 255) / 256 * 256; }
+size_t verify_bytes(const ot_verify_params& p) { return ((size_t)p.batch * (size_t)word_stride(p.n) * 8 + 255) / 256 * 256; }
 
 struct AppendKArgs {
     void *Kp, *Vp;
