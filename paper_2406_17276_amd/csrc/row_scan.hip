@@ -21,16 +21,17 @@
 // Two forms of step 1.  KEEP: few rows (the launch does not fill the chip): many threads per row, all loads in flight at
 // once, the vectors stay in registers and step 3 takes the candidates from there.  Rolling: many rows: 16 vectors per
 // lane pass through a ring of six in flight, which leaves a fourth of the fixed work per element, and the dozen vectors
-// that hold candidates are read again.
-#include "common.hpp"
+// that hold candidates are read again.  Short rows in great numbers take one wavefront each.
+#include <algorithm>
 #include <type_traits>
+
+#include "common.hpp"
 
 namespace ot {
 namespace {
 
 typedef unsigned long long u64;
 
-constexpr int kCandCap = 1024;         // candidates of one part
 constexpr int kVecCap = 512;           // rolling form: pairs of vectors that hold candidates
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kRollVpl = 16;
@@ -61,11 +62,13 @@ __device__ __forceinline__ int ordered(float v) {
     return i ^ ((i >> 31) & 0x7fffffff);
 }
 
-// max over groups of G consecutive lanes (4, 8 or 16), result in every lane of the group
+// max over groups of G consecutive lanes (1, 4, 8 or 16), result in every lane of the group
 template <int G>
 __device__ __forceinline__ float group_max(float v) {
-    v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR1>(__float_as_int(v), __float_as_int(v))));
-    v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR2>(__float_as_int(v), __float_as_int(v))));
+    if (G >= 4) {
+        v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR1>(__float_as_int(v), __float_as_int(v))));
+        v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR2>(__float_as_int(v), __float_as_int(v))));
+    }
     if (G >= 8) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(v), __float_as_int(v))));
     if (G >= 16) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(v), __float_as_int(v))));
     return v;
@@ -91,8 +94,11 @@ struct ScanShared {
     static constexpr int NW = NT / 64;
     // groups for the threshold (ranked one ballot per group and wavefront in the KEEP form: fewer for small workgroups)
     static constexpr int G = KEEP && NT < 512 ? NT / 8 : 64, GL = NT / G;
+    static_assert(GL == 1 || GL == 4 || GL == 8 || GL == 16, "group_max");
+    // candidates of one part (one wavefront: 5 KB of LDS, so that 29 rows share a compute unit)
+    static constexpr int kCandCap = NT == 64 ? 512 : 1024;
     u64 key[kCandCap];
-    int vec[KEEP ? 1 : kVecCap];
+    unsigned short vec[KEEP ? 1 : kVecCap];
     int g[G];
     float wm[NW];                      // reference exponent and sum of every wavefront
     double ws[NW];
@@ -148,6 +154,7 @@ struct Scan {
     static constexpr int VEC = VecOf<DT>::N, ESIZE = 16 / VEC;
     static constexpr int NW = NT / 64, G = ScanShared<NT, KEEP>::G, GL = ScanShared<NT, KEEP>::GL;
     static constexpr int R = KEEP ? VPL : 6;                  // vectors in flight per lane (64 registers in all)
+    static constexpr int kCandCap = ScanShared<NT, KEEP>::kCandCap;
     ScanShared<NT, KEEP>& sh;
     const ScanKArgs& a;
     const int wave;
@@ -306,14 +313,15 @@ struct Scan {
             for (int i = 0; i < VPL; i += 2)
                 if (vmax[i / 2] >= tau && i * NT + tid < nvec) {
                     const int p = atomicAdd(&sh.nvec, 1);
-                    if (p < kVecCap) sh.vec[p] = i * NT + tid;
+                    if (p < kVecCap) sh.vec[p] = (unsigned short)(i * NT + tid);
                 }
         }
         __syncthreads();
         return tau;
     }
 
-    // Step 4 of an item.  Rolling form: wavefronts 0 and 1 alone, unless an unusual number of vectors holds candidates.
+    // Step 4 of an item.  Rolling form: wavefronts 0 and 1 (or the only one) alone, unless an unusual number of vectors holds
+    // candidates.
     __device__ __forceinline__ void finish(const Item& it, float tau) {
         const int tid = threadIdx.x, lane = tid & 63;
         bool slow = false;
@@ -341,7 +349,7 @@ struct Scan {
             outi = a.part_topi + ((size_t)rid * a.parts + it.part) * a.k;
         }
         // ---- 4a. combine the wave partials in fp64 (one wavefront, 16 lanes) ----
-        if (wave == (KEEP ? NW - 1 : 1) && lane < 16) {
+        if (wave == (KEEP || NW == 1 ? NW - 1 : 1) && lane < 16) {
             const bool have = lane < NW;
             const float mw = have ? sh.wm[lane] : -INFINITY;
             const float M = group_max<16>(mw);
@@ -547,15 +555,26 @@ int launch_scan_dt(const ScanGeometry& g, const void* logits, ScanKArgs& a, hipS
         return ((g.vocab + a.parts - 1) / a.parts + vec - 1) / vec * vec;
     };
     // Which form: KEEP while a workgroup's registers hold the row and the rows do not fill the chip a few times over.
-    // The line is where rows of the registers' whole capacity break even (32000 bf16, 16000 fp32), KEEP / rolling: 512 rows
-    // 12.6 / 15.0 us, 1024 19.5 / 21.1, 1536 24.7 / 25.4, 2048 31.0 / 31.5, 4096 53.5 / 52.1, 8192 96.5 / 90.0; fp32 1024
-    // 19.1 / 18.5, 2048 31.1 / 28.8, 8192 96.9 / 86.5.  Shorter rows would roll profitably from about 700 rows on (their
-    // 1024 threads have less than a register set each): 16384 bf16 512 rows 11.1 / 13.0, 1024 18.0 / 16.4, 4096 50.6 / 32.7;
-    // 9000 bf16 512 11.7 / 12.1, 1024 17.9 / 14.8, 4096 51.0 / 27.4.  Longer rows would need parts and a merge launch (4 us
-    // and more) in the KEEP form, so they roll at any number of rows: 128256 bf16, 256 rows 20.2 / 17.3 us, 2048 rows 97 / 83.
+    // Rolling, a wavefront per row: short rows in great numbers, where what a workgroup does once per row -- a barrier and the
+    // threshold per wavefront -- is all that counts.  Up to half of the wavefront's 128 elements a lane it pays from 2000 to
+    // 4000 rows on, beyond from some 10000: KEEP / rolling, us, 2048, 4096, 16384 and 32000 rows: 1000 bf16 13.7 / 12.0,
+    // 20.4 / 14.2, 54.6 / 31.2, 100.6 / 52.4; 4096 bf16 13.3 / 15.4, 21.3 / 18.0, 58.1 / 41.3, 107 / 69; 2048 fp32 14.6 / 13.0,
+    // 21.0 / 16.2, 57.7 / 36.9, 105.8 / 62.0; 7743 bf16 15.4 / 17.2, 22.4 / 24.2, 61.4 / 56.7, 113 / 100.  (Four rows to a
+    // workgroup of four wavefronts, one row each or several in turn, gave 58 to 67 us instead of 52 for 32000 rows of 1000.)
+    // Rolling, 256 threads per row: rows of all that a workgroup's registers hold (32000 bf16, 16000 fp32) break even at
+    // some 1536 rows, shorter ones -- their 1024 threads have less than a register set each -- in proportion to their length,
+    // from some 700 rows on: KEEP / rolling 32000 bf16 1024 rows 19.5 / 21.1, 1536 24.7 / 25.4, 2048 31.0 / 31.5, 4096
+    // 53.5 / 52.1, 8192 96.5 / 90.0; 24000 bf16 1024 18.3 / 18.9, 2048 31.2 / 26.9, 4096 52.4 / 42.1; 16384 bf16 512
+    // 11.1 / 13.0, 1024 18.0 / 16.4, 4096 50.6 / 32.7; 9000 bf16 512 11.7 / 12.1, 1024 17.9 / 14.8, 4096 51.0 / 27.4; 12000
+    // fp32 512 11.8 / 13.0, 1024 19.6 / 16.6, 4096 54.4 / 39.2.
+    // Longer rows would need parts and a merge launch (4 us and more) in the KEEP form, so they roll at any number of rows:
+    // 128256 bf16, 256 rows 20.2 / 17.3 us, 2048 rows 97 / 83.
     a.parts = 1;
+    const int wave_cap = capacity(64, kRollVpl), roll_cap = capacity(256, kRollVpl);
+    if (g.vocab <= wave_cap && rows >= (g.vocab <= wave_cap / 2 ? 2560 : 12288))
+        return launch_scan_t<DT, 64, kRollVpl, false>(g, logits, a, g.vocab, s, ev0, ev1);
     if (g.vocab <= capacity(256, KV)) return launch_scan_t<DT, 256, KV, true>(g, logits, a, g.vocab, s, ev0, ev1);
-    if (rows >= 1536 && g.vocab <= capacity(256, kRollVpl))
+    if (g.vocab <= roll_cap && rows >= std::max(768LL, 1536LL * g.vocab / roll_cap))
         return launch_scan_t<DT, 256, kRollVpl, false>(g, logits, a, g.vocab, s, ev0, ev1);
     if (g.vocab <= capacity(1024, KV)) return launch_scan_t<DT, 1024, KV, true>(g, logits, a, g.vocab, s, ev0, ev1);
     if (g.vocab <= capacity(512, kRollVpl)) return launch_scan_t<DT, 512, kRollVpl, false>(g, logits, a, g.vocab, s, ev0, ev1);

@@ -379,6 +379,34 @@ def test_scan_forms_at_the_ends_of_their_ranges_and_rows_at_any_alignment(V, k, 
     U.assert_tree_equal(got, want, n)
 
 
+@pytest.mark.parametrize("V,B,dtype,offset,levels", [
+    (16, 8, "f32", 0, 0), (61, 8, "bf16", 7, 0), (1000, 8, "f32", 1, 0), (1856, 8, "bf16", 0, 0),   # a wavefront per row ...
+    (4096, 8, "bf16", 0, 0), (4089, 8, "bf16", 3, 0), (2048, 8, "f32", 0, 0), (2045, 8, "f32", 3, 0),   # ... its nearer end
+    (8192, 37, "bf16", 0, 0), (8185, 37, "bf16", 5, 0), (4096, 37, "f32", 0, 0), (4093, 37, "f32", 1, 0),   # ... its farther end
+    (3000, 8, "bf16", 1, 40), (3000, 8, "f32", 1, 2),              # 75 equal logits a level; more than the list holds
+    (9000, 3, "bf16", 1, 0), (12000, 4, "f32", 2, 0),              # 256 threads from 768 and from 1125 rows on
+])
+def test_rows_in_great_numbers_match_the_same_rows_in_small_batches(V, B, dtype, offset, levels):
+    """337 rows a sequence: all sequences at once take the forms for many rows, a sequence by itself the ones for few."""
+    import torch
+    from paper_2406_17276_amd import api
+    k, n, d = 16, 64, 7
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V + B)
+    big = torch.randn((B, d, n, V + offset + (-(V + offset)) % 8), generator=g, device="cuda") * 3.0
+    if levels:
+        big = (big * levels / 24.0).round().clamp(-levels // 2, levels // 2)
+    x = big.to(torch.bfloat16 if dtype == "bf16" else torch.float32)[..., offset:offset + V]
+    got = api.build_tree(x, k, n, d)
+    for b in range(0, B, max(1, B // 8)):
+        want = api.build_tree(x[b:b + 1], k, n, d)
+        torch.cuda.synchronize()
+        for name in ("token", "parent", "depth", "mask", "n_out"):
+            assert torch.equal(getattr(got, name)[b:b + 1], getattr(want, name)), (b, name)
+        # both normalisers add up V terms in fp32 inside a vector and fp64 above it: 2^-24 times a few each
+        torch.testing.assert_close(got.expect[b:b + 1], want.expect, rtol=2e-6, atol=0.0)
+
+
 @pytest.mark.parametrize("k,n,d", [
     (16, 16, 6), (16, 17, 6),          # 256 candidates per step; more: 512 threads
     (16, 32, 5), (16, 33, 5),          # 512; two per thread
