@@ -519,7 +519,9 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         // so that the matrix pipe and the vector ALU work at the same time inside one wavefront (S of block 1
         // while the exponentials of block 0 are taken, P V of block 0 while those of block 1 are).  A score beyond
         // the slack (every row's first tile, then rarely) leaves the loop before anything of the tile is added;
-        // the reference moves up, O and l are rescaled out here, and the loop is entered again at the same tile.
+        // the reference moves up, O and l are rescaled out here, and the loop is entered again at the same tile, which is then
+        // taken as it is: nothing of it exceeds the new reference, but c s - c ref of huge scores (1e9) may round past the
+        // slack, again and again.
         constexpr float kSlack = 12.f;
 #ifndef OT_ATTN_SUMCHECK
 #define OT_ATTN_SUMCHECK 1
@@ -556,6 +558,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         int t = t0;
         bool staged = false;                                      // tile t has been awaited and published
         float seen = -INFINITY;                                   // largest score of the tile that left the loop
+        int moved = -1;                                           // tile that the reference was last moved up for
         while (t < t_full) {
             if (!staged) {
                 stage_tile(t);
@@ -580,6 +583,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                     for (int v = 0; v < 16; ++v) oacc[d][v] *= alpha;
                 m_run = m_new;
             }
+            moved = t;
             const float mc = m_run * c;
             const float limit = m_run + kSlack / c;
             for (;;) {
@@ -645,7 +649,8 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 // anyway, while the maximum of sixteen scores costs a dozen instructions.  Nothing of the tile has
                 // been added yet.  The bound is on the sum of sixteen terms, so single terms up to 2^kSlack pass
                 // as before and a few somewhat larger ones may: the formats have the room.
-                if (__any(seen > limit || psum > kSumLimit)) break;
+                asm volatile("" : "+s"(moved));                   // (keeps the first tile of an entry from becoming a second loop body)
+                if (t != moved && __any(seen > limit || psum > kSumLimit)) break;
 #else
                 if (__any(seen > limit)) break;
 #endif

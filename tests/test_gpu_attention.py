@@ -372,6 +372,46 @@ def test_scores_that_jump_between_tiles(Hq, Hkv, n):
     assert np.abs(got - want).max() < TOL["bf16"]
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L", [0, 1, 63, 64, 65, 128, 191, 192, 256, 320, 447, 1000])
+def test_256_row_loop_with_few_full_tiles_and_jumps_in_either_block(D, L):
+    """33 sequences of 4 KV heads (no key splits), 150 rows each: no, one, two, ... full prefix tiles ahead of the general
+    path, and in half of the sequences a key band of far larger scores that starts inside a tile's first or second block."""
+    B, Hkv, n = 33, 4, 150
+    w = _shape("bf16", B, Hkv, Hkv, D, max(L, 1), n)
+    x = wl.make_attention_inputs(w, 5)
+    x["prefix_len"][:] = L
+    kp = wl.bf16_bits_to_f32(x["K_prefix"]).copy()
+    for b in range(1, B, 2):
+        for at in (64 * (b % 3) + 8 * b % 64, 64 * (b % 5) + 70, 64 * (b % 7) + 40):
+            kp[b, :, at:at + 9] *= 40.0
+    x["K_prefix"] = wl.store(kp, "bf16")
+    mask = _random_masks(B, n, 8)
+    got = _gpu_attention(x, mask, "bf16")
+    assert np.isfinite(got).all()
+    some = sorted({0, 1, 2, 3, 5, 9, 17, B - 1})
+    sub = {k: v[some] for k, v in x.items()}
+    # the oracle works in 64 bits on the stored values; p and O are rounded to bf16 once each (2^-9 of values up to 4)
+    assert np.abs(got[some] - _oracle_attention(sub, mask[some], "bf16")).max() < TOL["bf16"]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n", [70, 150])               # 128 rows per workgroup; 256
+def test_scores_that_round_by_more_than_the_slack(D, n):
+    """Scores of 1e9 in units of log2 e: a tile's own maximum minus itself rounds to anything up to 32 (64 from 2^30 on), so
+    its probability to 2^32, which must not send the loops over full tiles back to that tile for ever.  Each row ends up as
+    the V of its best key."""
+    w = _shape("bf16", 33, 4, 4, D, 500, n)
+    x = wl.make_attention_inputs(w, 6)
+    for k in ("K_prefix", "K_tree"):
+        x[k] = wl.store(wl.bf16_bits_to_f32(x[k]) * 2e8, "bf16")
+    mask = _random_masks(33, n, 2)
+    got = _gpu_attention(x, mask, "bf16")
+    some = [0, 13, 32]
+    want = _oracle_attention({k: v[some] for k, v in x.items()}, mask[some], "bf16")
+    assert np.abs(got[some] - want).max() < TOL["bf16"]
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
     (1, 2, 2, 64, 31, 32),             # 32 rows per workgroup, eight key slices; key blocks one short
     (1, 2, 2, 128, 33, 33),            # 33 rows in blocks of 32; one key past a block

@@ -66,6 +66,17 @@ def test_shapes_and_edges(B, Hq, Hkv, D, L, n, ragged, shape):
     assert np.abs(got - want).max() < TOL
 
 
+def test_scores_that_round_by_more_than_the_slack():
+    """As in the 16-bit cache's test of this name: scores of 1e9, here from the K factors."""
+    x = _inputs(33, 4, 4, 128, 500, 150, 0.0, 6)
+    x["k_scale"] = (x["k_scale"] * np.float32(2e8)).astype(np.float32)
+    mask = _masks(33, 150, 2)
+    got = _gpu(x, mask)
+    some = [0, 13, 32]
+    want = _oracle({k: v[some] for k, v in x.items()}, mask[some])
+    assert np.abs(got[some] - want).max() < TOL
+
+
 def test_every_byte_code_and_uneven_scales():
     """Rows holding all 254 finite byte codes (both zeros, subnormals, +-448), scales far from 1 that differ between
     K and V and between heads, and an explicit softmax scale."""
