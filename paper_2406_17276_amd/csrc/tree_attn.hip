@@ -305,17 +305,18 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     const int ptiles = (L + TK - 1) / TK, ttiles = (a_nk + TK - 1) / TK;
     int t0, t1;
     split_range(ptiles + ttiles, a_splits, a_inv_splits, split, t0, t1);
+    auto request_mask = [&](int t, int buf) {
+        const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(s_mw + (buf * NWAVES + wave) * 128);
+        const unsigned int* const wp = (const unsigned int*)(mask_row + (t - ptiles));
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w), "v"(wp) : "m0", "memory");
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w + 256), "v"(wp + 1) : "m0", "memory");
+    };
     auto request_tile = [&](int t, auto buf_c) {
         const int buf = buf_c;                 // a compile-time constant or, in the wide variant's fast loop, a value
         const bool tree = t >= ptiles;
         // the mask word of a tree tile travels ahead of the tile's K/V (older, so it has landed when the tile's
         // wait is over)
-        if (tree) {
-            const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(s_mw + (buf * NWAVES + wave) * 128);
-            const unsigned int* const wp = (const unsigned int*)(mask_row + (t - ptiles));
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w), "v"(wp) : "m0", "memory");
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w + 256), "v"(wp + 1) : "m0", "memory");
-        }
+        if (tree) request_mask(t, buf);
         const int key0 = tree ? (t - ptiles) * TK : t * TK;
         const int last = (tree ? a_nk : L) - 1;
         const long long ks = (tree ? a.kts[2] : a.kps[2]) * ESZ;      // row strides in bytes
@@ -413,12 +414,12 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     bf16x8 qf[SLABS];
 #pragma unroll
     for (int s = 0; s < SLABS; ++s) qf[s] = __builtin_bit_cast(bf16x8, qw[s]);
-    // One tile, out of buffer CUR.  The buffer index is a compile-time constant (the loop below is unrolled
+    // One tile, out of buffer CUR.  In the narrow variant the buffer index is a compile-time constant (its loop is unrolled
     // NBUF times), so that every LDS address of the operand reads is a loop-invariant per-lane value plus an
-    // immediate offset.
+    // immediate offset; a wide variant takes few tiles here.
     auto tile_step = [&](int t, auto cur_c) {
-        constexpr int CUR = decltype(cur_c)::value;
-        constexpr int PREV = (CUR + NBUF - 1) % NBUF;      // buffer of tile t - 1 (= of tile t + PD)
+        const int CUR = cur_c;
+        const int PREV = (CUR + NBUF - 1) % NBUF;          // buffer of tile t - 1 (= of tile t + PD)
         // my requests for tile t have landed (younger ones may still be in flight); after the barrier
         // everybody's have, and everybody is done reading the buffer of tile t - 1
         // (a request group holds LPT tile loads, plus one mask word for a tree tile: allowing only
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         if (ahead <= 0)      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
         else                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");
-        if (t + PD < t1) request_tile(t + PD, std::integral_constant<int, PREV>{});
+        if (t + PD < t1) request_tile(t + PD, PREV);
         if constexpr (KV8) widen_tile(CUR);
 
         const unsigned short* const s_k = (const unsigned short*)(s_buf + CUR * BUF);
@@ -510,6 +511,188 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         }
     };
     int t_done = t0;           // tiles [t0, t_done) are consumed
+    if constexpr (VAR == 2) {
+        // ---- fast loop of the 256-row variant over full prefix tiles: what the MFMA-bound shapes spend their time in.
+        // The softmax reference of a row stays FIXED while no probability of a 32-key block comes out too large: p =
+        // 2^(c s - c ref) may exceed one, which fp32 sums and bf16 operands take in their stride, and O is never rescaled
+        // inside the loop.  The loop is pipelined by 32-key blocks: in the phase of block j the matrix pipe forms S of
+        // block j + 1 and adds P V of block j - 1 while the vector ALU takes the exponentials of block j, so that nothing
+        // in a phase waits for anything of the same phase, and each matrix instruction has its share of the vector work
+        // and of the operand reads beside it.  Operands of the next phase are read into a register as soon as its
+        // instruction has been issued (half of a K block and a whole V block ahead), so tile t + 1 has to be there when
+        // tile t begins.
+        // Probabilities beyond the limit (every row's first block, then rarely) leave the loop before they are added: the
+        // reference, O and l move up out here.
+        // Measured (MI355X, the 128-row variant's loop, in which half of the matrix instructions had no vector work beside
+        // them, before): 32 sequences x 8 KV heads of 1024 rows, 8448 keys of 128 1125 -> 1070 us (1.06 PFLOP/s); 16 x 8 of
+        // 480 rows, 4156 keys 152 -> 137; 7 x 8 of 512 rows, 6428 keys 118 -> 105; 8 x 8 of 480 rows, 6060 keys of 64 79 -> 68;
+        // 2 x 8 of 164 rows, 595 keys 21.0 -> 19.2.  Now a SIMD's two wavefronts need 2048 matrix cycles per tile, and the
+        // operand reads of all eight some 2900 cycles of the LDS (128 bytes per cycle for K, 64 for V's transposing reads).
+        // 64 rows per wavefront, one wavefront per SIMD, halve those reads: 1139 us and 229 against 224 for a step of the
+        // 16 x 8 batch, since a wavefront by itself issues vector and matrix instructions one behind the other.
+        // Requests of the next tile spread over a phase instead of in one piece: 1051 us, but 140 at 16 x 8.
+        constexpr int NS = SLABS, NP = 2 * DB, KR = NS / 2;     // instructions per phase for S, for P V; K operands ahead
+        static_assert(NS == NP, "one P V instruction for each one of S");
+        constexpr float kSumLimit = 16.f * 4096.f;              // of the sixteen probabilities of a lane
+        const int t_full = min(t1, L / TK);                      // tiles below t_full are full prefix tiles
+        // tile t + 1 has landed for this lane when only the requests of tile t + 2 are outstanding; after the barrier it has
+        // for everybody, and everybody is done with tile t - 1, into whose buffer tile t + 3 goes
+        auto stage = [&](int t) {
+            if (t + 2 < t1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
+            else            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (t + PD < t1) request_tile(t + PD, (t + PD - t0) & (NBUF - 1));
+        };
+        // LDS addresses of the operands, moved from tile to tile: K of tile t + 1, what is still to be read of K of tile t, V
+        // of tile t; block 1 is at a fixed distance
+        typedef const u32x4 __attribute__((address_space(3))) * lds_u32x4;
+        typedef s16x4 __attribute__((address_space(3))) * lds_s16x4;
+        const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)s_buf;
+        unsigned ka[NS], kc[NS - KR], va[DB];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) ka[s] = lds0 + 2 * (l32 * D + (((2 * s) ^ kx) << 3));
+#pragma unroll
+        for (int d = 0; d < DB; ++d) va[d] = lds0 + 2 * (TK * D + (4 * h + tr_j) * D + (((2 * d) ^ vx) << 4) + tr_q);
+        auto kfrag = [&](unsigned a, int kb) { return __builtin_bit_cast(bf16x8, *(lds_u32x4)(a + 2 * 32 * D * kb)); };
+        auto vfrag = [&](int kb, int i) {
+            // slab u, d block d: column 32d+l32 of keys 32kb+16u+4h+{0..3} and of the same +8 (transpose loads, see tile_step)
+            const unsigned a = va[i % DB] + 2 * (32 * kb + 16 * (i / DB)) * D;
+            const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)a);
+            const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(a + 2 * 8 * D));
+            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
+        auto row_max = [&](const f32x16& x) {                   // eight three-input maxima
+            float m = fmaxf(fmaxf(x[0], x[1]), x[2]);
+#pragma unroll
+            for (int v = 3; v < 15; v += 2) m = fmaxf(fmaxf(m, x[v]), x[v + 1]);
+            return xhalf_max(fmaxf(m, x[15]));
+        };
+        auto mma = [](const bf16x8& x, const bf16x8& y, f32x16& acc) { acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, acc, 0, 0, 0); };
+        if (t0 < t_full) {
+            bf16x8 kf[KR], vf[NP];
+            u32x4 p0[2], p1[2];
+            f32x16 s0, s1;
+            float mc = 0.f;
+            int t = t0;
+            // reference, O and l move up to what block `s` needs
+            auto move_up = [&](const f32x16& s) {
+                const float m_new = fmaxf(m_run, row_max(s));
+                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);      // m_run = -inf gives 0
+                l_run *= alpha;
+#pragma unroll
+                for (int d = 0; d < DB; ++d)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) oacc[d][v] *= alpha;
+                m_run = m_new;
+                mc = m_new * c;
+            };
+            // a pair of probabilities, rounded to the MFMA's operand type, and their sum taken from the rounded pair (l then
+            // matches what P V multiplies by)
+            auto pair = [](float p, float q, float& sum) -> unsigned int {
+                const bf16x2 pr = {(__bf16)p, (__bf16)q}, ones = {(__bf16)1.f, (__bf16)1.f};
+                sum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, sum, false);
+                return __builtin_bit_cast(unsigned int, pr);
+            };
+            // One phase, block B of tile t: next = S of the block behind it, whose first KR operands are in kf; O += P V of the
+            // block ahead of it, whose V operands are in vf; pc = 2^(c cur - mc).  Returns this lane's sum of pc.
+            auto phase = [&](auto block_c, const f32x16& cur, f32x16& next, const u32x4 (&pp)[2], u32x4 (&pc)[2]) {
+                constexpr int B = decltype(block_c)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                float psum = 0.f;
+                f32x16 acc;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {
+                    mma(kf[i % KR], qf[i], acc);
+                    kf[i % KR] = i < NS - KR ? (B ? kfrag(ka[i + KR], 0) : kfrag(kc[i], 1)) : kfrag(ka[i + KR - NS], B);
+                    mma(vf[i], __builtin_bit_cast(bf16x8, pp[i / DB]), oacc[i % DB]);
+                    vf[i] = vfrag(B, i);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; v += 2)
+                    pc[v >> 3][(v & 7) >> 1] = pair(__builtin_amdgcn_exp2f(fmaf(cur[v], c, -mc)), __builtin_amdgcn_exp2f(fmaf(cur[v + 1], c, -mc)), psum);
+                next = acc;
+#pragma unroll
+                for (int i = 0; i < NS; ++i) {                   // a matrix instruction, its share of the reads, its share of the rest
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 24 / NS, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 24 / NS, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                return psum;
+            };
+            auto phase_a = [&]() { return phase(std::integral_constant<int, 0>{}, s0, s1, p1, p0); };
+            auto phase_b = [&]() { return phase(std::integral_constant<int, 1>{}, s1, s0, p0, p1); };
+            // behind phase B of tile t - 1: tile t
+            auto next_tile = [&](int t) {
+                stage(t);
+                const int v = (t - t0) & (NBUF - 1), k = (t + 1 - t0) & (NBUF - 1);
+#pragma unroll
+                for (int s = KR; s < NS; ++s) kc[s - KR] = ka[s];
+#pragma unroll
+                for (int s = 0; s < NS; ++s) ka[s] += k ? BUF * 4 : -(NBUF - 1) * BUF * 4;
+#pragma unroll
+                for (int d = 0; d < DB; ++d) va[d] += v ? BUF * 4 : -(NBUF - 1) * BUF * 4;
+            };
+            auto add_pv = [&]() {                    // P V of the block whose P is in p1 and whose V operands are in vf
+#pragma unroll
+                for (int i = 0; i < NP; ++i) mma(vf[i], __builtin_bit_cast(bf16x8, p1[i / DB]), oacc[i % DB]);
+            };
+            // S of the first block; its tile has landed when only the requests of the two behind it are outstanding
+            if (t0 + 2 < t1)      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");
+            else if (t0 + 1 < t1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
+            else                  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s0[v] = 0.f;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) mma(kfrag(ka[s], 0), qf[s], s0);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) vf[i] = vfrag(0, i);      // (any finite values: P is zero)
+            stage(t0);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                if (s >= KR) kc[s - KR] = ka[s];
+                ka[s] += BUF * 4;
+            }
+            const u32x4 zero = {0u, 0u, 0u, 0u};
+            int moved = -1;                          // tile whose block 0 has set the reference: taken as it is (see below)
+            while (t < t_full) {
+                move_up(s0);
+                moved = t;
+                p1[0] = p1[1] = zero;
+#pragma unroll
+                for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s] - (((t + 1 - t0) & (NBUF - 1)) ? BUF * 4 : -(NBUF - 1) * BUF * 4), 1);
+                bool in_b = false;
+                for (;;) {
+                    float psum = phase_a();
+                    asm volatile("" : "+s"(moved));     // (keeps the first tile of an entry from becoming a second loop body)
+                    if (t != moved && __any(psum > kSumLimit)) break;
+                    l_run += psum;
+                    psum = phase_b();
+                    if (__any(psum > kSumLimit)) { in_b = true; break; }
+                    l_run += psum;
+                    if (++t >= t_full) break;
+                    next_tile(t);
+                }
+                if (in_b) {                          // P V of block 0 has been added; block 1 by itself
+                    move_up(s1);
+                    p0[0] = p0[1] = zero;
+#pragma unroll
+                    for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s], 0);
+                    l_run += phase_b();
+                    add_pv();
+                    p1[0] = p1[1] = zero;
+                    if (++t < t_full) next_tile(t);
+                }
+            }
+            add_pv();                                // the last block's (P is zero if it has been added)
+            t_done = t_full;
+        }
+        for (int tt = t_done; tt < t1; ++tt) tile_step(tt, (tt - t0) & (NBUF - 1));       // the prefix tail and the tree tiles
+    } else
     if constexpr (WIDE) {
         // ---- fast loop of the 128-row variant over full prefix tiles: what the MFMA-bound shapes spend their time in.
         // The softmax reference of a row stays FIXED while scores do not exceed it by more than kSlack (in units
@@ -523,9 +706,6 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         // taken as it is: nothing of it exceeds the new reference, but c s - c ref of huge scores (1e9) may round past the
         // slack, again and again.
         constexpr float kSlack = 12.f;
-#ifndef OT_ATTN_SUMCHECK
-#define OT_ATTN_SUMCHECK 1
-#endif
         constexpr float kSumLimit = 16.f * 4096.f;          // sixteen terms of at most 2^kSlack
         static_assert((NBUF & (NBUF - 1)) == 0, "the buffer of a tile is (t - t0) mod NBUF");
         // tile t has landed for this lane when only the requests of the tiles behind it are outstanding; after the
@@ -604,10 +784,6 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int s = 0; s < SLABS; ++s) kf[s] = kfrag(s_k, 1, s);
-#if !OT_ATTN_SUMCHECK
-                seen = row_max(s0);
-                if (__any(seen > limit)) break;
-#endif
                 __builtin_amdgcn_sched_barrier(0);
                 // S of block 1 in the matrix pipe, the exponentials of block 0 in the vector ALU, the V operands of
                 // block 0 on their way.  One matrix instruction, then its share of the rest: the wavefront issues in
@@ -643,7 +819,6 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 seen = row_max(s1);
-#if OT_ATTN_SUMCHECK
                 // block 0 is tested on what its exponentials came to instead of on its scores: a probability beyond
                 // 2^kSlack shows in the lane's sum (all terms are positive; an overflow gives +inf), which is there
                 // anyway, while the maximum of sixteen scores costs a dozen instructions.  Nothing of the tile has
@@ -651,9 +826,6 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 // as before and a few somewhat larger ones may: the formats have the room.
                 asm volatile("" : "+s"(moved));                   // (keeps the first tile of an entry from becoming a second loop body)
                 if (t != moved && __any(seen > limit || psum > kSumLimit)) break;
-#else
-                if (__any(seen > limit)) break;
-#endif
                 __builtin_amdgcn_sched_barrier(0);
                 // P V of block 0 in the matrix pipe, the exponentials of block 1 in the vector ALU, the V operands of
                 // block 1 on their way
