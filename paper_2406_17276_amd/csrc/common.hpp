@@ -106,6 +106,7 @@ int launch_tree_esub(const SelectGeometry& g, int steps_done, double delta, cons
                      int32_t* go_on, hipStream_t s);
 
 struct AttnPlan {
+    int rows;            // packed query rows per workgroup
     int row_blocks;      // blocks of query rows per KV head
     int splits;          // KV splits per (b, kv head, row block)
     int balance;         // bf16 batches: workgroups take their jobs longest first, decided on the device

@@ -115,6 +115,10 @@ __device__ __forceinline__ void split_range(int T, int S, unsigned int inv_S, in
     t1 = fast_div(T * (s + 1), S, inv_S);
 }
 
+// Key splits that the merge of the bf16 kernel takes in one trip to memory (64 registers of partials, 96 in the narrow
+// variant; 128, or none for splits that are not there, were 0.5 to 2 us slower)
+constexpr int merge_chunk(int head_dim, bool wide) { return (wide ? 256 : 768) / head_dim; }
+
 // ---------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------
@@ -183,12 +187,16 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     constexpr int NKB = WIDE ? 2 : 1;      // 32-key blocks per wavefront per tile
     constexpr int ROWS = VAR == 2 ? 256 : (WIDE ? 128 : 64);   // packed query rows per workgroup
     constexpr int NQB = ROWS / 32;         // query blocks per workgroup
-    constexpr int NBUF = VAR == 2 ? 4 : (WIDE ? 2 : OT_ATTN_NBUF_NARROW);
-    constexpr int PD = NBUF - 1;           // tiles requested ahead of the one being computed
+    constexpr bool PIPE8 = KV8 && VAR == 2;   // tiles are widened two tiles ahead, into a ring of their own
+    constexpr int NBUF = VAR == 2 ? (KV8 ? 3 : 4) : (WIDE ? 2 : OT_ATTN_NBUF_NARROW);
+    constexpr int PD = PIPE8 ? NBUF : NBUF - 1;   // tiles requested ahead of the one being computed (PIPE8: being widened)
     static_assert(PD >= 1 && PD <= 3 && PD * LPT < 64, "prefetch depth fits the vmcnt counter");
 
     constexpr int BUF = TK * D;            // dwords of one staged tile: K [64][D] bf16, then V [64][D] bf16
-    extern __shared__ __attribute__((aligned(16))) unsigned int s_buf[];   // [NBUF][BUF]
+    constexpr int RAW = KV8 ? BUF / 2 : BUF;  // the same as it is stored
+    extern __shared__ __attribute__((aligned(16))) unsigned int s_buf[];   // [NBUF][BUF], PIPE8: then [NBUF][RAW]
+    unsigned int* const s_raw = s_buf + (PIPE8 ? NBUF * BUF : 0);           // where requested tiles land
+    constexpr int SLOT = PIPE8 ? RAW : BUF;
     __shared__ int s_last;
     constexpr int MST = DB * 16 + 4;       // floats per lane in the half-merge scratch (a multiple of four)
     static_assert(sizeof(unsigned int) * NBUF * BUF >= 2 * 64 * MST * 4, "merge scratch fits");
@@ -259,7 +267,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     // this lane's ancestor mask row: one 64-bit word per 64-key tree tile, requested with the tile and, like it,
     // delivered straight into LDS (s_mw: per buffer and wavefront the low words of the 64 lanes, then the high words)
     const uint64_t* const mask_row = a_mask + ((long long)b * n + node) * a_W;
-    unsigned int* const s_mw = s_buf + NBUF * BUF;                      // [NBUF][waves][2][64]
+    unsigned int* const s_mw = s_raw + NBUF * SLOT;                     // [NBUF][waves][2][64]
 
     const unsigned char* kp = (const unsigned char*)a.Kp + ((long long)b * a.kps[0] + (long long)hk * a.kps[1]) * ESZ;
     const unsigned char* vp = (const unsigned char*)a.Vp + ((long long)b * a.vps[0] + (long long)hk * a.vps[1]) * ESZ;
@@ -305,26 +313,25 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     const int ptiles = (L + TK - 1) / TK, ttiles = (a_nk + TK - 1) / TK;
     int t0, t1;
     split_range(ptiles + ttiles, a_splits, a_inv_splits, split, t0, t1);
-    auto request_mask = [&](int t, int buf) {
-        const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(s_mw + (buf * NWAVES + wave) * 128);
-        const unsigned int* const wp = (const unsigned int*)(mask_row + (t - ptiles));
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w), "v"(wp) : "m0", "memory");
-        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w + 256), "v"(wp + 1) : "m0", "memory");
-    };
     auto request_tile = [&](int t, auto buf_c) {
         const int buf = buf_c;                 // a compile-time constant or, in the wide variant's fast loop, a value
         const bool tree = t >= ptiles;
         // the mask word of a tree tile travels ahead of the tile's K/V (older, so it has landed when the tile's
         // wait is over)
-        if (tree) request_mask(t, buf);
+        if (tree && !PIPE8) {
+            const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(s_mw + (buf * NWAVES + wave) * 128);
+            const unsigned int* const wp = (const unsigned int*)(mask_row + (t - ptiles));
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w), "v"(wp) : "m0", "memory");
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w + 256), "v"(wp + 1) : "m0", "memory");
+        }
         const int key0 = tree ? (t - ptiles) * TK : t * TK;
         const int last = (tree ? a_nk : L) - 1;
         const long long ks = (tree ? a.kts[2] : a.kps[2]) * ESZ;      // row strides in bytes
         const long long vs = (tree ? a.vts[2] : a.vps[2]) * ESZ;
         const unsigned char* kbase = tree ? kt : kp;
         const unsigned char* vbase = tree ? vt : vp;
-        unsigned int* const lk = s_buf + buf * BUF;
-        unsigned int* const lv = lk + TK * D / 2;
+        unsigned int* const lk = s_raw + buf * SLOT;
+        unsigned int* const lv = lk + (PIPE8 ? RAW / 2 : TK * D / 2);
         if (key0 + TK - 1 <= last) {
             const unsigned kofs = tree ? kofs_t : kofs_p, vofs = tree ? vofs_t : vofs_p;
             const unsigned char* gk = kbase + (long long)key0 * ks;       // uniform: rows key0 + cc KSTEP of the tile
@@ -354,6 +361,61 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         }
     };
 
+    // The first PD tiles are requested at once.  A split with fewer tiles issues the same number of loads all the
+    // same (one word each, into the unused buffer's mask-word slots: a load without a destination register): the
+    // wait for Q below can then name a fixed count of younger requests.
+    auto pad_requests = [&](int buf) {
+        const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(s_mw + (buf * NWAVES + wave) * 128);
+#pragma unroll
+        for (int i = 0; i < LPT; ++i)
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w), "v"(a_prefix_len) : "m0", "memory");
+    };
+    // Sixteen E4M3 values as bf16, which holds each of them.  The conversion straight to bf16 is half the instructions: the
+    // 64-row variant gains 5 to 9 % (16 rows x 30 heads x 10, 2336 keys 114 -> 102 us), the 128-row variant at head_dim 64 6 %.
+    // At 128 that one gains 1 to 4 % at most shapes, but loses 10 % where ten row blocks share their keys (1264 rows x 4 heads
+    // x 2, 1080 keys 22.4 -> 24.5), and stays with the longer way.
+    auto widen = [](const u32x4& w, u32x4& lo, u32x4& hi) {
+        unsigned int o[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (VAR != 1 || D == 64) {   // straight to bf16
+                o[2 * i] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[i], 1.f, false));
+                o[2 * i + 1] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w[i], 1.f, true));
+            } else {                               // over fp32
+                const auto p01 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], false);     // bytes 0, 1 of the word
+                const auto p23 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], true);      // bytes 2, 3
+                o[2 * i] = (__float_as_uint(p01[0]) >> 16) | (__float_as_uint(p01[1]) & 0xffff0000u);
+                o[2 * i + 1] = (__float_as_uint(p23[0]) >> 16) | (__float_as_uint(p23[1]) & 0xffff0000u);
+            }
+        }
+        lo = u32x4{o[0], o[1], o[2], o[3]};
+        hi = u32x4{o[4], o[5], o[6], o[7]};
+    };
+    // PIPE8: tile u has landed, this lane's pieces of it are widened into its place in the bf16 ring, and tile u + 3 is requested.
+    // Every lane reads what it has asked for itself, so no
+    // barrier is needed in between.
+    auto widen_ahead = [&](int u, int slot) {
+        static_assert(!PIPE8 || CH == 1, "a piece of K and one of V per thread");
+        if (u >= t1) return;
+        const int ahead = t1 - 1 - u;
+        if (ahead <= 0)      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
+        else                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
+        const unsigned char* const raw = (const unsigned char*)(s_raw + slot * SLOT) + tid * 16;
+        unsigned short* const krow = (unsigned short*)(s_buf + slot * BUF) + kkey0 * D;
+        unsigned short* const vrow = krow + TK * D;
+        u32x4 lo, hi;
+        widen(*(const u32x4*)raw, lo, hi);
+        *(u32x4*)(krow + (((2 * pc) ^ (kkey0 & (CPR - 1))) << 3)) = lo;
+        *(u32x4*)(krow + (((2 * pc + 1) ^ (kkey0 & (CPR - 1))) << 3)) = hi;
+        widen(*(const u32x4*)(raw + RAW * 2), lo, hi);
+        unsigned short* const vseg = vrow + ((pc ^ v_swizzle(kkey0)) << 4);
+        *(u32x4*)vseg = lo;
+        *(u32x4*)(vseg + 8) = hi;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the raw tile has been read)
+        if (u + NBUF < t1) request_tile(u + NBUF, slot);
+    };
+
     // KV8: widen the tile that has just landed in buffer `buf`, in place.  Every thread reads the sixteen-byte pieces
     // it owns (sixteen values each), the workgroup meets (the bf16 tile overwrites the bytes), the pieces are written
     // as bf16 where the operand reads expect them (K: 16-byte chunk c of row r at position c ^ (r mod 16); V: 32-byte
@@ -368,18 +430,6 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             wv[cc] = *(const u32x4*)(rv + (cc * NT + tid) * 16);
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        auto widen = [](const u32x4& w, u32x4& lo, u32x4& hi) {
-            unsigned int o[8];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const auto p01 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], false);     // bytes 0, 1 of the word
-                const auto p23 = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], true);      // bytes 2, 3
-                o[2 * i] = (__float_as_uint(p01[0]) >> 16) | (__float_as_uint(p01[1]) & 0xffff0000u);
-                o[2 * i + 1] = (__float_as_uint(p23[0]) >> 16) | (__float_as_uint(p23[1]) & 0xffff0000u);
-            }
-            lo = u32x4{o[0], o[1], o[2], o[3]};
-            hi = u32x4{o[4], o[5], o[6], o[7]};
-        };
 #pragma unroll
         for (int cc = 0; cc < CH; ++cc) {
             const int sigma = cc * NT + tid, row = sigma / CPRG, c16 = sigma % CPRG;
@@ -395,18 +445,12 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     };
-    // The first PD tiles are requested at once.  A split with fewer tiles issues the same number of loads all the
-    // same (one word each, into the unused buffer's mask-word slots: a load without a destination register): the
-    // wait for Q below can then name a fixed count of younger requests.
-    auto pad_requests = [&](int buf) {
-        const unsigned lds_w = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(s_mw + (buf * NWAVES + wave) * 128);
-#pragma unroll
-        for (int i = 0; i < LPT; ++i)
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_w), "v"(a_prefix_len) : "m0", "memory");
-    };
     if (t0 < t1) request_tile(t0, std::integral_constant<int, 0>{}); else pad_requests(0);
     if (PD > 1) { if (t0 + 1 < t1) request_tile(t0 + 1, std::integral_constant<int, (PD > 1 ? 1 : 0)>{}); else pad_requests(1); }
     if (PD > 2) { if (t0 + 2 < t1) request_tile(t0 + 2, std::integral_constant<int, (PD > 2 ? 2 : 0)>{}); else pad_requests(2); }
+    // PIPE8: mask words do not travel with the tiles, whose places are taken again before they are computed: one tile ahead
+    uint64_t next_word = 0;
+    if (PIPE8 && max(t0, ptiles) < t1) next_word = mask_row[max(t0, ptiles) - ptiles];
     if (tid == 0 && hk == 0 && split == 0 && rb == 0) report_clamp(a.counters, L_raw, a_max_prefix);
     // Q has landed when at most the PD request groups issued behind it are outstanding (a tree tile's two mask
     // words are not counted: the wait is then on the safe side)
@@ -419,17 +463,28 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     // immediate offset; a wide variant takes few tiles here.
     auto tile_step = [&](int t, auto cur_c) {
         const int CUR = cur_c;
-        const int PREV = (CUR + NBUF - 1) % NBUF;          // buffer of tile t - 1 (= of tile t + PD)
+        // buffer of tile t - 1 (= of tile t + PD); a constant again if CUR is one
+        const auto PREV = [&](auto c) {
+            if constexpr (std::is_same_v<decltype(c), int>) return (c + NBUF - 1) % NBUF;
+            else return std::integral_constant<int, (decltype(c)::value + NBUF - 1) % NBUF>{};
+        }(cur_c);
         // my requests for tile t have landed (younger ones may still be in flight); after the barrier
         // everybody's have, and everybody is done reading the buffer of tile t - 1
         // (a request group holds LPT tile loads, plus one mask word for a tree tile: allowing only
         // ahead * LPT younger loads to be outstanding is then on the safe side)
         const int ahead = t1 - 1 - t < PD - 1 ? t1 - 1 - t : PD - 1;
-        if (ahead <= 0)      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
-        else                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");
-        if (t + PD < t1) request_tile(t + PD, PREV);
-        if constexpr (KV8) widen_tile(CUR);
+        const uint64_t word = next_word;
+        if constexpr (PIPE8) {
+            if (t >= ptiles && t + 1 < t1) next_word = mask_row[t + 1 - ptiles];
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            widen_ahead(t + 2, PREV);
+        } else {
+            if (ahead <= 0)      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
+            else                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");
+            if (t + PD < t1) request_tile(t + PD, PREV);
+            if constexpr (KV8) widen_tile(CUR);
+        }
 
         const unsigned short* const s_k = (const unsigned short*)(s_buf + CUR * BUF);
         const unsigned short* const s_v = s_k + TK * D;
@@ -441,7 +496,8 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         // tree tiles the row's ancestor bits
         const bool masked = tree || key0 + TK > kend;
         uint64_t vis = kend - key0 >= TK ? ~0ull : ((1ull << (kend - key0)) - 1ull);
-        if (tree) vis &= (uint64_t)s_mw[(CUR * NWAVES + wave) * 128 + lane] | ((uint64_t)s_mw[(CUR * NWAVES + wave) * 128 + 64 + lane] << 32);
+        if (tree && PIPE8) vis &= word;
+        else if (tree) vis &= (uint64_t)s_mw[(CUR * NWAVES + wave) * 128 + lane] | ((uint64_t)s_mw[(CUR * NWAVES + wave) * 128 + 64 + lane] << 32);
 
         // one 32-key block at a time: S^T = K Q^T, online softmax, O^T += V^T P^T
 #pragma unroll
@@ -511,6 +567,10 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         }
     };
     int t_done = t0;           // tiles [t0, t_done) are consumed
+    if constexpr (PIPE8) {                                     // the first two tiles, widened
+        widen_ahead(t0, 0);
+        widen_ahead(t0 + 1, 1);
+    }
     if constexpr (VAR == 2) {
         // ---- fast loop of the 256-row variant over full prefix tiles: what the MFMA-bound shapes spend their time in.
         // The softmax reference of a row stays FIXED while no probability of a 32-key block comes out too large: p =
@@ -537,10 +597,18 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         const int t_full = min(t1, L / TK);                      // tiles below t_full are full prefix tiles
         // tile t + 1 has landed for this lane when only the requests of tile t + 2 are outstanding; after the barrier it has
         // for everybody, and everybody is done with tile t - 1, into whose buffer tile t + 3 goes
+        // (PIPE8: tile t + 1 has been widened by everybody, and tile t + 2 is widened into the place of tile t - 1)
+        int at = 0, at1 = 1;                                     // places of tiles t and t + 1 in the ring
+        auto following = [](int at) { return at + 1 == NBUF ? 0 : at + 1; };
         auto stage = [&](int t) {
+            if constexpr (PIPE8) {
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                widen_ahead(t + 2, following(at1));
+                return;
+            }
             if (t + 2 < t1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
             else            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (t + PD < t1) request_tile(t + PD, (t + PD - t0) & (NBUF - 1));
+            if (t + PD < t1) request_tile(t + PD, at == 0 ? NBUF - 1 : at - 1);
         };
         // LDS addresses of the operands, moved from tile to tile: K of tile t + 1, what is still to be read of K of tile t, V
         // of tile t; block 1 is at a fixed distance
@@ -628,21 +696,23 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             auto phase_b = [&]() { return phase(std::integral_constant<int, 1>{}, s1, s0, p0, p1); };
             // behind phase B of tile t - 1: tile t
             auto next_tile = [&](int t) {
+                at = at1;
+                at1 = following(at);
                 stage(t);
-                const int v = (t - t0) & (NBUF - 1), k = (t + 1 - t0) & (NBUF - 1);
 #pragma unroll
                 for (int s = KR; s < NS; ++s) kc[s - KR] = ka[s];
 #pragma unroll
-                for (int s = 0; s < NS; ++s) ka[s] += k ? BUF * 4 : -(NBUF - 1) * BUF * 4;
+                for (int s = 0; s < NS; ++s) ka[s] += at1 ? BUF * 4 : -(NBUF - 1) * BUF * 4;
 #pragma unroll
-                for (int d = 0; d < DB; ++d) va[d] += v ? BUF * 4 : -(NBUF - 1) * BUF * 4;
+                for (int d = 0; d < DB; ++d) va[d] += at ? BUF * 4 : -(NBUF - 1) * BUF * 4;
             };
             auto add_pv = [&]() {                    // P V of the block whose P is in p1 and whose V operands are in vf
 #pragma unroll
                 for (int i = 0; i < NP; ++i) mma(vf[i], __builtin_bit_cast(bf16x8, p1[i / DB]), oacc[i % DB]);
             };
             // S of the first block; its tile has landed when only the requests of the two behind it are outstanding
-            if (t0 + 2 < t1)      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");
+            if constexpr (PIPE8)  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else if (t0 + 2 < t1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LPT) : "memory");
             else if (t0 + 1 < t1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPT) : "memory");
             else                  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
@@ -664,7 +734,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 moved = t;
                 p1[0] = p1[1] = zero;
 #pragma unroll
-                for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s] - (((t + 1 - t0) & (NBUF - 1)) ? BUF * 4 : -(NBUF - 1) * BUF * 4), 1);
+                for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s] - (at1 ? BUF * 4 : -(NBUF - 1) * BUF * 4), 1);
                 bool in_b = false;
                 for (;;) {
                     float psum = phase_a();
@@ -691,7 +761,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             add_pv();                                // the last block's (P is zero if it has been added)
             t_done = t_full;
         }
-        for (int tt = t_done; tt < t1; ++tt) tile_step(tt, (tt - t0) & (NBUF - 1));       // the prefix tail and the tree tiles
+        for (int tt = t_done; tt < t1; ++tt) tile_step(tt, (tt - t0) % NBUF);       // the prefix tail and the tree tiles
     } else
     if constexpr (WIDE) {
         // ---- fast loop of the 128-row variant over full prefix tiles: what the MFMA-bound shapes spend their time in.
@@ -1003,10 +1073,9 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     if (rho2 >= rows_all) return;                      // no row behind this lane (no barrier follows)
     const int live2 = min(32, rows_all - (rb * ROWS + cq * 32));
     // CHUNK splits at a time: all their loads are issued before the first one is used (each is a trip to
-    // memory), and the running maximum M is carried from chunk to chunk like in the main loop.  The narrow
-    // variant has the whole register file of its SIMD and takes eight splits -- normally all -- in one trip.
-    constexpr int MREGS = WIDE ? 64 : 96;
-    constexpr int CHUNK = MREGS / (DC * EPS * 2) < 1 ? 1 : MREGS / (DC * EPS * 2);   // register budget
+    // memory), and the running maximum M is carried from chunk to chunk like in the main loop.
+    constexpr int CHUNK = merge_chunk(D, WIDE);
+    static_assert(CHUNK * DC * EPS * 2 <= 96, "register budget");
     const u64* mlp = (const u64*)a.part_ml + ((size_t)group * a_splits * NQB + cq) * 32 + l32;
     const u64* pp = (const u64*)a.part_o + ((size_t)group * a_splits * NQB + cq) * (DB * EPS * 64) + d0 * EPS * 64 +
                     h * live2 + l32;
@@ -1377,28 +1446,39 @@ __global__ void attn_clear_sync_kernel(unsigned int* p) {
 
 static size_t align_up(size_t v, size_t al) { return (v + al - 1) / al * al; }
 
-// Workgroups that the split count of the bf16 path aims at: what the chip holds at once (256 compute
-// units; the narrow variant's three tile buffers allow one workgroup per unit at head_dim 128, the wide
-// variant's two buffers allow two).
-#ifndef OT_ATTN_NARROW_WGS
-#define OT_ATTN_NARROW_WGS 256
-#endif
-#ifndef OT_ATTN_WIDE_WGS
-#define OT_ATTN_WIDE_WGS 512
-#endif
+// Packed query rows per workgroup of the bf16 kernel: 64 (narrow: the wavefronts split each tile's keys), 128, or 256 --
+// eight wavefronts then share every staged K/V tile, which halves the traffic into LDS per MFMA and leaves room for a ring
+// of four tiles -- where the 256-row blocks are many or long enough: us at 128 / 256 rows, 16-bit cache of 128: 4 x 8 KV heads
+// of 480 rows, 1060 keys 23.8 / 26.7, 2060 keys 34.6 / 33.7, 8060 keys 83 / 76; 1 x 8 of 480 rows, 8060 keys 33 / 45;
+// 16 x 8 of 480 rows, 160 keys 18.4 / 18.7, 360 keys 29.1 / 25.0, 2060 keys 83 / 76; 8-bit cache: 2060 keys 84 / 74.
+static int attn_rows_per_workgroup(const ot_attn_params& p, bool kv8, int tiles) {
+    const int rows = p.q_heads / p.kv_heads * p.n;
+    if (rows <= 64) return 64;
+    if (rows <= 128 || (kv8 && p.head_dim == 64)) return 128;   // (64 one-byte rows of 64 have fewer pieces than 512 threads)
+    const long long blocks = (long long)p.batch * p.kv_heads * ((rows + 255) / 256);
+    return blocks >= 64 && blocks * tiles >= 2048 ? 256 : 128;
+}
 
-// Packed query rows per workgroup of the bf16 kernel: 64 (narrow: the wavefronts split each tile's keys), 128, or
-// 256 when a KV head has more rows than that -- eight wavefronts then share every staged K/V tile, which halves the
-// traffic into LDS per MFMA and leaves room for a ring of four tiles (three in flight).
-// Batches take their jobs longest first (1) or in the order of their sequences (0).
-#ifndef OT_ATTN_BALANCE
-#define OT_ATTN_BALANCE 1
-#endif
-#ifndef OT_ATTN_ROWS256_FROM
-#define OT_ATTN_ROWS256_FROM 129
-#endif
-static int attn_rows_per_workgroup(int rows_per_kv_head) {
-    return rows_per_kv_head <= 64 ? 64 : (rows_per_kv_head >= OT_ATTN_ROWS256_FROM ? 256 : 128);
+// Key splits of the bf16 kernel.  More splits shorten the streaming, but the workgroup that finishes last merges them all, 1.6 us
+// for every trip to memory: as many as fill the 256 compute units once, and eight (the narrow variant: what one trip takes,
+// at head_dim 128, six, two and more trips over long prefixes).  us by splits, one sequence unless noted:
+//   64 rows x 8 heads, 128: 1016 keys 3: 14.5, 6: 11.3, 9: 12.6; 4008 keys 6: 19.5, 11: 16.5, 32: 21.1; 8016 keys 8: 26.7, 16: 21.0
+//   64 rows x 8 heads, 64: 1016 keys 6: 9.8, 9: 9.2; 4016 keys 8: 13.6, 11: 12.0, 32: 16.3; two sequences 11: 12.9, 32: 23.7
+//   200 rows x 8 heads in blocks of 128, 128: 250 keys 1: 12.5, 3: 14.1, 5: 14.3; 1050 keys 1: 25.6, 3: 18.9, 6: 17.3, 9: 19.1;
+//   4050 keys 4: 30.4, 8: 23.8, 16: 25.8, 32: 34 to 45; 120 rows x 16 heads x 4, 4060 keys 4 (256 workgroups): 33.2, 8: 40.0;
+//   50 rows x 32 heads, 64: 4050 keys 8 (256): 14.1, 16: 17.8
+// Where one workgroup per unit leaves no split, the variants of which two fit a unit are split over those; two also hide each
+// other's widening of 8-bit tiles (1264 rows x 4 heads x 2, 2158 keys of 128 3: 33.5, 6: 30.1; 120 rows x 16 x 4, 4120 of 64
+// 4: 26.9, 8: 23.6).
+static int attn_splits(long long base, int tiles, int rows_wg, int head_dim, bool kv8) {
+    const bool wide = rows_wg > 64, two = rows_wg == 128 || (!wide && head_dim == 64);
+    if (tiles <= (wide || head_dim == 64 ? 5 : 1)) return 1;
+    long long s = 256 / base;
+    if (s < 2) s = two && tiles >= 24 ? 512 / base : 1;
+    else if (kv8 && two && s >= 3 && s <= 5) s = 512 / base;
+    const int most = wide ? 8 : merge_chunk(head_dim, false) * (head_dim == 128 ? 1 + tiles / 48 : 1);
+    s = std::min<long long>(s, most);
+    return (int)std::max(1LL, std::min<long long>(s, wide ? tiles / 2 : tiles));
 }
 
 // Packed query rows per workgroup of the f32 kernel (its eight wavefronts = rows / 32 row blocks x key slices): as many as
@@ -1416,20 +1496,18 @@ AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
     const int g = p.q_heads / p.kv_heads, nk = p.n_keys > 0 ? p.n_keys : p.n;
     int base, tile, rows_wg = 0, splits;
     if (p.dtype == OT_BF16) {
-        const bool wide = g * p.n > 64;                    // wide variants when one KV head has more than 64 rows
-        rows_wg = attn_rows_per_workgroup(g * p.n);
-        if (kv8 && rows_wg == 256) rows_wg = 128;
+        tile = 64;
+        const int tiles = (p.max_prefix + 63) / 64 + (nk + 63) / 64;
+        rows_wg = attn_rows_per_workgroup(p, kv8, tiles);
         pl.row_blocks = (g * p.n + rows_wg - 1) / rows_wg;
         base = p.batch * p.kv_heads * pl.row_blocks;
-        tile = 64;
-        int target = wide ? (rows_wg == 256 ? OT_ATTN_WIDE_WGS / 2 : OT_ATTN_WIDE_WGS) : OT_ATTN_NARROW_WGS;
-        if (!wide && p.head_dim == 64) target *= 2;
-        splits = target / base;                            // never more workgroups than fit at once
+        splits = attn_splits(base, tiles, rows_wg, p.head_dim, kv8);
         // A batch that fills the chip with one key range per (sequence, KV head): the lengths are known on the
         // device only, where the workgroups take their jobs longest first (see the kernel).  Measured: 3 % faster on
         // ragged batches of one and a half to three rounds of workgroups; from four rounds on the rounds even the
         // lengths out by themselves and the ranking's extra trip to memory per workgroup costs 1 %.
-        if (OT_ATTN_BALANCE && wide && p.batch > 1 && p.batch <= 64 && splits <= 1 && base < 4 * target) pl.balance = 1;
+        const int resident = rows_wg == 256 ? 256 : 512;   // workgroups that the chip holds at once
+        if (rows_wg > 64 && p.batch > 1 && p.batch <= 64 && splits == 1 && base > resident / 2 && base < 4 * resident) pl.balance = 1;
     } else {
         // One workgroup per compute unit at a time (eight wavefronts, two per SIMD).  Splitting costs 5 us (partials through
         // memory, the merge), a 32 x 32 block 2 us of a SIMD at head_dim 64 and 4 at 128: what is at most two blocks per SIMD
@@ -1448,14 +1526,10 @@ AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
     if (splits > max_tiles) splits = max_tiles;
     if (splits > kMaxSplits) splits = kMaxSplits;
     if (splits < 1) splits = 1;
-#ifndef OT_ATTN_EVEN_OUT
-#define OT_ATTN_EVEN_OUT 1
-#endif
-    if (OT_ATTN_EVEN_OUT) {
-        // even out: every split gets the same number of tiles (the last one possibly fewer)
-        const int per = (max_tiles + splits - 1) / splits;
-        splits = (max_tiles + per - 1) / per;
-    }
+    // even out: every split gets the same number of tiles (the last one possibly fewer)
+    const int per = (max_tiles + splits - 1) / splits;
+    splits = (max_tiles + per - 1) / per;
+    pl.rows = rows_wg;
     pl.splits = splits;
     // partials are stored per workgroup (rows padded to the row block)
     const size_t rows = (size_t)base * rows_wg;
@@ -1492,8 +1566,7 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
     auto magic = [](int d) { return d <= 1 ? 0u : (unsigned int)((0x100000000ull + (unsigned)d - 1) / (unsigned)d); };
     a.inv_splits = magic(a.splits); a.inv_kv_heads = magic(a.kv_heads); a.inv_n = magic(a.n);
     if (p.dtype == OT_BF16) {
-        int rows_wg = attn_rows_per_workgroup(a.g * p.n);
-        if (kv8 && rows_wg == 256) rows_wg = 128;
+        const int rows_wg = plan.rows;
         const long long units = (long long)p.batch * p.kv_heads * plan.splits;
         const long long unit_groups = (units + 7) / 8;      // the same count either way when pairs % 8 == 0
         a.splits_share_xcd = (!plan.balance && plan.splits > 1 && ((long long)p.batch * p.kv_heads) % 8 == 0) ? 1 : 0;
@@ -1504,8 +1577,9 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
 #define OT_ATTN_ARGS a.prefix_len, a.mask, a.Q, a.splits, a.inv_splits, a.kv_heads, a.inv_kv_heads, a.n, a.inv_n, a
 #define OT_ATTN_LAUNCH(DD, VV, K8, BB)                                                                       \
     do {                                                                                                   \
-        const int nbuf = (VV) == 2 ? 4 : ((VV) == 1 ? 2 : OT_ATTN_NBUF_NARROW), nwaves = (VV) == 2 ? 8 : 4; \
-        const size_t lds = (size_t)nbuf * (64 * DD + nwaves * 128) * sizeof(unsigned int);                 \
+        const int nbuf = (VV) == 2 ? ((K8) ? 3 : 4) : ((VV) == 1 ? 2 : OT_ATTN_NBUF_NARROW), nwaves = (VV) == 2 ? 8 : 4; \
+        const int raw = (VV) == 2 && (K8) ? 32 * DD : 0;                                                   \
+        const size_t lds = (size_t)nbuf * (64 * DD + raw + nwaves * 128) * sizeof(unsigned int);           \
         if (lds > 64 * 1024)                                                                               \
             OT_HIP_CHECK(hipFuncSetAttribute((const void*)attn_mfma_kernel<DD, VV, K8, BB>,                 \
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));       \
@@ -1513,12 +1587,13 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
         else hipLaunchKernelGGL((attn_mfma_kernel<DD, VV, K8, BB>), grid, dim3(64 * nwaves), lds, s, OT_ATTN_ARGS); \
     } while (0)
         const int var = rows_wg == 256 ? 2 : (rows_wg == 128 ? 1 : 0);
-        // (the 8-bit cache runs the 64- and 128-row variants; only wide variants take their jobs longest first)
+        // (only wide variants take their jobs longest first; the 8-bit cache has no 256-row variant at head_dim 64)
 #define OT_ATTN_PICK(DD, K8)                                                                                \
     do {                                                                                                    \
-        if (var == 2 && !(K8)) { if (plan.balance) OT_ATTN_LAUNCH(DD, ((K8) ? 1 : 2), K8, true); else OT_ATTN_LAUNCH(DD, ((K8) ? 1 : 2), K8, false); } \
-        else if (var >= 1)     { if (plan.balance) OT_ATTN_LAUNCH(DD, 1, K8, true); else OT_ATTN_LAUNCH(DD, 1, K8, false); } \
-        else                   OT_ATTN_LAUNCH(DD, 0, K8, false);                                            \
+        constexpr int V2 = (K8) && (DD) == 64 ? 1 : 2;                                                      \
+        if (var == 2)      { if (plan.balance) OT_ATTN_LAUNCH(DD, V2, K8, true); else OT_ATTN_LAUNCH(DD, V2, K8, false); } \
+        else if (var == 1) { if (plan.balance) OT_ATTN_LAUNCH(DD, 1, K8, true); else OT_ATTN_LAUNCH(DD, 1, K8, false); } \
+        else               OT_ATTN_LAUNCH(DD, 0, K8, false);                                                \
     } while (0)
         if (kv8) { if (p.head_dim == 128) OT_ATTN_PICK(128, true); else OT_ATTN_PICK(64, true); }
         else     { if (p.head_dim == 128) OT_ATTN_PICK(128, false); else OT_ATTN_PICK(64, false); }
@@ -1526,7 +1601,7 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
 #undef OT_ATTN_LAUNCH
 #undef OT_ATTN_ARGS
     } else {
-        const int rows_wg = f32_rows_per_workgroup(p);
+        const int rows_wg = plan.rows;
         const long long unit_groups = ((long long)p.batch * p.kv_heads * plan.splits + 7) / 8;
         if (unit_groups > 65535 || 8LL * plan.row_blocks > 0x7fffffffLL) return OT_ERR_UNSUPPORTED;   // cannot happen within the limits
         if (plan.splits > 1 && (long long)p.batch * p.kv_heads * plan.row_blocks * 4 > OT_ATTN_STATUS_OFFSET)

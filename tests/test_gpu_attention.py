@@ -413,6 +413,25 @@ def test_scores_that_round_by_more_than_the_slack(D, n):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
+    *[(1, 2, 2, D, 64 * t, 100) for D in (64, 128) for t in (3, 4, 5, 6, 8, 10, 12, 14, 30)],     # 128 rows: no, two, ... eight splits
+    (1, 2, 2, 128, 64 * 3 + 1, 40), (1, 2, 2, 128, 64 * 5, 40), (1, 2, 2, 128, 64 * 6, 40),       # 64 rows: as many splits as tiles,
+    (1, 2, 2, 128, 3000, 64), (1, 2, 1, 128, 3008, 32), (1, 2, 1, 128, 6100, 32),                 # one, two and three trips of six
+    (1, 2, 2, 64, 256, 40), (1, 2, 2, 64, 257, 40), (1, 2, 2, 64, 2000, 40),                      # 64 wide: no split; six; twelve
+    (8, 8, 8, 128, 2000, 150), (6, 16, 16, 64, 1300, 130),                                        # 256 rows, four splits; two
+])
+def test_key_splits_and_their_merge(B, Hq, Hkv, D, L, n):
+    w = _shape("bf16", B, Hq, Hkv, D, L, n)
+    x = wl.make_attention_inputs(w, 3)
+    x["prefix_len"][-1] = max(1, L // 3)                      # splits without a key, where there is a second sequence
+    mask = _random_masks(B, n, 5)
+    got = _gpu_attention(x, mask, "bf16")
+    seqs, heads = sorted({0, B - 1}), sorted({0, Hkv - 1})
+    q = [h * (Hq // Hkv) + i for h in heads for i in range(Hq // Hkv)]
+    sub = {k: v[seqs] if k == "prefix_len" else v[seqs][:, q if k == "Q" else heads] for k, v in x.items()}
+    assert np.abs(got[seqs][:, q] - _oracle_attention(sub, mask[seqs], "bf16")).max() < TOL["bf16"]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
     (1, 2, 2, 64, 31, 32),             # 32 rows per workgroup, eight key slices; key blocks one short
     (1, 2, 2, 128, 33, 33),            # 33 rows in blocks of 32; one key past a block
     (1, 2, 1, 64, 1, 32),              # 64 rows, a single prefix key

@@ -66,6 +66,23 @@ def test_shapes_and_edges(B, Hq, Hkv, D, L, n, ragged, shape):
     assert np.abs(got - want).max() < TOL
 
 
+@pytest.mark.parametrize("L", [0, 1, 63, 64, 65, 128, 191, 192, 256, 320, 447, 1000])
+def test_256_rows_with_few_tiles_and_jumps_in_either_block(L):
+    """150 rows a KV head, no key splits: fewer and more tiles than the ring of widened tiles holds, and in half of the
+    sequences key bands of far larger scores."""
+    x = _inputs(33, 4, 4, 128, max(L, 1), 150, 0.0, 5)
+    x["prefix_len"][:] = L
+    for b in range(1, 33, 2):                                  # the largest value of both signs
+        for at in (64 * (b % 3) + 8 * b % 64, 64 * (b % 5) + 70, 64 * (b % 7) + 40):
+            band = x["K_prefix"][b, :, at:at + 9]
+            band[...] = (band & 0x80) | 0x7E
+    mask = _masks(33, 150, 8)
+    got = _gpu(x, mask)
+    assert np.isfinite(got).all()
+    some = sorted({0, 1, 2, 3, 5, 9, 17, 32})
+    assert np.abs(got[some] - _oracle({k: v[some] for k, v in x.items()}, mask[some])).max() < TOL
+
+
 def test_scores_that_round_by_more_than_the_slack():
     """As in the 16-bit cache's test of this name: scores of 1e9, here from the K factors."""
     x = _inputs(33, 4, 4, 128, 500, 150, 0.0, 6)
