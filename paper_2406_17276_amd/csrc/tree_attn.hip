@@ -9,9 +9,9 @@
 // that a single small sequence still fills the chip; every split leaves an un-normalised
 // partial (running max m, sum l, O); the last workgroup of a row block to finish merges them.
 //
-// bf16 path (attn_mfma_kernel): one workgroup = 64 or 128 packed query rows of one KV head (GQA: the
+// bf16 path (attn_mfma_kernel): one workgroup = 64, 128 or 256 packed query rows of one KV head (GQA: the
 // g = q_heads/kv_heads query heads that share the KV head are stacked, row = head*n + node), four
-// wavefronts.  Each wavefront
+// wavefronts, eight for 256 rows.  Each wavefront
 //   S^T = K Q^T   v_mfma_f32_32x32x16_bf16, A = K rows from LDS, B = Q held in registers;
 //                 the accumulator leaves every lane with 16 scores of ONE query, so the
 //                 online-softmax statistics and the rescale factor are per-lane scalars;
@@ -19,7 +19,7 @@
 //                 inside a 16-key slab is whatever the accumulator layout gives; V is read in
 //                 the same order), A = V gathered from LDS.
 // K/V tiles go from global memory straight into LDS (global_load_lds_dwordx4: 16 bytes per lane, no
-// register staging), one or two tiles ahead of the computation, into a ring of two or three buffers; a tree
+// register staging), one to three tiles ahead of the computation, into a ring of two to four buffers; a tree
 // tile's mask words (one 64-bit word per query row) travel the same way, just ahead of the tile.  A
 // wavefront's 64 lanes land on 1 KB of consecutive LDS, so rows are unpadded and bank conflicts are
 // avoided by an XOR swizzle instead: lane -> global chunk is chosen such that 16-byte chunk c of key
@@ -127,7 +127,7 @@ constexpr int merge_chunk(int head_dim, bool wide) { return (wide ? 256 : 768) /
 //                Three tile buffers: two tiles are in flight while a third is being computed.
 // WIDE (VAR 1, 2): 128 or 256 packed rows per workgroup (four or eight wavefronts), wavefront = 32 rows x the whole tile; staging one
 //                tile in LDS is shared by twice as many MFMAs and nothing is merged at the end.
-//                Two tile buffers, so that two workgroups share a compute unit.
+//                128 rows: two tile buffers, so that two workgroups share a compute unit; 256 rows: four, one workgroup per unit.
 // Workgroups are numbered so that those which stream the same K/V (the row blocks of one
 // (sequence, KV head, split)) sit on the same XCD, next to each other in its dispatch order, and
 // share that XCD's L2: hardware hands workgroup L to XCD L % 8.  When the (sequence, KV head) pairs divide evenly
@@ -149,9 +149,10 @@ constexpr int merge_chunk(int head_dim, bool wide) { return (wide ? 256 : 768) /
 #define OT_ATTN_PART_BF16 1
 #endif
 // KV8: K and V arrive as FP8 E4M3 bytes with a scale factor per (sequence, KV head) each.  A tile is copied into LDS
-// as it is (half the bytes), then every thread widens its sixteen-byte pieces to bf16 in place -- every E4M3 value
-// is a bf16 value -- into the layout the operand reads expect (two more barriers per tile); the K factor joins the
-// softmax scale, the V factor the final normalisation.  Everything else is the bf16 kernel.
+// as it is (half the bytes), then every thread widens its sixteen-byte pieces to bf16 -- every E4M3 value is a bf16
+// value -- into the layout the operand reads expect: in place, behind two more barriers per tile, or (256 rows) two tiles
+// ahead from a ring of raw tiles into a ring of bf16 tiles, each lane the pieces that it has requested itself; the K factor
+// joins the softmax scale, the V factor the final normalisation.  Everything else is the bf16 kernel.
 //
 // BAL (wide variants, batches of 2 to 64 sequences that fill the chip, each (sequence, KV head) in one piece): the
 // sequences of a batch differ in length, workgroups are handed out in the order of their number, and a launch lasts
@@ -392,8 +393,8 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         hi = u32x4{o[4], o[5], o[6], o[7]};
     };
     // PIPE8: tile u has landed, this lane's pieces of it are widened into its place in the bf16 ring, and tile u + 3 is requested.
-    // Every lane reads what it has asked for itself, so no
-    // barrier is needed in between.
+    // Every lane reads what it has asked for itself, so no barrier is needed in between.  Against the 128-row variant, which
+    // widens every tile once per row block behind two barriers: 16 x 8 KV heads of 480 rows, 4096 keys +-25 % 182 -> 164 us.
     auto widen_ahead = [&](int u, int slot) {
         static_assert(!PIPE8 || CH == 1, "a piece of K and one of V per thread");
         if (u >= t1) return;
