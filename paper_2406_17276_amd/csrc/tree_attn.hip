@@ -119,12 +119,21 @@ __device__ __forceinline__ void split_range(int T, int S, unsigned int inv_S, in
 // variant; 128, or none for splits that are not there, were 0.5 to 2 us slower)
 constexpr int merge_chunk(int head_dim, bool wide) { return (wide ? 256 : 768) / head_dim; }
 
+// Tile buffers of a variant (0: 64 rows, 1: 128, 2: 256, 3: 64 rows of 128, 16-bit cache, more workgroups than compute units).
+// 64 rows: two buffers let two workgroups share a compute unit, one of which computes or widens while the other waits; with no
+// more workgroups than units that gains nothing and the third buffer's second tile in flight does (four are 3 to 7 % slower
+// than three).  An 8-bit tile is half the bytes in flight and has the widening in front of it: two buffers throughout.  us with
+// three / two, one key range a KV head: 9 x 32 heads of 50 rows, 1000 keys 49.5 / 38.5 (8-bit 52.5 / 37.5), 4000 keys 161 / 115
+// (165 / 113); 16 x 32 of 64 rows, 2000 keys 114 / 111 (101 / 81); 32 x 40 of 30 rows, 1000 keys 133 / 132 (127 / 93);
+// 32 x 8 = 256 of 60 rows, 3000 keys 77 / 81 (70 / 66); one sequence of 32 heads, 1024 keys 12.0 / 12.1 (13.3 / 12.8).
+constexpr int tile_buffers(int var, bool kv8) { return var == 2 ? (kv8 ? 3 : 4) : (var == 0 && !kv8 ? 3 : 2); }
+
 // ---------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------
 // WIDE = false: 64 packed rows per workgroup, wavefront = (query block of 32 rows) x (half of each
 //                64-key tile); the two halves are merged through LDS at the end.  For few rows.
-//                Three tile buffers: two tiles are in flight while a third is being computed.
+//                Three tile buffers -- two tiles are in flight while a third is being computed -- or two (tile_buffers).
 // WIDE (VAR 1, 2): 128 or 256 packed rows per workgroup (four or eight wavefronts), wavefront = 32 rows x the whole tile; staging one
 //                tile in LDS is shared by twice as many MFMAs and nothing is merged at the end.
 //                128 rows: two tile buffers, so that two workgroups share a compute unit; 256 rows: four, one workgroup per unit.
@@ -139,9 +148,6 @@ constexpr int merge_chunk(int head_dim, bool wide) { return (wide ? 256 : 768) /
 // of its (sequence, KV head, row block); the workgroup that draws the last ticket merges all the
 // partials of those rows and writes O.  Nobody waits for anybody: a workgroup that is not last simply
 // ends.  The counter is reset by the merging workgroup, so it is zero again when the kernel ends.
-#ifndef OT_ATTN_NBUF_NARROW
-#define OT_ATTN_NBUF_NARROW 3
-#endif
 // Partial results of the key splits travel as bf16 (0) or as fp32 (define to 0): bf16 halves the exchange and lets the
 // merging workgroup hold all of a row block's partials in registers at once, one trip to memory instead of two; the
 // extra rounding is of the size of the output's own (the output is bf16).
@@ -166,7 +172,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     const int32_t* a_prefix_len, const uint64_t* a_mask, const void* a_Q, const int a_splits, const unsigned a_inv_splits,
     const int a_kv_heads, const unsigned a_inv_kv_heads, const int a_n, const unsigned a_inv_n, const AttnKArgs a) {
     const int a_g = a.g, a_max_prefix = a.max_prefix, a_nk = a.nk, a_W = a.W, a_row_blocks = a.row_blocks;
-    constexpr bool WIDE = VAR >= 1;
+    constexpr bool WIDE = VAR == 1 || VAR == 2;
     constexpr int NWAVES = VAR == 2 ? 8 : 4;
     constexpr int NT = 64 * NWAVES;        // threads
     constexpr int TK = 64;                 // keys per tile
@@ -189,7 +195,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     constexpr int ROWS = VAR == 2 ? 256 : (WIDE ? 128 : 64);   // packed query rows per workgroup
     constexpr int NQB = ROWS / 32;         // query blocks per workgroup
     constexpr bool PIPE8 = KV8 && VAR == 2;   // tiles are widened two tiles ahead, into a ring of their own
-    constexpr int NBUF = VAR == 2 ? (KV8 ? 3 : 4) : (WIDE ? 2 : OT_ATTN_NBUF_NARROW);
+    constexpr int NBUF = tile_buffers(VAR, KV8);
     constexpr int PD = PIPE8 ? NBUF : NBUF - 1;   // tiles requested ahead of the one being computed (PIPE8: being widened)
     static_assert(PD >= 1 && PD <= 3 && PD * LPT < 64, "prefetch depth fits the vmcnt counter");
 
@@ -211,7 +217,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     int bz, split;
     int L_bal = 0;
     if constexpr (BAL) {
-        static_assert(VAR >= 1, "wide variants only");
+        static_assert(WIDE, "wide variants only");
         const int B = a.batch;                                   // 2..64, one key range per (sequence, KV head)
         const int Lj = lane < B ? a_prefix_len[lane] : 0;
         const int Tj = lane < B ? clamp_len(Lj, a_max_prefix) : -1;
@@ -1578,7 +1584,7 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
 #define OT_ATTN_ARGS a.prefix_len, a.mask, a.Q, a.splits, a.inv_splits, a.kv_heads, a.inv_kv_heads, a.n, a.inv_n, a
 #define OT_ATTN_LAUNCH(DD, VV, K8, BB)                                                                       \
     do {                                                                                                   \
-        const int nbuf = (VV) == 2 ? ((K8) ? 3 : 4) : ((VV) == 1 ? 2 : OT_ATTN_NBUF_NARROW), nwaves = (VV) == 2 ? 8 : 4; \
+        const int nbuf = tile_buffers(VV, K8), nwaves = (VV) == 2 ? 8 : 4; \
         const int raw = (VV) == 2 && (K8) ? 32 * DD : 0;                                                   \
         const size_t lds = (size_t)nbuf * (64 * DD + raw + nwaves * 128) * sizeof(unsigned int);           \
         if (lds > 64 * 1024)                                                                               \
@@ -1587,13 +1593,14 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
         if (ev0 || ev1) hipExtLaunchKernelGGL((attn_mfma_kernel<DD, VV, K8, BB>), grid, dim3(64 * nwaves), lds, s, ev0, ev1, 0, OT_ATTN_ARGS); \
         else hipLaunchKernelGGL((attn_mfma_kernel<DD, VV, K8, BB>), grid, dim3(64 * nwaves), lds, s, OT_ATTN_ARGS); \
     } while (0)
-        const int var = rows_wg == 256 ? 2 : (rows_wg == 128 ? 1 : 0);
+        const int var = rows_wg == 256 ? 2 : (rows_wg == 128 ? 1 : (units > 256 ? 3 : 0));   // (3: see tile_buffers)
         // (only wide variants take their jobs longest first; the 8-bit cache has no 256-row variant at head_dim 64)
 #define OT_ATTN_PICK(DD, K8)                                                                                \
     do {                                                                                                    \
-        constexpr int V2 = (K8) && (DD) == 64 ? 1 : 2;                                                      \
+        constexpr int V2 = (K8) && (DD) == 64 ? 1 : 2, V3 = (K8) || (DD) == 64 ? 0 : 3;                     \
         if (var == 2)      { if (plan.balance) OT_ATTN_LAUNCH(DD, V2, K8, true); else OT_ATTN_LAUNCH(DD, V2, K8, false); } \
         else if (var == 1) { if (plan.balance) OT_ATTN_LAUNCH(DD, 1, K8, true); else OT_ATTN_LAUNCH(DD, 1, K8, false); } \
+        else if (var == 3) OT_ATTN_LAUNCH(DD, V3, K8, false);                                               \
         else               OT_ATTN_LAUNCH(DD, 0, K8, false);                                                \
     } while (0)
         if (kv8) { if (p.head_dim == 128) OT_ATTN_PICK(128, true); else OT_ATTN_PICK(64, true); }

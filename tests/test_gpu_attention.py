@@ -431,6 +431,19 @@ def test_key_splits_and_their_merge(B, Hq, Hkv, D, L, n):
     assert np.abs(got[seqs][:, q] - _oracle_attention(sub, mask[seqs], "bf16")).max() < TOL["bf16"]
 
 
+@pytest.mark.parametrize("L", [1, 63, 64, 65, 128, 129, 192, 700])
+@pytest.mark.parametrize("B,n", [(32, 33), (33, 33), (33, 64)])
+def test_64_rows_in_great_numbers(B, n, L):
+    """256 and 264 (sequence, KV head) pairs around the line between three tile buffers and two; two to twelve tiles."""
+    w = _shape("bf16", B, 8, 8, 128, L, n)
+    x = wl.make_attention_inputs(w, 4)
+    x["prefix_len"][-1] = L // 2
+    mask = _random_masks(B, n, 6)
+    got = _gpu_attention(x, mask, "bf16")
+    some = [0, 17, B - 1]
+    assert np.abs(got[some] - _oracle_attention({k: v[some] for k, v in x.items()}, mask[some], "bf16")).max() < TOL["bf16"]
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
     (1, 2, 2, 64, 31, 32),             # 32 rows per workgroup, eight key slices; key blocks one short
     (1, 2, 2, 128, 33, 33),            # 33 rows in blocks of 32; one key past a block

@@ -66,6 +66,17 @@ def test_shapes_and_edges(B, Hq, Hkv, D, L, n, ragged, shape):
     assert np.abs(got - want).max() < TOL
 
 
+@pytest.mark.parametrize("L", [1, 63, 64, 65, 128, 129, 192, 700])
+def test_64_rows_in_great_numbers(L):
+    """264 (sequence, KV head) pairs, two workgroups to a compute unit; two to twelve tiles through two buffers."""
+    x = _inputs(33, 8, 8, 128, L, 40, 0.0, 7)
+    x["prefix_len"][-1] = L // 2
+    mask = _masks(33, 40, 9)
+    got = _gpu(x, mask)
+    some = [0, 17, 32]
+    assert np.abs(got[some] - _oracle({k: v[some] for k, v in x.items()}, mask[some])).max() < TOL
+
+
 @pytest.mark.parametrize("L", [0, 1, 63, 64, 65, 128, 191, 192, 256, 320, 447, 1000])
 def test_256_rows_with_few_tiles_and_jumps_in_either_block(L):
     """150 rows a KV head, no key splits: fewer and more tiles than the ring of widened tiles holds, and in half of the
