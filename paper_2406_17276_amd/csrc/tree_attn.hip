@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "internal.h"
 
 namespace ot {
 namespace {
@@ -726,20 +727,24 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             for (int v = 0; v < 16; ++v) s0[v] = 0.f;
 #pragma unroll
             for (int s = 0; s < NS; ++s) mma(kfrag(ka[s], 0), qf[s], s0);
-#pragma unroll
-            for (int i = 0; i < NP; ++i) vf[i] = vfrag(0, i);      // (any finite values: P is zero)
             stage(t0);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 if (s >= KR) kc[s - KR] = ka[s];
                 ka[s] += BUF * 4;
             }
+            // no block ahead: P and V of it are zero (V too, where zero times an infinity would not be)
             const u32x4 zero = {0u, 0u, 0u, 0u};
+            auto no_v = [&]() {
+#pragma unroll
+                for (int i = 0; i < NP; ++i) vf[i] = __builtin_bit_cast(bf16x8, zero);
+            };
             int moved = -1;                          // tile whose block 0 has set the reference: taken as it is (see below)
             while (t < t_full) {
                 move_up(s0);
                 moved = t;
                 p1[0] = p1[1] = zero;
+                no_v();
 #pragma unroll
                 for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s] - (at1 ? BUF * 4 : -(NBUF - 1) * BUF * 4), 1);
                 bool in_b = false;
@@ -757,15 +762,17 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 if (in_b) {                          // P V of block 0 has been added; block 1 by itself
                     move_up(s1);
                     p0[0] = p0[1] = zero;
+                    no_v();
 #pragma unroll
                     for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s], 0);
                     l_run += phase_b();
                     add_pv();
                     p1[0] = p1[1] = zero;
+                    no_v();
                     if (++t < t_full) next_tile(t);
                 }
             }
-            add_pv();                                // the last block's (P is zero if it has been added)
+            add_pv();                                // the last block's, unless it has been added
             t_done = t_full;
         }
         for (int tt = t_done; tt < t1; ++tt) tile_step(tt, (tt - t0) % NBUF);       // the prefix tail and the tree tiles
@@ -1675,6 +1682,14 @@ size_t ot_attn_workspace_bytes(const ot_attn_params* p) {
     // one workspace serves the 8-bit cache variant too, whose row blocks and key splits may differ
     const size_t kv8 = p->dtype == OT_BF16 ? plan_attention(*p, true).bytes : 0;
     return plain > kv8 ? plain : kv8;
+}
+
+int ot_internal_attn_plan(const ot_attn_params* p, int32_t kv8, int32_t* rows, int32_t* splits, int32_t* balance) {
+    const int st = validate_attn(p, kv8 != 0);
+    if (st != OT_OK) return st;
+    const AttnPlan pl = plan_attention(*p, kv8 != 0);
+    *rows = pl.rows; *splits = pl.splits; *balance = pl.balance;
+    return OT_OK;
 }
 
 static int attention_entry(const ot_attn_params* p, const void* Q, const void* K_prefix, const void* V_prefix,

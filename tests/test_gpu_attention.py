@@ -396,6 +396,36 @@ def test_256_row_loop_with_few_full_tiles_and_jumps_in_either_block(D, L):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+def test_an_infinite_value_makes_its_own_column_infinite(D):
+    """256 rows: one V element of a fully visible tile is infinite, in either block of a first or a later tile, with and
+    without scores that move the softmax reference up on the way.  Every key has weight, so the column is infinite and the
+    others are what they are without it."""
+    B, Hkv, n, Lmax = 33, 4, 150, 1000
+    assert U.attention_plan(B, Hkv, Hkv, D, n, Lmax)[0] == 256
+    x = wl.make_attention_inputs(_shape("bf16", B, Hkv, Hkv, D, Lmax, n), 5)
+    x["prefix_len"][:] = [[64, 128, 200, 447, 1000][b % 5] for b in range(B)]
+    at = [[3, 40, 63][b % 3] if b % 5 == 0 else [3, 40, 69, 110][b % 4] for b in range(B)]
+    kp = wl.bf16_bits_to_f32(x["K_prefix"]).copy()
+    for b in range(1, B, 2):
+        kp[b, :, 20:29] *= 6.0
+        kp[b, :, 64 * (b % 3) + 36:64 * (b % 3) + 45] *= 6.0
+    x["K_prefix"] = wl.store(kp, "bf16")
+    mask = _random_masks(B, n, 8)
+    some = list(range(0, B, 4)) + [1, 3, 7, 11]
+    want = _oracle_attention({k: v[some] for k, v in x.items()}, mask[some], "bf16")
+    vp = wl.bf16_bits_to_f32(x["V_prefix"]).copy()
+    for b in range(B):
+        vp[b, :, at[b], 7 * b % D] = np.inf if b % 2 else -np.inf
+    x["V_prefix"] = wl.store(vp, "bf16")
+    got = _gpu_attention(x, mask, "bf16")
+    for b in range(B):
+        assert (got[b, :, :, 7 * b % D] == (np.inf if b % 2 else -np.inf)).all(), (b, at[b])
+    for i, b in enumerate(some):
+        keep = np.arange(D) != 7 * b % D
+        assert np.abs(got[b] - want[i])[..., keep].max() < TOL["bf16"], b
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("n", [70, 150])               # 128 rows per workgroup; 256
 def test_scores_that_round_by_more_than_the_slack(D, n):
     """Scores of 1e9 in units of log2 e: a tile's own maximum minus itself rounds to anything up to 32 (64 from 2^30 on), so
