@@ -7,7 +7,7 @@
 // The keys of one (sequence, KV head) are cut into 64-key tiles: ceil(L_b/64) prefix tiles,
 // then ceil(n_keys/64) tree tiles.  Contiguous tile ranges ("splits") go to different workgroups so
 // that a single small sequence still fills the chip; every split leaves an un-normalised
-// partial (running max m, sum l, O); the last workgroup of a row block to finish merges them.
+// partial (softmax reference, sum l, O); the last workgroup of a row block to finish merges them.
 //
 // bf16 path (attn_mfma_kernel): one workgroup = 64, 128 or 256 packed query rows of one KV head (GQA: the
 // g = q_heads/kv_heads query heads that share the KV head are stacked, row = head*n + node), four
@@ -62,7 +62,7 @@ struct AttnKArgs {
     void* O;
     unsigned int* counters;   // one ticket counter per (sequence, KV head, row block), zero between launches
     float* part_o;      // per-split partial O   (layout: see the kernel that writes it)
-    float* part_ml;     // per-split (m, l)
+    float* part_ml;     // per-split (ref, l)
     int batch, kv_heads, g, n, nk, max_prefix, splits, W, row_blocks;   // n query rows, nk tree keys
     int splits_share_xcd;   // workgroup numbering of the bf16 kernel, see there
     unsigned int inv_splits, inv_kv_heads, inv_n;   // division by multiplication (fast_div): ceil(2^32 / d), unused for d = 1
@@ -288,10 +288,13 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     // V segment (2d + g1) of row 4h + tr_j (mod 4) -> position (2d) ^ vx
     const int kx = h ^ (l32 & (CPR - 1));
     const int vx = ((lane >> 4) & 1) ^ v_swizzle(4 * h + tr_j);
-    // scores are kept raw; p = 2^(c s - c m).  An 8-bit cache's K factor scales every score: it joins c.
+    // scores are kept raw; p = 2^(c s - ref), ref = the rounded product of c and the row's largest score so far.  What is already
+    // summed follows a change of ref by 2^(ref - ref'): with the rounded products on both sides, since their rounding errors
+    // (half a unit at 2^24) are in every p and have to cancel.  From |c s| = 2^31 on half a unit in the last place is more than
+    // an exponent holds: the row is then not finite.  An 8-bit cache's K factor scales every score: it joins c.
     const float c = KV8 ? a.scale_log2 * a.k_scale[bz] : a.scale_log2;
     const float v_factor = KV8 ? a.v_scale[bz] : 1.f;
-    float m_run = -INFINITY, l_run = 0.f;
+    float ref = -INFINITY, l_run = 0.f;
     f32x16 oacc[DB];
 #pragma unroll
     for (int d = 0; d < DB; ++d)
@@ -534,23 +537,22 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
 #pragma unroll
             for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, sacc[v]);
             tmax = xhalf_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);
+            const float ref_new = fmaxf(ref, tmax * c);
             bf16x8 pf[2];
-            if (m_new == -INFINITY) {
+            if (ref_new == -INFINITY) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) pf[v >> 3][v & 7] = (__bf16)0.f;
             } else {
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);      // m_run = -inf gives 0
-                const float mc = m_new * c;
+                const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);            // ref = -inf gives 0
                 float psum = 0.f;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(sacc[v], c, -mc));
+                    const float p = __builtin_amdgcn_exp2f(fmaf(sacc[v], c, -ref_new));
                     psum += p;
                     pf[v >> 3][v & 7] = (__bf16)p;
                 }
                 l_run = l_run * alpha + psum;
-                m_run = m_new;
+                ref = ref_new;
                 if (__any(alpha != 1.f)) {       // the running maximum rarely moves after the first tiles
 #pragma unroll
                     for (int d = 0; d < DB; ++d)
@@ -582,7 +584,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     if constexpr (VAR == 2) {
         // ---- fast loop of the 256-row variant over full prefix tiles: what the MFMA-bound shapes spend their time in.
         // The softmax reference of a row stays FIXED while no probability of a 32-key block comes out too large: p =
-        // 2^(c s - c ref) may exceed one, which fp32 sums and bf16 operands take in their stride, and O is never rescaled
+        // 2^(c s - ref) may exceed one, which fp32 sums and bf16 operands take in their stride, and O is never rescaled
         // inside the loop.  The loop is pipelined by 32-key blocks: in the phase of block j the matrix pipe forms S of
         // block j + 1 and adds P V of block j - 1 while the vector ALU takes the exponentials of block j, so that nothing
         // in a phase waits for anything of the same phase, and each matrix instruction has its share of the vector work
@@ -647,19 +649,17 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             bf16x8 kf[KR], vf[NP];
             u32x4 p0[2], p1[2];
             f32x16 s0, s1;
-            float mc = 0.f;
             int t = t0;
             // reference, O and l move up to what block `s` needs
             auto move_up = [&](const f32x16& s) {
-                const float m_new = fmaxf(m_run, row_max(s));
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);      // m_run = -inf gives 0
+                const float ref_new = fmaxf(ref, row_max(s) * c);
+                const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);            // ref = -inf gives 0
                 l_run *= alpha;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) oacc[d][v] *= alpha;
-                m_run = m_new;
-                mc = m_new * c;
+                ref = ref_new;
             };
             // a pair of probabilities, rounded to the MFMA's operand type, and their sum taken from the rounded pair (l then
             // matches what P V multiplies by)
@@ -669,7 +669,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 return __builtin_bit_cast(unsigned int, pr);
             };
             // One phase, block B of tile t: next = S of the block behind it, whose first KR operands are in kf; O += P V of the
-            // block ahead of it, whose V operands are in vf; pc = 2^(c cur - mc).  Returns this lane's sum of pc.
+            // block ahead of it, whose V operands are in vf; pc = 2^(c cur - ref).  Returns this lane's sum of pc.
             auto phase = [&](auto block_c, const f32x16& cur, f32x16& next, const u32x4 (&pp)[2], u32x4 (&pc)[2]) {
                 constexpr int B = decltype(block_c)::value;
                 __builtin_amdgcn_sched_barrier(0);
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 }
 #pragma unroll
                 for (int v = 0; v < 16; v += 2)
-                    pc[v >> 3][(v & 7) >> 1] = pair(__builtin_amdgcn_exp2f(fmaf(cur[v], c, -mc)), __builtin_amdgcn_exp2f(fmaf(cur[v + 1], c, -mc)), psum);
+                    pc[v >> 3][(v & 7) >> 1] = pair(__builtin_amdgcn_exp2f(fmaf(cur[v], c, -ref)), __builtin_amdgcn_exp2f(fmaf(cur[v + 1], c, -ref)), psum);
                 next = acc;
 #pragma unroll
                 for (int i = 0; i < NS; ++i) {                   // a matrix instruction, its share of the reads, its share of the rest
@@ -780,14 +780,14 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     if constexpr (WIDE) {
         // ---- fast loop of the 128-row variant over full prefix tiles: what the MFMA-bound shapes spend their time in.
         // The softmax reference of a row stays FIXED while scores do not exceed it by more than kSlack (in units
-        // of log2 e / scale): p = 2^(c s - c ref) may then exceed one, which fp32 sums and bf16 operands take in
+        // of log2 e / scale): p = 2^(c s - ref) may then exceed one, which fp32 sums and bf16 operands take in
         // their stride, and O is never rescaled inside the loop -- the accumulators stay in their registers, the
         // loop body has no data-dependent path, and the two 32-key blocks of a tile are skewed against each other
         // so that the matrix pipe and the vector ALU work at the same time inside one wavefront (S of block 1
         // while the exponentials of block 0 are taken, P V of block 0 while those of block 1 are).  A score beyond
         // the slack (every row's first tile, then rarely) leaves the loop before anything of the tile is added;
         // the reference moves up, O and l are rescaled out here, and the loop is entered again at the same tile, which is then
-        // taken as it is: nothing of it exceeds the new reference, but c s - c ref of huge scores (1e9) may round past the
+        // taken as it is: nothing of it exceeds the new reference, but c s - ref of huge scores (1e9) may round past the
         // slack, again and again.
         constexpr float kSlack = 12.f;
         constexpr float kSumLimit = 16.f * 4096.f;          // sixteen terms of at most 2^kSlack
@@ -822,6 +822,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         int t = t0;
         bool staged = false;                                      // tile t has been awaited and published
         float seen = -INFINITY;                                   // largest score of the tile that left the loop
+        float m_run = -INFINITY;                                  // largest score that the reference was moved up for
         int moved = -1;                                           // tile that the reference was last moved up for
         while (t < t_full) {
             if (!staged) {
@@ -838,17 +839,17 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                     sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kfrag(s_k, 0, s)), qf[s], sa, 0, 0, 0);
                     sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kfrag(s_k, 1, s)), qf[s], sb, 0, 0, 0);
                 }
-                const float m_new = fmaxf(m_run, fmaxf(row_max(sa), row_max(sb)));
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);      // m_run = -inf gives 0
+                m_run = fmaxf(m_run, fmaxf(row_max(sa), row_max(sb)));
+                const float ref_new = fmaxf(ref, m_run * c);                          // (the maximum keeps the product rounded)
+                const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);            // ref = -inf gives 0
                 l_run *= alpha;
 #pragma unroll
                 for (int d = 0; d < DB; ++d)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) oacc[d][v] *= alpha;
-                m_run = m_new;
+                ref = ref_new;
             }
             moved = t;
-            const float mc = m_run * c;
             const float limit = m_run + kSlack / c;
             for (;;) {
                 if (!staged) stage_tile(t);
@@ -886,8 +887,8 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int v = 0; v < 16; v += 2) {
                     // a pair of probabilities, rounded to the MFMA's operand type, and their sum taken from the
                     // rounded pair with one dot-product instruction (l then matches what P V multiplies by)
-                    const bf16x2 pr = {(__bf16)__builtin_amdgcn_exp2f(fmaf(s0[v], c, -mc)),
-                                       (__bf16)__builtin_amdgcn_exp2f(fmaf(s0[v + 1], c, -mc))};
+                    const bf16x2 pr = {(__bf16)__builtin_amdgcn_exp2f(fmaf(s0[v], c, -ref)),
+                                       (__bf16)__builtin_amdgcn_exp2f(fmaf(s0[v + 1], c, -ref))};
                     psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, psum, false);
                     p0[v >> 3][v & 7] = pr[0];
                     p0[v >> 3][(v & 7) + 1] = pr[1];
@@ -925,8 +926,8 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int v = 0; v < 16; v += 2) {
                     // a pair of probabilities, rounded to the MFMA's operand type, and their sum taken from the
                     // rounded pair with one dot-product instruction (l then matches what P V multiplies by)
-                    const bf16x2 pr = {(__bf16)__builtin_amdgcn_exp2f(fmaf(s1[v], c, -mc)),
-                                       (__bf16)__builtin_amdgcn_exp2f(fmaf(s1[v + 1], c, -mc))};
+                    const bf16x2 pr = {(__bf16)__builtin_amdgcn_exp2f(fmaf(s1[v], c, -ref)),
+                                       (__bf16)__builtin_amdgcn_exp2f(fmaf(s1[v + 1], c, -ref))};
                     psum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones2, psum, false);
                     p1[v >> 3][v & 7] = pr[0];
                     p1[v >> 3][(v & 7) + 1] = pr[1];
@@ -981,20 +982,20 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int v4 = 0; v4 < 4; ++v4)
                     *(f32x4*)(mine + d * 16 + 4 * v4) =
                         f32x4{oacc[d][4 * v4], oacc[d][4 * v4 + 1], oacc[d][4 * v4 + 2], oacc[d][4 * v4 + 3]};
-            *(f32x4*)(mine + DB * 16) = f32x4{m_run, l_run, 0.f, 0.f};
+            *(f32x4*)(mine + DB * 16) = f32x4{ref, l_run, 0.f, 0.f};
         }
         __syncthreads();
         if (kh == 0) {
             const f32x4 ml2 = *(const f32x4*)(mine + DB * 16);
-            const float m2 = ml2.x, l2 = ml2.y;
-            const float mm = fmaxf(m_run, m2);
+            const float ref2 = ml2.x, l2 = ml2.y;
+            const float top = fmaxf(ref, ref2);
             float a1 = 0.f, a2 = 0.f;
-            if (mm != -INFINITY) {
-                a1 = __builtin_amdgcn_exp2f((m_run - mm) * c);
-                a2 = __builtin_amdgcn_exp2f((m2 - mm) * c);
+            if (top != -INFINITY) {
+                a1 = __builtin_amdgcn_exp2f(ref - top);
+                a2 = __builtin_amdgcn_exp2f(ref2 - top);
             }
             l_run = l_run * a1 + l2 * a2;
-            m_run = mm;
+            ref = top;
 #pragma unroll
             for (int d = 0; d < DB; ++d)
 #pragma unroll
@@ -1007,7 +1008,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 }
         }
     }
-    const bool holder = WIDE || kh == 0;         // this wavefront holds finished (O, m, l) of its 32 rows
+    const bool holder = WIDE || kh == 0;         // this wavefront holds finished (O, ref, l) of its 32 rows
 
     if (a_splits == 1) {
         if (holder && row_ok) {
@@ -1042,7 +1043,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     //         -- or (d block, pair of floats) when the exchange is fp32 -- and the live lanes of the two half-waves
     //         packed at the front of each 64-slot line (slot h live + l32): every store and load instruction touches
     //         one contiguous run, and nothing is moved for rows that do not exist
-    // part_ml [group][split][query block][row] (m c, l) as two floats
+    // part_ml [group][split][query block][row] (ref, l) as two floats
     typedef unsigned long long u64;
     // EPS 64-bit elements per (lane, d block): pairs of floats, or with bf16 partials groups of four values
     constexpr int EPS = OT_ATTN_PART_BF16 ? 4 : 8;
@@ -1067,8 +1068,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             }
         if (h == 0)                                                  // lanes l and l + 32 hold the same row
             __hip_atomic_store((u64*)a.part_ml + (((size_t)group * a_splits + split) * NQB + qb) * 32 + l32,
-                               pack2(m_run == -INFINITY ? -INFINITY : m_run * c /* log2 units */, l_run),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                               pack2(ref, l_run), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -1259,7 +1259,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
 
     const float c = a.scale_log2;
-    float m_run = -INFINITY, l_run = 0.f;
+    float ref = -INFINITY, l_run = 0.f;                              // ref: see the bf16 kernel
     f32x16 o[EV];
 #pragma unroll
     for (int e = 0; e < EV; ++e)
@@ -1293,20 +1293,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         float tmax = sc[0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, sc[v]);
-        const float m_new = fmaxf(m_run, xhalf_max(tmax));
-        if (m_new == -INFINITY) {
+        const float ref_new = fmaxf(ref, xhalf_max(tmax) * c);
+        if (ref_new == -INFINITY) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) sc[v] = 0.f;
         } else {
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c), mc = m_new * c;      // m_run = -inf gives 0
+            const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);       // ref = -inf gives 0
             float sum = 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -mc));
+                sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], c, -ref_new));
                 sum += sc[v];
             }
             l_run = l_run * alpha + sum;
-            m_run = m_new;
+            ref = ref_new;
             if (__any(alpha != 1.f)) {
 #pragma unroll
                 for (int e = 0; e < EV; ++e)
@@ -1339,19 +1339,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                     for (int v4 = 0; v4 < 4; ++v4)
                         slot[(e * 4 + v4) * 64] = f32x4{o[e][4 * v4], o[e][4 * v4 + 1], o[e][4 * v4 + 2], o[e][4 * v4 + 3]};
-                slot[EV * 4 * 64] = f32x4{m_run, l_run, 0.f, 0.f};
+                slot[EV * 4 * 64] = f32x4{ref, l_run, 0.f, 0.f};
             }
             __syncthreads();
             if (ks < half && ks + half < slices) {
                 const f32x4 ml = slot[EV * 4 * 64];
-                const float mm = fmaxf(m_run, ml.x);
+                const float top = fmaxf(ref, ml.x);
                 float a1 = 0.f, a2 = 0.f;
-                if (mm != -INFINITY) {
-                    a1 = __builtin_amdgcn_exp2f((m_run - mm) * c);
-                    a2 = __builtin_amdgcn_exp2f((ml.x - mm) * c);
+                if (top != -INFINITY) {
+                    a1 = __builtin_amdgcn_exp2f(ref - top);
+                    a2 = __builtin_amdgcn_exp2f(ml.x - top);
                 }
                 l_run = l_run * a1 + ml.y * a2;
-                m_run = mm;
+                ref = top;
 #pragma unroll
                 for (int e = 0; e < EV; ++e)
 #pragma unroll
@@ -1380,7 +1380,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
         return;
     }
-    // part_o [group][split][ROWS][D], part_ml [group][split][ROWS] (m c, l): written through and read around the caches, in
+    // part_o [group][split][ROWS][D], part_ml [group][split][ROWS] (ref, l): written through and read around the caches, in
     // the order stores - barrier - ticket (see the bf16 kernel)
     auto pack2 = [](float x, float y) -> u64 { return (u64)__float_as_uint(x) | ((u64)__float_as_uint(y) << 32); };
     const int group = bz * a.row_blocks + rb;
@@ -1394,8 +1394,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 __hip_atomic_store(po + (EV * (8 * (v >> 2) + 4 * h + (v & 3)) + e) / 2, pack2(o[e][v], o[e + 1][v]), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         if (h == 0)
-            __hip_atomic_store((u64*)a.part_ml + pr, pack2(m_run == -INFINITY ? -INFINITY : m_run * c, l_run), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store((u64*)a.part_ml + pr, pack2(ref, l_run), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();

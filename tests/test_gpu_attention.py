@@ -442,6 +442,38 @@ def test_scores_that_round_by_more_than_the_slack(D, n):
     assert np.abs(got[some] - want).max() < TOL["bf16"]
 
 
+def large_exact_scores(B, Hkv, D, L, n, seed, first=2.0 ** 13):
+    """Scores 2^26 + x, x a multiple of 8 that grows along the keys: exact in fp32, while c times a score is rounded to a
+    multiple of 1/2 or 1 (in units of log2 e).  Keys differ in weight by 2^(c x): q = (2^13, 1, 0, ...), k = (2^13, x, 0, ...)."""
+    rng = np.random.default_rng(seed)
+    x = wl.make_attention_inputs(_shape("bf16", B, Hkv, Hkv, D, L, n), seed)
+    for name, rows, base in (("K_prefix", L, 0), ("K_tree", n, 8 * (L // 100) + 8)):
+        k = np.zeros((B, Hkv, rows, D), dtype=np.float32)
+        k[..., 0] = first
+        k[..., 1] = base + 8 * (np.arange(rows) // 100) + 8 * rng.integers(-3, 3, size=(B, Hkv, rows))
+        x[name] = k
+    x["Q"] = np.zeros((B, Hkv, n, D), dtype=np.float32)
+    x["Q"][..., 0], x["Q"][..., 1] = 2.0 ** 26 / first, 1.0
+    return x
+
+
+@pytest.mark.parametrize("dtype,B,Hkv,D,L,n,rows", [
+    ("bf16", 1, 2, 64, 700, 40, 64), ("bf16", 33, 8, 128, 700, 40, 64),      # 64 rows: key ranges; halves of a tile only
+    ("bf16", 33, 4, 128, 500, 70, 128), ("bf16", 33, 4, 64, 1000, 150, 256), ("bf16", 33, 4, 128, 1000, 150, 256),
+    ("f32", 1, 2, 64, 1000, 40, 64), ("f32", 2, 2, 128, 60, 33, 32),         # fp32: ranges; slices that meet in LDS
+])
+def test_weights_are_kept_when_the_reference_of_large_scores_moves(dtype, B, Hkv, D, L, n, rows):
+    assert U.attention_plan(B, Hkv, Hkv, D, n, L, dtype)[0] == rows
+    x = large_exact_scores(B, Hkv, D, L, n, 4)
+    x["V_prefix"], x["V_tree"] = [wl.bf16_bits_to_f32(x[k]) for k in ("V_prefix", "V_tree")]
+    x = {k: v if k == "prefix_len" else wl.store(v, dtype) for k, v in x.items()}
+    mask = _random_masks(B, n, 2)
+    got = _gpu_attention(x, mask, dtype)
+    some = sorted({0, B // 2, B - 1})
+    # bf16: as elsewhere.  fp32: a weight is off by the rounding of c, 2^-24 of exponents up to 40, and by its own rounding
+    assert np.abs(got[some] - _oracle_attention({k: v[some] for k, v in x.items()}, mask[some], dtype)).max() < TOL[dtype]
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
     *[(1, 2, 2, D, 64 * t, 100) for D in (64, 128) for t in (3, 4, 5, 6, 8, 10, 12, 14, 30)],     # 128 rows: no, two, ... eight splits
     (1, 2, 2, 128, 64 * 3 + 1, 40), (1, 2, 2, 128, 64 * 5, 40), (1, 2, 2, 128, 64 * 6, 40),       # 64 rows: as many splits as tiles,

@@ -8,6 +8,7 @@ from oracle import opt_tree as ot_oracle
 from oracle import tree_attention as ta_oracle
 import workloads as wl
 from tests import _util as U
+from tests.test_gpu_attention import large_exact_scores
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
@@ -103,6 +104,22 @@ def test_scores_that_round_by_more_than_the_slack():
     some = [0, 13, 32]
     want = _oracle({k: v[some] for k, v in x.items()}, mask[some])
     assert np.abs(got[some] - want).max() < TOL
+
+
+@pytest.mark.parametrize("n,rows", [(40, 64), (70, 128), (150, 256)])
+def test_weights_are_kept_when_the_reference_of_large_scores_moves(n, rows):
+    """As in the 16-bit cache's test of this name: scores 2^26 + x, exact in fp32, from K bytes 2^8 and x."""
+    B, Hkv, D, L = 33, 4, 128, 1000
+    assert U.attention_plan(B, Hkv, Hkv, D, n, L, kv8=True)[0] == rows
+    x = large_exact_scores(B, Hkv, D, L, n, 4, first=2.0 ** 8)
+    kp, kt = wl.f32_to_e4m3_bits(x["K_prefix"]), wl.f32_to_e4m3_bits(x["K_tree"])       # multiples of 8 up to 128: exact
+    vp, vt, vs = wl.quantise_cache_e4m3(x["V_prefix"], x["V_tree"], "bf16")
+    x = dict(Q=wl.store(x["Q"], "bf16"), K_prefix=kp, V_prefix=vp, K_tree=kt, V_tree=vt, k_scale=np.ones_like(vs), v_scale=vs,
+             prefix_len=x["prefix_len"])
+    mask = _masks(B, n, 2)
+    got = _gpu(x, mask)
+    some = [0, 16, 32]
+    assert np.abs(got[some] - _oracle({k: v[some] for k, v in x.items()}, mask[some])).max() < TOL
 
 
 def test_every_byte_code_and_uneven_scales():
