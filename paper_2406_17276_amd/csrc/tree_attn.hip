@@ -294,6 +294,9 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
     // an exponent holds: the row is then not finite.  An 8-bit cache's K factor scales every score: it joins c.
     const float c = KV8 ? a.scale_log2 * a.k_scale[bz] : a.scale_log2;
     const float v_factor = KV8 ? a.v_scale[bz] : 1.f;
+    // The fast loops have no branch for a row without a score above -inf so far: its reference there is the lowest finite number,
+    // from which -inf gives p = 0 and any finite score an infinite p, which leaves the loop.
+    constexpr float kNoRef = -3.402823466e38f;
     float ref = -INFINITY, l_run = 0.f;
     f32x16 oacc[DB];
 #pragma unroll
@@ -652,7 +655,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             int t = t0;
             // reference, O and l move up to what block `s` needs
             auto move_up = [&](const f32x16& s) {
-                const float ref_new = fmaxf(ref, row_max(s) * c);
+                const float ref_new = fmaxf(fmaxf(ref, row_max(s) * c), kNoRef);
                 const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);            // ref = -inf gives 0
                 l_run *= alpha;
 #pragma unroll
@@ -840,7 +843,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                     sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kfrag(s_k, 1, s)), qf[s], sb, 0, 0, 0);
                 }
                 m_run = fmaxf(m_run, fmaxf(row_max(sa), row_max(sb)));
-                const float ref_new = fmaxf(ref, m_run * c);                          // (the maximum keeps the product rounded)
+                const float ref_new = fmaxf(fmaxf(ref, m_run * c), kNoRef);           // (the maximum keeps the product rounded)
                 const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);            // ref = -inf gives 0
                 l_run *= alpha;
 #pragma unroll

@@ -442,6 +442,27 @@ def test_scores_that_round_by_more_than_the_slack(D, n):
     assert np.abs(got[some] - want).max() < TOL["bf16"]
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n,rows", [(70, 128), (150, 256)])
+def test_first_keys_that_score_minus_infinity_have_no_weight(D, n, rows):
+    """The keys up to somewhere inside or beyond the first 32-key block or tile score -inf against every row (as do a few
+    later ones): weight zero, and the row goes on from the first finite score."""
+    B, Hkv, Lmax = 33, 4, 1000
+    assert U.attention_plan(B, Hkv, Hkv, D, n, Lmax)[0] == rows
+    x = wl.make_attention_inputs(_shape("bf16", B, Hkv, Hkv, D, Lmax, n), 5)
+    x["prefix_len"][:] = [[64, 128, 200, 447, 1000][b % 5] for b in range(B)]
+    q, kp = wl.bf16_bits_to_f32(x["Q"]).copy(), wl.bf16_bits_to_f32(x["K_prefix"]).copy()
+    q[..., 0] = np.abs(q[..., 0]) + 0.01
+    for b in range(B):
+        kp[b, :, :[1, 31, 32, 33, 63, 64, 96, 128, 190][b % 9], 0] = -np.inf
+        kp[b, :, 300:340, 0] = -np.inf
+    x["Q"], x["K_prefix"] = wl.store(q, "bf16"), wl.store(kp, "bf16")
+    mask = _random_masks(B, n, 8)
+    got = _gpu_attention(x, mask, "bf16")
+    some = sorted(set(range(0, B, 3)) | set(range(9)))
+    assert np.abs(got[some] - _oracle_attention({k: v[some] for k, v in x.items()}, mask[some], "bf16")).max() < TOL["bf16"]
+
+
 def large_exact_scores(B, Hkv, D, L, n, seed, first=2.0 ** 13):
     """Scores 2^26 + x, x a multiple of 8 that grows along the keys: exact in fp32, while c times a score is rounded to a
     multiple of 1/2 or 1 (in units of log2 e).  Keys differ in weight by 2^(c x): q = (2^13, 1, 0, ...), k = (2^13, x, 0, ...)."""
