@@ -752,6 +752,9 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s] - (at1 ? BUF * 4 : -(NBUF - 1) * BUF * 4), 1);
                 bool in_b = false;
                 for (;;) {
+                    // 64 wide, a phase is short enough for instruction fetch to show: the loop begins a cache line (6 x 8 KV heads of
+                    // 1024 rows, 24722 keys 440 us at 12 bytes into one, 423 so; at head_dim 128 it is no faster, 1102 and 1110)
+                    if constexpr (D == 64) asm volatile(".p2align 6");
                     float psum = phase_a();
                     asm volatile("" : "+s"(moved));     // (keeps the first tile of an entry from becoming a second loop body)
                     if (t != moved && __any(psum > kSumLimit)) break;
