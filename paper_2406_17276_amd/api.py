@@ -114,6 +114,8 @@ def lib():
         L.ot_yardstick_mfma_loop.argtypes = [C.c_int32, C.c_void_p, C.c_void_p]
         L.ot_attn_workspace_bytes.restype = C.c_size_t
         L.ot_attn_workspace_bytes.argtypes = [C.POINTER(AttnParams)]
+        L.ot_attn_workspace_bytes_full.restype = C.c_size_t
+        L.ot_attn_workspace_bytes_full.argtypes = [C.POINTER(AttnParams)]
         L.ot_attn_workspace_prepare.restype = C.c_int
         L.ot_attn_workspace_prepare.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p]
         L.ot_tree_verify_attention.restype = C.c_int
@@ -294,11 +296,12 @@ def attn_workspace_bytes(p: AttnParams) -> int:
 
 def attn_workspace(p: AttnParams, device):
     """A workspace for ot_tree_verify_attention, already prepared (ot_attn_workspace_prepare on the
-    current stream): its ticket counters are zero, and every completed call leaves them zero."""
+    current stream): its ticket counters are zero, and every completed call leaves them zero.  It holds as many key
+    ranges as are fastest (ot_attn_workspace_bytes_full)."""
     import torch
-    need = attn_workspace_bytes(p)
+    need = int(lib().ot_attn_workspace_bytes_full(C.byref(p)))
     if need == 0:
-        raise OptTreeError(-2, "ot_attn_workspace_bytes")
+        raise OptTreeError(-2, "ot_attn_workspace_bytes_full")
     ws = torch.empty(need, dtype=torch.uint8, device=device)
     _check(lib().ot_attn_workspace_prepare(ws.data_ptr(), ws.numel(), _stream()), "ot_attn_workspace_prepare")
     torch.cuda.current_stream().synchronize()      # the workspace may be used on any stream afterwards

@@ -112,7 +112,7 @@ struct AttnPlan {
     int balance;         // bf16 batches: workgroups take their jobs longest first, decided on the device
     size_t part_o_bytes, part_ml_bytes, bytes;
 };
-AttnPlan plan_attention(const ot_attn_params& p, bool kv8 = false);
+AttnPlan plan_attention(const ot_attn_params& p, bool kv8, size_t room);   // room: bytes of the workspace
 int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const void* Q, const void* Kp, const void* Vp,
                           const void* Kt, const void* Vt, const int32_t* prefix_len, const uint64_t* mask, void* O,
                           void* workspace, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,

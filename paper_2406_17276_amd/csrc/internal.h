@@ -13,8 +13,8 @@ OT_API int ot_internal_tree_begin(const ot_build_params* p, void* workspace, siz
                                   int32_t* frontier_parent_slot, int32_t* frontier_count, void* hip_stream);
 
 /* How an attention call is cut up (host only): packed query rows per workgroup, key ranges per row block, whether the
- * sequences of the batch are taken longest first.  kv8: for the 8-bit cache. */
-OT_API int ot_internal_attn_plan(const ot_attn_params* p, int32_t kv8, int32_t* rows, int32_t* splits, int32_t* balance);
+ * sequences of the batch are taken longest first.  kv8: for the 8-bit cache; room: bytes of the workspace. */
+OT_API int ot_internal_attn_plan(const ot_attn_params* p, int32_t kv8, size_t room, int32_t* rows, int32_t* splits, int32_t* balance);
 
 #ifdef __cplusplus
 }

@@ -1478,7 +1478,14 @@ static int attn_rows_per_workgroup(const ot_attn_params& p, bool kv8, int tiles)
     return blocks >= 64 && blocks * tiles >= 2048 ? 256 : 128;
 }
 
-// Key splits of the bf16 kernel.  More splits shorten the streaming, but the workgroup that finishes last merges them all, 1.6 us
+// `splits` ranges that take the same number of tiles (the last one possibly fewer)
+static int even_out(int tiles, long long splits) {
+    const int s = (int)std::max(1LL, std::min<long long>({splits, tiles, kMaxSplits})), per = (tiles + s - 1) / s;
+    return (tiles + per - 1) / per;
+}
+
+// Key splits of the bf16 kernel: at least `least`, which is what a workspace has to hold, and `best` where it holds that.
+// More splits shorten the streaming, but the workgroup that finishes last merges them all, 1.6 us
 // for every trip to memory: as many as fill the 256 compute units once, and eight (the narrow variant: what one trip takes,
 // at head_dim 128, six, two and more trips over long prefixes).  us by splits, one sequence unless noted:
 //   64 rows x 8 heads, 128: 1016 keys 3: 14.5, 6: 11.3, 9: 12.6; 4008 keys 6: 19.5, 11: 16.5, 32: 21.1; 8016 keys 8: 26.7, 16: 21.0
@@ -1489,15 +1496,39 @@ static int attn_rows_per_workgroup(const ot_attn_params& p, bool kv8, int tiles)
 // Where one workgroup per unit leaves no split, the variants of which two fit a unit are split over those; two also hide each
 // other's widening of 8-bit tiles (1264 rows x 4 heads x 2, 2158 keys of 128 3: 33.5, 6: 30.1; 120 rows x 16 x 4, 4120 of 64
 // 4: 26.9, 8: 23.6).
-static int attn_splits(long long base, int tiles, int rows_wg, int head_dim, bool kv8) {
+struct AttnSplits { int least, best; };
+static AttnSplits attn_splits(long long base, int tiles, int rows_wg, int row_blocks, int head_dim, bool kv8) {
     const bool wide = rows_wg > 64, two = rows_wg == 128 || (!wide && head_dim == 64);
-    if (tiles <= (wide || head_dim == 64 ? 5 : 1)) return 1;
+    if (tiles <= (wide || head_dim == 64 ? 5 : 1)) return {1, 1};
     long long s = 256 / base;
     if (s < 2) s = two && tiles >= 24 ? 512 / base : 1;
     else if (kv8 && two && s >= 3 && s <= 5) s = 512 / base;
     const int most = wide ? 8 : merge_chunk(head_dim, false) * (head_dim == 128 ? 1 + tiles / 48 : 1);
     s = std::min<long long>(s, most);
-    return (int)std::max(1LL, std::min<long long>(s, wide ? tiles / 2 : tiles));
+    const int least = even_out(tiles, std::min<long long>(s, wide ? tiles / 2 : tiles));
+    if (least == 1 || !two || tiles < (kv8 ? 16 : 24)) return {least, least};
+    // Longer prefixes, variants of which two workgroups fit a unit: what more ranges save grows with the prefix, what their merge
+    // costs does not.  Both in units of the time that a tile takes a workgroup with a unit to itself (1.2 us at head_dim 128,
+    // 0.8 at 64; 8-bit 1.6 and 1.0): with two workgroups to a unit a tile takes each `shared`, least where one widens while the
+    // other computes, all of twice as long where each key is read once and memory is what bounds; the merge adds `merge` a range
+    // (narrow: a trip of twelve), the rest of a launch some 8.  us, `least` / more ranges, one sequence unless noted:
+    //   200 rows x 8 heads, 128: 16384 keys 8: 50.7, 16: 38.6; 32768 keys 8: 86.9, 16: 57.6, 32: 59.7; 131072 keys 307, 180, 158;
+    //   8-bit 32768 keys 114, 70, 67; 64 wide 32768 keys 60.7, 39.7, 36.6; x 2 heads 32768 keys 84, 53, 44
+    //   480 rows x 8 heads, 128: 8192 keys 8: 32.9, 16: 35.0; 32768 keys 90, 83; x 24 heads 8192 keys 2: 85.5, 5: 65.6
+    //   120 rows x 100 heads, 128: 2048 keys 2: 33.3, 5: 36.2; 8192 keys 100, 90; 8-bit 1000 keys 26.7, 24.6; 8192 keys 112, 81
+    //   64 rows x 8 heads, 64: 8192 keys 12: 15.1, 24: 15.2; 16384 keys 22.2, 18.7; 131072 keys 120, 24: 69, 32: 59
+    const float shared = kv8 ? (wide ? 1.4f : 1.3f) : !wide ? 1.85f : head_dim == 64 ? 1.5f : row_blocks > 1 ? 1.6f : 2.f;
+    auto time = [&](int x) {
+        const bool one = base * x <= 256;
+        const float merge = wide ? (head_dim == 128 ? (one ? 0.42f : 0.7f) : (one ? 0.3f : 0.54f)) * (kv8 ? 0.8f : 1.f) * x
+                                 : (one ? 5.f : 7.f) * ((x + 11) / 12);
+        return (one ? 1.f : shared) * ((tiles + x - 1) / x) + merge + 8.f;
+    };
+    int best = least;
+    float best_time = (tiles < 80 ? 0.88f : 0.94f) * time(least);        // (what the estimate is good for)
+    for (int x = least + 1; x <= kMaxSplits && x <= tiles && base * x <= 512; ++x)
+        if (even_out(tiles, x) == x && time(x) < best_time) { best = x; best_time = time(x); }
+    return {least, best};
 }
 
 // Packed query rows per workgroup of the f32 kernel (its eight wavefronts = rows / 32 row blocks x key slices): as many as
@@ -1509,18 +1540,20 @@ static int f32_rows_per_workgroup(const ot_attn_params& p) {
     return p.head_dim == 64 ? 64 : 32;
 }
 
-AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
+AttnPlan plan_attention(const ot_attn_params& p, bool kv8, size_t room) {
     AttnPlan pl;
     pl.balance = 0;
     const int g = p.q_heads / p.kv_heads, nk = p.n_keys > 0 ? p.n_keys : p.n;
-    int base, tile, rows_wg = 0, splits;
+    int base, tile, rows_wg = 0, splits, least;
     if (p.dtype == OT_BF16) {
         tile = 64;
         const int tiles = (p.max_prefix + 63) / 64 + (nk + 63) / 64;
         rows_wg = attn_rows_per_workgroup(p, kv8, tiles);
         pl.row_blocks = (g * p.n + rows_wg - 1) / rows_wg;
         base = p.batch * p.kv_heads * pl.row_blocks;
-        splits = attn_splits(base, tiles, rows_wg, p.head_dim, kv8);
+        const AttnSplits sp = attn_splits(base, tiles, rows_wg, pl.row_blocks, p.head_dim, kv8);
+        splits = sp.best;
+        least = sp.least;
         // A batch that fills the chip with one key range per (sequence, KV head): the lengths are known on the
         // device only, where the workgroups take their jobs longest first (see the kernel).  Measured: 3 % faster on
         // ragged batches of one and a half to three rounds of workgroups; from four rounds on the rounds even the
@@ -1542,17 +1575,18 @@ AttnPlan plan_attention(const ot_attn_params& p, bool kv8) {
         splits = blocks <= 8 ? 1 : std::min(256 / base, (blocks + 3) / 4);
     }
     const int max_tiles = (p.max_prefix + tile - 1) / tile + (nk + tile - 1) / tile;
-    if (splits > max_tiles) splits = max_tiles;
-    if (splits > kMaxSplits) splits = kMaxSplits;
-    if (splits < 1) splits = 1;
-    // even out: every split gets the same number of tiles (the last one possibly fewer)
-    const int per = (max_tiles + splits - 1) / splits;
-    splits = (max_tiles + per - 1) / per;
-    pl.rows = rows_wg;
-    pl.splits = splits;
+    splits = even_out(max_tiles, splits);
+    if (p.dtype != OT_BF16) least = splits;
     // partials are stored per workgroup (rows padded to the row block)
     const size_t rows = (size_t)base * rows_wg;
     const size_t part_elem = (p.dtype == OT_BF16 && OT_ATTN_PART_BF16) ? 2 : 4;
+    const size_t fixed = OT_ATTN_SYNC_BYTES + 256, range = rows * (p.head_dim * part_elem + 2 * 4);   // (a multiple of 256)
+    if (splits > least && fixed + splits * range > room) {
+        const size_t held = room > fixed ? (room - fixed) / range : 0;      // fewer than `splits`
+        splits = std::max(least, even_out(max_tiles, (long long)held));
+    }
+    pl.rows = rows_wg;
+    pl.splits = splits;
     pl.part_o_bytes = splits > 1 ? align_up(rows * splits * p.head_dim * part_elem, 256) : 0;
     pl.part_ml_bytes = splits > 1 ? align_up(rows * splits * 2 * 4, 256) : 0;
     pl.bytes = OT_ATTN_SYNC_BYTES + pl.part_o_bytes + pl.part_ml_bytes + 256;
@@ -1679,20 +1713,26 @@ static int validate_attn(const ot_attn_params* p, bool kv8 = false) {
     return OT_OK;
 }
 
+// one workspace serves both caches, whose row blocks and key splits may differ
+static size_t attn_bytes(const ot_attn_params& p, size_t room) {
+    return std::max(plan_attention(p, false, room).bytes, p.dtype == OT_BF16 ? plan_attention(p, true, room).bytes : 0);
+}
+
 extern "C" {
 
 size_t ot_attn_workspace_bytes(const ot_attn_params* p) {
     if (validate_attn(p) != OT_OK) return 0;
-    const size_t plain = plan_attention(*p).bytes;
-    // one workspace serves the 8-bit cache variant too, whose row blocks and key splits may differ
-    const size_t kv8 = p->dtype == OT_BF16 ? plan_attention(*p, true).bytes : 0;
-    return plain > kv8 ? plain : kv8;
+    // the library's own array goes on serving what it can hold with the fewest ranges
+    const size_t full = attn_bytes(*p, SIZE_MAX);
+    return full > OT_ATTN_SCRATCH_BYTES && attn_bytes(*p, 0) <= OT_ATTN_SCRATCH_BYTES ? attn_bytes(*p, OT_ATTN_SCRATCH_BYTES) : full;
 }
 
-int ot_internal_attn_plan(const ot_attn_params* p, int32_t kv8, int32_t* rows, int32_t* splits, int32_t* balance) {
+size_t ot_attn_workspace_bytes_full(const ot_attn_params* p) { return validate_attn(p) != OT_OK ? 0 : attn_bytes(*p, SIZE_MAX); }
+
+int ot_internal_attn_plan(const ot_attn_params* p, int32_t kv8, size_t room, int32_t* rows, int32_t* splits, int32_t* balance) {
     const int st = validate_attn(p, kv8 != 0);
     if (st != OT_OK) return st;
-    const AttnPlan pl = plan_attention(*p, kv8 != 0);
+    const AttnPlan pl = plan_attention(*p, kv8 != 0, room);
     *rows = pl.rows; *splits = pl.splits; *balance = pl.balance;
     return OT_OK;
 }
@@ -1710,7 +1750,7 @@ static int attention_entry(const ot_attn_params* p, const void* Q, const void* K
     for (int i = 0; i < 7; ++i)
         if (ptrs[i] && ((uintptr_t)ptrs[i] % 16)) return OT_ERR_INVALID_ARG;
     if (((uintptr_t)prefix_len % 4) || ((uintptr_t)mask % 8)) return OT_ERR_INVALID_ARG;
-    const AttnPlan plan = plan_attention(*p, kv8);
+    const AttnPlan plan = plan_attention(*p, kv8, workspace_bytes);
     if (workspace_bytes < plan.bytes) return OT_ERR_WORKSPACE_TOO_SMALL;
     return launch_tree_attention(*p, plan, Q, K_prefix, V_prefix, K_tree, V_tree, prefix_len, mask, O, workspace,
                                  (hipStream_t)hip_stream, (hipEvent_t)ev0, (hipEvent_t)ev1, kv8 ? k_scale : nullptr,

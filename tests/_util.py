@@ -96,14 +96,22 @@ def assert_tree_invariants(got, n, depth):
         np.testing.assert_allclose(ex[b], np.exp(sc[b, :m]).sum(), rtol=5e-6)      # score is stored as float32
 
 
-def attention_plan(B, Hq, Hkv, D, n, max_prefix, dtype="bf16", n_keys=0, kv8=False):
-    """How the library cuts this attention up: (query rows per workgroup, key ranges, sequences taken longest first)."""
+def attention_params(B, Hq, Hkv, D, n, max_prefix, dtype="bf16", n_keys=0):
+    """The library's parameters for contiguous tensors of these sizes."""
     import ctypes as C
     from paper_2406_17276_amd import api
     s = lambda h, r: (C.c_int64 * 3)(h * r * D, r * D, D)
     nk = n_keys or n
-    p = api.AttnParams(B, Hq, Hkv, D, n, max_prefix, api.OT_BF16 if dtype == "bf16" else api.OT_F32, 0.0, s(Hq, n),
-                       s(Hkv, max_prefix), s(Hkv, max_prefix), s(Hkv, nk), s(Hkv, nk), s(Hq, n), n_keys)
+    return api.AttnParams(B, Hq, Hkv, D, n, max_prefix, api.OT_BF16 if dtype == "bf16" else api.OT_F32, 0.0, s(Hq, n),
+                          s(Hkv, max_prefix), s(Hkv, max_prefix), s(Hkv, nk), s(Hkv, nk), s(Hq, n), n_keys)
+
+
+def attention_plan(B, Hq, Hkv, D, n, max_prefix, dtype="bf16", n_keys=0, kv8=False, room=1 << 40):
+    """How the library cuts this attention up, given a workspace of `room` bytes: (query rows per workgroup, key ranges,
+    sequences taken longest first)."""
+    import ctypes as C
+    from paper_2406_17276_amd import api
+    p = attention_params(B, Hq, Hkv, D, n, max_prefix, dtype, n_keys)
     out = [C.c_int32() for _ in range(3)]
-    assert api.lib().ot_internal_attn_plan(C.byref(p), int(kv8), *[C.byref(o) for o in out]) == 0
+    assert api.lib().ot_internal_attn_plan(C.byref(p), int(kv8), C.c_size_t(room), *[C.byref(o) for o in out]) == 0
     return tuple(o.value for o in out)

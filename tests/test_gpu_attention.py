@@ -514,6 +514,29 @@ def test_key_splits_and_their_merge(B, Hq, Hkv, D, L, n):
     assert np.abs(got[seqs][:, q] - _oracle_attention(sub, mask[seqs], "bf16")).max() < TOL["bf16"]
 
 
+@pytest.mark.parametrize("D,n,L", [(128, 100, 9000), (64, 100, 20000), (64, 40, 12000)])
+def test_more_ranges_where_the_workspace_holds_them(D, n, L):
+    """One sequence over a long prefix with the fewest ranges, some, and the best number, as three workspaces allow."""
+    import torch
+    from paper_2406_17276_amd import api
+    x = wl.make_attention_inputs(_shape("bf16", 1, 2, 2, D, L, n), 3)
+    mask = _random_masks(1, n, 5)
+    want = _oracle_attention(x, mask, "bf16")
+    dev = {k: U.to_device(v, "bf16") for k, v in x.items() if k != "prefix_len"}
+    plen, md = torch.from_numpy(x["prefix_len"].astype(np.int32)).cuda(), U.mask_to_device(mask)
+    rows, most, _ = U.attention_plan(1, 2, 2, D, n, L)
+    few = U.attention_plan(1, 2, 2, D, n, L, room=0)[1]
+    assert few < most
+    for splits in (few, (few + most) // 2, most):
+        room = 4096 + 256 + 2 * rows * splits * (2 * D + 8)
+        assert few <= U.attention_plan(1, 2, 2, D, n, L, room=room)[1] <= splits
+        ws = torch.full((room,), 255, dtype=torch.uint8, device="cuda")
+        api._check(api.lib().ot_attn_workspace_prepare(ws.data_ptr(), ws.numel(), api._stream()), "prepare")
+        out = api.tree_verify_attention(dev["Q"], dev["K_prefix"], dev["V_prefix"], dev["K_tree"], dev["V_tree"], plen, md, workspace=ws)
+        torch.cuda.synchronize()
+        assert np.abs(U.from_device_f64(out) - want).max() < TOL["bf16"], splits
+
+
 @pytest.mark.parametrize("L", [1, 63, 64, 65, 128, 129, 192, 700])
 @pytest.mark.parametrize("B,n", [(32, 33), (33, 33), (33, 64)])
 def test_64_rows_in_great_numbers(B, n, L):
