@@ -27,6 +27,15 @@ def test_long_prefixes_go_in_as_many_ranges_as_pay(B, Hkv, g, n, D, L, kv8, fewe
     assert U.attention_plan(B, Hkv * g, Hkv, D, n, L, kv8=kv8)[1] >= fewest
 
 
+@pytest.mark.parametrize("Hkv,D,L,n,kv8,ranges", [
+    (8, 128, 190, 120, True, 5), (8, 128, 30, 65, True, 3), (8, 128, 100, 65, True, 4), (64, 128, 120, 100, True, 4),
+    (8, 64, 120, 100, False, 4), (8, 128, 120, 100, False, 4), (16, 128, 120, 100, False, 1), (65, 64, 120, 100, False, 1),
+])
+def test_few_tiles_go_in_a_range_each(Hkv, D, L, n, kv8, ranges):
+    """Up to a fourth slower in one range, but for many heads."""
+    assert U.attention_plan(1, Hkv, Hkv, D, n, L, kv8=kv8)[1] == ranges
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("Hkv,g", [(1, 1), (8, 1), (32, 1), (8, 4), (8, 8), (2, 8)])
 def test_ranges_follow_the_workspace(Hkv, g, D):

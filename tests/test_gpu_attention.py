@@ -496,7 +496,7 @@ def test_weights_are_kept_when_the_reference_of_large_scores_moves(dtype, B, Hkv
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,L,n", [
-    *[(1, 2, 2, D, 64 * t, 100) for D in (64, 128) for t in (3, 4, 5, 6, 8, 10, 12, 14, 30)],     # 128 rows: no, two, ... eight splits
+    *[(1, 2, 2, D, 64 * t, 100) for D in (64, 128) for t in (1, 2, 3, 4, 5, 6, 8, 10, 12, 14, 30)],    # 128 rows: one, a tile each, three, ...
     (1, 2, 2, 128, 64 * 3 + 1, 40), (1, 2, 2, 128, 64 * 5, 40), (1, 2, 2, 128, 64 * 6, 40),       # 64 rows: as many splits as tiles,
     (1, 2, 2, 128, 3000, 64), (1, 2, 1, 128, 3008, 32), (1, 2, 1, 128, 6100, 32),                 # one, two and three trips of six
     (1, 2, 2, 64, 256, 40), (1, 2, 2, 64, 257, 40), (1, 2, 2, 64, 2000, 40),                      # 64 wide: no split; six; twelve

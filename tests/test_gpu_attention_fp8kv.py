@@ -78,6 +78,18 @@ def test_64_rows_in_great_numbers(L):
     assert np.abs(got[some] - _oracle({k: v[some] for k, v in x.items()}, mask[some])).max() < TOL
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L,n", [(120, 100), (190, 100), (250, 100), (250, 130)])
+def test_a_range_for_every_tile(D, L, n):
+    """128-row blocks over few tiles; in the second sequence some ranges have no key."""
+    x = _inputs(2, 4, 2, D, L, n // 2, 0.0, 3)
+    x["prefix_len"][-1] = L // 3
+    mask = _masks(2, n // 2, 4)
+    tiles = -(-L // 64) + -(-(n // 2) // 64)
+    assert U.attention_plan(2, 4, 2, D, n // 2, L, kv8=True) == (128, tiles, 0)
+    assert np.abs(_gpu(x, mask) - _oracle(x, mask)).max() < TOL
+
+
 @pytest.mark.parametrize("L", [0, 1, 63, 64, 65, 128, 191, 192, 256, 320, 447, 1000])
 def test_256_rows_with_few_tiles_and_jumps_in_either_block(L):
     """150 rows a KV head, no key splits: fewer and more tiles than the ring of widened tiles holds, and in half of the
