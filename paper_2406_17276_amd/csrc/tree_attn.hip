@@ -1469,12 +1469,19 @@ static size_t align_up(size_t v, size_t al) { return (v + al - 1) / al * al; }
 // eight wavefronts then share every staged K/V tile, which halves the traffic into LDS per MFMA and leaves room for a ring
 // of four tiles -- where the 256-row blocks are many or long enough: us at 128 / 256 rows, 16-bit cache of 128: 4 x 8 KV heads
 // of 480 rows, 1060 keys 23.8 / 26.7, 2060 keys 34.6 / 33.7, 8060 keys 83 / 76; 1 x 8 of 480 rows, 8060 keys 33 / 45;
-// 16 x 8 of 480 rows, 160 keys 18.4 / 18.7, 360 keys 29.1 / 25.0, 2060 keys 83 / 76; 8-bit cache: 2060 keys 84 / 74.
+// 16 x 8 of 480 rows, 160 keys 18.4 / 18.7, 360 keys 29.1 / 25.0, 2060 keys 83 / 76; 8-bit cache: 2060 keys 84 / 74.  An 8-bit
+// tile has to be widened two tiles ahead: a workgroup with few of them waits for that, each of several on a unit: 25 x 40 KV heads
+// of 800 rows, 60 keys 159 / 207, 200 keys 259 / 303; 32 x 8 of 800 rows, 320 keys 78 / 87, 500 keys (nine tiles) 106 / 111;
+// 1000 heads of 480 rows, 500 keys 237 / 230.  Nor does it pay to start one more round of 256-row blocks where half a round of
+// 128-row ones does, unless tiles are many: 160 heads of 480 rows, 400 keys 46.6 / 49.8, 700 keys 61.5 / 65.2, 1500 keys 109 / 111,
+// 6000 keys 360 / 358; 320 heads 73 / 79, 98 / 101, 180 / 171; 200 heads (almost two full rounds) 57 / 52, 75 / 67.
 static int attn_rows_per_workgroup(const ot_attn_params& p, bool kv8, int tiles) {
     const int rows = p.q_heads / p.kv_heads * p.n;
     if (rows <= 64) return 64;
     if (rows <= 128 || (kv8 && p.head_dim == 64)) return 128;   // (64 one-byte rows of 64 have fewer pieces than 512 threads)
-    const long long blocks = (long long)p.batch * p.kv_heads * ((rows + 255) / 256);
+    const long long heads = (long long)p.batch * p.kv_heads, blocks = heads * ((rows + 255) / 256);
+    const bool half_round = blocks > 256 && (heads * ((rows + 127) / 128) + 255) / 256 < 2 * ((blocks + 255) / 256);
+    if (kv8 && ((tiles < 8 && blocks > 512) || (tiles < 20 && half_round))) return 128;
     return blocks >= 64 && blocks * tiles >= 2048 ? 256 : 128;
 }
 

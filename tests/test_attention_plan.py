@@ -36,6 +36,17 @@ def test_few_tiles_go_in_a_range_each(Hkv, D, L, n, kv8, ranges):
     assert U.attention_plan(1, Hkv, Hkv, D, n, L, kv8=kv8)[1] == ranges
 
 
+@pytest.mark.parametrize("B,Hkv,g,n,L,kv8,rows", [
+    (25, 40, 16, 50, 149, True, 128), (32, 8, 16, 64, 384, True, 128), (32, 8, 16, 64, 385, True, 256), (32, 8, 8, 60, 320, True, 256), (16, 8, 8, 60, 4096, True, 256),
+    (20, 8, 8, 60, 700, True, 128), (20, 8, 8, 60, 1300, True, 256), (25, 8, 8, 60, 700, True, 256), (16, 8, 8, 60, 700, True, 256),
+    (25, 40, 16, 50, 149, False, 256), (16, 8, 8, 60, 4096, False, 256),
+])
+def test_few_tiles_of_an_8_bit_cache_stay_with_128_rows(B, Hkv, g, n, L, kv8, rows):
+    """Up to a third slower in 256-row blocks, which widen each tile two tiles ahead; and where half a round of the compute units
+    is enough in 128-row blocks."""
+    assert U.attention_plan(B, Hkv * g, Hkv, 128, n, L, kv8=kv8)[0] == rows
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("Hkv,g", [(1, 1), (8, 1), (32, 1), (8, 4), (8, 8), (2, 8)])
 def test_ranges_follow_the_workspace(Hkv, g, D):
