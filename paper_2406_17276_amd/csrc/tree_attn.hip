@@ -1521,6 +1521,10 @@ static AttnSplits attn_splits(long long base, int tiles, int rows_wg, int row_bl
     s = std::min<long long>(s, most);
     const int least = even_out(tiles, std::min<long long>(s, wide ? tiles / 2 : tiles));
     if (one_each) return {least, tiles};
+    // 64 rows of 128, few heads: the second trip of six pays somewhat earlier than many heads let it.  us, six / up to twelve: 17 rows
+    // x 8 heads, 1900 keys 12.6 / 11.5, 2720 keys 14.6 / 12.6, 8-bit 14.0 / 12.1, 17.0 / 13.5; 50 rows, 1900 keys 13.9 / 13.0, 2720
+    // keys 15.8 / 14.3; x 16 heads, 1900 keys 14.0 / 14.3, 2720 keys 16.0 / 15.7
+    if (!wide && head_dim == 128 && base <= 10 && tiles >= 28 && tiles < 48) return {least, even_out(tiles, 12)};
     if (least == 1 || !two || tiles < (kv8 ? 16 : 24)) return {least, least};
     // Longer prefixes, variants of which two workgroups fit a unit: what more ranges save grows with the prefix, what their merge
     // costs does not.  Both in units of the time that a tile takes a workgroup with a unit to itself (1.2 us at head_dim 128,
@@ -1536,11 +1540,11 @@ static AttnSplits attn_splits(long long base, int tiles, int rows_wg, int row_bl
     auto time = [&](int x) {
         const bool one = base * x <= 256;
         const float merge = wide ? (head_dim == 128 ? (one ? 0.42f : 0.7f) : (one ? 0.3f : 0.54f)) * (kv8 ? 0.8f : 1.f) * x
-                                 : (one ? 5.f : 7.f) * ((x + 11) / 12);
+                                 : (one ? 5.f : kv8 ? 6.f : 7.f) * ((x + 11) / 12);
         return (one ? 1.f : shared) * ((tiles + x - 1) / x) + merge + 8.f;
     };
     int best = least;
-    float best_time = (tiles < 80 ? 0.88f : 0.94f) * time(least);        // (what the estimate is good for)
+    float best_time = (tiles < 80 ? 0.89f : 0.94f) * time(least);        // (what the estimate is good for)
     for (int x = least + 1; x <= kMaxSplits && x <= tiles && base * x <= 512; ++x)
         if (even_out(tiles, x) == x && time(x) < best_time) { best = x; best_time = time(x); }
     return {least, best};

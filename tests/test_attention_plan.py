@@ -20,6 +20,7 @@ def _bytes(B, Hkv, g, n, D, plan):
     (1, 8, 4, 50, 128, 32768, False, 16), (1, 8, 4, 50, 128, 131072, True, 28), (1, 2, 4, 50, 64, 32768, False, 24),
     (1, 8, 8, 60, 128, 131072, False, 16), (1, 1, 2, 60, 128, 56997, False, 24), (1, 8, 1, 64, 64, 16384, False, 22),
     (1, 8, 1, 64, 64, 65536, True, 28), (25, 4, 2, 60, 128, 8192, True, 5), (3, 8, 8, 60, 128, 8192, False, 5),
+    (3, 2, 1, 17, 128, 2720, True, 11), (5, 8, 1, 17, 64, 4732, True, 11), (25, 4, 1, 50, 64, 1000, True, 5),
 ])
 def test_long_prefixes_go_in_as_many_ranges_as_pay(B, Hkv, g, n, D, L, kv8, fewest):
     """Shapes measured to take up to 2.4 times as long with eight ranges (twelve in 64-row blocks of 64), or with as many as
