@@ -652,6 +652,9 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
             bf16x8 kf[KR], vf[NP];
             u32x4 p0[2], p1[2];
             f32x16 s0, s1;
+            // -ref by itself: with the sign as an operand modifier of the loop's multiply-adds 25 x 1 KV heads of 800 rows, 30000 keys of
+            // 64 take 281 us instead of 274, 3 x 30 of 256 rows, 6000 keys 69.4 instead of 67.6
+            float nref = 0.f;
             int t = t0;
             // reference, O and l move up to what block `s` needs
             auto move_up = [&](const f32x16& s) {
@@ -663,6 +666,8 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
 #pragma unroll
                     for (int v = 0; v < 16; ++v) oacc[d][v] *= alpha;
                 ref = ref_new;
+                nref = -ref_new;
+                asm volatile("" : "+v"(nref));
             };
             // a pair of probabilities, rounded to the MFMA's operand type, and their sum taken from the rounded pair (l then
             // matches what P V multiplies by)
@@ -672,7 +677,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 return __builtin_bit_cast(unsigned int, pr);
             };
             // One phase, block B of tile t: next = S of the block behind it, whose first KR operands are in kf; O += P V of the
-            // block ahead of it, whose V operands are in vf; pc = 2^(c cur - ref).  Returns this lane's sum of pc.
+            // block ahead of it, whose V operands are in vf; pc = 2^(c cur + nref).  Returns this lane's sum of pc.
             auto phase = [&](auto block_c, const f32x16& cur, f32x16& next, const u32x4 (&pp)[2], u32x4 (&pc)[2]) {
                 constexpr int B = decltype(block_c)::value;
                 __builtin_amdgcn_sched_barrier(0);
@@ -689,7 +694,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 }
 #pragma unroll
                 for (int v = 0; v < 16; v += 2)
-                    pc[v >> 3][(v & 7) >> 1] = pair(__builtin_amdgcn_exp2f(fmaf(cur[v], c, -ref)), __builtin_amdgcn_exp2f(fmaf(cur[v + 1], c, -ref)), psum);
+                    pc[v >> 3][(v & 7) >> 1] = pair(__builtin_amdgcn_exp2f(fmaf(cur[v], c, nref)), __builtin_amdgcn_exp2f(fmaf(cur[v + 1], c, nref)), psum);
                 next = acc;
 #pragma unroll
                 for (int i = 0; i < NS; ++i) {                   // a matrix instruction, its share of the reads, its share of the rest
@@ -752,12 +757,10 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
                 for (int s = 0; s < KR; ++s) kf[s] = kfrag(ka[s] - (at1 ? BUF * 4 : -(NBUF - 1) * BUF * 4), 1);
                 bool in_b = false;
                 for (;;) {
-                    // 64 wide, a phase is short enough for instruction fetch to show: the loop begins a cache line (6 x 8 KV heads of
-                    // 1024 rows, 24722 keys 440 us at 12 bytes into one, 423 so; at head_dim 128 it is no faster, 1102 and 1110)
-                    if constexpr (D == 64) asm volatile(".p2align 6");
                     float psum = phase_a();
                     asm volatile("" : "+s"(moved));     // (keeps the first tile of an entry from becoming a second loop body)
-                    if (t != moved && __any(psum > kSumLimit)) break;
+                    const uint64_t over = __ballot(psum > kSumLimit);      // (one test: each branch taken between the phases shows at 64)
+                    if ((t == moved ? 0ull : over) != 0ull) break;
                     l_run += psum;
                     psum = phase_b();
                     if (__any(psum > kSumLimit)) { in_b = true; break; }
