@@ -187,6 +187,9 @@ OT_API int ot_tree_esub(const ot_build_params* p, int32_t steps_done, double del
  *   O[b,h,i,:] = sum_j softmax_j(scale * Q[b,h,i,:] . K[b,h/g,j,:]) V[b,h/g,j,:]
  * over j in {prefix rows 0..prefix_len[b]-1} U {tree rows j : bit j of mask[b][i]},
  * g = q_heads / kv_heads.  A node whose row has no visible key yields zeros.
+ * Q, K and V are finite in every row that the call covers (prefix rows up to prefix_len[b], all tree rows, hidden ones too: their
+ * weight is 0, and 0 times infinity is NaN), and |scale * log2(e) * Q.K| stays below 2^31; beyond that, infinities and NaNs go where
+ * IEEE arithmetic takes them.
  * The root token's K/V is the last prefix row.  Q and K arrive already
  * position-encoded.  bf16 inputs use bf16 MFMA with fp32 accumulation and fp32
  * softmax; f32 inputs use fp32 arithmetic throughout.

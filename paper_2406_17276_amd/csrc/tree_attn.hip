@@ -149,9 +149,9 @@ constexpr int tile_buffers(int var, bool kv8) { return var == 2 ? (kv8 ? 3 : 4) 
 // of its (sequence, KV head, row block); the workgroup that draws the last ticket merges all the
 // partials of those rows and writes O.  Nobody waits for anybody: a workgroup that is not last simply
 // ends.  The counter is reset by the merging workgroup, so it is zero again when the kernel ends.
-// Partial results of the key splits travel as bf16 (0) or as fp32 (define to 0): bf16 halves the exchange and lets the
-// merging workgroup hold all of a row block's partials in registers at once, one trip to memory instead of two; the
-// extra rounding is of the size of the output's own (the output is bf16).
+// Partial results of the key splits travel as bf16, or as fp32 (define to 0): bf16 halves the exchange and lets the merging
+// workgroup take twice as many ranges in a trip to memory (merge_chunk); the extra rounding is of the size of the output's
+// own (the output is bf16).
 #ifndef OT_ATTN_PART_BF16
 #define OT_ATTN_PART_BF16 1
 #endif
@@ -599,10 +599,11 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         // Measured (MI355X, the 128-row variant's loop, in which half of the matrix instructions had no vector work beside
         // them, before): 32 sequences x 8 KV heads of 1024 rows, 8448 keys of 128 1125 -> 1070 us (1.06 PFLOP/s); 16 x 8 of
         // 480 rows, 4156 keys 152 -> 137; 7 x 8 of 512 rows, 6428 keys 118 -> 105; 8 x 8 of 480 rows, 6060 keys of 64 79 -> 68;
-        // 2 x 8 of 164 rows, 595 keys 21.0 -> 19.2.  Now a SIMD's two wavefronts need 2048 matrix cycles per tile, and the
-        // operand reads of all eight some 2900 cycles of the LDS (128 bytes per cycle for K, 64 for V's transposing reads).
-        // 64 rows per wavefront, one wavefront per SIMD, halve those reads: 1139 us and 229 against 224 for a step of the
-        // 16 x 8 batch, since a wavefront by itself issues vector and matrix instructions one behind the other.
+        // 2 x 8 of 164 rows, 595 keys 21.0 -> 19.2.  Now a SIMD's two wavefronts need 2048 matrix cycles per tile (the
+        // pipe is busy 52 % of the time), the operand reads of all eight 1030 cycles of the LDS (SQ_LDS_IDX_ACTIVE: 256 bytes a
+        // cycle), which are not what bounds: 64 rows per wavefront, one wavefront per SIMD, halve them, and take 1139 us and 229
+        // against 224 for a step of the 16 x 8 batch, since a wavefront by itself issues vector and matrix instructions one behind
+        // the other.
         // Requests of the next tile spread over a phase instead of in one piece: 1051 us, but 140 at 16 x 8.
         constexpr int NS = SLABS, NP = 2 * DB, KR = NS / 2;     // instructions per phase for S, for P V; K operands ahead
         static_assert(NS == NP, "one P V instruction for each one of S");
@@ -800,7 +801,7 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         // slack, again and again.
         constexpr float kSlack = 12.f;
         constexpr float kSumLimit = 16.f * 4096.f;          // sixteen terms of at most 2^kSlack
-        static_assert((NBUF & (NBUF - 1)) == 0, "the buffer of a tile is (t - t0) mod NBUF");
+        static_assert(NBUF == 2, "the buffer of a tile is (t - t0) mod 2");
         // tile t has landed for this lane when only the requests of the tiles behind it are outstanding; after the
         // barrier it has for everybody, and everybody is done with the buffer that tile t + PD goes into
         auto stage_tile = [&](int t) {
@@ -962,18 +963,15 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
         // the remaining tiles (the prefix tail and the tree tiles) take the general path, whose buffer index is a
         // compile-time constant: tile t sits in buffer (t - t0) mod NBUF
         for (int tt = t_done; tt < t1; ++tt) {
-            const int bi = (tt - t0) & (NBUF - 1);
-            if (bi == 0)                   tile_step(tt, std::integral_constant<int, 0>{});
-            else if (bi == 1)              tile_step(tt, std::integral_constant<int, 1>{});
-            else if (NBUF > 2 && bi == 2)  tile_step(tt, std::integral_constant<int, (NBUF > 2 ? 2 : 0)>{});
-            else if (NBUF > 3)             tile_step(tt, std::integral_constant<int, (NBUF > 3 ? 3 : 0)>{});
+            if (((tt - t0) & 1) == 0) tile_step(tt, std::integral_constant<int, 0>{});
+            else                      tile_step(tt, std::integral_constant<int, 1>{});
         }
     } else {
+        static_assert(NBUF == 2 || NBUF == 3, "unrolled so");
         for (int t = t0; t < t1; t += NBUF) {
             tile_step(t, std::integral_constant<int, 0>{});
             if (t + 1 < t1) tile_step(t + 1, std::integral_constant<int, 1>{});
             if (NBUF > 2 && t + 2 < t1) tile_step(t + 2, std::integral_constant<int, (NBUF > 2 ? 2 : 0)>{});
-            if (NBUF > 3 && t + 3 < t1) tile_step(t + 3, std::integral_constant<int, (NBUF > 3 ? 3 : 0)>{});
         }
     }
     (void)t_done;
