@@ -130,20 +130,21 @@ def test_full_batch_as_the_bench_launches_it_sampled_groups(name, groups):
         assert np.abs(got - want).max() < TOL["bf16"]
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,D,n,lengths", [
-    (33, 16, 8, 128, 40, "ragged"),        # 128-row blocks, 264 workgroups: one more round than the chip holds at once
-    (64, 8, 4, 128, 70, "ragged"),         # 256-row blocks, 256 workgroups, the largest batch that is ranked
-    (40, 16, 8, 64, 33, "ties"),           # head_dim 64; many equal lengths, some zero, some beyond the buffer
-    (65, 8, 4, 128, 70, "ragged"),         # one sequence too many for the ranking: the order of the sequences
+@pytest.mark.parametrize("B,Hq,Hkv,D,n,lengths,plan", [
+    (33, 16, 8, 128, 40, "ragged", (128, 1, 1)),        # 128-row blocks, 264 workgroups: one more round than the chip holds at once
+    (64, 8, 4, 128, 70, "ragged", (256, 1, 1)),         # 256-row blocks, 256 workgroups, the largest batch that is ranked
+    (40, 16, 8, 64, 33, "ties", (128, 1, 1)),           # head_dim 64; many equal lengths, some zero, some beyond the buffer
+    (65, 8, 4, 128, 70, "ragged", (256, 1, 0)),         # one sequence too many for the ranking: the order of the sequences
 ])
-def test_batches_that_take_their_jobs_longest_first(B, Hq, Hkv, D, n, lengths):
+def test_batches_that_take_their_jobs_longest_first(B, Hq, Hkv, D, n, lengths, plan):
     """Batches that fill the chip with one key range per (sequence, KV head): every workgroup ranks the sequences by
     prefix length on the device and takes its job in that order.  Whatever the order, every (sequence, KV head) must
     come out exactly once: all outputs are finite and non-zero, and sampled sequences (the longest, the shortest, ties,
     clamped ones) agree with the oracle."""
     import torch
     from paper_2406_17276_amd import api
-    Lmax, g = 320, Hq // Hkv
+    Lmax, g = 448, Hq // Hkv
+    assert U.attention_plan(B, Hq, Hkv, D, n, Lmax) == plan
     rng = np.random.default_rng(B * 1000 + n)
     if lengths == "ragged":
         plen = rng.integers(1, Lmax + 1, size=B).astype(np.int32)
@@ -329,6 +330,25 @@ def test_drafting_phase_attention_frontier_against_pool(dtype, B, Hq, Hkv, D, L,
     assert np.abs(want).max() > 0.01
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_256_rows_against_a_drafting_pool(D):
+    """13 sequences of 8 KV heads of 240 rows, two key ranges each, over the prefix and 600 pool keys: the second range has
+    tree tiles only where the prefix is short.  Random masks, a few rows of which see no pool key."""
+    B, Hq, Hkv, n, nk, L = 13, 32, 8, 60, 600, 700
+    assert U.attention_plan(B, Hq, Hkv, D, n, L, n_keys=nk) == (256, 2, 0)
+    x = wl.make_attention_inputs(_shape("bf16", B, Hq, Hkv, D, L, nk), 12)
+    x["Q"] = np.ascontiguousarray(x["Q"][:, :, :n])
+    x["prefix_len"][:] = [[700, 1, 64, 130, 448, 0, 200][b % 7] for b in range(B)]
+    rng = np.random.default_rng(3)
+    mask = rng.integers(0, 2 ** 64, size=(B, n, 10), dtype=np.uint64) & rng.integers(0, 2 ** 64, size=(B, n, 10), dtype=np.uint64)
+    mask[:, ::17] = 0
+    got = _gpu_attention(x, mask, "bf16")
+    seqs, heads = [0, 3, 5, 8, 12], [0, 7]
+    q = [h * 4 + i for h in heads for i in range(4)]
+    sub = {k: v[seqs] if k == "prefix_len" else v[seqs][:, q if k == "Q" else heads] for k, v in x.items()}
+    assert np.abs(got[seqs][:, q] - _oracle_attention(sub, mask[seqs], "bf16")).max() < TOL["bf16"]
+
+
 def test_repeated_launches_are_bit_identical():
     """Split-heavy shape, 300 launches on one prepared workspace: the merge inside the kernel adds the splits
     in a fixed order, so every launch must reproduce the first bit for bit, and the ticket counters end at zero."""
@@ -354,22 +374,23 @@ def test_repeated_launches_are_bit_identical():
     assert int(pa.ws[:4096].view(torch.int32).abs().sum().item()) == 0
 
 
-@pytest.mark.parametrize("Hq,Hkv,n", [(8, 2, 25), (16, 2, 40), (4, 4, 70)])      # 100, 320 and 70 packed rows per KV head
-def test_scores_that_jump_between_tiles(Hq, Hkv, n):
+@pytest.mark.parametrize("B,Hq,Hkv,n,L,rows", [(2, 8, 2, 25, 1000, 128), (8, 16, 8, 75, 2000, 256), (2, 4, 4, 70, 1000, 128)])
+def test_scores_that_jump_between_tiles(B, Hq, Hkv, n, L, rows):
     """The 128- and 256-row variants keep a row's softmax reference fixed while scores stay within a slack of it and
     move it up otherwise: key bands whose scores differ by factors of up to 400 (beyond what 2^x can hold in fp32
     relative to the first band) force that path again and again, in the middle of a split."""
-    w = _shape("bf16", 2, Hq, Hkv, 128, 1000, n)
+    assert U.attention_plan(B, Hq, Hkv, 128, n, L)[0] == rows
+    w = _shape("bf16", B, Hq, Hkv, 128, L, n)
     x = wl.make_attention_inputs(w, 31)
     kp = wl.bf16_bits_to_f32(x["K_prefix"]).copy()
     for lo, f in [(0, 0.1), (200, 1.0), (400, 8.0), (600, 0.5), (800, 40.0), (930, 3.0)]:
         kp[:, :, lo:] = wl.bf16_bits_to_f32(x["K_prefix"])[:, :, lo:] * f
     x["K_prefix"] = wl.store(kp, "bf16")
-    mask = _random_masks(2, n, 8)
+    mask = _random_masks(B, n, 8)
     got = _gpu_attention(x, mask, "bf16")
-    want = _oracle_attention(x, mask, "bf16")
     assert np.isfinite(got).all()
-    assert np.abs(got - want).max() < TOL["bf16"]
+    some = [0, B - 1]
+    assert np.abs(got[some] - _oracle_attention({k: v[some] for k, v in x.items()}, mask[some], "bf16")).max() < TOL["bf16"]
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -377,8 +398,9 @@ def test_scores_that_jump_between_tiles(Hq, Hkv, n):
 def test_256_row_loop_with_few_full_tiles_and_jumps_in_either_block(D, L):
     """33 sequences of 4 KV heads (no key splits), 150 rows each: no, one, two, ... full prefix tiles ahead of the general
     path, and in half of the sequences a key band of far larger scores that starts inside a tile's first or second block."""
-    B, Hkv, n = 33, 4, 150
-    w = _shape("bf16", B, Hkv, Hkv, D, max(L, 1), n)
+    B, Hkv, n, Lmax = 33, 4, 150, 1000
+    assert U.attention_plan(B, Hkv, Hkv, D, n, Lmax) == (256, 1, 1)          # the plan goes by the rows that the cache has
+    w = _shape("bf16", B, Hkv, Hkv, D, Lmax, n)
     x = wl.make_attention_inputs(w, 5)
     x["prefix_len"][:] = L
     kp = wl.bf16_bits_to_f32(x["K_prefix"]).copy()
@@ -391,7 +413,7 @@ def test_256_row_loop_with_few_full_tiles_and_jumps_in_either_block(D, L):
     assert np.isfinite(got).all()
     some = sorted({0, 1, 2, 3, 5, 9, 17, B - 1})
     sub = {k: v[some] for k, v in x.items()}
-    # the oracle works in 64 bits on the stored values; p and O are rounded to bf16 once each (2^-9 of values up to 4)
+    # the oracle works in 64 bits on the stored values; O, up to 4, and p, averaged over a row's keys, are rounded to 8 bits
     assert np.abs(got[some] - _oracle_attention(sub, mask[some], "bf16")).max() < TOL["bf16"]
 
 
@@ -431,8 +453,10 @@ def test_scores_that_round_by_more_than_the_slack(D, n):
     """Scores of 1e9 in units of log2 e: a tile's own maximum minus itself rounds to anything up to 32 (64 from 2^30 on), so
     its probability to 2^32, which must not send the loops over full tiles back to that tile for ever.  Each row ends up as
     the V of its best key."""
-    w = _shape("bf16", 33, 4, 4, D, 500, n)
+    assert U.attention_plan(33, 4, 4, D, n, 1000)[0] == (256 if n == 150 else 128)
+    w = _shape("bf16", 33, 4, 4, D, 1000, n)
     x = wl.make_attention_inputs(w, 6)
+    x["prefix_len"][:] = 500
     for k in ("K_prefix", "K_tree"):
         x[k] = wl.store(wl.bf16_bits_to_f32(x[k]) * 2e8, "bf16")
     mask = _random_masks(33, n, 2)
@@ -503,6 +527,8 @@ def test_weights_are_kept_when_the_reference_of_large_scores_moves(dtype, B, Hkv
     (8, 8, 8, 128, 2000, 150), (6, 16, 16, 64, 1300, 130),                                        # 256 rows, four splits; two
 ])
 def test_key_splits_and_their_merge(B, Hq, Hkv, D, L, n):
+    if B > 1:
+        assert U.attention_plan(B, Hq, Hkv, D, n, L)[:2] == (256, 256 // (B * Hkv))
     w = _shape("bf16", B, Hq, Hkv, D, L, n)
     x = wl.make_attention_inputs(w, 3)
     x["prefix_len"][-1] = max(1, L // 3)                      # splits without a key, where there is a second sequence

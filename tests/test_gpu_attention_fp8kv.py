@@ -94,7 +94,8 @@ def test_a_range_for_every_tile(D, L, n):
 def test_256_rows_with_few_tiles_and_jumps_in_either_block(L):
     """150 rows a KV head, no key splits: fewer and more tiles than the ring of widened tiles holds, and in half of the
     sequences key bands of far larger scores."""
-    x = _inputs(33, 4, 4, 128, max(L, 1), 150, 0.0, 5)
+    assert U.attention_plan(33, 4, 4, 128, 150, 1000, kv8=True) == (256, 1, 1)       # (by the rows that the cache has)
+    x = _inputs(33, 4, 4, 128, 1000, 150, 0.0, 5)
     x["prefix_len"][:] = L
     for b in range(1, 33, 2):                                  # the largest value of both signs
         for at in (64 * (b % 3) + 8 * b % 64, 64 * (b % 5) + 70, 64 * (b % 7) + 40):
@@ -107,15 +108,75 @@ def test_256_rows_with_few_tiles_and_jumps_in_either_block(L):
     assert np.abs(got[some] - _oracle({k: v[some] for k, v in x.items()}, mask[some])).max() < TOL
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,n,nk,L,strided,plan", [
+    (8, 8, 8, 150, 150, 2000, False, (256, 4, 0)),       # key ranges: empty ones, ones that begin among the tree tiles
+    (65, 6, 3, 70, 70, 600, True, (256, 1, 0)),          # a batch too large to be ranked; K and V as views
+    (13, 32, 8, 60, 600, 700, False, (256, 2, 0)),       # a drafting pool of ten tiles
+])
+def test_256_rows_in_ranges_unranked_and_against_a_pool(B, Hq, Hkv, n, nk, L, strided, plan):
+    import torch
+    D, g = 128, Hq // Hkv
+    assert U.attention_plan(B, Hq, Hkv, D, n, L, n_keys=nk if nk != n else 0, kv8=True) == plan
+    x = _inputs(B, Hq, Hkv, D, L, nk, 0.0, 7)
+    x["Q"] = np.ascontiguousarray(x["Q"][:, :, :n])
+    x["prefix_len"][:] = [[L, 0, 1, 64, 130, 500, L - 1, 200][b % 8] for b in range(B)]
+    rng = np.random.default_rng(3)
+    W = (nk + 63) // 64
+    mask = rng.integers(0, 2 ** 64, size=(B, n, W), dtype=np.uint64) & rng.integers(0, 2 ** 64, size=(B, n, W), dtype=np.uint64)
+    mask[:, ::17] = 0
+
+    def views(kv):
+        pre = torch.stack([kv["K_prefix"], kv["V_prefix"]], dim=3)
+        tre = torch.stack([kv["K_tree"], kv["V_tree"]], dim=3)
+        return dict(K_prefix=pre[:, :, :, 0], V_prefix=pre[:, :, :, 1], K_tree=tre[:, :, :, 0], V_tree=tre[:, :, :, 1])
+
+    got = _gpu(x, mask, views=views if strided else None)
+    seqs, heads = sorted({0, 1, 2, 3, 4, 6, B - 1}), [0, Hkv - 1]
+    q = [h * g + i for h in heads for i in range(g)]
+    sub = {k: v[seqs] if k == "prefix_len" else v[seqs][:, q if k == "Q" else heads] for k, v in x.items()}
+    assert np.abs(got[seqs][:, q] - _oracle(sub, mask[seqs])).max() < TOL
+
+
+def test_the_70b_batch_on_sampled_groups():
+    """16 sequences of 8 KV heads of 480 rows, ragged prefixes around 4096, inputs drawn on the device: 256-row blocks, jobs
+    longest first."""
+    import torch
+    from paper_2406_17276_amd import api
+    w = wl.WORKLOADS["70b"]
+    B, Hkv, g, D, n, L = w.batch, w.kv_heads, w.q_heads // w.kv_heads, w.head_dim, w.n, w.max_prefix()
+    assert U.attention_plan(B, Hkv * g, Hkv, D, n, L, kv8=True) == (256, 1, 1)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(17)
+    draw = lambda rows: (torch.randn((B, Hkv, rows, D), generator=gen, device="cuda") * 64).to(torch.float8_e4m3fn).view(torch.uint8)
+    kv = dict(K_prefix=draw(L), V_prefix=draw(L), K_tree=draw(n), V_tree=draw(n))
+    Q = torch.randn((B, Hkv * g, n, D), generator=gen, device="cuda").to(torch.bfloat16)
+    ks, vs = [(torch.rand((B, Hkv), generator=gen, device="cuda") + 0.5) / 64 for _ in range(2)]
+    plen, mask = wl.prefix_lengths(w, 4).astype(np.int32), _masks(B, n, 23)
+    out = api.tree_verify_attention_fp8kv(Q, kv["K_prefix"], kv["V_prefix"], kv["K_tree"], kv["V_tree"], ks, vs,
+                                          torch.from_numpy(plen).cuda(), U.mask_to_device(mask))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(out.float()).all())
+    host = lambda t: t.cpu().numpy()
+    for b, h in [(0, 0), (3, 5), (9, 2), (15, 7), (int(plen.argmax()), 1), (int(plen.argmin()), 6)]:
+        sub = {k: host(v[b:b + 1, h:h + 1]) for k, v in kv.items()}
+        sub.update(Q=host(Q[b:b + 1, h * g:h * g + g].view(torch.int16)).view(np.uint16), k_scale=host(ks[b:b + 1, h:h + 1]),
+                   v_scale=host(vs[b:b + 1, h:h + 1]), prefix_len=plen[b:b + 1])
+        got = U.from_device_f64(out[b:b + 1, h * g:h * g + g])
+        assert np.abs(got - _oracle(sub, mask[b:b + 1])).max() < TOL, (b, h)
+
+
 def test_scores_that_round_by_more_than_the_slack():
     """As in the 16-bit cache's test of this name: scores of 1e9, here from the K factors."""
-    x = _inputs(33, 4, 4, 128, 500, 150, 0.0, 6)
+    assert U.attention_plan(33, 4, 4, 128, 150, 1000, kv8=True)[0] == 256
+    x = _inputs(33, 4, 4, 128, 1000, 150, 0.0, 6)
+    x["prefix_len"][:] = 500
     x["k_scale"] = (x["k_scale"] * np.float32(2e8)).astype(np.float32)
     mask = _masks(33, 150, 2)
     got = _gpu(x, mask)
     some = [0, 13, 32]
     want = _oracle({k: v[some] for k, v in x.items()}, mask[some])
-    assert np.abs(got[some] - want).max() < TOL
+    # a row is the V of its best key, whose probability is any number here: rounded to 8 significant bits, like O
+    assert (np.abs(got[some] - want) <= 1.01 * 2 * 2.0 ** -8 * np.abs(want) + 1e-6).all()
 
 
 @pytest.mark.parametrize("n,rows", [(40, 64), (70, 128), (150, 256)])
