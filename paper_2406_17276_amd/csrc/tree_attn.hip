@@ -1510,10 +1510,10 @@ static AttnSplits attn_splits(long long base, int tiles, int rows_wg, int row_bl
     // Few tiles, 128-row blocks: a range of one tile each has nothing to stream behind and nothing to widen while it computes, and
     // pays for its merge.  us, one range / one a tile, 120 rows x 8 heads: 8-bit of 128, 120 keys 11.8 / 11.3, 190 keys 13.2 / 11.5,
     // 250 keys 14.9 / 12.5, 320 keys (three ranges) 13.6 / 12.6 and with 32 heads 13.9 / 13.8; 8-bit of 64, 250 keys 10.1 / 9.3;
-    // 16-bit of 64, 190 keys 8.8 / 8.1, 250 keys 9.3 / 9.0; of 128, 190 keys 11.3 / 10.9, 250 keys 12.4 / 12.0, with 64 heads 11.7 /
+    // 16-bit of 64, 190 keys 8.8 / 8.1, 250 keys 9.3 / 9.0, 11 x 2 heads of 240 rows, 134 keys 8.4 / 8.9; of 128, 190 keys 11.3 / 10.9, 250 keys 12.4 / 12.0, with 64 heads 11.7 /
     // 12.6.
     const bool one_each = rows_wg == 128 && tiles >= (kv8 ? 3 : 4) && tiles <= (kv8 ? 6 : 5) &&
-                          base * tiles <= (tiles == 6 ? 96 : kv8 || head_dim == 64 ? 256 : 48);
+                          base * tiles <= (tiles == 6 ? 96 : kv8 ? 256 : head_dim == 64 ? 128 : 48);
     if (tiles <= (wide || head_dim == 64 ? 5 : 1)) return {1, one_each ? tiles : 1};
     long long s = 256 / base;
     if (s < 2) s = two && tiles >= 24 ? 512 / base : 1;

@@ -30,7 +30,7 @@ def test_long_prefixes_go_in_as_many_ranges_as_pay(B, Hkv, g, n, D, L, kv8, fewe
 
 @pytest.mark.parametrize("Hkv,D,L,n,kv8,ranges", [
     (8, 128, 190, 120, True, 5), (8, 128, 30, 65, True, 3), (8, 128, 100, 65, True, 4), (64, 128, 120, 100, True, 4),
-    (8, 64, 120, 100, False, 4), (8, 128, 120, 100, False, 4), (16, 128, 120, 100, False, 1), (65, 64, 120, 100, False, 1),
+    (32, 64, 120, 100, False, 4), (33, 64, 120, 100, False, 1), (8, 128, 120, 100, False, 4), (16, 128, 120, 100, False, 1), (65, 64, 120, 100, True, 1),
 ])
 def test_few_tiles_go_in_a_range_each(Hkv, D, L, n, kv8, ranges):
     """Up to a fourth slower in one range, but for many heads."""
