@@ -49,3 +49,26 @@ def test_no_allocation_entry_point_matches_the_workspace_one():
                                                x["prefix_len"], mask)
         assert np.abs(U.from_device_f64(out) - want).max() < tol
         assert torch.equal(out, ref), "same kernels, same plan: the two entry points agree bit for bit"
+
+
+def test_long_prefix_takes_as_many_ranges_as_the_library_s_array_holds():
+    """One sequence of 8 KV heads of 200 rows over 20000 keys: more ranges pay than the array has room for."""
+    import ctypes as C
+    import torch
+    from paper_2406_17276_amd import api
+    B, Hq, Hkv, D, L, n = 1, 32, 8, 128, 20000, 50
+    ranges = [U.attention_plan(B, Hq, Hkv, D, n, L, room=room)[1] for room in (0, 8 << 20, 1 << 40)]
+    assert ranges[0] < ranges[1] < ranges[2]
+    p = U.attention_params(B, Hq, Hkv, D, n, L)
+    assert api.attn_workspace_bytes(p) <= 8 << 20 < api.lib().ot_attn_workspace_bytes_full(C.byref(p))
+    x, mask = _case("bf16", B, Hq, Hkv, D, L, n, 3)
+    dev = {k: U.to_device(v, "bf16") for k, v in x.items() if k != "prefix_len"}
+    out = torch.full_like(dev["Q"], float("nan"))
+    api.tree_verify_attention_noalloc(dev["Q"], dev["K_prefix"], dev["V_prefix"], dev["K_tree"], dev["V_tree"],
+                                      torch.from_numpy(x["prefix_len"].astype(np.int32)).cuda(), U.mask_to_device(mask), out)
+    torch.cuda.synchronize()
+    heads = [0, 5]
+    q = [h * 4 + i for h in heads for i in range(4)]
+    f = {k: wl.to_f64(v[:, q if k == "Q" else heads], "bf16") for k, v in x.items() if k != "prefix_len"}
+    want = ta_oracle.tree_verify_attention(f["Q"], f["K_prefix"], f["V_prefix"], f["K_tree"], f["V_tree"], x["prefix_len"], mask)
+    assert np.abs(U.from_device_f64(out)[:, q] - want).max() < 2e-2
