@@ -218,8 +218,9 @@ OT_API size_t ot_attn_workspace_bytes(const ot_attn_params* p);     /* 0 if p is
 
 /* A call cuts long prefixes into as many key ranges as are fastest, as far as its workspace holds their partial results.
  * A workspace of ot_attn_workspace_bytes is what is needed, and holds all of them as long as that is no more than
- * OT_ATTN_SCRATCH_BYTES; one of ot_attn_workspace_bytes_full always does (same result up to the rounding of the partials;
- * one sequence over more than 16384 keys, or some hundred KV heads, gain up to a third).  0 if p is invalid. */
+ * OT_ATTN_SCRATCH_BYTES; one of ot_attn_workspace_bytes_full always does (same result up to the rounding of the partials; some
+ * hundred KV heads of more than 64 rows over an 8-bit cache gain a fourth by it, a few over more than 65536 keys a tenth).  0 if p
+ * is invalid. */
 OT_API size_t ot_attn_workspace_bytes_full(const ot_attn_params* p);
 
 /* The first OT_ATTN_SYNC_BYTES bytes of an attention workspace hold the ticket counters with which the
