@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libopttree.so")
 BINDING = os.path.join(HERE, "_binding.so")
-SOURCES = ["api.hip", "row_scan.hip", "tree_build.hip", "tree_select.hip", "tree_attn.hip", "verify.hip", "yardstick.hip"]
+SOURCES = ["api.hip", "row_scan.hip", "tree_build.hip", "build_fused.hip", "tree_select.hip", "tree_attn.hip", "verify.hip", "yardstick.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
@@ -29,7 +29,10 @@ FLAGS = [
 # honoured), which saves the quieting instruction in front of every maximum.  (Not for verify.hip, whose rows may hold NaNs.)
 # -disable-machine-licm: without it 1 % slower (13B-shaped adaptive build 23.2 -> 23.5 us, builds of 128256-token rows 2191 ->
 # 2201 us), at the same number of registers and no spills either way.
-EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"]}
+# build_fused.hip: without -disable-machine-licm constants of the exponential are kept in registers throughout (79 registers
+# instead of 55, and 64 are what two workgroups of 1024 threads leave).
+EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"],
+               "build_fused.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def build(verbose: bool = False) -> str:

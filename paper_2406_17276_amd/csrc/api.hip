@@ -136,9 +136,12 @@ static long long chunk_bytes(long long before) {
     return std::max({192 * mb, std::min(before / 2, 1024 * mb), before / 6});
 }
 
+// Polls of a drafting workgroup for a row, some 30 ms: longer than any launch that has the chip to itself takes
+constexpr int kArrivalPolls = 30000;
+
 static int build_steps(const ot_build_params* p, bool adapt, double delta, const void* logits, void* workspace,
                        size_t workspace_bytes, const ot_tree_out* out, int32_t* steps_used, double* e_sub, void* hip_stream,
-                       void* ev0, void* ev1) {
+                       void* ev0, void* ev1, int polls = kArrivalPolls, int32_t* one_launch = nullptr) {
     int st = validate_build(p, true);
     if (st != OT_OK) return st;
     if (!logits || !workspace) return OT_ERR_INVALID_ARG;
@@ -166,6 +169,10 @@ static int build_steps(const ot_build_params* p, bool adapt, double delta, const
         if ((f.rows - f.row_start[t1]) * row_bytes < least) t1 = p->depth;
         if (ev0 || ev1) t1 = p->depth;                         // the timed form brackets one scan of everything
         sg.row0 = f.row_start[t0]; sg.rows = f.row_start[t1] - f.row_start[t0];
+        const bool fused = t0 == 0 && t1 == p->depth && !ev0 && !ev1 && fuse_build(sg, g, logits);
+        if (one_launch) *one_launch = fused;
+        if (fused)
+            return launch_fused_build(sg, g, logits, adapt, delta, ws, *out, steps_used, e_sub, polls, s);
         st = launch_row_scan(sg, logits, ws, s, (hipEvent_t)ev0, (hipEvent_t)ev1, t0 > 0);
         if (st != OT_OK) return st;
         st = launch_tree_build(g, t0, t1, adapt, delta, ws, *out, steps_used, e_sub, s);
@@ -178,6 +185,14 @@ static int build_steps(const ot_build_params* p, bool adapt, double delta, const
 int ot_build_tree(const ot_build_params* p, const void* logits, void* workspace, size_t workspace_bytes,
                   const ot_tree_out* out, void* hip_stream) {
     return build_steps(p, false, 0.0, logits, workspace, workspace_bytes, out, nullptr, nullptr, hip_stream, nullptr, nullptr);
+}
+
+int ot_internal_build_tree(const ot_build_params* p, int32_t adapt, double delta, const void* logits, void* workspace,
+                           size_t workspace_bytes, const ot_tree_out* out, int32_t* steps_used, double* e_sub, int32_t polls,
+                           int32_t* one_launch, void* hip_stream) {
+    if (adapt && (!(delta == delta) || !steps_used || !e_sub)) return OT_ERR_INVALID_ARG;
+    return build_steps(p, adapt != 0, delta, logits, workspace, workspace_bytes, out, steps_used, e_sub, hip_stream, nullptr, nullptr,
+                       polls, one_launch);
 }
 
 int ot_build_tree_timed(const ot_build_params* p, const void* logits, void* workspace, size_t workspace_bytes,

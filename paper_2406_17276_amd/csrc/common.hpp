@@ -94,6 +94,11 @@ struct SelectGeometry {
 // several launches per build ws.seq_active says which sequences go on.
 int launch_tree_build(const SelectGeometry& g, int t0, int t1, bool adapt, double delta, const BuildWorkspace& ws,
                       const ot_tree_out& out, int32_t* steps_used, double* e_sub, hipStream_t s);
+// Scan and build of all steps as one launch: does it apply (build_fused.hip says when), and the launch.
+// spin: polls for a row before the drafting workgroup leaves its work to the workgroup that publishes the last row.
+bool fuse_build(const ScanGeometry& sg, const SelectGeometry& g, const void* logits);
+int launch_fused_build(const ScanGeometry& sg, const SelectGeometry& g, const void* logits, bool adapt, double delta,
+                       const BuildWorkspace& ws, const ot_tree_out& out, int32_t* steps_used, double* e_sub, int spin, hipStream_t s);
 int launch_tree_step(const SelectGeometry& g, int step, const BuildWorkspace& ws, int32_t* frontier_token,
                      int32_t* frontier_parent, int32_t* frontier_count, hipStream_t s);
 int launch_tree_finalize(const SelectGeometry& g, int steps_done, const BuildWorkspace& ws, const ot_tree_out& out,
@@ -141,6 +146,17 @@ __device__ __forceinline__ double key_f64(unsigned long long k) {
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Words that workgroups of one launch hand to each other: device-scope stores write through, device-scope loads pass by the
+// caches of this XCD.  SHARED false: ordinary accesses.
+template <bool SHARED, typename T> __device__ __forceinline__ T get(const T* p) {
+    if constexpr (SHARED) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
+}
+template <bool SHARED, typename T> __device__ __forceinline__ void put(T* p, T v) {
+    if constexpr (SHARED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
 
 // The elements of a 16-byte vector of logits as floats
 template <int DT> struct VecOf {

@@ -1,0 +1,132 @@
+"""Builds whose scan and drafting are one launch (needs an MI355X), at the ends of the ranges of its forms: the trees must be
+those of the two launches of the timed entry point bit for bit (the scan's forms and the order of every sum are the same), on a
+workspace of any contents, again on the workspace that a build has left, and also where the drafting workgroup gives up waiting at once
+and the workgroup of the last row drafts instead."""
+import ctypes as C
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("token", "parent", "depth", "score", "mask", "n_out", "expect")
+
+
+def _logits(V, n, d, B, dtype, seed, ragged=0):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    x = torch.randn((B, d, n, V + ragged), generator=g, device="cuda").mul_(3.5)
+    x.scatter_add_(3, torch.randint(0, V, (B, d, n, 1), generator=g, device="cuda"), torch.full((B, d, n, 1), 6.0, device="cuda"))
+    return x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)[..., :V]
+
+
+class _Build:
+    def __init__(self, x, k, n, d):
+        import torch
+        from paper_2406_17276_amd import api
+        self.x, self.p = x, api.build_params(x, k, n, d)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(5)
+        self.ws = torch.randint(0, 256, (api.build_workspace_bytes(self.p),), generator=g, device="cuda", dtype=torch.uint8)
+        self.out = api.alloc_tree(self.p.batch, n)
+        self.steps = torch.empty(self.p.batch, dtype=torch.int32, device="cuda")
+        self.e = torch.empty(self.p.batch, dtype=torch.float64, device="cuda")
+
+    def __call__(self, polls, delta=None):
+        import torch
+        from paper_2406_17276_amd import api
+        for f in FIELDS:
+            getattr(self.out, f).fill_(-7)
+        one, o = C.c_int32(-1), self.out.c_struct()
+        st = api.lib().ot_internal_build_tree(
+            C.byref(self.p), C.c_int32(delta is not None), C.c_double(delta or 0.0), C.c_void_p(self.x.data_ptr()),
+            C.c_void_p(self.ws.data_ptr()), C.c_size_t(self.ws.numel()), C.byref(o), C.c_void_p(self.steps.data_ptr()),
+            C.c_void_p(self.e.data_ptr()), C.c_int32(polls), C.byref(one), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0, st
+        torch.cuda.synchronize()
+        return one.value, [getattr(self.out, f).clone() for f in FIELDS] + ([self.steps.clone(), self.e.clone()] if delta is not None else [])
+
+
+def _equal(a, b):
+    import torch
+    return all(torch.equal(x.view(torch.uint8), y.view(torch.uint8)) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("V,k,n,d,B,dtype,ragged", [
+    (1000, 4, 16, 4, 1, "f32", 0),          # 256 threads a row; one candidate each
+    (8192, 16, 32, 5, 3, "bf16", 0),        # its longest row, two candidates each (512)
+    (8184, 2, 200, 10, 2, "bf16", 1),       # rows at any alignment; more than 64 nodes, pool of many
+    (500, 3, 1, 12, 32, "f32", 0),          # one node, the most sequences
+    (8193, 10, 50, 10, 1, "bf16", 0),       # 1024 threads; one candidate each by 512 of them
+    (32000, 16, 64, 4, 2, "bf16", 0),       # 1024 candidates
+    (32003, 6, 33, 7, 3, "bf16", 3),
+    (20000, 9, 65, 5, 2, "f32", 0),         # 640 threads draft
+    (40000, 16, 64, 3, 2, "bf16", 0),       # 512 threads, rolling; two candidates each
+    (33000, 5, 20, 6, 2, "f32", 0),         # 1024 threads, rolling
+    (131072, 4, 9, 4, 2, "bf16", 0),        # the longest row of one part
+])
+def test_one_launch_equals_two(V, k, n, d, B, dtype, ragged):
+    import torch
+    from paper_2406_17276_amd import api
+    x = _logits(V, n, d, B, dtype, V + n, ragged)
+    ref = api.PreparedBuild(x, k, n, d)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    ref.timed(torch.cuda.current_stream().cuda_stream, ev[0].cuda_event, ev[1].cuda_event)
+    torch.cuda.synchronize()
+    want = [getattr(ref.out, f).clone() for f in FIELDS]
+    build = _Build(x, k, n, d)
+    for polls in (30000, 30000, 0, 1, 30000):
+        print(V, k, n, d, B, dtype, "polls", polls, flush=True)
+        one, got = build(polls)
+        assert one == 1
+        assert _equal(got, want), polls
+    first = None
+    for polls in (30000, 0, 30000):
+        one, got = build(polls, 0.05)
+        assert one == 1
+        first = first or got
+        assert _equal(got, first), polls
+        assert int(got[-2].min()) >= 1
+
+
+@pytest.mark.parametrize("V,k,n,d,B,dtype", [
+    (1000, 1, 16, 6, 1, "f32"), (4000, 8, 32, 2, 1, "bf16"), (131080, 4, 9, 3, 1, "bf16"), (1000, 4, 16, 4, 33, "f32"),
+    (4000, 16, 33, 4, 1, "bf16"), (32000, 16, 65, 4, 1, "bf16"),
+])
+def test_builds_that_go_in_two_launches(V, k, n, d, B, dtype):
+    build = _Build(_logits(V, n, d, B, dtype, 3), k, n, d)
+    one, got = build(30000)
+    assert one == 0
+    assert _equal(build(30000)[1], got)
+
+
+def test_replays_of_a_captured_build_with_other_inputs():
+    import torch
+    from paper_2406_17276_amd import api
+    V, k, n, d, B = 9000, 8, 40, 6, 2
+    x = _logits(V, n, d, B, "bf16", 1)
+    ws = torch.empty(api.build_workspace_bytes(api.build_params(x, k, n, d)), dtype=torch.uint8, device="cuda")
+    out = api.alloc_tree(B, n)
+    api.build_tree(x, k, n, d, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        for _ in range(2):
+            api.build_tree(x, k, n, d, out=out, workspace=ws)
+    for replay in range(4):
+        x.copy_(_logits(V, n, d, B, "bf16", 10 + replay))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [getattr(out, f).clone() for f in FIELDS]
+        assert _build_equal_eager(x, k, n, d, got), replay
+
+
+def _build_equal_eager(x, k, n, d, got):
+    import torch
+    from paper_2406_17276_amd import api
+    eager = api.build_tree(x, k, n, d)
+    torch.cuda.synchronize()
+    return _equal([getattr(eager, f) for f in FIELDS], got)
