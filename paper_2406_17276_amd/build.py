@@ -13,7 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libopttree.so")
 BINDING = os.path.join(HERE, "_binding.so")
-SOURCES = ["api.hip", "row_scan.hip", "tree_build.hip", "build_fused.hip", "tree_select.hip", "tree_attn.hip", "verify.hip", "yardstick.hip"]
+SOURCES = ["api.hip", "row_scan.hip", "tree_build.hip", "build_fused.hip", "tree_select.hip", "tree_expand.hip", "tree_attn.hip", "verify.hip", "yardstick.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -257,10 +257,12 @@ int ot_tree_expand(const ot_build_params* p, int32_t step, const void* rows, int
     sg.nsteps = 1; sg.rows_per_seq = f.F[step]; sg.row0 = 0; sg.rows = f.F[step];
     sg.grow_k = 1; sg.grow_n = 1;
     sg.stride_seq = stride_seq; sg.stride_depth = 0; sg.stride_row = stride_row;
-    st = launch_row_scan(sg, rows, ws, s, nullptr, nullptr, true);      // rows of frozen sequences are not read
-    if (st != OT_OK) return st;
     SelectGeometry g = select_geometry(*p, f);
     g.rows_per_seq = f.F[step];
+    if (fuse_expand(sg, rows))
+        return launch_fused_expand(sg, g, rows, step, ws, frontier_token, frontier_parent_slot, frontier_count, s);
+    st = launch_row_scan(sg, rows, ws, s, nullptr, nullptr, true);      // rows of frozen sequences are not read
+    if (st != OT_OK) return st;
     return launch_tree_step(g, step, ws, frontier_token, frontier_parent_slot, frontier_count, s);
 }
 

@@ -130,3 +130,60 @@ def _build_equal_eager(x, k, n, d, got):
     eager = api.build_tree(x, k, n, d)
     torch.cuda.synchronize()
     return _equal([getattr(eager, f) for f in FIELDS], got)
+
+
+@pytest.mark.parametrize("V,k,n,d,B,dtype,ragged", [
+    (1000, 4, 16, 4, 1, "f32", 0),          # steps of one launch: 256 threads a row
+    (8184, 16, 65, 5, 3, "bf16", 1),        # more than 64 nodes, more than ten candidates a node
+    (8192, 11, 64, 4, 4, "bf16", 0),        # 256 rows in the last steps: the most that go in one launch
+    (8192, 8, 52, 4, 5, "bf16", 0),         # 260: two launches there
+    (32000, 10, 50, 10, 1, "bf16", 0),      # 1024 threads
+    (9000, 16, 256, 4, 1, "f32", 0),        # 256 rows of 1024 threads, four wavefronts in the step
+    (40000, 8, 20, 5, 4, "bf16", 0),        # 512 threads, rolling
+    (131072, 12, 9, 3, 2, "bf16", 0),       # the longest row of one part
+    (131080, 3, 9, 3, 2, "bf16", 0),        # two parts
+])
+def test_streaming_steps_equal_the_one_shot_build(V, k, n, d, B, dtype, ragged):
+    import torch
+    from paper_2406_17276_amd import api
+    x = _logits(V, n, d, B, dtype, 3 * V + n, ragged)
+    want = api.build_tree(x, k, n, d)
+    F = api.frontier_sizes(k, n, d)
+    for go in (range(2)):                   # a second builder on the memory that the first has left
+        ts = api.TreeStream(B, V, k, n, d, api.OT_BF16 if dtype == "bf16" else api.OT_F32, "cuda")
+        for t in range(d):
+            print(V, k, n, d, B, dtype, "step", t, flush=True)
+            ts.expand(x[:, t])
+            torch.cuda.synchronize()
+            assert ts.frontier_count.tolist() == [F[t + 1]] * B
+        got = ts.finalize()
+        torch.cuda.synchronize()
+        for f in ("token", "parent", "depth", "mask", "n_out"):
+            assert torch.equal(getattr(got, f), getattr(want, f)), f
+        # fp32 roundings of doubles that differ in the last places (scan forms differ with the number of rows)
+        assert torch.allclose(got.score, want.score, rtol=1e-6, atol=1e-6)
+        del ts
+
+
+def test_a_stopped_sequence_stays_as_it_is_in_steps_of_one_launch():
+    import torch
+    from paper_2406_17276_amd import api
+    V, k, n, d, B = 2000, 6, 30, 5, 3
+    x = _logits(V, n, d, B, "bf16", 11)
+    x[1] = 0
+    x[1, ..., 7] = 60.0                     # one token has all of the probability: E grows by one node a step, of which nearly none adds
+    ts = api.TreeStream(B, V, k, n, d, api.OT_BF16, "cuda")
+    counts = []
+    for t in range(d):
+        ts.expand(x[:, t])
+        e, go = ts.e_sub(1.0)
+        torch.cuda.synchronize()
+        counts.append((ts.frontier_count.tolist(), go.tolist()))
+    tree, steps, _ = api.build_tree_adaptive(x, k, n, d, 1.0)
+    got = ts.finalize()
+    torch.cuda.synchronize()
+    for b in range(B):
+        for t in range(d):
+            assert (counts[t][0][b] == 0) == (t >= int(steps[b])), (b, t, counts, steps)
+    for f in ("token", "parent", "depth", "mask", "n_out"):
+        assert torch.equal(getattr(got, f), getattr(tree, f)), f
