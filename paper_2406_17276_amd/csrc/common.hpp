@@ -176,6 +176,20 @@ template <int DT> struct VecOf {
     }
 };
 
+// max of three as one instruction whether or not this file honours NaNs (which otherwise costs a quieting instruction per operand)
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+template <int N> __device__ __forceinline__ float max_of(const float (&x)[N]) {
+    static_assert(N % 2 == 0, "pairs");
+    float v = max3(x[0], x[0], x[1]);
+#pragma unroll
+    for (int c = 2; c < N; c += 2) v = max3(v, x[c], x[c + 1]);
+    return v;
+}
+
 // DPP moves inside a 64-lane wavefront (GCN/CDNA encodings).
 // BOUND (bound_ctrl): a lane whose source does not exist reads 0 instead of keeping `old`.  The quad and mirror
 // permutations have a source for every lane, so the flag changes nothing there -- except that the compiler may

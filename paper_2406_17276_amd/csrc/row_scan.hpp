@@ -61,20 +61,6 @@ __device__ __forceinline__ int ordered(float v) {
     return i ^ ((i >> 31) & 0x7fffffff);
 }
 
-// max of three as one instruction whether or not this file honours NaNs (which otherwise costs a quieting instruction per operand)
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-template <int N> __device__ __forceinline__ float max_of(const float (&x)[N]) {
-    static_assert(N % 2 == 0, "pairs");
-    float v = max3(x[0], x[0], x[1]);
-#pragma unroll
-    for (int c = 2; c < N; c += 2) v = max3(v, x[c], x[c + 1]);
-    return v;
-}
-
 // max over groups of G consecutive lanes (1, 4, 8 or 16), result in every lane of the group
 template <int G>
 __device__ __forceinline__ float group_max(float v) {

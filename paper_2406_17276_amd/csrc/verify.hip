@@ -230,13 +230,18 @@ __global__ __launch_bounds__(NT) void verify_greedy_kernel(const VerifyKArgs a) 
     if (wave == 0) publish_and_walk(a, b, j, s_tok < row.len ? s_tok : 0, lane);     // (a row of NaNs only: token 0)
 }
 
-// inclusive prefix sum over the lanes of a wavefront
-__device__ __forceinline__ double wave_scan_f64(double v, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const double t = __shfl_up(v, o);
-        if (lane >= o) v += t;
-    }
+// inclusive prefix sum over the lanes of a wavefront, as wave_incl_scan (lane exchanges through LDS instead: 800 cycles, not 200)
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ double dpp_zero_d(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xf, false));
+}
+__device__ __forceinline__ double wave_scan_f64(double v) {
+    v += dpp_zero_d<0x111, 0xf>(v);                           // row_shr 1, 2, 4, 8
+    v += dpp_zero_d<0x112, 0xf>(v);
+    v += dpp_zero_d<0x114, 0xf>(v);
+    v += dpp_zero_d<0x118, 0xf>(v);
+    v += dpp_zero_d<DPP_ROW_BCAST15, 0xa>(v);
+    v += dpp_zero_d<DPP_ROW_BCAST31, 0xc>(v);
     return v;
 }
 
@@ -247,7 +252,17 @@ __device__ __forceinline__ double wave_scan_f64(double v, int lane) {
 // The reference of a segment is the wavefront's maximum so far: no term exceeds 1, whatever the temperature, and the terms
 // that matter have exponents near 0, which fp32 rounds least.
 constexpr int kMaxSeg = 512;
-__device__ __forceinline__ float sample_term(float x, float ref, float c) { return __builtin_amdgcn_exp2f((x - ref) * c); }
+// The bound, beside the memory, are the vector ALU's cycles (976 rows of 32000 bf16 at four a compute unit: 344 cycles per 64
+// vectors before, 270 now): the reference is carried as the exponent rc = fl(ref c), so that a term is one multiply-add and the
+// rounding of rc cancels.  Beyond 2^20 (vanishing temperatures, extreme logits), where that rounding is more than a sixteenth of
+// an exponent, the difference is taken first.
+struct Term {
+    float ref, c, rc;
+    bool fine;
+    __device__ __forceinline__ Term(float ref_, float c_) : ref(ref_), c(c_), rc(ref_ * c_) { fine = fabsf(rc) <= 0x1p20f; }
+    __device__ __forceinline__ float operator()(float x) const { return __builtin_amdgcn_exp2f(fine ? fmaf(x, c, -rc) : (x - ref) * c); }
+    __device__ __forceinline__ double exponent() const { return fine ? (double)rc : (double)ref * (double)c; }
+};
 template <int DT, int NT>
 __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) {
     constexpr int VEC = Row<DT>::VEC, PER_MAX = kMaxSeg / 64 + 1;    // (the longest row may start inside a vector)
@@ -278,14 +293,17 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
                 float x[VEC];
                 VecOf<DT>::unpack(w[i], x);
                 if (row.edge(v, NT)) row.mask(x, v + tid);
-                float q = x[0];
-#pragma unroll
-                for (int c = 1; c < VEC; ++c) q = fmaxf(q, x[c]);
+                const float q = max_of(x);                           // (NaN: the vector weighs nothing whatever the reference is)
                 if (__any(q > ref)) ref = wave_max_f(q);
-                const float r = ref == -INFINITY ? 0.f : ref;        // (no logit yet: every term is 0)
+                const Term term(ref == -INFINITY ? 0.f : ref, a.c);  // (no logit yet: every term is 0)
                 float e = 0.f;
+                if (term.fine) {
 #pragma unroll
-                for (int c = 0; c < VEC; ++c) e += sample_term(x[c], r, a.c);
+                    for (int c = 0; c < VEC; ++c) e += term(x[c]);
+                } else {
+#pragma unroll 1
+                    for (int c = 0; c < VEC; ++c) e += term(x[c]);
+                }
                 s_e[v + tid] = fmaxf(e, 0.f);                        // (a vector with a NaN weighs nothing)
                 if (lane == 0) s_ref[seg] = ref;
             }
@@ -321,19 +339,20 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
     M = wave_max_f(M);
     int truth = 0;                                                   // no finite logit in the row: nothing to draw from
     if (M != -INFINITY) {
+        const double top = Term(M, a.c).exponent();
         double sc[PER_MAX], wt[PER_MAX], lane_sum = 0.0;
 #pragma unroll
         for (int i = 0; i < PER_MAX; ++i) {
             sc[i] = wt[i] = 0.0;
             if (i < per) {
                 // weight of the segment relative to the largest reference (double exp2: relative error 1e-16)
-                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2(((double)ms[i] - (double)M) * (double)a.c);
+                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2(Term(ms[i], a.c).exponent() - top);
                 wt[i] = ms[i] == -INFINITY ? 0.0 : s_seg[lane * per + i] * sc[i];
                 lane_sum += wt[i];
             }
         }
-        const double incl = wave_scan_f64(lane_sum, lane);
-        const double target = (double)u * __shfl(incl, 63);
+        const double incl = wave_scan_f64(lane_sum);
+        const double target = (double)u * rl_d(incl, 63);
         // first lane whose segments reach past the target; by rounding there may be none: the last lane with weight
         const u64 past = __ballot(incl > target), any = __ballot(lane_sum > 0.0);
         if (past || any) {
@@ -353,25 +372,29 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
                 }
                 if (!found) before += wt[i];
             }
-            seg = __shfl(seg, Ls);
-            mseg = __shfl(mseg, Ls);
-            rs = __shfl(rs, Ls);
-            // inside the segment: the vector
+            seg = rl(seg, Ls);
+            mseg = rl_f(mseg, Ls);
+            rs = rl_d(rs, Ls);
+            // inside the segment: the vector (all of them are asked for while it is looked for)
             const int v = seg * 64 + lane;
+            const u32x4 mine = row.load(v);
             const double e = v < row.nvec ? (double)s_e[v] : 0.0;
-            const double incl_e = wave_scan_f64(e, lane);
+            const double incl_e = wave_scan_f64(e);
             const u64 past_e = __ballot(incl_e > rs), any_e = __ballot(e > 0.0);
             const int Le = past_e ? __ffsll((long long)past_e) - 1 : max(63 - __clzll((long long)any_e), 0);
             // inside the vector: the element (every lane does the same)
-            const double start = __shfl(incl_e - e, Le);
+            const double start = rl_d(incl_e - e, Le);
+            u32x4 found_vec;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) found_vec[i] = (unsigned)rl((int)mine[i], Le);
             float x[VEC];
-            VecOf<DT>::unpack(row.load(seg * 64 + Le), x);
+            VecOf<DT>::unpack(found_vec, x);
             row.mask(x, seg * 64 + Le);
             double acc = start;
             int k = -1, lastk = 0;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
-                const float p = sample_term(x[i], mseg, a.c);
+                const float p = Term(mseg, a.c)(x[i]);
                 acc += (double)p;
                 if (p > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
             }
