@@ -140,6 +140,48 @@ __device__ void finalize_tree(const SelKArgs& a, const Pool& P, int steps, int b
             if (t > 0) my_pi[t] = P.oidx[(t - 1) * NT + P.par[t * NT + tid]];
         }
     }
+    if (SINGLE) {
+        // n <= 64: node i becomes lane i (tables by output index in place of the mask rows and the keys).  Every round doubles
+        // the stretch of a root path that a mask holds: the mask of the node at its end is added, and that node's end is the
+        // new one.  (Layer by layer, with a trip to LDS each, and two trips to memory for the layers above: 9.6 us for ten
+        // layers of 50 nodes, now 8.5.)
+        int* const r_tok = (int*)P.mrow;
+        int* const r_par = r_tok + NT;
+        int* const r_dep = r_par + NT;
+        double* const r_key = P.key;
+#pragma unroll
+        for (int t = 0; t < DMAX; ++t)
+            if (t < steps && ((sel >> t) & 1u)) {
+                const int i = my_i[t];
+                r_key[i] = pk[t]; r_tok[i] = P.tok[t * NT + tid]; r_par[i] = my_pi[t]; r_dep[i] = t + 1;
+            }
+        lds_sync<SINGLE>();
+        const bool node = tid < n_out;
+        const double key = node ? r_key[tid] : -INFINITY;
+        const int par = node ? r_par[tid] : -1;
+        u64 row = node ? 1ull << tid : 0ull;
+        int up = par;
+        while (__any(up >= 0)) {
+            const int at = max(up, 0);
+            const u64 above = (u64)(unsigned)__shfl((int)(row >> 32), at) << 32 | (unsigned)__shfl((int)row, at);
+            const int next = __shfl(up, at);
+            if (up >= 0) { row |= above; up = next; }
+        }
+        if (tid < n) {
+            const size_t o = (size_t)b * n + tid;
+            a.out.token[o] = node ? r_tok[tid] : -1;
+            a.out.parent[o] = par;
+            a.out.depth[o] = node ? r_dep[tid] : 0;
+            a.out.score[o] = (float)key;
+            a.out.mask[o] = row;
+        }
+        const double e = wave_sum_d(node ? exp(key) : 0.0);            // E = sum of p^ (Eq. 3)
+        if (tid == 0) {
+            a.out.expect[b] = e;
+            a.out.n_out[b] = n_out;
+        }
+        return;
+    }
     // ancestor masks, layer by layer (a parent's row is complete before its children read it), and
     // the per-node outputs.  The key region is free again: it collects log p^ by output index.
     const size_t ob = (size_t)b * n;
@@ -201,7 +243,7 @@ __global__ __launch_bounds__(256) void tree_finalize_kernel(const SelKArgs a) {
     const Pool P = carve_pool(smem, a.depth, NT, DMAX, 0);
     const size_t pb = (size_t)b * a.depth * n;
     double lo0 = nan_d();
-    constexpr int BATCH = 8;                    // layers requested at once
+    constexpr int BATCH = DMAX < 16 ? DMAX : 16;   // layers requested at once
 #pragma unroll
     for (int t0 = 0; t0 < DMAX; t0 += BATCH) {
         if (t0 >= a.step) break;
@@ -394,7 +436,9 @@ int launch_tree_esub(const SelectGeometry& g, int steps_done, double delta, cons
     a.step = steps_done; a.delta = delta; a.e_sub = e_sub; a.go_on = go_on;
     const int NT = threads_for(g.n);
     if (NT == 64) {
+        if (steps_done <= 4) return launch_esub_t<4, true>(a, g.batch, NT, s);
         if (steps_done <= 8) return launch_esub_t<8, true>(a, g.batch, NT, s);
+        if (steps_done <= 12) return launch_esub_t<12, true>(a, g.batch, NT, s);
         if (steps_done <= 16) return launch_esub_t<16, true>(a, g.batch, NT, s);
         return launch_esub_t<32, true>(a, g.batch, NT, s);
     }
