@@ -1200,7 +1200,9 @@ __global__ __launch_bounds__(VAR == 2 ? 512 : 256) __attribute__((amdgpu_waves_p
 // shorten: 33 rows over 128 keys of 128 13.4 -> 16.8 us, the longest loss seen over 88 shapes but for 512 workgroups of one
 // row and one key each (9 -> 15 us).
 template <int D, int QB, int KS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(const AttnKArgs a) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_f32_kernel(
+    const int32_t* a_prefix_len, const uint64_t* a_mask, const void* a_Q, const int a_splits, const unsigned a_inv_splits,
+    const int a_kv_heads, const unsigned a_inv_kv_heads, const int a_n, const unsigned a_inv_n, const AttnKArgs a) {
     static_assert(QB * KS == 8, "eight wavefronts");
     constexpr int NT = 512, ROWS = 32 * QB, J = D / 8, EV = D / 32, QST = D + 4;
     typedef float fv __attribute__((ext_vector_type(EV)));
@@ -1212,20 +1214,37 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int qb = wave % QB, ks = wave / QB;
     const int xcd = blockIdx.x & 7, rb = blockIdx.x >> 3;            // numbering: see the bf16 kernel
     const int unit = blockIdx.y * 8 + xcd;
-    if (unit >= a.batch * a.kv_heads * a.splits) return;
-    const int bz = unit / a.splits, split = unit - bz * a.splits;
-    const int b = bz / a.kv_heads, hk = bz - b * a.kv_heads;
-    const int n = a.n, rows_all = a.g * n;
-    const int L = clamp_len(a.prefix_len[b], a.max_prefix);
-    if (tid == 0 && hk == 0 && split == 0 && rb == 0) report_clamp(a.counters, a.prefix_len[b], a.max_prefix);
+    if (unit >= a.batch * a_kv_heads * a_splits) return;
+    const int bz = fast_div(unit, a_splits, a_inv_splits), split = unit - bz * a_splits;
+    const int b = fast_div(bz, a_kv_heads, a_inv_kv_heads), hk = bz - b * a_kv_heads;
+    const int L_raw = a_prefix_len[b];
+    const int n = a_n, rows_all = a.g * n;
+    // Q is asked for first, from the arguments that are in registers at the start, and without integer divisions: with Q last and
+    // arguments from memory 13 x 16 KV heads of 1024 rows, 253 keys of 128 363 -> 343 us, 14 x 2 of 944 rows 95 -> 88, 4 heads of 16
+    // rows, 144 keys of 64 10.05 -> 9.86
+    constexpr int QI = ROWS * D / 4 / NT;
+    f32x4 qr[QI];
+#pragma unroll
+    for (int i = 0; i < QI; ++i) {
+        const int rr = (i * NT + tid) / (D / 4), cc = ((i * NT + tid) % (D / 4)) * 4, r = min(rb * ROWS + rr, rows_all - 1);
+        const int hh = fast_div(r, n, a_inv_n);
+        qr[i] = *(const f32x4*)((const float*)a_Q + (long long)b * a.qs[0] + (long long)(hk * a.g + hh) * a.qs[1] +
+                                (long long)(r - hh * n) * a.qs[2] + cc);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const int L = clamp_len(L_raw, a.max_prefix);
     const int pblocks = (L + 31) / 32, T = pblocks + (a.nk + 31) / 32;
-    const int t0 = (int)((long long)T * split / a.splits), t1 = (int)((long long)T * (split + 1) / a.splits);
+    int t0 = 0, t1 = T;
+    if (a_splits > 1) {
+        t0 = (int)((long long)T * split / a_splits);
+        t1 = (int)((long long)T * (split + 1) / a_splits);
+    }
 
     const int rho = rb * ROWS + qb * 32 + l32;                       // packed row inside the KV head
     const bool row_ok = rho < rows_all;
     const int rho_c = row_ok ? rho : rows_all - 1;
-    const int head = rho_c / n, hq = hk * a.g + head, node = rho_c - head * n;
-    const uint64_t* const mask_row = a.mask + ((long long)b * n + node) * a.W;
+    const int head = fast_div(rho_c, n, a_inv_n), hq = hk * a.g + head, node = rho_c - head * n;
+    const uint64_t* const mask_row = a_mask + ((long long)b * n + node) * a.W;
     const float* const kp = (const float*)a.Kp + (long long)b * a.kps[0] + (long long)hk * a.kps[1];
     const float* const vp = (const float*)a.Vp + (long long)b * a.vps[0] + (long long)hk * a.vps[1];
     const float* const kt = (const float*)a.Kt + (long long)b * a.kts[0] + (long long)hk * a.kts[1];
@@ -1252,18 +1271,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         mword = tree ? mask_row[key0 >> 6] : 0ull;
     };
     int t = t0 + ks;
-    if (t < t1) { load_k(t); load_v(t); }
-    for (int i = tid; i < ROWS * D / 4; i += NT) {
-        const int rr = i / (D / 4), cc = (i % (D / 4)) * 4, r = rb * ROWS + rr;
-        f32x4 w = {0.f, 0.f, 0.f, 0.f};
-        if (r < rows_all) {
-            const int hh = r / n;
-            w = *(const f32x4*)((const float*)a.Q + (long long)b * a.qs[0] + (long long)(hk * a.g + hh) * a.qs[1] +
-                                (long long)(r - hh * n) * a.qs[2] + cc);
-        }
-        *(f32x4*)(s_f + rr * QST + cc) = w;
+    if (t < t1) { load_k(t); load_v(t); }                            // (slices that only wait must not ask for blocks: 2 to 9 % slower)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < QI; ++i) {
+        const int rr = (i * NT + tid) / (D / 4), cc = ((i * NT + tid) % (D / 4)) * 4;
+        *(f32x4*)(s_f + rr * QST + cc) = rb * ROWS + rr < rows_all ? qr[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    __syncthreads();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // (K and V stay under way)
+    if (tid == 0 && hk == 0 && split == 0 && rb == 0) report_clamp(a.counters, L_raw, a.max_prefix);
 
     const float c = a.scale_log2;
     float ref = -INFINITY, l_run = 0.f;                              // ref: see the bf16 kernel
@@ -1638,6 +1654,7 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
     a.row_blocks = plan.row_blocks;
     auto magic = [](int d) { return d <= 1 ? 0u : (unsigned int)((0x100000000ull + (unsigned)d - 1) / (unsigned)d); };
     a.inv_splits = magic(a.splits); a.inv_kv_heads = magic(a.kv_heads); a.inv_n = magic(a.n);
+#define OT_ATTN_ARGS a.prefix_len, a.mask, a.Q, a.splits, a.inv_splits, a.kv_heads, a.inv_kv_heads, a.n, a.inv_n, a
     if (p.dtype == OT_BF16) {
         const int rows_wg = plan.rows;
         const long long units = (long long)p.batch * p.kv_heads * plan.splits;
@@ -1647,7 +1664,6 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
         if (plan.splits > 1 && (long long)p.batch * p.kv_heads * plan.row_blocks * 4 > OT_ATTN_STATUS_OFFSET)
             return OT_ERR_UNSUPPORTED;      // cannot happen: splits > 1 only with few workgroups
         const dim3 grid((unsigned)(8 * plan.row_blocks), (unsigned)unit_groups);
-#define OT_ATTN_ARGS a.prefix_len, a.mask, a.Q, a.splits, a.inv_splits, a.kv_heads, a.inv_kv_heads, a.n, a.inv_n, a
 #define OT_ATTN_LAUNCH(DD, VV, K8, BB)                                                                       \
     do {                                                                                                   \
         const int nbuf = tile_buffers(VV, K8), nwaves = (VV) == 2 ? 8 : 4; \
@@ -1673,7 +1689,6 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
         else     { if (p.head_dim == 128) OT_ATTN_PICK(128, false); else OT_ATTN_PICK(64, false); }
 #undef OT_ATTN_PICK
 #undef OT_ATTN_LAUNCH
-#undef OT_ATTN_ARGS
     } else {
         const int rows_wg = plan.rows;
         const long long unit_groups = ((long long)p.batch * p.kv_heads * plan.splits + 7) / 8;
@@ -1688,8 +1703,8 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
         if (lds > 64 * 1024)                                                                                           \
             OT_HIP_CHECK(hipFuncSetAttribute((const void*)attn_f32_kernel<DD, QQ, KK>,                                  \
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));                   \
-        if (ev0 || ev1) hipExtLaunchKernelGGL((attn_f32_kernel<DD, QQ, KK>), grid, dim3(512), lds, s, ev0, ev1, 0, a);  \
-        else hipLaunchKernelGGL((attn_f32_kernel<DD, QQ, KK>), grid, dim3(512), lds, s, a);                             \
+        if (ev0 || ev1) hipExtLaunchKernelGGL((attn_f32_kernel<DD, QQ, KK>), grid, dim3(512), lds, s, ev0, ev1, 0, OT_ATTN_ARGS);  \
+        else hipLaunchKernelGGL((attn_f32_kernel<DD, QQ, KK>), grid, dim3(512), lds, s, OT_ATTN_ARGS);                             \
     } while (0)
 #define OT_F32_PICK(DD)                                                                                                \
     do {                                                                                                               \
@@ -1701,6 +1716,7 @@ int launch_tree_attention(const ot_attn_params& p, const AttnPlan& plan, const v
 #undef OT_F32_PICK
 #undef OT_F32_LAUNCH
     }
+#undef OT_ATTN_ARGS
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
