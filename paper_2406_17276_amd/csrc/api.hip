@@ -259,7 +259,7 @@ int ot_tree_expand(const ot_build_params* p, int32_t step, const void* rows, int
     sg.stride_seq = stride_seq; sg.stride_depth = 0; sg.stride_row = stride_row;
     SelectGeometry g = select_geometry(*p, f);
     g.rows_per_seq = f.F[step];
-    if (fuse_expand(sg, rows))
+    if (fuse_expand(sg, p->n, rows))
         return launch_fused_expand(sg, g, rows, step, ws, frontier_token, frontier_parent_slot, frontier_count, s);
     st = launch_row_scan(sg, rows, ws, s, nullptr, nullptr, true);      // rows of frozen sequences are not read
     if (st != OT_OK) return st;

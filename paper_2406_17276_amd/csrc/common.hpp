@@ -102,7 +102,7 @@ int launch_fused_build(const ScanGeometry& sg, const SelectGeometry& g, const vo
 int launch_tree_step(const SelectGeometry& g, int step, const BuildWorkspace& ws, int32_t* frontier_token,
                      int32_t* frontier_parent, int32_t* frontier_count, hipStream_t s);
 // The scan of a step's rows and the step as one launch (tree_expand.hip)
-bool fuse_expand(const ScanGeometry& sg, const void* rows);
+bool fuse_expand(const ScanGeometry& sg, int n, const void* rows);
 int launch_fused_expand(const ScanGeometry& sg, const SelectGeometry& g, const void* rows, int step, const BuildWorkspace& ws,
                         int32_t* frontier_token, int32_t* frontier_parent, int32_t* frontier_count, hipStream_t s);
 int launch_tree_finalize(const SelectGeometry& g, int steps_done, const BuildWorkspace& ws, const ot_tree_out& out,

@@ -14,12 +14,11 @@ namespace {
 struct ExpandArgs {
     ScanKArgs scan;
     SelKArgs step;
-    int threads;                       // of the step
 };
 
 // Rows of a sequence are counted in its flag of the adaptive depth, by twos: 0 is a stopped sequence, 1 + 2 m one that goes on, m
 // of whose rows are done.  The workgroup that finds all others done sets it to 1 again and takes the step.
-template <int DT, int NT, int VPL, bool KEEP, int KMAX, bool SINGLE>
+template <int DT, int NT, int VPL, bool KEEP, int KMAX>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void tree_expand_kernel(
     const void* logits, const long long stride_seq, const long long stride_row, const int vocab, const int part_geom, const int F,
     const ExpandArgs a) {
@@ -48,40 +47,37 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         if (s_last) put<true>(flag, 1);
     }
     __syncthreads();
-    if (!s_last || tid >= a.threads) return;
-    draft_step<KMAX, SINGLE, true>(a.step, b, a.threads, (double*)smem);
+    if (!s_last || tid >= 64) return;
+    draft_step<KMAX, true, true>(a.step, b, 64, (double*)smem);
 }
 
-template <int DT, int NT, int VPL, bool KEEP, int KMAX, bool SINGLE>
+template <int DT, int NT, int VPL, bool KEEP, int KMAX>
 int launch_t(const ScanGeometry& g, const void* rows, const ExpandArgs& a, hipStream_t s) {
-    const size_t lds = std::max(sizeof(ScanShared<NT, KEEP>), (size_t)KMAX * a.threads * 8);
-    hipLaunchKernelGGL((tree_expand_kernel<DT, NT, VPL, KEEP, KMAX, SINGLE>), dim3((unsigned)(g.batch * g.rows)), dim3(NT), lds, s, rows,
+    const size_t lds = std::max(sizeof(ScanShared<NT, KEEP>), (size_t)KMAX * 64 * 8);
+    hipLaunchKernelGGL((tree_expand_kernel<DT, NT, VPL, KEEP, KMAX>), dim3((unsigned)(g.batch * g.rows)), dim3(NT), lds, s, rows,
                        g.stride_seq, g.stride_row, g.vocab, 1 | (g.vocab << 4), g.rows, a);
     OT_HIP_CHECK(hipGetLastError());
     return OT_OK;
 }
-template <int DT, int NT, int VPL, bool KEEP, bool SINGLE>
-int launch_k(const ScanGeometry& g, const void* rows, const ExpandArgs& a, hipStream_t s) {
-    if (a.step.k <= 4) return launch_t<DT, NT, VPL, KEEP, 4, SINGLE>(g, rows, a, s);
-    if (a.step.k <= 8) return launch_t<DT, NT, VPL, KEEP, 8, SINGLE>(g, rows, a, s);
-    if (a.step.k <= 10) return launch_t<DT, NT, VPL, KEEP, 10, SINGLE>(g, rows, a, s);
-    return launch_t<DT, NT, VPL, KEEP, 16, SINGLE>(g, rows, a, s);
-}
 template <int DT, int NT, int VPL, bool KEEP>
 int launch_n(const ScanGeometry& g, const void* rows, const ExpandArgs& a, hipStream_t s) {
-    return a.threads == 64 ? launch_k<DT, NT, VPL, KEEP, true>(g, rows, a, s) : launch_k<DT, NT, VPL, KEEP, false>(g, rows, a, s);
+    if (a.step.k <= 4) return launch_t<DT, NT, VPL, KEEP, 4>(g, rows, a, s);
+    if (a.step.k <= 8) return launch_t<DT, NT, VPL, KEEP, 8>(g, rows, a, s);
+    if (a.step.k <= 10) return launch_t<DT, NT, VPL, KEEP, 10>(g, rows, a, s);
+    return launch_t<DT, NT, VPL, KEEP, 16>(g, rows, a, s);
 }
 
 }  // namespace
 
-// Where one launch is faster: called one by one, wherever it applies (ten steps of 50 rows of 32000, with masks and E_sub, 193 -> 158 us:
-// the host's launches).  Replayed from a graph, up to a row per compute unit: the same ten steps 149 -> 141 us, 8 sequences of 7 nodes
-// 185 -> 171, 15 of 6 168 -> 158, the others within 3 %; with more rows the step's registers leave the scan too few wavefronts (375 rows
-// of 4736 155 -> 166, 966 of 3392 fp32 92 -> 98).
-bool fuse_expand(const ScanGeometry& sg, const void* rows) {
+// Where one launch is faster: steps of one wavefront (n <= 64), with a row per compute unit at most.  Called one by one, ten steps of 50
+// rows of 32000 with masks and E_sub 193 -> 156 us (the host's launches), seven other loops 1.02 to 1.2 times as fast; five loops of
+// 74 to 239 nodes 0.4 to 1 % slower.  Replayed from a graph, the same ten steps 149 -> 141 us, 8 sequences of 7 nodes 185 -> 171,
+// 15 of 6 168 -> 158, the others within 3 %; with more rows the step's registers leave the scan too few wavefronts (375 rows of 4736
+// 155 -> 166, 966 of 3392 fp32 92 -> 98).
+bool fuse_expand(const ScanGeometry& sg, int n, const void* rows) {
     const ScanForm f = scan_form(sg, rows);
     if (f.parts > 1 || f.threads == 64 || (f.threads == 256 && !f.keep)) return false;
-    return (long long)sg.batch * sg.rows <= 256;
+    return n <= 64 && (long long)sg.batch * sg.rows <= 256;
 }
 
 int launch_fused_expand(const ScanGeometry& sg, const SelectGeometry& g, const void* rows, int step, const BuildWorkspace& ws,
@@ -93,7 +89,6 @@ int launch_fused_expand(const ScanGeometry& sg, const SelectGeometry& g, const v
     a.step = make_args(g, ws);
     a.step.step = step;
     a.step.frontier_token = frontier_token; a.step.frontier_parent = frontier_parent; a.step.frontier_count = frontier_count;
-    a.threads = threads_for(g.n);
     const ScanForm f = scan_form(sg, rows);
     auto launch = [&](auto dt) {
         constexpr int DT = decltype(dt)::value, KV = 32 / VecOf<DT>::N;

@@ -14,7 +14,7 @@
 // The greedy form needs no exponentials and, since the threshold of the builder's scan would be the maximum itself, no
 // candidate lists.  Measured (MI355X, verification and append together; before: scan with statistics + walk + append,
 // segment sums + pick + walk + append): one sequence of 51 rows of 32000, greedy 14.3 -> 10.5 us; 16 x 61 rows, sampled 28.0 ->
-// 20.6 us (its rows end 7 to 13.5 us after the start, 62 MB; the draw takes 3 us behind the last, word and walk 1.5).
+// 20.7 us (its rows end 7 to 13.5 us after the start, 62 MB; the draw takes 3 us behind the last, word and walk 1.5).
 #include <string.h>
 
 #include <algorithm>
@@ -230,7 +230,10 @@ __global__ __launch_bounds__(NT) void verify_greedy_kernel(const VerifyKArgs a) 
     if (wave == 0) publish_and_walk(a, b, j, s_tok < row.len ? s_tok : 0, lane);     // (a row of NaNs only: token 0)
 }
 
-// inclusive prefix sum over the lanes of a wavefront, as wave_incl_scan (lane exchanges by __shfl are trips to LDS)
+// inclusive prefix sum over the lanes of a wavefront, as wave_incl_scan (lane exchanges by __shfl are trips
+// to LDS: 31 x 156 rows of 1792 bf16 with the append 19.1 -> 18.3 us, 2 x 55 of 70400 fp32 17.3 -> 16.5.  Not kept: terms as one
+// multiply-add with the rounded product of reference and factor as exponent, and asking for the whole segment's vectors while the drawn
+// one is looked for: 4 % slower than before at short rows)
 template <int CTRL, int ROW_MASK> __device__ __forceinline__ double dpp_zero_d(double v) {
     return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xf, false),
                             __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xf, false));
@@ -252,16 +255,7 @@ __device__ __forceinline__ double wave_scan_f64(double v) {
 // The reference of a segment is the wavefront's maximum so far: no term exceeds 1, whatever the temperature, and the terms
 // that matter have exponents near 0, which fp32 rounds least.
 constexpr int kMaxSeg = 512;
-// The reference is carried as the exponent rc = fl(ref c), so that a term is one multiply-add with one rounding, and the
-// rounding of rc cancels.  Beyond 2^20 (vanishing temperatures, extreme logits), where that rounding is more than a sixteenth of
-// an exponent, the difference is taken first.  (With prefix sums that do not pass through LDS, 16 x 61 rows of 32000 21.0 -> 20.6 us.)
-struct Term {
-    float ref, c, rc;
-    bool fine;
-    __device__ __forceinline__ Term(float ref_, float c_) : ref(ref_), c(c_), rc(ref_ * c_) { fine = fabsf(rc) <= 0x1p20f; }
-    __device__ __forceinline__ float operator()(float x) const { return __builtin_amdgcn_exp2f(fine ? fmaf(x, c, -rc) : (x - ref) * c); }
-    __device__ __forceinline__ double exponent() const { return fine ? (double)rc : (double)ref * (double)c; }
-};
+__device__ __forceinline__ float sample_term(float x, float ref, float c) { return __builtin_amdgcn_exp2f((x - ref) * c); }
 template <int DT, int NT>
 __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) {
     constexpr int VEC = Row<DT>::VEC, PER_MAX = kMaxSeg / 64 + 1;    // (the longest row may start inside a vector)
@@ -292,17 +286,14 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
                 float x[VEC];
                 VecOf<DT>::unpack(w[i], x);
                 if (row.edge(v, NT)) row.mask(x, v + tid);
-                const float q = max_of(x);                           // (NaN: the vector weighs nothing whatever the reference is)
-                if (__any(q > ref)) ref = wave_max_f(q);
-                const Term term(ref == -INFINITY ? 0.f : ref, a.c);  // (no logit yet: every term is 0)
-                float e = 0.f;
-                if (term.fine) {
+                float q = x[0];
 #pragma unroll
-                    for (int c = 0; c < VEC; ++c) e += term(x[c]);
-                } else {
-#pragma unroll 1
-                    for (int c = 0; c < VEC; ++c) e += term(x[c]);
-                }
+                for (int c = 1; c < VEC; ++c) q = fmaxf(q, x[c]);
+                if (__any(q > ref)) ref = wave_max_f(q);
+                const float r = ref == -INFINITY ? 0.f : ref;        // (no logit yet: every term is 0)
+                float e = 0.f;
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) e += sample_term(x[c], r, a.c);
                 s_e[v + tid] = fmaxf(e, 0.f);                        // (a vector with a NaN weighs nothing)
                 if (lane == 0) s_ref[seg] = ref;
             }
@@ -338,14 +329,13 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
     M = wave_max_f(M);
     int truth = 0;                                                   // no finite logit in the row: nothing to draw from
     if (M != -INFINITY) {
-        const double top = Term(M, a.c).exponent();
         double sc[PER_MAX], wt[PER_MAX], lane_sum = 0.0;
 #pragma unroll
         for (int i = 0; i < PER_MAX; ++i) {
             sc[i] = wt[i] = 0.0;
             if (i < per) {
                 // weight of the segment relative to the largest reference (double exp2: relative error 1e-16)
-                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2(Term(ms[i], a.c).exponent() - top);
+                sc[i] = ms[i] == -INFINITY ? 0.0 : exp2(((double)ms[i] - (double)M) * (double)a.c);
                 wt[i] = ms[i] == -INFINITY ? 0.0 : s_seg[lane * per + i] * sc[i];
                 lane_sum += wt[i];
             }
@@ -374,26 +364,22 @@ __global__ __launch_bounds__(NT) void verify_sample_kernel(const VerifyKArgs a) 
             seg = rl(seg, Ls);
             mseg = rl_f(mseg, Ls);
             rs = rl_d(rs, Ls);
-            // inside the segment: the vector (all of them are asked for while it is looked for)
+            // inside the segment: the vector
             const int v = seg * 64 + lane;
-            const u32x4 mine = row.load(v);
             const double e = v < row.nvec ? (double)s_e[v] : 0.0;
             const double incl_e = wave_scan_f64(e);
             const u64 past_e = __ballot(incl_e > rs), any_e = __ballot(e > 0.0);
             const int Le = past_e ? __ffsll((long long)past_e) - 1 : max(63 - __clzll((long long)any_e), 0);
             // inside the vector: the element (every lane does the same)
             const double start = rl_d(incl_e - e, Le);
-            u32x4 found_vec;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) found_vec[i] = (unsigned)rl((int)mine[i], Le);
             float x[VEC];
-            VecOf<DT>::unpack(found_vec, x);
+            VecOf<DT>::unpack(row.load(seg * 64 + Le), x);
             row.mask(x, seg * 64 + Le);
             double acc = start;
             int k = -1, lastk = 0;
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
-                const float p = Term(mseg, a.c)(x[i]);
+                const float p = sample_term(x[i], mseg, a.c);
                 acc += (double)p;
                 if (p > 0.f) { lastk = i; if (k < 0 && acc > rs) k = i; }
             }

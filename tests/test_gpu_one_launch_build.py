@@ -134,11 +134,12 @@ def _build_equal_eager(x, k, n, d, got):
 
 @pytest.mark.parametrize("V,k,n,d,B,dtype,ragged", [
     (1000, 4, 16, 4, 1, "f32", 0),          # steps of one launch: 256 threads a row
-    (8184, 16, 65, 5, 3, "bf16", 1),        # more than 64 nodes, more than ten candidates a node
+    (8184, 16, 64, 5, 3, "bf16", 1),        # the most nodes, more than ten candidates a node
+    (8184, 16, 65, 5, 3, "bf16", 1),        # 65 nodes: two launches a step
     (8192, 11, 64, 4, 4, "bf16", 0),        # 256 rows in the last steps: the most that go in one launch
     (8192, 8, 52, 4, 5, "bf16", 0),         # 260: two launches there
     (32000, 10, 50, 10, 1, "bf16", 0),      # 1024 threads
-    (9000, 16, 256, 4, 1, "f32", 0),        # 256 rows of 1024 threads, four wavefronts in the step
+    (9000, 4, 32, 5, 8, "f32", 0),          # 256 rows of 1024 threads
     (40000, 8, 20, 5, 4, "bf16", 0),        # 512 threads, rolling
     (131072, 12, 9, 3, 2, "bf16", 0),       # the longest row of one part
     (131080, 3, 9, 3, 2, "bf16", 0),        # two parts
