@@ -1219,19 +1219,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int b = fast_div(bz, a_kv_heads, a_inv_kv_heads), hk = bz - b * a_kv_heads;
     const int L_raw = a_prefix_len[b];
     const int n = a_n, rows_all = a.g * n;
-    // Q is asked for first, from the arguments that are in registers at the start, and without integer divisions: with Q last and
-    // arguments from memory 13 x 16 KV heads of 1024 rows, 253 keys of 128 363 -> 343 us, 14 x 2 of 944 rows 95 -> 88, 4 heads of 16
-    // rows, 144 keys of 64 10.05 -> 9.86
-    constexpr int QI = ROWS * D / 4 / NT;
-    f32x4 qr[QI];
-#pragma unroll
-    for (int i = 0; i < QI; ++i) {
-        const int rr = (i * NT + tid) / (D / 4), cc = ((i * NT + tid) % (D / 4)) * 4, r = min(rb * ROWS + rr, rows_all - 1);
-        const int hh = fast_div(r, n, a_inv_n);
-        qr[i] = *(const f32x4*)((const float*)a_Q + (long long)b * a.qs[0] + (long long)(hk * a.g + hh) * a.qs[1] +
-                                (long long)(r - hh * n) * a.qs[2] + cc);
-    }
-    __builtin_amdgcn_sched_barrier(0);
     const int L = clamp_len(L_raw, a.max_prefix);
     const int pblocks = (L + 31) / 32, T = pblocks + (a.nk + 31) / 32;
     int t0 = 0, t1 = T;
@@ -1271,6 +1258,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         mword = tree ? mask_row[key0 >> 6] : 0ull;
     };
     int t = t0 + ks;
+    // Q is asked for ahead of K and V: it goes to LDS while they are under way, and the scores wait for K alone.  With it the
+    // arguments that are in registers at the start, and no integer divisions: 13 x 16 KV heads of 1024 rows, 253 keys of 128 363 ->
+    // 342 us, 14 x 2 of 944 rows 94 -> 88, 4 heads of 16 rows, 144 keys of 64 9.87 -> 9.65 (ahead of the prefix length's use 15 x 8
+    // KV heads of 36 rows, 4313 keys of 64 96 -> 98 us, here 96)
+    constexpr int QI = ROWS * D / 4 / NT;
+    f32x4 qr[QI];
+#pragma unroll
+    for (int i = 0; i < QI; ++i) {
+        const int rr = (i * NT + tid) / (D / 4), cc = ((i * NT + tid) % (D / 4)) * 4, r = min(rb * ROWS + rr, rows_all - 1);
+        const int hh = fast_div(r, n, a_inv_n);
+        qr[i] = *(const f32x4*)((const float*)a_Q + (long long)b * a.qs[0] + (long long)(hk * a.g + hh) * a.qs[1] +
+                                (long long)(r - hh * n) * a.qs[2] + cc);
+    }
     if (t < t1) { load_k(t); load_v(t); }                            // (slices that only wait must not ask for blocks: 2 to 9 % slower)
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
