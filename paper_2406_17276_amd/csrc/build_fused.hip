@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
         // the drafting workgroup is gone
         ar.wait = false;
         ar.there = a.there + (size_t)b * rows;
-        const bool all = rows_there(ar, 0, tid & 63);
+        const bool all = take_over(ChipWave{tid & 63}, ar);
         __syncthreads();
         if (tid < 64) *over = all;
         __syncthreads();

@@ -31,6 +31,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "arrivals.hpp"
 
 namespace ot {
 namespace {
@@ -109,7 +110,7 @@ struct alignas(16) Shared {
     Hist pool;                         // pool nodes
     struct { double key; int idx, pad; } list[kList + 4];
     int lcnt;
-    int gave_up;                       // kArrive: 1: too many polls; 2: and rows are missing
+    Quit quit;                         // kArrive
     u64 mn, mx;
     int wc[NW * kPoolPerThread];
     double red[NW];
@@ -239,54 +240,22 @@ __device__ __forceinline__ unsigned pool_best(const double* pkey, int pool, int 
 //   kArrive   workgroups of the same launch, which publish them one by one (build_fused.hip)
 enum Source { kStep, kStaged, kArrive };
 
-// kArrive.  A row's results are in memory once its word is kRowThere.  The workspace needs no preparation: no other value
-// counts, and the workgroup that has drafted the tree clears the words of its sequence again, when all of them are there.
-// A drafting workgroup does not wait for ever (rows of this launch might not get a place on the chip while other launches'
-// drafting workgroups wait there): after `spin` polls it marks the words of all rows that are missing with kRowLate and ends.
-// A workgroup that finds that mark as it publishes its row looks whether all rows are there now -- at least the last one sees
-// them all -- and then drafts the tree from the beginning.  Should two draft it, both write the same.
-constexpr u64 kRowThere = 0x9d3f5be1c7604a2bull, kRowLate = 0x6b1e88d2f0957c43ull;
-struct Arrivals {
-    u64* there;                        // [rows] of this sequence
-    int rows, spin;
-    bool wait;                         // false: all rows are there
+// A wavefront of the GPU (arrivals.hpp)
+struct ChipWave {
+    static constexpr int kLanes = 64;
+    int lane;
+    __device__ __forceinline__ u64 load(const u64* p) const { return ot::get<true>(p); }
+    __device__ __forceinline__ void store(u64* p, u64 v) const { ot::put<true>(p, v); }
+    __device__ __forceinline__ bool swap_if(u64* p, u64& v, u64 x) const {
+        return __hip_atomic_compare_exchange_strong(p, &v, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ void stores_done() const { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+    __device__ __forceinline__ bool all(bool ok) const { return __all(ok); }
+    __device__ __forceinline__ void pause() const { __builtin_amdgcn_s_sleep(1); }
+    __device__ __forceinline__ void set(short& flag, int v) const { flag = (short)v; }
+    __device__ __forceinline__ int get(const short& flag) const { return flag; }
+    __device__ __forceinline__ void barrier() const { lds_barrier(); }
 };
-// All rows from `first` on, as seen by one wavefront
-__device__ __forceinline__ bool rows_there(const Arrivals& ar, int first, int lane) {
-    bool ok = true;
-    for (int r0 = first; r0 < ar.rows; r0 += 8 * 64) {        // eight loads per trip to memory
-        u64 w[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) w[u] = get<true>(ar.there + min(r0 + 64 * u + lane, ar.rows - 1));
-#pragma unroll
-        for (int u = 0; u < 8; ++u) ok = ok && w[u] == kRowThere;
-    }
-    return __all(ok);
-}
-// One wavefront: marks the rows that are missing, then looks whether all are there after all.  If not, those that are missing
-// now were missing before, so all of them are marked, and the last of them to come finds the others there.  (Without the
-// second look a row could come, unmarked, between the marks and the visits of rows that found it missing.)
-__device__ __forceinline__ bool leave_or_all_there(const Arrivals& ar, int lane) {
-    for (int r = lane; r < ar.rows; r += 64) {
-        u64 v = get<true>(ar.there + r);
-        while (v != kRowThere)                                // (a word changes twice at most while this looks at it)
-            if (__hip_atomic_compare_exchange_strong(ar.there + r, &v, kRowLate, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    return rows_there(ar, 0, lane);
-}
-// One wavefront, tree drafted from the rows before `first`: clears the words
-__device__ __forceinline__ void clear_arrivals(const Arrivals& ar, int first, int lane) {
-    int polls = 0;
-    while (ar.wait && !rows_there(ar, first, lane)) {
-        if (++polls > ar.spin) {
-            if (leave_or_all_there(ar, lane)) break;
-            return;
-        }
-        __builtin_amdgcn_s_sleep(1);
-    }
-    for (int r = lane; r < ar.rows; r += 64) put<true>(ar.there + r, (u64)0);
-}
 
 // KPT candidates per thread.  ADAPT: Algorithm 1 with its stopping rule -- after every step E_sub(T, n) = sum of p^ over the n
 // best pool nodes, and drafting stops when E_sub - E <= delta.
@@ -354,6 +323,7 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
         for (int i = 0; i < KPT; ++i) cj[i] = (i * nt + tid) / k;
     }
     // kArrive: rows of the next step that this wavefront's candidates need; are they there (the same for the wavefront)
+    const ChipWave chip{lane};
     bool next_there = false;
     u64 word[KPT], word2[KPT];                                // words of the next step's rows, of those of the step after
     auto request = [&](u64 (&w)[KPT], int first, int count) {
@@ -366,36 +336,26 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
         for (int i = 0; i < KPT; ++i) ok = ok && w[i] == kRowThere;
         return (bool)__all(ok);
     };
-    // Rows whose words are requested: wait for them; too many polls: gave_up
-    auto poll = [&](int first, int count) {
+    // Rows of a step, whose words are requested: wait for them; too many polls: quit
+    auto poll = [&](int step, int first, int count) {
         int polls = 0;
         while (!here(word)) {
-            if (++polls > ar.spin) { s.gave_up = 1; return; }
+            if (++polls > ar.spin) { quit_waiting(chip, s.quit, step); return; }
             __builtin_amdgcn_s_sleep(1);
             request(word, first, count);
         }
     };
-    // Behind a barrier: some wavefront gave up.  False: another workgroup drafts the tree (the same for the workgroup).
-    auto on_alone = [&]() {
-        if (!leave_or_all_there(ar, lane)) s.gave_up = 2;
-        lds_barrier();
-        const int state = s.gave_up;
-        lds_barrier();                                        // everybody has looked
-        if (tid == 0) s.gave_up = 0;
-        ar.wait = false;
-        return state != 2;
-    };
     if (ARRIVE) {
-        if (tid == 0) s.gave_up = 0;
+        if (tid == 0) quit_none(chip, s.quit);
         lds_barrier();
         if (ar.wait) {
             request(word, 0, 1);
             if (t1 > 1) request(word2, 1, min(n, k));
-            poll(0, 1);
+            poll(0, 0, 1);
             next_there = t1 > 1 && here(word2);
         }
         lds_barrier();
-        if (s.gave_up && !on_alone()) return;
+        if (has_quit(chip, s.quit, 0) && !go_alone(chip, s.quit, ar)) return;
     }
     if (!STAGE) {
 #pragma unroll
@@ -543,14 +503,14 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
         if (ADAPT && tid == 0) s.lcnt = 0;
         if (ARRIVE && t + 1 < t1) {
             if (!fetched) {
-                poll(rs + F, Fn);
+                poll(t + 1, rs + F, Fn);
                 fetch();
             }
             next_there = ar.wait && t + 2 < t1 && here(word2);
         }
         lds_barrier();
-        if (ARRIVE && s.gave_up) {
-            if (!on_alone()) return;
+        if (ARRIVE && has_quit(chip, s.quit, t + 1)) {
+            if (!go_alone(chip, s.quit, ar)) return;
             if (t + 1 < t1) fetch();
         }
         arrived();
@@ -656,7 +616,7 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
             return;
         }
         if (wave > 1) {
-            if (ARRIVE && wave == 2) clear_arrivals(ar, seen, lane);
+            if (ARRIVE && wave == 2) clear_arrivals(chip, ar, seen);
             return;
         }
     }
@@ -701,7 +661,7 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
         if (a.seq_active) a.seq_active[b] = 0;
         if (ADAPT) { a.steps_used[b] = steps; a.e_sub[b] = E_sub; }
     }
-    if (ARRIVE && n > 64 && wave == nw - 1) clear_arrivals(ar, seen, lane);
+    if (ARRIVE && n > 64 && wave == nw - 1) clear_arrivals(chip, ar, seen);
 }
 
 }  // namespace

@@ -188,3 +188,18 @@ def test_a_stopped_sequence_stays_as_it_is_in_steps_of_one_launch():
             assert (counts[t][0][b] == 0) == (t >= int(steps[b])), (b, t, counts, steps)
     for f in ("token", "parent", "depth", "mask", "n_out"):
         assert torch.equal(getattr(got, f), getattr(tree, f)), f
+
+
+@pytest.mark.parametrize("V,k,n,d,B,dtype", [
+    (8184, 2, 200, 10, 2, "bf16"),          # seven steps that keep all of their candidates, and so have one barrier each
+    (9000, 4, 65, 6, 3, "f32"),             # 1024 threads; more than 64 nodes
+    (1000, 4, 16, 4, 1, "f32"),
+])
+def test_a_wait_that_is_given_up_at_any_step(V, k, n, d, B, dtype):
+    build = _Build(_logits(V, n, d, B, dtype, 17), k, n, d)
+    _, want = build(30000)
+    for polls in range(24):
+        print(V, k, n, d, B, dtype, "polls", polls, flush=True)
+        one, got = build(polls)
+        assert one == 1
+        assert _equal(got, want), polls
