@@ -10,12 +10,15 @@ typedef unsigned long long u64;
 // A row's results are in memory once its word is kRowThere.  The workspace needs no preparation: no other value
 // counts, and the workgroup that has drafted the tree clears the words of its sequence again, when all of them are there.
 // A drafting workgroup does not wait for ever (rows of this launch might not get a place on the chip while other launches'
-// drafting workgroups wait there): after `spin` polls it marks the words of all rows that are missing with kRowLate and ends.
-// A workgroup that finds that mark as it publishes its row looks whether all rows are there now -- at least the last one sees
-// them all -- and then drafts the tree from the beginning.  Should two draft it, both write the same.
-constexpr u64 kRowThere = 0x9d3f5be1c7604a2bull, kRowLate = 0x6b1e88d2f0957c43ull;
+// drafting workgroups wait there): after `spin` polls it marks the words of all rows that are missing with kRowLate, says in the
+// sequence's own word that it has done so, and ends.  A workgroup that finds its row's word marked as it publishes the row looks
+// whether all rows are there now -- at least the last one sees them all -- and then, once the marks are made, drafts the tree from
+// the beginning.  (Sooner, it could clear words that are still being marked, and these marks would be found by the next launch.)
+// Should two draft it, both write the same.
+constexpr u64 kRowThere = 0x9d3f5be1c7604a2bull, kRowLate = 0x6b1e88d2f0957c43ull, kMarksMade = 0x5c27f4a98e61d03bull;
 struct Arrivals {
-    u64* there;                   // [rows] of this sequence
+    u64* there;                        // [rows] of this sequence
+    u64* marks;                        // the sequence's own word
     int rows, spin;
     bool wait;                         // false: all rows are there
 };
@@ -36,17 +39,16 @@ template <class W> __device__ __forceinline__ bool rows_there(const W& w, const 
     return w.all(ok);
 }
 
-// One wavefront: marks the rows that are missing, then looks whether all are there after all.  If not, those that are missing
-// now were missing before, so all of them are marked, and the last of them to come finds the others there.  (Without the
-// second look a row could come, unmarked, between the marks and the visits of rows that found it missing.)
-template <class W> __device__ __forceinline__ bool leave_or_all_there(const W& w, const Arrivals& ar) {
+// One wavefront: marks the rows that are missing.  A look behind it tells who drafts: rows that are missing then were missing
+// before, so all of them are marked, and the last of them to come finds the others there.  (A look ahead of it would not do: a row
+// could come, unmarked, in between.)
+template <class W> __device__ __forceinline__ void mark_missing(const W& w, const Arrivals& ar) {
     for (int r = w.lane; r < ar.rows; r += W::kLanes) {
         u64 v = w.load(ar.there + r);
-        while (v != kRowThere)                                // (a word changes twice at most while this looks at it)
+        while (v != kRowThere)                                // (no word is cleared before kMarksMade: a second try finds the row there)
             if (w.swap_if(ar.there + r, v, kRowLate)) break;
     }
     w.stores_done();
-    return rows_there(w, ar, 0);
 }
 
 // What the wavefronts of a drafting workgroup tell each other (LDS).  A wavefront that stops waiting names the step whose rows it
@@ -62,27 +64,43 @@ template <class W> __device__ __forceinline__ bool has_quit(const W& w, const Qu
 
 // Every wavefront, behind a barrier, some wavefront having quit.  False: another workgroup drafts the tree.
 template <class W> __device__ __forceinline__ bool go_alone(const W& w, Quit& q, Arrivals& ar) {
-    if (!leave_or_all_there(w, ar)) w.set(q.gone, 1);
+    mark_missing(w, ar);
+    w.barrier();
+    if (w.first) { w.store(ar.marks, kMarksMade); w.stores_done(); }
+    if (!rows_there(w, ar, 0)) w.set(q.gone, 1);
     w.barrier();
     ar.wait = false;
     return w.get(q.gone) == 0;
 }
 
-// One wavefront, tree drafted from the rows before `first`: clears the words
+// One wavefront, tree drafted from the rows before `first`: clears the words, the sequence's own last (take_over)
 template <class W> __device__ __forceinline__ void clear_arrivals(const W& w, Arrivals ar, int first) {
     int polls = 0;
     while (ar.wait && !rows_there(w, ar, first)) {
         if (++polls > ar.spin) {
-            if (leave_or_all_there(w, ar)) break;
-            return;
+            mark_missing(w, ar);
+            w.store(ar.marks, kMarksMade);
+            if (!rows_there(w, ar, 0)) return;
+            ar.wait = false;
+            break;
         }
         w.pause();
     }
     for (int r = w.lane; r < ar.rows; r += W::kLanes) w.store(ar.there + r, 0);
+    if (ar.wait) return;
+    w.stores_done();
+    if (w.lane == 0) w.store(ar.marks, 0);
 }
 
-// A wavefront of the workgroup that has found its row's word marked: does it draft the tree
-template <class W> __device__ __forceinline__ bool take_over(const W& w, const Arrivals& ar) { return rows_there(w, ar, 0); }
+// A wavefront of a workgroup that has found its row's word marked: does it draft the tree.  The wait ends: whoever marks has a
+// place on the chip and says so next, and is seen here or by rows that are cleared, which they are before the sequence's word.
+template <class W> __device__ __forceinline__ bool take_over(const W& w, const Arrivals& ar) {
+    while (rows_there(w, ar, 0)) {
+        if (w.load(ar.marks) == kMarksMade) return true;
+        w.pause();
+    }
+    return false;
+}
 
 }  // namespace
 }  // namespace ot

@@ -17,6 +17,7 @@ struct FusedArgs {
     ScanKArgs scan;
     TreeBuildArgs tree;
     u64* there;                        // [batch][rows]
+    u64* marks;                        // [batch]
     int n, depth, spin;
     int draft_threads;                 // wavefronts that draft: as many as a step has candidates for
 };
@@ -52,18 +53,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 1024 ?
             *over = __hip_atomic_exchange(a.there + it.rid, kRowThere, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kRowLate;
         __syncthreads();
         if (!*over) return;
-        // the drafting workgroup is gone
+        // the drafting workgroup has marked this row
         ar.wait = false;
-        ar.there = a.there + (size_t)b * rows;
-        const bool all = take_over(ChipWave{tid & 63}, ar);
-        __syncthreads();
-        if (tid < 64) *over = all;
+        ar.there = a.there + (size_t)b * rows; ar.marks = a.marks + b;
+        __syncthreads();                                      // (everybody has looked)
+        if (tid < 64) *over = take_over(ChipWave{tid, true}, ar);
         __syncthreads();
         if (!*over) return;
         __syncthreads();
     }
     if (tid >= a.draft_threads) return;
-    ar.there = a.there + (size_t)b * rows;
+    ar.there = a.there + (size_t)b * rows; ar.marks = a.marks + b;
     Shared<SNT>& s = *(Shared<SNT>*)smem;
     draft_tree<SNT, KPT, kArrive, ADAPT>(s, smem + sizeof(Shared<SNT>), a.draft_threads, b, a.scan.row_topv, a.scan.row_lse, a.scan.k, rows, a.n, a.depth, 0,
                                          a.depth, a.tree, ar);
@@ -137,6 +137,7 @@ int launch_fused_build(const ScanGeometry& sg, const SelectGeometry& g, const vo
     a.tree.out = out;
     // state of a streaming build, which a one-shot build has no use for
     a.there = (u64*)ws.pool_p;
+    a.marks = (u64*)ws.step_tau;
     a.n = g.n; a.depth = g.depth; a.spin = spin;
     const ScanForm f = scan_form(sg, logits);
     const int wide = widest(g);

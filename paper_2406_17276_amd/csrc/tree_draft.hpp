@@ -244,6 +244,7 @@ enum Source { kStep, kStaged, kArrive };
 struct ChipWave {
     static constexpr int kLanes = 64;
     int lane;
+    bool first;                        // of its workgroup
     __device__ __forceinline__ u64 load(const u64* p) const { return ot::get<true>(p); }
     __device__ __forceinline__ void store(u64* p, u64 v) const { ot::put<true>(p, v); }
     __device__ __forceinline__ bool swap_if(u64* p, u64& v, u64 x) const {
@@ -323,7 +324,7 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
         for (int i = 0; i < KPT; ++i) cj[i] = (i * nt + tid) / k;
     }
     // kArrive: rows of the next step that this wavefront's candidates need; are they there (the same for the wavefront)
-    const ChipWave chip{lane};
+    const ChipWave chip{lane, wave == 0};
     bool next_there = false;
     u64 word[KPT], word2[KPT];                                // words of the next step's rows, of those of the step after
     auto request = [&](u64 (&w)[KPT], int first, int count) {
@@ -355,7 +356,7 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
             next_there = t1 > 1 && here(word2);
         }
         lds_barrier();
-        if (has_quit(chip, s.quit, 0) && !go_alone(chip, s.quit, ar)) return;
+        if (__builtin_expect(has_quit(chip, s.quit, 0), 0) && !go_alone(chip, s.quit, ar)) return;
     }
     if (!STAGE) {
 #pragma unroll
@@ -509,7 +510,7 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
             next_there = ar.wait && t + 2 < t1 && here(word2);
         }
         lds_barrier();
-        if (ARRIVE && has_quit(chip, s.quit, t + 1)) {
+        if (ARRIVE && __builtin_expect(has_quit(chip, s.quit, t + 1), 0)) {
             if (!go_alone(chip, s.quit, ar)) return;
             if (t + 1 < t1) fetch();
         }

@@ -67,6 +67,7 @@ struct Wave {
 struct World {
     std::vector<u64> word;
     std::vector<char> result;          // rows whose results are in memory
+    u64 marks;
     Quit quit;
     int drafted;
     std::vector<int> starts;           // rows before step t
@@ -144,12 +145,14 @@ int main(int argc, char** argv) {
         g_rng = 0x9e3779b97f4a7c15ull * (unsigned)(run + 1);
         world.word.assign(5, rnd(2) ? 0 : 77);
         world.result.assign(5, 0);
+        world.marks = rnd(2) ? 0 : 77;
         world.quit = Quit{9, 9};
         world.drafted = 0;
         g_live = 2;
         g_error = nullptr;
         Arrivals ar{};
         ar.there = world.word.data(); ar.rows = 5; ar.spin = (int)rnd(4); ar.wait = true;
+        ar.marks = &world.marks;
         g_tasks.clear();
         for (int i = 0; i < 7; ++i) {
             Task& t = tasks[i];
@@ -183,6 +186,9 @@ int main(int argc, char** argv) {
             swapcontext(&g_main, &g_now->ctx);
         }
         if (!g_error && !world.drafted) fail("nobody has drafted the tree");
+        for (u64 v : world.word)
+            if (!g_error && (v == kRowThere || v == kRowLate)) fail("a word is left set");
+        if (!g_error && world.marks != 0 && world.marks != 77) fail("the sequence's word is left set");
         if (g_error) { printf("run %d: %s\n", run, g_error); return 1; }
     }
     printf("ok %d\n", runs);

@@ -192,14 +192,19 @@ def test_a_stopped_sequence_stays_as_it_is_in_steps_of_one_launch():
 
 @pytest.mark.parametrize("V,k,n,d,B,dtype", [
     (8184, 2, 200, 10, 2, "bf16"),          # seven steps that keep all of their candidates, and so have one barrier each
+    (1000, 2, 200, 14, 1, "bf16"),          # 1455 rows: marking them takes 23 trips
     (9000, 4, 65, 6, 3, "f32"),             # 1024 threads; more than 64 nodes
     (1000, 4, 16, 4, 1, "f32"),
 ])
 def test_a_wait_that_is_given_up_at_any_step(V, k, n, d, B, dtype):
+    import torch
     build = _Build(_logits(V, n, d, B, dtype, 17), k, n, d)
     _, want = build(30000)
+    words = [0x9d3f5be1c7604a2b - 2**64, 0x6b1e88d2f0957c43, 0x5c27f4a98e61d03b]      # kRowThere, kRowLate, kMarksMade
     for polls in range(24):
         print(V, k, n, d, B, dtype, "polls", polls, flush=True)
         one, got = build(polls)
         assert one == 1
         assert _equal(got, want), polls
+        left = build.ws[:build.ws.numel() // 8 * 8].view(torch.int64)
+        assert not any(bool((left == w).any()) for w in words), polls
