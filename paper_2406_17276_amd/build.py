@@ -24,14 +24,11 @@ FLAGS = [
     "-mllvm", "-amdgpu-kernarg-preload-count=12",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
-# per-file additions, row_scan.hip.
-# -fno-honor-nans: the maxima over logits need no NaN handling (logits are finite or -inf by contract; infinities stay
-# honoured), which saves the quieting instruction in front of every maximum.  (Not for verify.hip, whose rows may hold NaNs.)
-# -disable-machine-licm: without it 1 % slower (13B-shaped adaptive build 23.2 -> 23.5 us, builds of 128256-token rows 2191 ->
-# 2201 us), at the same number of registers and no spills either way.
+# per-file additions, row_scan.hip: without -disable-machine-licm 1 % slower (13B-shaped adaptive build 23.2 -> 23.5 us, builds of
+# 128256-token rows 2191 -> 2201 us), at the same number of registers and no spills either way.
 # build_fused.hip: without -disable-machine-licm constants of the exponential are kept in registers throughout (79 registers
 # instead of 55, and 64 are what two workgroups of 1024 threads leave).
-EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm", "-fno-honor-nans"],
+EXTRA_FLAGS = {"row_scan.hip": ["-mllvm", "-disable-machine-licm"],
                "build_fused.hip": ["-mllvm", "-disable-machine-licm"]}
 
 

@@ -176,7 +176,13 @@ template <int DT> struct VecOf {
     }
 };
 
-// max of three as one instruction whether or not this file honours NaNs (which otherwise costs a quieting instruction per operand)
+// Maxima as the instruction itself: the compiler puts a quieting instruction in front of every operand of its own.  A NaN operand
+// loses.
+__device__ __forceinline__ float max2(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 __device__ __forceinline__ float max3(float a, float b, float c) {
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));

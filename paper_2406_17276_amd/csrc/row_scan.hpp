@@ -61,17 +61,39 @@ __device__ __forceinline__ int ordered(float v) {
     return i ^ ((i >> 31) & 0x7fffffff);
 }
 
+// order-preserving map from int to float, the inverse
+__device__ __forceinline__ float unordered(int o) { return __int_as_float(o ^ ((o >> 31) & 0x7fffffff)); }
+
 // max over groups of G consecutive lanes (1, 4, 8 or 16), result in every lane of the group
 template <int G>
-__device__ __forceinline__ float group_max(float v) {
+__device__ __forceinline__ int group_max(int v) {
     if (G >= 4) {
-        v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR1>(__float_as_int(v), __float_as_int(v))));
-        v = fmaxf(v, __int_as_float(dpp_i<DPP_QUAD_XOR2>(__float_as_int(v), __float_as_int(v))));
+        v = max(v, dpp_i<DPP_QUAD_XOR1>(v, v));
+        v = max(v, dpp_i<DPP_QUAD_XOR2>(v, v));
     }
-    if (G >= 8) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_HALF_MIRROR>(__float_as_int(v), __float_as_int(v))));
-    if (G >= 16) v = fmaxf(v, __int_as_float(dpp_i<DPP_ROW_MIRROR>(__float_as_int(v), __float_as_int(v))));
+    if (G >= 8) v = max(v, dpp_i<DPP_ROW_HALF_MIRROR>(v, v));
+    if (G >= 16) v = max(v, dpp_i<DPP_ROW_MIRROR>(v, v));
     return v;
 }
+// max over each row of 16 lanes, result in every lane of the row, and over the wavefront, as a scalar.  Written out because of the
+// quieting instructions (max2), which would also keep the lane exchange out of the maximum.  A lane exchange may read what the
+// instruction before the last one or earlier wrote.  (row_scan.hip alone used to be compiled without NaNs instead; in the kernels
+// that share the scan with a selection, which counts on NaNs, the quieting took 190 of 4900 instructions of the rolling form:
+// streaming loops replayed from a graph, 11 steps of 5 nodes of 70016 bf16 246.6 -> 241.9 us, 10 of 24 of 40000 192.8 -> 189.4, 1 %
+// over 49; row_scan.hip as before, 32 sequences of 128256 2130 -> 2123)
+#define OT_MAX_DPP(CTRL) "s_nop 1\n\tv_max_f32_dpp %0, %0, %0 " CTRL "\n\t"
+#define OT_MAX_ROW16 OT_MAX_DPP("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf") OT_MAX_DPP("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf") \
+                     OT_MAX_DPP("row_half_mirror row_mask:0xf bank_mask:0xf") OT_MAX_DPP("row_mirror row_mask:0xf bank_mask:0xf")
+__device__ __forceinline__ float row_max(float v) {
+    asm volatile(OT_MAX_ROW16 : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ float wavefront_max(float v) {
+    asm volatile(OT_MAX_ROW16 OT_MAX_DPP("row_bcast:15 row_mask:0xa bank_mask:0xf") OT_MAX_DPP("row_bcast:31 row_mask:0xc bank_mask:0xf") : "+v"(v));
+    return rl_f(v, 63);
+}
+#undef OT_MAX_ROW16
+#undef OT_MAX_DPP
 
 // 2^x in fp64 for the factor between two references, to 1e-8 (Taylor series of e^t on |t| <= ln 2 / 2, seven terms): the
 // exponential instruction's 2^-24 would be an error of everything summed so far
@@ -212,8 +234,8 @@ struct Scan {
             }
             m = vmax[0];
 #pragma unroll
-            for (int i = 1; i < VPL; ++i) m = fmaxf(m, vmax[i]);
-            const float mw = wave_max_f(m);
+            for (int i = 1; i < VPL; ++i) m = max2(m, vmax[i]);
+            const float mw = wavefront_max(m);
             mc = mw * kLog2e;
             if (mw > -INFINITY) {
 #pragma unroll
@@ -240,12 +262,12 @@ struct Scan {
                         mask_edges(x, i * NT + tid);
                     }
                     const float v = max_of(x);
-                    vmax[i / 2] = i % 2 == 0 ? v : fmaxf(vmax[i / 2], v);
+                    vmax[i / 2] = i % 2 == 0 ? v : max2(vmax[i / 2], v);
                     // e^(x - m) = 2^(x log2e - mc) with mc = fl(m log2e): one fma per element.  mc is carried along as the
                     // wave's reference exponent, so its rounding cancels when the partial sums are combined.
                     if (__any(v > ref)) {
-                        ref = wave_max_f(v);
-                        const float mn = fmaxf(ref, -1e38f) * kLog2e;                      // (finite for the lowest masks too)
+                        ref = wavefront_max(v);
+                        const float mn = max2(ref, -1e38f) * kLog2e;                     // (finite for the lowest masks too)
                         if (i > 0) acc = acc > 0.0 ? acc * exp2_factor((double)mc - (double)mn) : 0.0;
                         mc = mn;
                     }
@@ -261,12 +283,12 @@ struct Scan {
             }
             m = vmax[0];
 #pragma unroll
-            for (int i = 1; i < VPL / 2; ++i) m = fmaxf(m, vmax[i]);
+            for (int i = 1; i < VPL / 2; ++i) m = max2(m, vmax[i]);
             s_w = wave_sum_d(acc);
         }
         if (lane == 0) { sh.wm[wave] = s_w > 0.0 ? mc : -INFINITY; sh.ws[wave] = s_w; }
-        const float gm = group_max<GL>(m);
-        if ((lane & (GL - 1)) == 0) sh.g[tid / GL] = ordered(gm);
+        const int gm = group_max<GL>(ordered(m));
+        if ((lane & (GL - 1)) == 0) sh.g[tid / GL] = gm;
         __syncthreads();
 
         // ---- 2. tau -----------------------------------------------------------
@@ -282,8 +304,7 @@ struct Scan {
                 if (__popcll(before) == kk - 1 && lane == 0) sh.tau = v;
             }
             __syncthreads();
-            const int o = sh.tau;
-            tau = __int_as_float(o ^ ((o >> 31) & 0x7fffffff));
+            tau = unordered(sh.tau);
         } else {
             // issue slots count: every wavefront bisects for a value that k to k + 2 of the maxima reach, one vector
             // instruction per round
@@ -295,7 +316,7 @@ struct Scan {
                 if (cnt >= kk) { lo = mid; if (cnt <= kk + 2) break; }
                 else hi = mid;
             }
-            tau = __int_as_float(lo ^ ((lo >> 31) & 0x7fffffff));
+            tau = unordered(lo);
         }
 
         // ---- 3. candidates ----------------------------------------------------
@@ -347,7 +368,7 @@ struct Scan {
         if (wave == (KEEP || NW == 1 ? NW - 1 : 1) && lane < 16) {
             const bool have = lane < NW;
             const float mw = have ? sh.wm[lane] : -INFINITY;
-            const float M = group_max<16>(mw);
+            const float M = row_max(mw);
             double part_sum = (have && mw > -INFINITY) ? sh.ws[lane] * (double)__builtin_amdgcn_exp2f(mw - M) : 0.0;
             part_sum += dpp_d<DPP_QUAD_XOR1>(part_sum);
             part_sum += dpp_d<DPP_QUAD_XOR2>(part_sum);

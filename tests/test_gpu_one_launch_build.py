@@ -208,3 +208,99 @@ def test_a_wait_that_is_given_up_at_any_step(V, k, n, d, B, dtype):
         assert _equal(got, want), polls
         left = build.ws[:build.ws.numel() // 8 * 8].view(torch.int64)
         assert not any(bool((left == w).any()) for w in words), polls
+
+
+def _timed(x, k, n, d):
+    """The same trees by scan and drafting as two launches."""
+    import torch
+    from paper_2406_17276_amd import api
+    ref = api.PreparedBuild(x, k, n, d)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for e in ev:
+        e.record()
+    ref.timed(torch.cuda.current_stream().cuda_stream, ev[0].cuda_event, ev[1].cuda_event)
+    torch.cuda.synchronize()
+    return [getattr(ref.out, f).clone() for f in FIELDS]
+
+
+def _streamed(x, k, n, d, delta):
+    """Algorithm 1's loop by the streaming calls: tree fields, steps drafted and last E_sub of every sequence."""
+    import torch
+    from paper_2406_17276_amd import api
+    ts = api.TreeStream(x.shape[0], x.shape[3], k, n, d, api.OT_BF16 if x.dtype == torch.bfloat16 else api.OT_F32, "cuda")
+    steps, last = None, None
+    for t in range(d):
+        ts.expand(x[:, t])
+        e, go = ts.e_sub(delta)
+        if t == 0:
+            steps, last, live = torch.ones_like(go), e.clone(), go.clone()
+        else:
+            steps, last, live = steps + live, torch.where(live != 0, e, last), go.clone()
+    tree = ts.finalize()
+    torch.cuda.synchronize()
+    return [getattr(tree, f) for f in FIELDS], steps, last
+
+
+# Rows that one workgroup scans in the same form however many there are
+FORMS = [
+    (8000, 6, 33, 5, "bf16"),               # 256 threads, rows in registers
+    (20000, 12, 70, 4, "f32"),              # 1024
+    (40000, 8, 20, 5, "bf16"),              # 512 threads, rolling
+    (100000, 5, 9, 6, "bf16"),              # 1024, rolling
+]
+
+
+@pytest.mark.parametrize("V,k,n,d,dtype", FORMS)
+@pytest.mark.parametrize("what", ["masked", "few", "none", "lowest", "nan"])
+def test_masked_tokens_and_nans(V, k, n, d, dtype, what):
+    import torch
+    x = _logits(V, n, d, 2, dtype, V + k)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    if what == "masked":                    # nine tokens in ten, whole vectors among them
+        x[torch.rand(x.shape, generator=g, device="cuda") < 0.9] = -float("inf")
+        x[..., 64:4096] = -float("inf")
+    elif what == "few":                     # fewer tokens than children
+        x[0, :, ::2, 3:] = -float("inf")
+    elif what == "none":
+        x[0, 0], x[1, 1, ::3] = -float("inf"), -float("inf")
+    elif what == "lowest":
+        x[0, :, ::2, k // 2:] = torch.finfo(x.dtype).min
+    else:                                   # outside of what is promised, but the same in every form; a wavefront of them in a row
+        x[torch.rand(x.shape, generator=g, device="cuda") < 1e-3] = float("nan")
+        x[1, 1, 1, 1024:2048] = float("nan")
+    want = _timed(x, k, n, d)
+    build = _Build(x, k, n, d)
+    one, got = build(30000)
+    assert one == 1
+    assert _equal(got, want)
+    if what in ("masked", "few", "lowest"):
+        fields, steps, e = _streamed(x, k, n, d, -1.0)
+        for f, a, b in zip(FIELDS, got, fields):
+            if f not in ("score", "expect"):
+                assert a.equal(b), f
+
+
+@pytest.mark.parametrize("V,k,n,d,dtype", [c for c in FORMS if c[2] <= 64])
+@pytest.mark.parametrize("masked", [False, True])
+def test_streaming_steps_equal_two_launches(V, k, n, d, dtype, masked):
+    import torch
+    from paper_2406_17276_amd import api
+    x = _logits(V, n, d, 1, dtype, V + 2 * n)
+    if masked:
+        x[..., 5:V // 2] = -float("inf")
+        x[:, 2, ::2, 2:] = -float("inf")
+    got = []
+    for B in (1, 300):                      # more than 256 rows: two launches a step
+        ts = api.TreeStream(B, V, k, n, d, api.OT_BF16 if dtype == "bf16" else api.OT_F32, "cuda")
+        step = []
+        for t in range(d):
+            ts.expand(x[:, t].expand(B, -1, -1))
+            step += [a.clone() for a in (ts.frontier_token, ts.frontier_parent, ts.frontier_count, ts.frontier_mask())]
+            step += [a.clone() for a in ts.e_sub(-1.0)]
+        tree = ts.finalize()
+        torch.cuda.synchronize()
+        got.append(step + [getattr(tree, f) for f in FIELDS])
+    for a, b in zip(*got):
+        for i in (0, 1, 299):
+            assert _equal([a[:1]], [b[i:i + 1]])
