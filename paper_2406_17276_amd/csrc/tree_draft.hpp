@@ -603,7 +603,8 @@ __device__ __forceinline__ void draft_tree(Shared<NT>& s, char* const smem, cons
         if (wave == 0) {
             u64 row = node ? 1ull << lane : 0ull;
             int up = par;
-            while (__any(up >= 0)) {
+            for (int stretch = 1; stretch < OT_MAX_DEPTH; stretch *= 2) {
+                if (!__any(up >= 0)) break;
                 const int at = max(up, 0);
                 const u64 above = (u64)(unsigned)__shfl((int)(row >> 32), at) << 32 | (unsigned)__shfl((int)row, at);
                 const int next = __shfl(up, at);

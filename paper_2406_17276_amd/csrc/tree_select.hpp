@@ -368,13 +368,15 @@ __device__ void layer_cut(const double (&ck)[KMAX], double* kt, int* hist, bool 
     off = g.excl_scan(cnt);
 }
 
-// candidate scores of one frontier slot: log p^(child) = log p^(parent) + (x - lse)   (Eq. 2)
+// candidate scores of one frontier slot: log p^(child) = log p^(parent) + (x - lse)   (Eq. 2).  log p <= 0 up to the rounding of
+// lse: a child that scored above its parent could be in the tree without it.  A score that is not defined (a row of -inf) counts as
+// the lowest: only slots that are not there are absent, so a step always fills its frontier.
 template <int KMAX>
 __device__ __forceinline__ void candidate_scores(double S, double lse, const float (&v)[KMAX], bool active, int k,
                                                  double (&ck)[KMAX]) {
+    if (!(lse > -INFINITY)) lse = INFINITY;
 #pragma unroll
-    for (int r = 0; r < KMAX; ++r)
-        ck[r] = (active && r < k) ? S + ((double)v[r] - lse) : __longlong_as_double(0x7ff8000000000000ll);
+    for (int r = 0; r < KMAX; ++r) ck[r] = (active && r < k) ? S + fmin((double)v[r] - lse, 0.0) : nan_d();
 }
 
 #define OT_SELECT_SHARED(THREADS)                          \

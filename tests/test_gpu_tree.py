@@ -536,6 +536,28 @@ def test_one_shot_and_streaming_builds_agree_on_e(V, k, n, d):
         torch.testing.assert_close(value, ref, rtol=1e-13, atol=0.0)
 
 
+@pytest.mark.parametrize("k,n,d,dtype", [(4, 4, 10, "f32"), (4, 4, 32, "bf16"), (3, 20, 32, "f32"), (16, 64, 20, "f32"), (2, 80, 32, "f32")])
+def test_streaming_tree_of_rows_with_one_token(k, n, d, dtype):
+    """log p of a row's only token is 0 but for the rounding of the normaliser, above or below: no child comes before its parent."""
+    import torch
+    from paper_2406_17276_amd import api
+    B, V = 4, 1000
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    x = torch.zeros((B, d, n, V), device="cuda")
+    x.scatter_(3, torch.randint(0, V, (B, d, n, 1), generator=g, device="cuda"),
+               30 + 60 * torch.rand((B, d, n, 1), generator=g, device="cuda"))
+    x = x.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ts = api.TreeStream(B, V, k, n, d, api.OT_BF16 if dtype == "bf16" else api.OT_F32, "cuda")
+    for t in range(d):
+        ts.expand(x[:, t])
+    got = ts.finalize()
+    want = api.build_tree(x, k, n, d)
+    torch.cuda.synchronize()
+    U.assert_tree_invariants(got, n, d)
+    for f in ("token", "parent", "depth", "mask", "n_out"):
+        assert torch.equal(getattr(got, f), getattr(want, f)), f
+
+
 def test_builds_of_more_threads_than_a_grid_holds():
     """2^24 + 3 sequences of one row: at 256 threads each more than 2^32 threads, in the scan as in the tree kernel."""
     import torch
