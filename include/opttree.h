@@ -17,9 +17,7 @@
  *     distinct workspaces.  (One documented exception: ot_tree_verify_attention_noalloc
  *     works in a fixed array that the library's code object holds on every GPU.);
  *   - alignment of device pointers: workspaces and the attention tensors (Q, K, V, O) 16 bytes; logits
- *     rows the size of one element (rows that are 16-byte aligned, with strides and a vocabulary that are
- *     multiples of 16 bytes, take the vector-load path, anything else a slower element-load path); int32 /
- *     float arrays 4 bytes; uint64 / double arrays 8 bytes;
+ *     rows the size of one element; int32 / float arrays 4 bytes; uint64 / double arrays 8 bytes;
  *   - arguments are validated on the host before anything is launched; an
  *     invalid call enqueues nothing.
  */
@@ -65,7 +63,8 @@ OT_API int ot_last_hip_error(void);                /* hipError_t of the last fai
  * root) and frontier slot j < F_t, one row of `vocab` next-token logits of the
  * draft model, where F_0 = 1 and F_{t+1} = min(n, k*F_t).  Row (b,t,j) starts
  * at  logits + b*stride_seq + t*stride_depth + j*stride_row  (strides in
- * elements; rows j >= F_t are never read).  p_d = softmax(row).
+ * elements; rows j >= F_t are never read).  p_d = softmax(row).  Logits are finite or -inf (a token of probability 0); the
+ * children of a row without a finite logit have no defined score and are kept after all others.
  *
  * Per row: the k most probable tokens become the node's children (equal logits:
  * smaller token id first); a child's score is log p^ = score(parent) + log p_d
@@ -114,13 +113,10 @@ OT_API int ot_build_tree_timed(const ot_build_params* p, const void* logits,
 /* ot_build_tree with the stopping rule of Algorithm 1 applied inside the kernel: after every drafting step
  * E_sub(T, n) (the sum of the n largest p^ drafted so far) is compared with its value E one step earlier
  * (E = 0 at the start), and drafting ends when E_sub - E <= delta or after p->depth steps.  The logits of
- * all p->depth steps are passed as for ot_build_tree; rows of steps that are not drafted are scanned but not
+ * all p->depth steps are passed as for ot_build_tree; rows of steps that are not drafted may be scanned, and are not
  * used.  steps_used[b] (int32, device) receives the number of steps drafted, e_sub[b] (double, device) the
- * last E_sub.  Shapes on the single-wavefront path (n <= 64 and (rows per sequence + 1) * k within the LDS
- * budget -- the 7B, 13B and 70B shapes) run the loop inside one kernel; all other shapes run it step by step on
- * the stream with the kernels of the streaming calls below (the scan of a step's rows, the step, E_sub and the
- * loop condition; a sequence that stops is frozen on the device, nothing is read back, and the rows of the steps
- * it does not draft are not read).  Either way the call returns without waiting for the device. */
+ * last E_sub.  The loop runs on the device, in the build's own launches, and the call returns without waiting
+ * for it. */
 OT_API int ot_build_tree_adaptive(const ot_build_params* p, double delta, const void* logits,
                   void* workspace, size_t workspace_bytes,
                   const ot_tree_out* out, int32_t* steps_used, double* e_sub, void* hip_stream);
@@ -139,7 +135,8 @@ OT_API int ot_build_tree_adaptive(const ot_build_params* p, double delta, const 
  *                   its frontier outputs are left as they were); steps must be
  *                   fed in order t = 0,1,..;
  *   ot_tree_finalize selects and emits the tree over the steps fed so far.
- * The three calls of one tree must use the same workspace and stream order. */
+ * The three calls of one tree must use the same workspace and stream order.  A one-shot build on that workspace in between
+ * overwrites the builder's state. */
 OT_API int ot_tree_begin(const ot_build_params* p, void* workspace, size_t workspace_bytes, void* hip_stream);
 OT_API int ot_tree_expand(const ot_build_params* p, int32_t step, const void* rows,
                    int64_t stride_seq, int64_t stride_row,

@@ -122,7 +122,7 @@ size_t ot_build_workspace_bytes(const ot_build_params* p) {
 }
 
 // One-shot build: the rows of all steps are scanned, then the tree is drafted from their statistics.  A tree is usually
-// complete long before the last step (tree_build.hip), so big inputs go in chunks of steps: scan a chunk, draft it, and
+// complete long before the last step (tree_draft.hpp), so big inputs go in chunks of steps: scan a chunk, draft it, and
 // leave the rows of finished sequences unread from then on.  A chunk costs two more launches and another pass over the
 // pool, 8 to 14 us on the stream, which is all that it brings where no tree is complete before the last step (rows in which
 // one token has nearly all of the probability).  So a chunk has at least 192 MB of rows, some 35 us of reading, and later

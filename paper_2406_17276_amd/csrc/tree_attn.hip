@@ -1259,9 +1259,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
     int t = t0 + ks;
     // Q is asked for ahead of K and V: it goes to LDS while they are under way, and the scores wait for K alone.  With it the
-    // arguments that are in registers at the start, and no integer divisions: 13 x 16 KV heads of 1024 rows, 253 keys of 128 363 ->
-    // 342 us, 14 x 2 of 944 rows 94 -> 88, 4 heads of 16 rows, 144 keys of 64 9.87 -> 9.65 (ahead of the prefix length's use 15 x 8
-    // KV heads of 36 rows, 4313 keys of 64 96 -> 98 us, here 96)
+    // arguments that are in registers at the start, and divisions by multiplication but for a split's key range (two 64-bit ones):
+    // 13 x 16 KV heads of 1024 rows, 253 keys of 128 363 -> 344 us, 14 x 2 of 944 rows 95 -> 89, 4 heads of 16 rows, 144 keys of 64
+    // 9.92 -> 9.82, 0 to 7 % over 26 shapes, 1.5 % in the mean (ahead of the prefix length's use 15 x 8 KV heads of 36 rows, 4313 keys
+    // of 64 96 -> 98 us, here 96.5)
     constexpr int QI = ROWS * D / 4 / NT;
     f32x4 qr[QI];
 #pragma unroll

@@ -1,5 +1,5 @@
-// One-shot tree construction: everything of Algorithm 1 that follows the row scan, for a launch whose rows are all in
-// memory (ot_build_tree, ot_build_tree_adaptive).
+// One-shot tree construction (ot_build_tree, ot_build_tree_adaptive): everything of Algorithm 1 that follows the row scan, for rows
+// that are all in memory or that workgroups of the same launch scan meanwhile.
 //   per drafting step t: candidate score = score(parent) + (x - lse)            (Eq. 2 in log space)
 //                        keep the F_{t+1} = min(n, k F_t) best candidates       (Algorithm 1, "topk")
 //                        number them by (parent slot, rank)

@@ -72,7 +72,7 @@ int launch_n(const ScanGeometry& g, const void* rows, const ExpandArgs& a, hipSt
 // Where one launch is faster: steps of one wavefront (n <= 64), with a row per compute unit at most.  Called one by one, ten steps of 50
 // rows of 32000 with masks and E_sub 193 -> 156 us (the host's launches), seven other loops 1.02 to 1.2 times as fast; five loops of
 // 74 to 239 nodes 0.4 to 1 % slower.  Replayed from a graph, the same ten steps 149 -> 141 us, 8 sequences of 7 nodes 185 -> 171,
-// 15 of 6 168 -> 158, the others within 3 %; with more rows the step's registers leave the scan too few wavefronts (375 rows of 4736
+// 15 of 6 168 -> 158, 0.93 to 1.02 over 40 loops, 0.97 in the mean; with more rows the step's registers leave the scan too few wavefronts (375 rows of 4736
 // 155 -> 166, 966 of 3392 fp32 92 -> 98).
 bool fuse_expand(const ScanGeometry& sg, int n, const void* rows) {
     const ScanForm f = scan_form(sg, rows);
